@@ -6,6 +6,7 @@
 
 #include "api_common.h"
 #include "epilogue.h"
+#include "gemm_f32.h"
 #include "gemm_generic.h"
 #include "gemm_mfma.h"
 #include "group_select.h"
@@ -47,7 +48,8 @@ inline int streamk_workgroups() { return std::min(persistent_workgroups(), kStre
 // `sk`, if given and carved, lets a product whose whole tiles would leave part of the chip idle in their last
 // round split its work along the contraction instead (256 x 256 tiles, contraction a multiple of 32).
 template <class E, bool AKM, bool BKM, class Epi>
-moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, hipStream_t st, const StreamKArea* sk = nullptr) {
+moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, hipStream_t st, const StreamKArea* sk = nullptr,
+                    bool ascending = false) {
     Span span(name, st);
     if constexpr (std::is_same<E, bf16_t>::value) {
         if (!options().force_generic && mfma_problem_ok(pr)) {
@@ -77,6 +79,13 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
             hipError_t e = best == 0   ? launch_mfma_tail<256, 256, AKM, BKM, Epi>(pr, epi, st)
                            : best == 1 ? launch_mfma_tail<256, 192, AKM, BKM, Epi>(pr, epi, st)
                                        : launch_mfma_tail<128, 128, AKM, BKM, Epi>(pr, epi, st);
+            if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+            return MOC_OK;
+        }
+    }
+    if constexpr (std::is_same<E, float>::value) {
+        if (!options().force_generic && f32_problem_ok(pr)) {
+            hipError_t e = launch_gemm_f32<AKM, BKM, Epi, 1>(F32Batch<Epi, 1>{{pr}, {epi}}, ascending, device_cu_count(), st);
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -128,6 +137,15 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
             return MOC_OK;
         }
     }
+    if constexpr (std::is_same<E, float>::value) {
+        if (!options().force_generic && f32_problem_ok(pr[0]) && f32_problem_ok(pr[1]) && f32_problem_ok(pr[2])) {
+            Span span(name, st);
+            hipError_t e = launch_gemm_f32<true, true, EpiStore<E>, 3>(F32Batch<EpiStore<E>, 3>{{pr[0], pr[1], pr[2]}, {epi[0], epi[1], epi[2]}},
+                                                                       false, device_cu_count(), st);
+            if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+            return MOC_OK;
+        }
+    }
     for (int i = 0; i < 3; ++i) {
         moc_status s = run_gemm<E, true, true>(names[i], pr[i], epi[i], st, sk);
         if (s != MOC_OK) return s;
@@ -135,8 +153,8 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
     return MOC_OK;
 }
 
-// Two independent products of one shape (both operands k-contiguous, contraction a multiple of 32)
-// with different epilogues in one launch when the MFMA kernel takes them; otherwise one run_gemm each.
+// Two independent products of one shape (both operands k-contiguous; bf16: contraction a multiple of 32)
+// with different epilogues in one launch when a matrix-core kernel takes them; otherwise one run_gemm each.
 template <class E, class EpiA, class EpiB>
 moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_b, const GemmProblem<E>& pa, const EpiA& ea,
                          const GemmProblem<E>& pb, const EpiB& eb, hipStream_t st, const StreamKArea* sk = nullptr) {
@@ -172,7 +190,15 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
             return MOC_OK;
         }
     }
-    moc_status s = run_gemm<E, false, false>(name_a, pa, ea, st, sk);
+    if constexpr (std::is_same<E, float>::value && std::is_same<EpiA, EpiB>::value) {
+        if (!options().force_generic && f32_problem_ok(pa) && f32_problem_ok(pb)) {
+            Span span(name, st);
+            hipError_t e = launch_gemm_f32<false, false, EpiA, 2>(F32Batch<EpiA, 2>{{pa, pb}, {ea, eb}}, true, device_cu_count(), st);
+            if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+            return MOC_OK;
+        }
+    }
+    moc_status s = run_gemm<E, false, false>(name_a, pa, ea, st, sk, true);
     if (s != MOC_OK) return s;
     return run_gemm<E, false, false>(name_b, pb, eb, st, sk);
 }

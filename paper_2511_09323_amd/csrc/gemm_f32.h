@@ -1,0 +1,262 @@
+// fp32 GEMM on the gfx950 matrix cores (v_mfma_f32_16x16x4_f32: fp32 inputs, fp32 products and sums).
+//
+//   C[m, n] = sum_k A(m, k) B(n, k)   (+ a second operand pair accumulated into the same tile)
+//
+// Same operand layouts as the bf16 kernel (k-contiguous or k-major, gemm_generic.h), staged as they lie in
+// memory: k-contiguous tiles as [row][BK + 4] floats, k-major tiles as [k][ROWS + 16] floats.  Both pitches
+// put the 16 rows x 4 k that one fragment read touches on 64 different banks.
+//
+// What bounds it: at the sizes fp32 is used for (a few hundred tokens, d of 512 to 768) a product has less than
+// one GFLOP, 2 to 5 us of matrix-core time for the chip, so the launch, the load latency and the length of a
+// wavefront's chain of MFMAs decide.  Hence small tiles (enough workgroups for all compute units), four k-slices of
+// 32 to 128 in flight in registers ahead of two LDS stages, and, where even 32 x 32 tiles do not fill the chip
+// and the contraction is long, KW = 4: the four wavefronts of a workgroup take a quarter of every k-slice each and
+// their tiles are added through LDS in a fixed order.  With KW = 1 a result is one sum over ascending k from zero.
+//
+// Measured at T 256, d 512, F 1376 (forward + backward, ten products in five launches): gate + up 15.6 us, down 10.4, dZ' 10.0,
+// three weight gradients 19.7, dX 18.0, against 125, 222, 63, 143 and 424 us on the fp32-FMA kernel of gemm_generic.h, which has 32
+// to 88 workgroups and waits for every 16-k slice; about 72 TFLOP/s at the margin (142 on a large library product), the rest launch
+// and first loads.
+#pragma once
+#include "common.h"
+#include "gemm_generic.h"
+#include "kernel_attrs.h"
+
+namespace moc {
+
+// NB problems of one shape and layout in one launch (blockIdx.y).
+template <class Epi, int NB> struct F32Batch {
+    GemmProblem<float> pr[NB];
+    Epi epi[NB];
+};
+
+constexpr int kF32Sets = 4;      // k-slices in flight in registers
+
+template <int BM, int BN, int KW, bool AKM, bool BKM> struct F32Cfg {
+    static constexpr int BK = KW > 1 ? 128 : (BM < 64 ? 64 : 32);
+    static constexpr int kPitchA = AKM ? BM + 16 : BK + 4, kPitchB = BKM ? BN + 16 : BK + 4;       // floats
+    static constexpr int kFloatsA = (AKM ? BK : BM) * kPitchA, kFloatsB = (BKM ? BK : BN) * kPitchB;
+    static constexpr int kStage = kFloatsA + kFloatsB;
+    static constexpr int kLds = 2 * kStage * (int)sizeof(float);
+};
+
+// (three workgroups per compute unit for the small-slice tiles: the weight-gradient launch then runs in one round)
+template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB>
+__global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32Batch<Epi, NB> batch, int tiles_n) {
+    using Cfg = F32Cfg<BM, BN, KW, AKM, BKM>;
+    static_assert(KW == 1 || KW == 4, "the wavefronts split the tile 2 x 2 or the k-slice in four");
+    constexpr int BK = Cfg::BK, NT = 256;
+    constexpr int WM = KW == 1 ? BM / 2 : BM, WN = KW == 1 ? BN / 2 : BN;
+    constexpr int TM = WM / 16, TN = WN / 16;
+    constexpr int LA = BM * BK / 4 / NT, LB = BN * BK / 4 / NT;      // 16-byte chunks per thread and slice
+    extern __shared__ __align__(16) float f32_smem[];
+    const GemmProblem<float>& pr = batch.pr[NB == 1 ? 0 : blockIdx.y];
+    const Epi& epi = batch.epi[NB == 1 ? 0 : blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int M = pr.M, N = pr.N;
+    const int m0 = (blockIdx.x / tiles_n) * BM, n0 = (blockIdx.x % tiles_n) * BN;
+    const int wm0 = KW == 1 ? (wave >> 1) * WM : 0, wn0 = KW == 1 ? (wave & 1) * WN : 0;
+    const int k_wave = KW == 1 ? 0 : wave * (BK / KW);               // first k of this wavefront inside a slice
+    const int nk0 = (pr.Kc + BK - 1) / BK, nk = nk0 + (pr.Kc2 + BK - 1) / BK;
+
+    f32x4_t ga[kF32Sets][LA], gb[kF32Sets][LB];
+    // one operand's chunks of k-slice kt -> registers.  Branch-free: rows and k past the end are clamped to readable
+    // ones (a predicated load would make the wavefront wait for its predecessors); rows past the edge give results
+    // that the epilogue drops, k past the end is zeroed when the slice goes to LDS.
+    int a_off[LA], b_off[LB], a_koff[LA], b_koff[LB];      // element offsets of the chunks: row part, k part inside a slice
+    auto offsets = [&](auto km_c, auto rows_c, const GemmOperand<float>& o, int row0, int rows, int* off, int* koff) {
+        constexpr bool KM = decltype(km_c)::value;
+        constexpr int ROWS = decltype(rows_c)::value, L = ROWS * BK / 4 / NT;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            const int c = tid + i * NT;
+            off[i] = KM ? min(row0 + (c % (ROWS / 4)) * 4, o.ext - 4) : min(row0 + c / (BK / 4), rows - 1) * (int)o.ld;
+            koff[i] = KM ? c / (ROWS / 4) * (int)o.ld : (c % (BK / 4)) * 4;
+        }
+    };
+    offsets(std::integral_constant<bool, AKM>{}, std::integral_constant<int, BM>{}, pr.A, m0, M, a_off, a_koff);
+    offsets(std::integral_constant<bool, BKM>{}, std::integral_constant<int, BN>{}, pr.B, n0, N, b_off, b_koff);
+    auto fetch = [&](auto buf_c, int kt) {
+        constexpr int buf = decltype(buf_c)::value;
+        kt = min(kt, nk - 1);
+        const bool seg = kt >= nk0;
+        const int k0 = (seg ? kt - nk0 : kt) * BK, left = (seg ? pr.Kc2 : pr.Kc) - k0;      // left >= 1
+        const float* pa = (seg ? pr.A.p2 : pr.A.p) + (AKM ? k0 * pr.A.ld : (int64_t)k0);
+        const float* pb = (seg ? pr.B.p2 : pr.B.p) + (BKM ? k0 * pr.B.ld : (int64_t)k0);
+        const int a_last = AKM ? (left - 1) * (int)pr.A.ld : ((left + 3) & ~3) - 4;
+        const int b_last = BKM ? (left - 1) * (int)pr.B.ld : ((left + 3) & ~3) - 4;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) ga[buf][i] = *reinterpret_cast<const f32x4_t*>(pa + (uint32_t)(a_off[i] + min(a_koff[i], a_last)));
+#pragma unroll
+        for (int i = 0; i < LB; ++i) gb[buf][i] = *reinterpret_cast<const f32x4_t*>(pb + (uint32_t)(b_off[i] + min(b_koff[i], b_last)));
+    };
+    // `left`: k of the slice that count, the rest is zeroed (CUT is the uniform "left < BK")
+    auto stash_operand = [&](auto km_c, auto rows_c, auto pitch_c, auto cut_c, float* base, const f32x4_t* g, int left) {
+        constexpr bool KM = decltype(km_c)::value, CUT = decltype(cut_c)::value;
+        constexpr int ROWS = decltype(rows_c)::value, PITCH = decltype(pitch_c)::value, L = ROWS * BK / 4 / NT;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            const int c = tid + i * NT;
+            f32x4_t v = g[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (CUT && (KM ? c / (ROWS / 4) : (c % (BK / 4)) * 4 + e) >= left) v[e] = 0.0f;
+            *reinterpret_cast<f32x4_t*>(KM ? base + (c / (ROWS / 4)) * PITCH + (c % (ROWS / 4)) * 4
+                                           : base + (c / (BK / 4)) * PITCH + (c % (BK / 4)) * 4) = v;
+        }
+    };
+    auto stash = [&](auto buf_c, int kt) {                           // register set s goes to LDS stage s % 2
+        constexpr int buf = decltype(buf_c)::value;
+        float* a = f32_smem + (buf & 1) * Cfg::kStage;
+        const int left = kt >= nk0 ? pr.Kc2 - (kt - nk0) * BK : pr.Kc - kt * BK;
+        auto both = [&](auto cut_c) {
+            stash_operand(std::integral_constant<bool, AKM>{}, std::integral_constant<int, BM>{},
+                          std::integral_constant<int, Cfg::kPitchA>{}, cut_c, a, ga[buf], left);
+            stash_operand(std::integral_constant<bool, BKM>{}, std::integral_constant<int, BN>{},
+                          std::integral_constant<int, Cfg::kPitchB>{}, cut_c, a + Cfg::kFloatsA, gb[buf], left);
+        };
+        if (left >= BK) both(std::false_type{});
+        else both(std::true_type{});
+    };
+
+    f32x4_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    // fragment of 16 rows x 4 k: lane l gets row l % 16, k = l / 16
+    auto compute = [&](auto stage_c) {
+        constexpr int stage = decltype(stage_c)::value;
+        const float* a = f32_smem + stage * Cfg::kStage;
+        const float* b = a + Cfg::kFloatsA;
+        const int r = lane & 15, kq = k_wave + (lane >> 4);
+        const float* pa = AKM ? a + kq * Cfg::kPitchA + wm0 + r : a + (wm0 + r) * Cfg::kPitchA + kq;
+        const float* pb = BKM ? b + kq * Cfg::kPitchB + wn0 + r : b + (wn0 + r) * Cfg::kPitchB + kq;
+        // groups of four fragments deep, the next group's reads ahead of this group's MFMAs
+        constexpr int GK = 4, NG = BK / KW / (4 * GK);
+        static_assert(NG >= 1, "a wavefront's share of a slice is at least one group");
+        float fa[2][GK][TM], fb[2][GK][TN];
+        auto read = [&](int g, int d) {
+#pragma unroll
+            for (int q = 0; q < GK; ++q) {
+                const int k = (g * GK + q) * 4;
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[d][q][i] = AKM ? pa[k * Cfg::kPitchA + i * 16] : pa[i * 16 * Cfg::kPitchA + k];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fb[d][q][j] = BKM ? pb[k * Cfg::kPitchB + j * 16] : pb[j * 16 * Cfg::kPitchB + k];
+            }
+        };
+        read(0, 0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) read(g + 1, (g + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < GK; ++q)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[g & 1][q][j], fa[g & 1][q][i], acc[i][j], 0, 0, 0);
+        }
+    };
+    fetch(std::integral_constant<int, 0>{}, 0);
+    fetch(std::integral_constant<int, 1>{}, 1);
+    fetch(std::integral_constant<int, 2>{}, 2);
+    fetch(std::integral_constant<int, 3>{}, 3);
+    stash(std::integral_constant<int, 0>{}, 0);
+    fetch(std::integral_constant<int, 0>{}, 4);
+    __syncthreads();
+    // slice kt is in LDS stage kt % 2, slices kt + 1 .. kt + 4 are in or on their way to registers
+    auto step = [&](auto set_c, int kt) {
+        constexpr int set = decltype(set_c)::value, nxt = (set + 1) % kF32Sets;
+        // the other stage was last read in the slice before this one, a barrier ago (past the end: zeros nobody multiplies)
+        stash(std::integral_constant<int, nxt>{}, kt + 1);
+        fetch(std::integral_constant<int, nxt>{}, kt + 5);
+        compute(std::integral_constant<int, set & 1>{});
+        __syncthreads();
+    };
+    int kt = 0;
+    for (; kt + 4 <= nk; kt += 4) {
+        step(std::integral_constant<int, 0>{}, kt);
+        step(std::integral_constant<int, 1>{}, kt + 1);
+        step(std::integral_constant<int, 2>{}, kt + 2);
+        step(std::integral_constant<int, 3>{}, kt + 3);
+    }
+    if (kt < nk) step(std::integral_constant<int, 0>{}, kt);
+    if (kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
+    if (kt + 2 < nk) step(std::integral_constant<int, 2>{}, kt + 2);
+
+    // acc[i][j][r] is C[m0 + wm0 + 16 i + lane % 16, n0 + wn0 + 16 j + 4 (lane / 16) + r]
+    if (KW == 1) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int m = m0 + wm0 + i * 16 + (lane & 15), n = n0 + wn0 + j * 16 + 4 * (lane >> 4);
+                const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+                if (m < M) epi.store4(m, n, v);
+            }
+    } else {
+        // (the stages are free: the loop ended with a barrier)
+        constexpr int PITCH = BN + 4;
+        static_assert(KW * BM * PITCH <= 2 * Cfg::kStage, "partial tiles must fit in the stage memory");
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                *reinterpret_cast<f32x4_t*>(f32_smem + (wave * BM + i * 16 + (lane & 15)) * PITCH + j * 16 + 4 * (lane >> 4)) = acc[i][j];
+        __syncthreads();
+        for (int c = tid; c < BM * BN / 4; c += NT) {
+            const int m = c / (BN / 4), n = (c % (BN / 4)) * 4;
+            f32x4_t s = *reinterpret_cast<const f32x4_t*>(f32_smem + m * PITCH + n);
+#pragma unroll
+            for (int w = 1; w < KW; ++w) s += *reinterpret_cast<const f32x4_t*>(f32_smem + (w * BM + m) * PITCH + n);
+            const float v[4] = {s[0], s[1], s[2], s[3]};
+            if (m0 + m < M) epi.store4(m0 + m, n0 + n, v);
+        }
+    }
+}
+
+// Host-side check of the kernel's layout assumptions: 16-byte aligned bases and rows, and whole 16-byte chunks
+// readable (a k-contiguous operand up to the next multiple of 4 past the contraction length).
+inline bool f32_problem_ok(const GemmProblem<float>& p) {
+    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+    const bool two = p.Kc2 != 0;
+    auto operand_ok = [&](const GemmOperand<float>& o, int rows) {
+        bool ok = o.p && al16(o.p) && o.ld % 4 == 0 && (!two || (o.p2 && al16(o.p2)));
+        ok = ok && (int64_t)(o.km ? 128 : rows) * o.ld < (1ll << 29);      // 32-bit byte offsets inside a tile
+        if (o.km) return ok && o.ext % 4 == 0 && o.ext >= 4 && o.ext <= o.ld && rows <= o.ext;
+        return ok && o.ld >= round_up(p.Kc > p.Kc2 ? p.Kc : p.Kc2, 4);
+    };
+    return p.M >= 1 && p.N >= 1 && p.Kc >= 1 && operand_ok(p.A, p.M) && operand_ok(p.B, p.N);
+}
+
+template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB>
+inline hipError_t launch_gemm_f32_tile(const F32Batch<Epi, NB>& b, hipStream_t st) {
+    using Cfg = F32Cfg<BM, BN, KW, AKM, BKM>;
+    auto kern = gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB>;
+    LdsAttr<gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB>, Cfg::kLds>::use();
+    const int tiles_m = (b.pr[0].M + BM - 1) / BM, tiles_n = (b.pr[0].N + BN - 1) / BN;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n, NB), dim3(256), Cfg::kLds, st, b, tiles_n);
+    return hipGetLastError();
+}
+
+// Tile shape: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
+// fragment reads); below that 32 x 32, with the k-slices split over the wavefronts when the contraction is long (several
+// 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate product, so
+// that the selection does not depend on the tile choice).
+template <bool AKM, bool BKM, class Epi, int NB>
+inline hipError_t launch_gemm_f32(const F32Batch<Epi, NB>& b, bool ascending, int num_cu, hipStream_t st) {
+    const GemmProblem<float>& p = b.pr[0];
+    const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) * NB;
+    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32) * NB;
+    if (t64 >= num_cu) return launch_gemm_f32_tile<64, 64, 1, AKM, BKM, Epi, NB>(b, st);
+    if (!ascending && (t32 < num_cu || p.Kc + p.Kc2 > 1024)) {
+        if (t32 < num_cu) return launch_gemm_f32_tile<16, 32, 4, AKM, BKM, Epi, NB>(b, st);
+        return launch_gemm_f32_tile<32, 32, 4, AKM, BKM, Epi, NB>(b, st);
+    }
+    return launch_gemm_f32_tile<32, 32, 1, AKM, BKM, Epi, NB>(b, st);
+}
+
+}  // namespace moc
