@@ -173,6 +173,11 @@ template <class E> struct FwdWs {      // dense scratch of the forward: fp32 gat
     }
 };
 
+constexpr int kMaxExperts = 8;
+constexpr int kRowPad = 32;      // k-slice of the weight-gradient products, which contract over the rows below
+
+// Rows of the dense backward operands: every expert's rows (one "expert" for the plain layer) are followed by zero rows up
+// to a whole k-slice, so that the weight-gradient products need no handling of contraction tails.
 template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mask of the fallback path)
     uint32_t* maskw;
     uint16_t* pref;
@@ -184,9 +189,10 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
         maskw = dense ? nullptr : c.take<uint32_t>((size_t)D.T * D.nw);
         pref = dense ? nullptr : c.take<uint16_t>((size_t)D.T * D.nw);
         dZd = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
-        Zd = c.take<E>((size_t)D.T * D.ldF);
-        dGd = c.take<E>((size_t)D.T * D.ldF);
-        dUd = c.take<E>((size_t)D.T * D.ldF);
+        const size_t rows = (size_t)D.T + kMaxExperts * (kRowPad - 1);
+        Zd = c.take<E>(rows * D.ldF);
+        dGd = c.take<E>(rows * D.ldF);
+        dUd = c.take<E>(rows * D.ldF);
         sk.carve<E>(c, D);
         bytes = c.off;
     }
@@ -244,8 +250,5 @@ template <class E> size_t workspace_for(const Dims& D, int op) {
     }
     return 0;
 }
-
-
-constexpr int kMaxExperts = 8;
 
 }  // namespace mocapi

@@ -21,64 +21,161 @@ using namespace moc;
 // or 0 (one workgroup per tile) with MOC_GEMM_PERSISTENT=0.
 inline int persistent_workgroups() { return options().gemm_persistent ? device_cu_count() : 0; }
 
-template <int BM, int BN, bool AKM, bool BKM, class Epi>
-hipError_t launch_mfma_tail(const MfmaProblem& pr, const Epi& epi, hipStream_t st) {
-    const bool tail = pr.Kc % kMfmaBK != 0 || pr.Kc2 % kMfmaBK != 0;
-    // Four wavefronts, three k-slices in flight from global memory.  Measured over the whole training step:
-    // three slices beat two by 1.3 %, four give nothing more; eight wavefronts (2 x 4) are faster in
-    // isolation at short contractions but 2.5 % slower over the step.
-    if (!tail) return launch_gemm_bf16_mfma<BM, BN, AKM, BKM, 0, Epi, 4, 3>(pr, epi, st, persistent_workgroups());
-    if constexpr (AKM != BKM) {
-        const GemmOperand<bf16_t>& kc = AKM ? pr.B : pr.A;
-        const int kmax = std::max(pr.Kc, pr.Kc2);
-        if (pr.kc_zero_padded && kc.ld >= round_up(kmax, kMfmaBK))
-            return launch_gemm_bf16_mfma<BM, BN, AKM, BKM, 2, Epi, 4, 3>(pr, epi, st, persistent_workgroups());
-    }
-    return launch_gemm_bf16_mfma<BM, BN, AKM, BKM, 1, Epi, 4, 3>(pr, epi, st, persistent_workgroups());
+// Tile shapes of the bf16 matrix-core kernel and what a launch of each costs, in microseconds: `o` once per round of
+// tiles (launch, first loads, epilogue), `lo` .. `hi` per 32-k slice with few .. all compute units busy (the chip is
+// power-limited with the large tiles, so a full round runs slower), `co` per slice and workgroup where several
+// workgroups share a compute unit (`resident` of them; 1 = one persistent workgroup per compute unit).
+// Measured with 64 .. 768 tiles at contractions of 768, 2048 and 5472; the three operand layouts agree within 5 %.
+struct GemmTile {
+    int bm, bn, sets, resident;      // sets: k-slices in flight in registers
+    double o, lo, hi, co;
+};
+constexpr int kGemmTiles = 8;
+constexpr GemmTile kGemmTile[kGemmTiles] = {
+    {256, 256, 3, 1, 12.0, 0.592, 0.851, 0.0}, {256, 192, 3, 1, 11.5, 0.457, 0.680, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
+    {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.283, 0.378, 0.0},  {192, 128, 3, 1, 7.0, 0.290, 0.385, 0.0},
+    {128, 128, 3, 3, 5.7, 0.222, 0.275, 0.275}, {64, 128, 5, 4, 4.7, 0.216, 0.225, 0.200}};
+constexpr unsigned kTilesAll = 0xFF, kTilesBasic = 0x43 /* 256x256, 256x192, 128x128 */, kTilesGroup = 0xCB /* and 256x128, 64x128 */;
+constexpr int kTile128 = 6;
+
+inline double gemm_cost(const GemmTile& t, int64_t tiles, int nk, int cus) {
+    const int64_t n = tiles % cus;
+    const double f = std::max(0.0, ((double)n / cus - 0.25) / 0.75);
+    const double partial = n ? t.o + nk * (t.lo + (t.hi - t.lo) * f * f) : 0.0;      // a round that leaves compute units idle
+    if (t.resident == 1 || tiles <= cus) return (double)(tiles / cus) * (t.o + nk * t.hi) + partial;
+    const double w = 0.6 * tiles / cus + 0.4 * ((tiles + cus - 1) / cus);             // workgroups on the busiest compute unit, softened
+    return 1.5 + t.o * ((tiles + (int64_t)cus * t.resident - 1) / ((int64_t)cus * t.resident)) + nk * t.co * w;
 }
 
-// Runs C = A B^T (+ second segment) with the epilogue `epi`.  AKM / BKM state the operand layouts
-// at compile time (they must match pr.A.km / pr.B.km).  bf16 problems that satisfy the MFMA
-// kernel's assumptions go to the matrix cores, everything else to the generic kernel.
+// The cheapest of the tile shapes in MASK; tiles_of(tile) counts the tiles of the launch.
+template <unsigned MASK, class TilesOf> int choose_tile(const TilesOf& tiles_of, int nk, double* cost_out = nullptr) {
+    const int forced = options().tile == 256 ? 0 : options().tile == 192 ? 1 : options().tile == 128 ? kTile128 : -1;
+    const int cus = std::max(1, device_cu_count());
+    int best = -1;
+    double best_cost = 0.0;
+    for (int c = 0; c < kGemmTiles; ++c) {
+        if (!((MASK >> c) & 1u) || (forced >= 0 && c != forced)) continue;
+        const double cost = gemm_cost(kGemmTile[c], tiles_of(kGemmTile[c]), nk, cus);
+        if (best < 0 || cost < best_cost) { best = c; best_cost = cost; }
+    }
+    if (cost_out) *cost_out = best_cost;
+    return best;
+}
+inline int64_t tile_count(int M, int N, const GemmTile& t) {
+    return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+}
+inline int slice_count(int Kc, int Kc2) { return (Kc + kMfmaBK - 1) / kMfmaBK + (Kc2 + kMfmaBK - 1) / kMfmaBK; }
+
+// f(tile index as a compile-time constant) for the tile shape `t` of MASK.
+template <unsigned MASK, int C = 0, class F> hipError_t with_tile(int t, const F& f) {
+    if constexpr (C < kGemmTiles) {
+        if constexpr ((MASK >> C) & 1u)
+            if (t == C) return f(std::integral_constant<int, C>{});
+        return with_tile<MASK, C + 1>(t, f);
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+// One persistent workgroup per compute unit for the tiles that fill one, a workgroup per tile for the others.
+template <int C> int tile_workgroups() { return kGemmTile[C].resident == 1 ? persistent_workgroups() : 0; }
+
+inline bool gemm_has_tail(const MfmaProblem& pr) { return pr.Kc % kMfmaBK != 0 || pr.Kc2 % kMfmaBK != 0; }
+// Whether a contraction tail can run as "padded" (TAILMODE 2, see gemm_mfma.h).
+inline bool gemm_padded(const MfmaProblem& pr) {
+    return pr.a_zero_padded && pr.B.km && (pr.A.km || pr.A.ld >= round_up(std::max(pr.Kc, pr.Kc2), kMfmaBK));
+}
+
 inline StreamKArgs streamk_args(const StreamKArea& a, int nk) {
     return StreamKArgs{a.part, a.flag, next_streamk_tag(), std::max(1, nk / 8), std::max(0, options().gemm_streamk_spin)};
 }
 inline int streamk_workgroups() { return std::min(persistent_workgroups(), kStreamKSlots) / 8 * 8; }
 
+// Memory of a launch's workspace that holds nothing while a product runs, for the shares of a split contraction.
+struct ShareScratch {
+    float* p = nullptr;
+    size_t bytes = 0;
+};
+
+// C = A B^T with A k-contiguous and padded, B k-major, stored contiguously: where the tiles leave most of the chip idle and
+// the contraction is long, every tile's k-slices are cut into shares that run as workgroups of their own and are summed
+// afterwards.  Worth it when the cost model says so including the shares' way through memory (written and read once at
+// about 4 TB/s) and the second launch; fills `done`.
+template <class E>
+moc_status run_gemm_shares(const char* name, const GemmProblem<E>& pr, const EpiStore<E>& epi, hipStream_t st, const ShareScratch& sc,
+                           double whole_cost, bool* done) {
+    *done = false;
+    if (!sc.p || epi.ldc != epi.N || epi.N != pr.N || epi.N % 4 != 0 || options().tile != 0 || !gemm_padded(pr)) return MOC_OK;
+    const int nk = slice_count(pr.Kc, pr.Kc2), cus = std::max(1, device_cu_count());
+    const int64_t out = (int64_t)pr.M * pr.N;
+    constexpr unsigned kMask = 0xE0;      // 192x128, 128x128, 64x128
+    int best = -1, shares = 0;
+    double best_cost = 0.95 * whole_cost;
+    for (int c = 5; c < kGemmTiles; ++c)
+        for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= sc.bytes; ++z) {
+            const double cost = gemm_cost(kGemmTile[c], z * tile_count(pr.M, pr.N, kGemmTile[c]), (nk + z - 1) / z, cus) + 3.5 +
+                                (8.0 * z + sizeof(E)) * out / 4.0e6;
+            if (cost < best_cost) { best = c; best_cost = cost; shares = z; }
+        }
+    if (best < 0) return MOC_OK;
+    const EpiShare es{sc.p, pr.N, out, pr.N};
+    hipError_t e = with_tile<kMask>(best, [&](auto c) {
+        constexpr GemmTile t = kGemmTile[decltype(c)::value];
+        return launch_gemm_bf16_mfma_split<t.bm, t.bn, false, true, 2, EpiShare, 4, t.sets>(pr, es, shares, st);
+    });
+    if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+    const int64_t n4 = out / 4;
+    hipLaunchKernelGGL((reduce_shares_kernel<E>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, sc.p, shares, out, n4, epi.C);
+    HIP_TRY(hipGetLastError());
+    *done = true;
+    return MOC_OK;
+}
+
+// Runs C = A B^T (+ second segment) with the epilogue `epi`.  AKM / BKM state the operand layouts
+// at compile time (they must match pr.A.km / pr.B.km).  bf16 and fp32 problems that satisfy the assumptions of a matrix-core
+// kernel go there, everything else to the generic kernel.
 // `sk`, if given and carved, lets a product whose whole tiles would leave part of the chip idle in their last
-// round split its work along the contraction instead (256 x 256 tiles, contraction a multiple of 32).
+// round split its work along the contraction instead (256 x 256 tiles, contraction a multiple of 32); `scratch` is memory for
+// run_gemm_shares; `ascending` see launch_gemm_f32.
 template <class E, bool AKM, bool BKM, class Epi>
 moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, hipStream_t st, const StreamKArea* sk = nullptr,
-                    bool ascending = false) {
+                    bool ascending = false, const ShareScratch& scratch = ShareScratch{}) {
     Span span(name, st);
-    if constexpr (std::is_same<E, bf16_t>::value) {
+    if constexpr (std::is_same<E, bf16_t>::value && !(AKM && BKM)) {      // (k-major x k-major products: run_gemm_batch3, run_gemm_grouped)
         if (!options().force_generic && mfma_problem_ok(pr)) {
-            if (sk && sk->part && options().gemm_streamk && options().tile == 0 && pr.Kc % kMfmaBK == 0 && pr.Kc2 % kMfmaBK == 0) {
-                const int64_t tiles = (int64_t)((pr.M + 255) / 256) * ((pr.N + 255) / 256);
-                const int nk = (pr.Kc + pr.Kc2) / kMfmaBK, wgs = streamk_workgroups();
-                if (streamk_pays(tiles, nk, wgs)) {
+            const int nk = slice_count(pr.Kc, pr.Kc2);
+            const bool tail = gemm_has_tail(pr), padded = gemm_padded(pr);
+            if (sk && sk->part && options().gemm_streamk && options().tile == 0 && !tail) {
+                const int wgs = streamk_workgroups();
+                if (streamk_pays(tile_count(pr.M, pr.N, kGemmTile[0]), nk, wgs)) {
                     hipError_t e = launch_gemm_bf16_mfma_streamk<256, 256, AKM, BKM, 0, Epi, 4, 3>(pr, epi, streamk_args(*sk, nk), wgs, st);
                     if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
                     return MOC_OK;
                 }
             }
-            // tile shape: fewest rounds of workgroups over the 256 CUs, weighted by tile area and the
-            // measured efficiency of the smaller shapes (they stage more LDS bytes per FLOP)
-            struct Cand { int bm, bn; double penalty; };
-            static const Cand cands[3] = {{256, 256, 1.0}, {256, 192, 1.15}, {128, 128, 1.6}};
-            int best = 0;
-            double best_cost = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                const int64_t tiles = (int64_t)((pr.M + cands[c].bm - 1) / cands[c].bm) * ((pr.N + cands[c].bn - 1) / cands[c].bn);
-                const double cost = (double)((tiles + 255) / 256) * cands[c].bm * cands[c].bn * cands[c].penalty;
-                if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
+            constexpr bool kStore = std::is_same<Epi, EpiStore<bf16_t>>::value || std::is_same<Epi, EpiStore<float>>::value;
+            constexpr unsigned kMask = kStore ? kTilesAll : kTilesBasic;
+            double cost = 0.0;
+            const int best = choose_tile<kMask>([&](const GemmTile& t) { return tile_count(pr.M, pr.N, t); }, nk, &cost);
+            if constexpr (!AKM && BKM && std::is_same<Epi, EpiStore<E>>::value) {
+                bool done;
+                moc_status s = run_gemm_shares<E>(name, pr, epi, st, scratch, cost, &done);
+                if (s != MOC_OK || done) return s;
             }
-            if (options().tile == 256) best = 0;
-            if (options().tile == 192) best = 1;
-            if (options().tile == 128) best = 2;
-            hipError_t e = best == 0   ? launch_mfma_tail<256, 256, AKM, BKM, Epi>(pr, epi, st)
-                           : best == 1 ? launch_mfma_tail<256, 192, AKM, BKM, Epi>(pr, epi, st)
-                                       : launch_mfma_tail<128, 128, AKM, BKM, Epi>(pr, epi, st);
+            hipError_t e;
+            if (!tail)
+                e = with_tile<kMask>(best, [&](auto c) {
+                    constexpr int C = decltype(c)::value;
+                    constexpr GemmTile t = kGemmTile[C];
+                    return launch_gemm_bf16_mfma<t.bm, t.bn, AKM, BKM, 0, Epi, 4, t.sets>(pr, epi, st, tile_workgroups<C>());
+                });
+            else if (BKM && padded)
+                e = with_tile<kMask>(best, [&](auto c) {
+                    constexpr int C = decltype(c)::value;
+                    constexpr GemmTile t = kGemmTile[C];
+                    return launch_gemm_bf16_mfma<t.bm, t.bn, AKM, BKM, BKM ? 2 : 1, Epi, 4, t.sets>(pr, epi, st, tile_workgroups<C>());
+                });
+            else      // a contraction tail without padding: only d % 32 != 0, which no model has
+                e = launch_gemm_bf16_mfma<128, 128, AKM, BKM, 1, Epi, 4, 3>(pr, epi, st);
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -96,43 +193,38 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
 }
 
 // Three independent products of one shape (both operands k-major, plain stores) in one launch when
-// the MFMA kernel takes them; otherwise one run_gemm each.  Same tile choice as run_gemm, over the
+// a matrix-core kernel takes them; otherwise one run_gemm each.  Same tile choice as run_gemm, over the
 // tiles of all three.
 template <class E>
 moc_status run_gemm_batch3(const char* name, const char* const names[3], const GemmProblem<E> pr[3], const EpiStore<E> epi[3],
                            hipStream_t st, const StreamKArea* sk = nullptr) {
     if constexpr (std::is_same<E, bf16_t>::value) {
         const bool same = pr[0].M == pr[1].M && pr[0].M == pr[2].M && pr[0].N == pr[1].N && pr[0].N == pr[2].N &&
-                          pr[0].Kc == pr[1].Kc && pr[0].Kc == pr[2].Kc && pr[0].Kc % kMfmaBK == 0 && pr[0].Kc2 == 0 &&
-                          pr[1].Kc2 == 0 && pr[2].Kc2 == 0;
-        if (same && !options().force_generic && mfma_problem_ok(pr[0]) && mfma_problem_ok(pr[1]) && mfma_problem_ok(pr[2])) {
-            struct Cand { int bm, bn; double penalty; };
-            static const Cand cands[3] = {{256, 256, 1.0}, {256, 192, 1.15}, {128, 128, 1.6}};
-            int best = 0;
-            double best_cost = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                const int64_t tiles = 3 * (int64_t)((pr[0].M + cands[c].bm - 1) / cands[c].bm) * ((pr[0].N + cands[c].bn - 1) / cands[c].bn);
-                const double cost = (double)((tiles + 255) / 256) * cands[c].bm * cands[c].bn * cands[c].penalty;
-                if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
-            }
-            if (options().tile == 256) best = 0;
-            if (options().tile == 192) best = 1;
-            if (options().tile == 128) best = 2;
+                          pr[0].Kc == pr[1].Kc && pr[0].Kc == pr[2].Kc && pr[0].Kc2 == 0 && pr[1].Kc2 == 0 && pr[2].Kc2 == 0;
+        const bool tail = gemm_has_tail(pr[0]);
+        const bool padded = gemm_padded(pr[0]) && gemm_padded(pr[1]) && gemm_padded(pr[2]);
+        if (same && (!tail || padded) && !options().force_generic && mfma_problem_ok(pr[0]) && mfma_problem_ok(pr[1]) && mfma_problem_ok(pr[2])) {
+            const int nk = slice_count(pr[0].Kc, 0);
+            const int best = choose_tile<kTilesAll>([&](const GemmTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); }, nk);
             MfmaBatch<EpiStore<E>, 3> b;
             for (int i = 0; i < 3; ++i) { b.pr[i] = pr[i]; b.epi[i] = epi[i]; }
             Span span(name, st);
-            if (sk && sk->part && options().gemm_streamk && options().tile == 0) {
-                const int64_t tiles = 3 * (int64_t)((pr[0].M + 255) / 256) * ((pr[0].N + 255) / 256);
-                const int nk = pr[0].Kc / kMfmaBK, wgs = streamk_workgroups();
-                if (streamk_pays(tiles, nk, wgs)) {
+            if (sk && sk->part && options().gemm_streamk && options().tile == 0 && !tail) {
+                const int wgs = streamk_workgroups();
+                if (streamk_pays(3 * tile_count(pr[0].M, pr[0].N, kGemmTile[0]), nk, wgs)) {
                     hipError_t e = launch_gemm_bf16_mfma_batch_streamk<256, 256, true, true, 0, EpiStore<E>, 3, 4, 3>(b, streamk_args(*sk, nk), wgs, st);
                     if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
                     return MOC_OK;
                 }
             }
-            hipError_t e = best == 0   ? launch_gemm_bf16_mfma_batch<256, 256, true, true, 0, EpiStore<E>, 3, 4, 3>(b, st, persistent_workgroups())
-                           : best == 1 ? launch_gemm_bf16_mfma_batch<256, 192, true, true, 0, EpiStore<E>, 3, 4, 3>(b, st, persistent_workgroups())
-                                       : launch_gemm_bf16_mfma_batch<128, 128, true, true, 0, EpiStore<E>, 3, 4, 3>(b, st, persistent_workgroups());
+            auto launch = [&](auto mode) {
+                return with_tile<kTilesAll>(best, [&](auto c) {
+                    constexpr int C = decltype(c)::value;
+                    constexpr GemmTile t = kGemmTile[C];
+                    return launch_gemm_bf16_mfma_batch<t.bm, t.bn, true, true, decltype(mode)::value, EpiStore<E>, 3, 4, t.sets>(b, st, tile_workgroups<C>());
+                });
+            };
+            const hipError_t e = tail ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 0>{});
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -161,33 +253,20 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
     if constexpr (std::is_same<E, bf16_t>::value) {
         const bool same = pa.M == pb.M && pa.N == pb.N && pa.Kc == pb.Kc && pa.Kc % kMfmaBK == 0 && pa.Kc2 == 0 && pb.Kc2 == 0;
         if (same && !options().force_generic && mfma_problem_ok(pa) && mfma_problem_ok(pb)) {
-            struct Cand { int bm, bn; double penalty; };
-            static const Cand cands[3] = {{256, 256, 1.0}, {256, 192, 1.15}, {128, 128, 1.6}};
-            int best = 0;
-            double best_cost = 0.0, best_single = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                const int64_t tiles = (int64_t)((pa.M + cands[c].bm - 1) / cands[c].bm) * ((pa.N + cands[c].bn - 1) / cands[c].bn);
-                const double unit = (double)cands[c].bm * cands[c].bn * cands[c].penalty;
-                const double cost = (double)((2 * tiles + 255) / 256) * unit;
-                const double single = (double)((tiles + 255) / 256) * unit;
-                if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
-                if (c == 0 || single < best_single) best_single = single;
+            const int nk = slice_count(pa.Kc, 0);
+            double cost = 0.0, single = 0.0;
+            const int best = choose_tile<kTilesAll>([&](const GemmTile& t) { return 2 * tile_count(pa.M, pa.N, t); }, nk, &cost);
+            (void)choose_tile<kTilesAll>([&](const GemmTile& t) { return tile_count(pa.M, pa.N, t); }, nk, &single);
+            // one launch when the two together cost less than apart, which they do unless both fill whole rounds of tiles
+            if (cost < 2.0 * single) {
+                Span span(name, st);
+                const hipError_t e = with_tile<kTilesAll>(best, [&](auto c) {
+                    constexpr GemmTile t = kGemmTile[decltype(c)::value];
+                    return launch_gemm_bf16_mfma_pair<t.bm, t.bn, false, false, 0, EpiA, EpiB, 4, t.sets>(pa, ea, pb, eb, st);
+                });
+                if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                return MOC_OK;
             }
-            if (options().tile == 256) best = 0;
-            if (options().tile == 192) best = 1;
-            if (options().tile == 128) best = 2;
-            // worth one launch only when the two together need fewer rounds of workgroups than apart
-            if (!(best_cost < 2.0 * best_single)) {
-                moc_status s = run_gemm<E, false, false>(name_a, pa, ea, st, sk);
-                if (s != MOC_OK) return s;
-                return run_gemm<E, false, false>(name_b, pb, eb, st, sk);
-            }
-            Span span(name, st);
-            hipError_t e = best == 0   ? launch_gemm_bf16_mfma_pair<256, 256, false, false, 0, EpiA, EpiB, 4, 3>(pa, ea, pb, eb, st)
-                           : best == 1 ? launch_gemm_bf16_mfma_pair<256, 192, false, false, 0, EpiA, EpiB, 4, 3>(pa, ea, pb, eb, st)
-                                       : launch_gemm_bf16_mfma_pair<128, 128, false, false, 0, EpiA, EpiB, 4, 3>(pa, ea, pb, eb, st);
-            if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
-            return MOC_OK;
         }
     }
     if constexpr (std::is_same<E, float>::value && std::is_same<EpiA, EpiB>::value) {
@@ -211,41 +290,38 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
     if constexpr (std::is_same<E, bf16_t>::value) {
         bool ok = !options().force_generic && nprob <= NB;
         bool tail = false, padded = true;
-        int64_t total_m = 0;
+        int64_t total_m = 0, slices = 0;
         for (int z = 0; z < nprob && ok; ++z) {
             if (pr[z].M == 0) continue;
             ok = mfma_problem_ok(pr[z]) && pr[z].N == pr[0].N && (pr[z].Kc2 == 0) == (pr[0].Kc2 == 0);
-            tail = tail || pr[z].Kc % kMfmaBK != 0 || pr[z].Kc2 % kMfmaBK != 0;
-            const GemmOperand<bf16_t>& kc = AKM ? pr[z].B : pr[z].A;
-            padded = padded && pr[z].kc_zero_padded && kc.ld >= round_up(std::max(pr[z].Kc, pr[z].Kc2), kMfmaBK);
+            tail = tail || gemm_has_tail(pr[z]);
+            padded = padded && gemm_padded(pr[z]);
             total_m += pr[z].M;
+            slices += (int64_t)pr[z].M * slice_count(pr[z].Kc, pr[z].Kc2);
         }
-        if (ok && total_m > 0) {
-            struct Cand { int bm, bn; double penalty; };
-            static const Cand cands[3] = {{256, 256, 1.0}, {256, 192, 1.15}, {128, 128, 1.6}};
-            int best = 0;
-            double best_cost = 0.0;
-            for (int c = 0; c < 3; ++c) {
+        if (ok && total_m > 0 && !(BKM && tail && !padded)) {
+            const int best = choose_tile<kTilesGroup>([&](const GemmTile& t) {
                 int64_t tiles = 0;
-                for (int z = 0; z < nprob; ++z)
-                    tiles += (int64_t)((pr[z].M + cands[c].bm - 1) / cands[c].bm) * ((pr[0].N + cands[c].bn - 1) / cands[c].bn);
-                const double cost = (double)((tiles + 255) / 256) * cands[c].bm * cands[c].bn * cands[c].penalty;
-                if (c == 0 || cost < best_cost) { best = c; best_cost = cost; }
-            }
-            if (options().tile == 256) best = 0;
-            if (options().tile == 192) best = 1;
-            if (options().tile == 128) best = 2;
+                for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
+                return tiles;
+            }, (int)(slices / total_m));
             MfmaGroup<Epi, NB> g;
             for (int z = 0; z < nprob; ++z) { g.pr[z] = pr[z]; g.epi[z] = epi[z]; }
-            const int mode = !tail ? 0 : ((AKM != BKM && padded) ? 2 : 1);
             Span span(name, st);
-            hipError_t e = hipSuccess;
-#define MOC_GROUP_LAUNCH(BM_, BN_)                                                                                          \
-    (mode == 0   ? launch_gemm_bf16_mfma_group<BM_, BN_, AKM, BKM, 0, Epi, NB, 4, 3>(g, nprob, st)                            \
-     : mode == 2 ? launch_gemm_bf16_mfma_group<BM_, BN_, AKM, BKM, (AKM != BKM ? 2 : 1), Epi, NB, 4, 3>(g, nprob, st)        \
-                 : launch_gemm_bf16_mfma_group<BM_, BN_, AKM, BKM, 1, Epi, NB, 4, 3>(g, nprob, st))
-            e = best == 0 ? MOC_GROUP_LAUNCH(256, 256) : best == 1 ? MOC_GROUP_LAUNCH(256, 192) : MOC_GROUP_LAUNCH(128, 128);
-#undef MOC_GROUP_LAUNCH
+            hipError_t e;
+            if constexpr (BKM) {
+                // (the padded mode also serves contractions without a tail: one set of kernels)
+                e = with_tile<kTilesGroup>(best, [&](auto c) {
+                    constexpr GemmTile t = kGemmTile[decltype(c)::value];
+                    return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 2, Epi, NB, 4, t.sets>(g, nprob, st);
+                });
+            } else {
+                e = tail ? launch_gemm_bf16_mfma_group<128, 128, AKM, BKM, 1, Epi, NB, 4, 3>(g, nprob, st)
+                         : with_tile<kTilesGroup>(best, [&](auto c) {
+                               constexpr GemmTile t = kGemmTile[decltype(c)::value];
+                               return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 0, Epi, NB, 4, t.sets>(g, nprob, st);
+                           });
+            }
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -336,9 +412,9 @@ inline moc_status launch_key_transform(const float* g, float* keys, int64_t n, i
 
 // D = Z' W_down (Eq. MoC-2 / FFN-2): Z' is [T, ldF] with zeros past F, W_down [F, d] is read k-major.
 template <class E>
-moc_status down_projection(const Dims& D, const E* Zd, const E* wd, E* y, hipStream_t st) {
+moc_status down_projection(const Dims& D, const E* Zd, const E* wd, E* y, hipStream_t st, const ShareScratch& scratch = ShareScratch{}) {
     GemmProblem<E> pr{kc_operand<E>(Zd, D.ldF), km_operand<E>(wd, D.d, D.d), D.T, D.d, D.F, 0, true};
-    return run_gemm<E, false, true>("gemm_down", pr, EpiStore<E>{y, D.d, D.d, 0}, st);
+    return run_gemm<E, false, true>("gemm_down", pr, EpiStore<E>{y, D.d, D.d, 0}, st, nullptr, false, scratch);
 }
 
 }  // namespace mocapi

@@ -40,6 +40,29 @@ template <class OutT> struct EpiStore {
     }
 };
 
+// Sums of one share of a product whose contraction is split: fp32 [M, ldc] per share, share z at C + z * stride.
+struct EpiShare {
+    float* C;
+    int64_t ldc, stride;
+    int N;
+    __device__ __forceinline__ EpiShare share(int z) const { return EpiShare{C + z * stride, ldc, stride, N}; }
+    __device__ __forceinline__ void store4(int m, int n0, const float v[4]) const {      // N and ldc are multiples of 4
+        if (n0 < N) *reinterpret_cast<f32x4_t*>(C + (int64_t)m * ldc + n0) = f32x4_t{v[0], v[1], v[2], v[3]};
+    }
+};
+
+// out = sum over the shares, in a fixed order; n4 groups of four elements, contiguous.  Bound by reading the shares.
+template <class E>
+__global__ __launch_bounds__(256) void reduce_shares_kernel(const float* __restrict__ part, int nsplit, int64_t stride, int64_t n4,
+                                                            E* __restrict__ out) {
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= n4) return;
+    f32x4_t s = *reinterpret_cast<const f32x4_t*>(part + i * 4);
+    for (int z = 1; z < nsplit; ++z) s += *reinterpret_cast<const f32x4_t*>(part + z * stride + i * 4);
+    const float v[4] = {s[0], s[1], s[2], s[3]};
+    store_vec4<E>(out + i * 4, v);
+}
+
 // Dense SwiGLU forward, second GEMM (m = token, n = channel): acc = U.  Reads the stored gate,
 // writes u_save and the dense activation Z = SiLU(G) . U (Eq. FFN-2) padded with zeros to ldz.
 template <class E> struct EpiSwigluAct {

@@ -21,16 +21,17 @@
 // a lane ends up with four consecutive n for one m -- the shape the epilogues want.
 //
 // Requirements checked by the host: 16-byte aligned bases, leading dimensions multiples of 8,
-// contraction lengths >= 32; a KM operand must be readable up to `ext` columns (multiple of 8).
+// contraction lengths >= 32 (>= 1 in TAILMODE 2); a KM operand must be readable up to `ext` columns (multiple of 8).
 // Contraction lengths that are not multiples of 32 take one of two tail modes:
-//   TAILMODE 2 ("padded"): one operand is KC, readable and zero up to the next multiple of 32
-//     (the library's own dense intermediates are), the other is KM: the KM k-rows past the end
+//   TAILMODE 2 ("padded"): A is readable and zero up to the next multiple of 32 (the library's own dense
+//     intermediates are, along the channels as along the tokens), B is KM: the B k-rows past the end
 //     are clamped to the last row and meet those zeros.  Nearly free.
 //   TAILMODE 1 (general): the last slice re-reads the final 32-wide window (8-aligned, so a KC
 //     operand must be readable and zero up to the next multiple of 8) and zeroes what lies
 //     before the part still to be accumulated or past the end; KM rows are clamped as well.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "gemm_generic.h"
@@ -104,6 +105,12 @@ template <int R, int N, int RA, int RB, int NR, int WA, int WB, int NW, int VA, 
     }
 };
 
+// f(0), f(1), ... f(N - 1) with the index as a compile-time constant.
+template <int N, class F, int... I> __device__ __forceinline__ void static_for_impl(const F& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(const F& f) { static_for_impl<N>(f, std::make_integer_sequence<int, N>{}); }
+
 // Workgroup g of `total` runs on XCD g % 8.  Gives every XCD a contiguous range of the logical work
 // items 0 .. total-1, so that neighbouring items (tiles that share operand panels) meet in one L2.
 __device__ __forceinline__ int xcd_contiguous_index(int g, int total) {
@@ -173,10 +180,12 @@ __device__ __forceinline__ int streamk_start(int r, int ranks, int units, int nk
 // global loads of the next tile's first two k-slices before it writes the current tile out, so that the
 // epilogue and the next prologue overlap; one barrier separates the epilogue's use of the stage memory
 // from the next tile's staging.
-template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV, int NSETS, bool SK = false, bool MULTI = true>
+// SPLIT: the items are `nsplit` times the tiles of one problem, and copy z of a tile multiplies the z-th share of its
+// k-slices and hands its sums to epis[0].share(z).
+template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV, int NSETS, bool SK = false, bool MULTI = true, bool SPLIT = false>
 __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, const Epi* epis, int tiles_m, int tiles_n,
                                                      int item_first, int item_stride, int item_total, bool xcd_map,
-                                                     const StreamKArgs* sk = nullptr) {
+                                                     const StreamKArgs* sk = nullptr, int nsplit = 1) {
     using Cfg = MfmaCfg<BM, BN, AKM, BKM>;
     using TA = typename Cfg::TA;
     using TB = typename Cfg::TB;
@@ -229,7 +238,7 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
         const int mapped = (xcd_map && !SK) ? xcd_contiguous_index(item, item_total) : item;
         z = mapped / nblk;
         const int logical = mapped - z * nblk;
-        const MfmaProblem& pr = prs[z];
+        const MfmaProblem& pr = prs[SPLIT ? 0 : z];
         // band height, measured: at the 1B shape (22 tile columns) heights 2 / 4 / 6 / 8 / 16 give 1.591 / 1.596 / 1.599 / 1.605 /
         // 1.619 ms per layer step and 425 / 280 / 312 / 291 / 463 MB beyond L2 for the gate product; at the 7B shape (43 tile
         // columns) 8 is ahead of 4 and 2 (gate + up 1.285 / 1.294 / 1.299 ms)
@@ -246,8 +255,8 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
         t.Kc = pr.Kc; t.Kc2 = pr.Kc2;
         t.nk0 = (pr.Kc + BK - 1) / BK;
         t.nk = t.nk0 + (pr.Kc2 + BK - 1) / BK;
-        t.ks = 0;
-        t.ke = t.nk;
+        t.ks = SPLIT ? t.nk * z / nsplit : 0;
+        t.ke = SPLIT ? t.nk * (z + 1) / nsplit : t.nk;
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int c = tid + i * NT;
@@ -282,7 +291,7 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             int off = t.a_off[i];
-            if (AKM) off += (TAILMODE ? min(a_k[i] * t.lda, klast * t.lda) : a_k[i] * t.lda);
+            if (AKM) off += (TAILMODE == 1 ? min(a_k[i] * t.lda, klast * t.lda) : a_k[i] * t.lda);
             // uniform base + unsigned 32-bit byte offset: the load takes the base from scalar registers
             ga[buf][i] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(ap) + (uint32_t)off * 2u);
             if (TAILMODE == 1) {
@@ -467,16 +476,10 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
         };
         const int nk = cur.ke - cur.ks;
         int kt = 0;
-        for (; kt + NSETS <= nk; kt += NSETS) {
-            slice(std::integral_constant<int, 0>{}, kt);
-            slice(std::integral_constant<int, 1>{}, kt + 1);
-            if constexpr (NSETS > 2) slice(std::integral_constant<int, 2>{}, kt + 2);
-            if constexpr (NSETS > 3) slice(std::integral_constant<int, 3>{}, kt + 3);
-        }
-        if (kt < nk) slice(std::integral_constant<int, 0>{}, kt++);
-        if (kt < nk) slice(std::integral_constant<int, 1>{}, kt++);
-        if constexpr (NSETS > 3)
-            if (kt < nk) slice(std::integral_constant<int, 2>{}, kt++);
+        for (; kt + NSETS <= nk; kt += NSETS) static_for<NSETS>([&](auto i) { slice(i, kt + i); });
+        static_for<NSETS - 1>([&](auto i) {
+            if (kt + i < nk) slice(i, kt + i);
+        });
 
         // ---- the next tile's first two slices go out before this tile is written
         int next_item = item + item_stride;
@@ -522,7 +525,10 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
         //      Wave tiles whose row segments do not divide the 64 lanes (96 columns: 24 lanes per row,
         //      16 lanes idle) store straight from the accumulator layout instead, which measured faster
         //      for them: 16 or 32 contiguous bytes per row and store instruction.
-        const Epi& epi = epis[zc];
+        const auto epi = [&] {
+            if constexpr (SPLIT) return epis[0].share(zc);
+            else return epis[zc];
+        }();
         const int M = cur.M, m0 = cur.m0, n0 = cur.n0;
         constexpr bool kDirectStores = 64 % (WN / 4) != 0;
         if (SK && contributed) {
@@ -594,6 +600,14 @@ template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV =
 __global__ __launch_bounds__(NWV * 64) void gemm_bf16_mfma_kernel(MfmaProblem pr, int tiles_m, int tiles_n, Epi epi) {
     gemm_bf16_mfma_tiles<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS>(&pr, &epi, tiles_m, tiles_n, blockIdx.x, gridDim.x,
                                                                       tiles_m * tiles_n, true);
+}
+
+// One problem with every tile's contraction cut into nsplit shares of whole k-slices (each at least one slice), for
+// products whose tiles alone leave most of the chip idle; the shares are summed by reduce_shares_kernel (epilogue.h).
+template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV = 4, int NSETS = 2>
+__global__ __launch_bounds__(NWV * 64) void gemm_bf16_mfma_split_kernel(MfmaProblem pr, int tiles_m, int tiles_n, int nsplit, Epi epi) {
+    gemm_bf16_mfma_tiles<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS, false, false, true>(&pr, &epi, tiles_m, tiles_n, blockIdx.x, 1 << 30,
+                                                                                          tiles_m * tiles_n * nsplit, true, nullptr, nsplit);
 }
 
 // The same with the work split along k (see StreamKArgs); the grid is a multiple of 8 workgroups, all resident.
@@ -670,7 +684,8 @@ inline bool mfma_problem_ok(const MfmaProblem& p) {
         return ok;
     };
     const bool two = p.Kc2 != 0;
-    bool ok = p.M >= 1 && p.N >= 1 && p.Kc >= kMfmaBK && (!two || p.Kc2 >= kMfmaBK);
+    const int kmin = p.a_zero_padded && p.B.km ? 1 : kMfmaBK;
+    bool ok = p.M >= 1 && p.N >= 1 && p.Kc >= kmin && (!two || p.Kc2 >= kmin);
     return ok && operand_ok(p.A, p.M, two) && operand_ok(p.B, p.N, two);
 }
 
@@ -683,13 +698,23 @@ inline int mfma_grid(int tiles, int persistent_wgs) {
 
 template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV = 4, int NSETS = 2>
 inline hipError_t launch_gemm_bf16_mfma(const MfmaProblem& p, const Epi& epi, hipStream_t st, int persistent_wgs = 0) {
-    static_assert(NSETS >= 2 && NSETS <= 4, "two to four slices in flight");
+    static_assert(NSETS >= 2, "at least two slices in flight");
     using Cfg = MfmaCfg<BM, BN, AKM, BKM>;
     auto kern = gemm_bf16_mfma_kernel<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS>;
     LdsAttr<gemm_bf16_mfma_kernel<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS>, Cfg::kLds>::use();      // attribute set at library set-up
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     hipLaunchKernelGGL(kern, dim3(mfma_grid(tiles_m * tiles_n, persistent_wgs)), dim3(NWV * 64), Cfg::kLds, st, p, tiles_m,
                        tiles_n, epi);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, bool AKM, bool BKM, int TAILMODE, class Epi, int NWV = 4, int NSETS = 2>
+inline hipError_t launch_gemm_bf16_mfma_split(const MfmaProblem& p, const Epi& epi, int nsplit, hipStream_t st) {
+    using Cfg = MfmaCfg<BM, BN, AKM, BKM>;
+    auto kern = gemm_bf16_mfma_split_kernel<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS>;
+    LdsAttr<gemm_bf16_mfma_split_kernel<BM, BN, AKM, BKM, TAILMODE, Epi, NWV, NSETS>, Cfg::kLds>::use();
+    const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * nsplit), dim3(NWV * 64), Cfg::kLds, st, p, tiles_m, tiles_n, nsplit, epi);
     return hipGetLastError();
 }
 

@@ -55,23 +55,42 @@ static __global__ __launch_bounds__(256) void build_mask_kernel(const int32_t* _
 // z' = s u and forms du = s dz', dg = u dz' SiLU'(g) (Eqs. bp-1 ... bp-3, S' and Z' recomputed from
 // the stored G.M as in MoC+GCP).  The three rows z', dg, du are assembled in LDS -- zero everywhere
 // except at the K selected channels -- and streamed out with 16-byte stores, padding included.
+// One workgroup per row of the dense operands, in which every expert's tokens are followed by zero rows (see RowGroups);
+// dz' has one row per token.
+struct RowGroups {                  // group e: tokens tok[e] .. tok[e + 1] - 1 at dense rows row[e] .., zero rows up to row[e + 1]
+    int n;
+    int tok[9], row[9];
+};
+// token of dense row r, or -1 for a zero row
+__device__ __forceinline__ int row_token(const RowGroups& g, int r) {
+    int e = 0;
+    while (e + 1 < g.n && r >= g.row[e + 1]) ++e;
+    const int t = g.tok[e] + r - g.row[e];
+    return t < g.tok[e + 1] ? t : -1;
+}
+// zero rows of [rows, ldf] arrays whose other rows something else fills (the epilogue forms of the pointwise step)
+template <class E> __global__ __launch_bounds__(256) void zero_rows_kernel(int row0, int64_t ldf, E* __restrict__ a, E* __restrict__ b, E* __restrict__ c) {
+    const int64_t off = (row0 + (int64_t)blockIdx.x) * ldf;
+    for (int i = threadIdx.x; i < ldf; i += 256) a[off + i] = b[off + i] = c[off + i] = E(0);
+}
+
 template <class E>
 __global__ __launch_bounds__(256) void bwd_expand_kernel(const int32_t* __restrict__ idx, const E* __restrict__ gvals,
                                                          const E* __restrict__ uvals, const E* __restrict__ dzd,
-                                                         int K, int F, int64_t ldf, E* __restrict__ zd,
+                                                         RowGroups groups, int K, int F, int64_t ldf, E* __restrict__ zd,
                                                          E* __restrict__ dgd, E* __restrict__ dud) {
     extern __shared__ __align__(16) unsigned char exp_smem[];
     E* rz = reinterpret_cast<E*>(exp_smem);
     E* rg = rz + ldf;
     E* ru = rg + ldf;
     const int tid = threadIdx.x;
-    const int64_t t = blockIdx.x;
+    const int64_t t = row_token(groups, blockIdx.x);
     constexpr int PER16 = 16 / sizeof(E);
     const int nvec = (int)(3 * ldf) / PER16;
     for (int i = tid; i < nvec; i += 256) reinterpret_cast<u32x4_t*>(exp_smem)[i] = u32x4_t{0, 0, 0, 0};
     __syncthreads();
     const E* dzrow = dzd + t * ldf;
-    for (int s = tid; s < K; s += 256) {
+    for (int s = tid; s < (t < 0 ? 0 : K); s += 256) {
         const int j = idx[t * K + s];
         if (j < 0 || j >= F) continue;
         const float g = Elem<E>::load(gvals + t * K + s);
@@ -85,9 +104,9 @@ __global__ __launch_bounds__(256) void bwd_expand_kernel(const int32_t* __restri
     }
     __syncthreads();
     const int rowvec = (int)ldf / PER16;
-    u32x4_t* oz = reinterpret_cast<u32x4_t*>(zd + t * ldf);
-    u32x4_t* og = reinterpret_cast<u32x4_t*>(dgd + t * ldf);
-    u32x4_t* ou = reinterpret_cast<u32x4_t*>(dud + t * ldf);
+    u32x4_t* oz = reinterpret_cast<u32x4_t*>(zd + blockIdx.x * ldf);
+    u32x4_t* og = reinterpret_cast<u32x4_t*>(dgd + blockIdx.x * ldf);
+    u32x4_t* ou = reinterpret_cast<u32x4_t*>(dud + blockIdx.x * ldf);
     const u32x4_t* lz = reinterpret_cast<const u32x4_t*>(rz);
     const u32x4_t* lg = reinterpret_cast<const u32x4_t*>(rg);
     const u32x4_t* lu = reinterpret_cast<const u32x4_t*>(ru);

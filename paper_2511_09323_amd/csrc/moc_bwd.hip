@@ -9,6 +9,19 @@ using namespace mocapi;
 
 namespace {
 
+// Dense rows of n groups of tokens off[0] .. off[n], each padded to whole k-slices.
+RowGroups row_groups(int n, const int32_t* off) {
+    RowGroups g;
+    g.n = n;
+    g.row[0] = 0;
+    g.tok[0] = off[0];
+    for (int e = 0; e < n; ++e) {
+        g.tok[e + 1] = off[e + 1];
+        g.row[e + 1] = g.row[e] + round_up(off[e + 1] - off[e], kRowPad);
+    }
+    return g;
+}
+
 // ---------------------------------------------------------------------------- backward
 template <class E, bool DENSE>
 moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E* wd, const int32_t* idx,
@@ -26,8 +39,9 @@ moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
         auto kern = bwd_expand_kernel<E>;
         LdsAttr<bwd_expand_kernel<E>, kMaxDynLds>::use();
         Span span("bwd_pointwise_expand", st);
-        hipLaunchKernelGGL(kern, dim3(D.T), dim3(256), expand_lds, st, idx, gvals, uvals, W.dZd, D.K, D.F,
-                           (int64_t)D.ldF, W.Zd, W.dGd, W.dUd);
+        const int32_t off[2] = {0, D.T};
+        hipLaunchKernelGGL(kern, dim3(round_up(D.T, kRowPad)), dim3(256), expand_lds, st, idx, gvals, uvals, W.dZd, row_groups(1, off), D.K,
+                           D.F, (int64_t)D.ldF, W.Zd, W.dGd, W.dUd);
         HIP_TRY(hipGetLastError());
     } else {
         if (!DENSE) {
@@ -39,20 +53,26 @@ moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
         // dZ' = dD W_down^T (bp-1) with the pointwise part (bp-2, bp-3) in the epilogue
         EpiBwdPointwise<E, DENSE> epi{W.maskw, W.pref, D.nw, gvals, uvals, DENSE ? D.F : D.K, W.Zd, W.dGd, W.dUd, D.F, D.ldF};
         if ((s = run_gemm<E, false, false>("gemm_dz_pointwise", pz, epi, st)) != MOC_OK) return s;
+        if (D.T % kRowPad != 0) {
+            hipLaunchKernelGGL((zero_rows_kernel<E>), dim3(round_up(D.T, kRowPad) - D.T), dim3(256), 0, st, D.T, (int64_t)D.ldF, W.Zd, W.dGd, W.dUd);
+            HIP_TRY(hipGetLastError());
+        }
     }
     // dW_down = Z'^T dD (bp-1); dW_gate = X^T dG, dW_up = X^T dU (bp-4): contractions over tokens,
     // both operands read k-major (token index leading)
     // (one launch for the three of them)
     const GemmProblem<E> pw[3] = {
-        {km_operand<E>(W.Zd, D.ldF, D.ldF), km_operand<E>(dy, D.d, D.d), D.F, D.d, D.T, 0, false},
-        {km_operand<E>(W.dGd, D.ldF, D.ldF), km_operand<E>(x, D.d, D.d), D.F, D.d, D.T, 0, false},
-        {km_operand<E>(W.dUd, D.ldF, D.ldF), km_operand<E>(x, D.d, D.d), D.F, D.d, D.T, 0, false}};
+        {km_operand<E>(W.Zd, D.ldF, D.ldF), km_operand<E>(dy, D.d, D.d), D.F, D.d, D.T, 0, true},
+        {km_operand<E>(W.dGd, D.ldF, D.ldF), km_operand<E>(x, D.d, D.d), D.F, D.d, D.T, 0, true},
+        {km_operand<E>(W.dUd, D.ldF, D.ldF), km_operand<E>(x, D.d, D.d), D.F, D.d, D.T, 0, true}};
     const EpiStore<E> ew[3] = {{dwd, D.d, D.d, 0}, {dwg, D.d, D.d, 0}, {dwu, D.d, D.d, 0}};
     static const char* const wnames[3] = {"gemm_dwd", "gemm_dwg", "gemm_dwu"};
     if ((s = run_gemm_batch3<E>("gemm_dw3", wnames, pw, ew, st, &W.sk)) != MOC_OK) return s;
     // dX = dG W_gate^T + dU W_up^T (bp-5): one GEMM over the concatenated contraction
     GemmProblem<E> px{kc_operand<E>(W.dGd, D.ldF, W.dUd), km_operand<E>(wg, D.d, D.d, wu), D.T, D.d, D.F, D.F, true};
-    return run_gemm<E, false, true>("gemm_dx", px, EpiStore<E>{dx, D.d, D.d, 0}, st);
+    // (the dense dZ' and Z' are not needed any more)
+    const ShareScratch scratch{reinterpret_cast<float*>(DENSE ? W.Zd : W.dZd), (size_t)D.T * D.ldF * (DENSE ? 1 : 2) * sizeof(E)};
+    return run_gemm<E, false, true>("gemm_dx", px, EpiStore<E>{dx, D.d, D.d, 0}, st, nullptr, false, scratch);
 }
 
 template <class E> __global__ void fill_zero_kernel(E* p, int64_t n) {
@@ -73,6 +93,7 @@ moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
     if (expand_lds > 160 * 1024 - 64) return fail(MOC_ERR_UNSUPPORTED, "F = %d too large for the expert backward", D.F);
     GemmProblem<E> pr[3 * kMaxExperts];
     EpiStore<E> ee[3 * kMaxExperts];
+    const RowGroups rg = row_groups(n_exp, off);      // the dense operands' rows (dz' and everything of the caller's: off)
     moc_status s;
     for (int e = 0; e < n_exp; ++e) {
         const int64_t r0 = off[e];
@@ -84,7 +105,7 @@ moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
         auto kern = bwd_expand_kernel<E>;
         LdsAttr<bwd_expand_kernel<E>, kMaxDynLds>::use();
         Span span("bwd_pointwise_expand", st);
-        hipLaunchKernelGGL(kern, dim3(D.T), dim3(256), expand_lds, st, idx, gvals, uvals, W.dZd, D.K, D.F, (int64_t)D.ldF, W.Zd,
+        hipLaunchKernelGGL(kern, dim3(rg.row[n_exp]), dim3(256), expand_lds, st, idx, gvals, uvals, W.dZd, rg, D.K, D.F, (int64_t)D.ldF, W.Zd,
                            W.dGd, W.dUd);
         HIP_TRY(hipGetLastError());
     }
@@ -103,8 +124,8 @@ moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
         const E* rhs[3] = {dy, x, x};
         E* outs[3] = {dwd, dwg, dwu};
         for (int k = 0; k < 3; ++k) {
-            pr[np] = GemmProblem<E>{km_operand<E>(ops[k] + r0 * D.ldF, D.ldF, D.ldF), km_operand<E>(rhs[k] + r0 * D.d, D.d, D.d),
-                                    D.F, D.d, rows, 0, false};
+            pr[np] = GemmProblem<E>{km_operand<E>(ops[k] + (int64_t)rg.row[e] * D.ldF, D.ldF, D.ldF), km_operand<E>(rhs[k] + r0 * D.d, D.d, D.d),
+                                    D.F, D.d, rows, 0, true};
             ee[np] = EpiStore<E>{outs[k] + e * wsz, D.d, D.d, 0};
             ++np;
         }
@@ -112,7 +133,8 @@ moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
     if ((s = run_gemm_grouped<E, true, true, EpiStore<E>, 3 * kMaxExperts>("gemm_dw_experts", np, pr, ee, st)) != MOC_OK) return s;
     for (int e = 0; e < n_exp; ++e) {
         const int64_t r0 = off[e];
-        pr[e] = GemmProblem<E>{kc_operand<E>(W.dGd + r0 * D.ldF, D.ldF, W.dUd + r0 * D.ldF),
+        const int64_t rp = (int64_t)rg.row[e] * D.ldF;
+        pr[e] = GemmProblem<E>{kc_operand<E>(W.dGd + rp, D.ldF, W.dUd + rp),
                                km_operand<E>(wg + e * wsz, D.d, D.d, wu + e * wsz), off[e + 1] - off[e], D.d, D.F, D.F, true};
         ee[e] = EpiStore<E>{dx + r0 * D.d, D.d, D.d, 0};
     }

@@ -58,7 +58,8 @@ moc_status fwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
             return MOC_OK;
         }
     }
-    return down_projection<E>(D, W.Zd, wd, y, st);
+    // (G and U, one after the other, are not needed any more)
+    return down_projection<E>(D, W.Zd, wd, y, st, ShareScratch{W.G, (size_t)D.T * D.ldF * (sizeof(float) + sizeof(E))});
 }
 
 // ------------------------------------------------------------ MoC inside MoE experts

@@ -1,0 +1,24 @@
+"""bf16 products at the sizes where the choice of tile, the padded token rows and the split contraction can go wrong: few
+tokens (64-row tiles, down and dX products cut into shares), a last share with fewer slices than the others, token counts
+one short of and one past a k-slice, experts with fewer rows than a slice.  Against the float64 oracle at the bf16 tolerance
+of the other parity tests."""
+import pytest
+
+from tests.test_gpu_experts import run_experts_case
+from tests.test_gpu_parity import run_fwd_bwd_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,F,K", [
+    (17, 512, 1365, 170),      # fewer tokens than a k-slice; shares of a contraction with a tail
+    (33, 1024, 2736, 342),     # one token past a slice
+    (129, 256, 5461, 682),     # one row past a tile, 171 slices that no number of shares divides
+    (1999, 768, 2048, 409),    # token rows padded by 17
+])
+def test_tiles_shares_and_padded_rows(T, d, F, K):
+    run_fwd_bwd_case("tiles", 98, T, d, F, K, "bf16")
+
+
+def test_experts_with_fewer_rows_than_a_slice():
+    run_experts_case("few rows", 980, [1, 0, 31, 33, 64, 5, 100, 2], 128, 333, 41, "bf16")
