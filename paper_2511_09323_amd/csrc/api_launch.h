@@ -373,11 +373,12 @@ moc_status run_topk(const char* name, const TopkArgs<E>& a, int T, hipStream_t s
         if (nch <= 1) return launch_topk_reg<E, NT, 1, FUSED>(name, a, T, st);
         if (nch <= 2) return launch_topk_reg<E, NT, 2, FUSED>(name, a, T, st);
         if (nch <= 3) return launch_topk_reg<E, NT, 3, FUSED>(name, a, T, st);
-        if (NT == 256 || NT == 512) {
+        if constexpr (NT < 1024) {
             if (nch <= 4) return launch_topk_reg<E, NT, 4, FUSED>(name, a, T, st);
             if (nch <= 6) return launch_topk_reg<E, NT, 6, FUSED>(name, a, T, st);
             if (nch <= 8) return launch_topk_reg<E, NT, 8, FUSED>(name, a, T, st);
-            if (NT == 256 && nch <= 11) return launch_topk_reg<E, NT, 11, FUSED>(name, a, T, st);
+            if constexpr (NT == 256)
+                if (nch <= 11) return launch_topk_reg<E, NT, 11, FUSED>(name, a, T, st);
         }
         return run_topk_lds<E, NT, 4, FUSED>(name, a, T, st);
     }

@@ -74,9 +74,52 @@ __device__ __forceinline__ int mbcnt(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
+// Largest of three (fmaxf would first quiet every operand, an instruction each).
+__device__ __forceinline__ float max3_f32(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Wavefront reductions: lanes l and l ^ 32, then ^ 16, 8, 4, 2, 1 are combined; every lane gets the result.  The exchanges are register
+// moves (gfx950's half- and quarter-wavefront swaps, then rotations inside 16 lanes, which reach the xor partner because the values
+// repeat with the period of the step before); the same reduction through __shfl_xor costs six trips to LDS.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(v), __float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+template <class Op> __device__ __forceinline__ float wave_reduce(float v, const Op& op) {
+    {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    v = op(v, dpp_move<0x128>(v));      // row_ror:8
+    v = op(v, dpp_move<0x124>(v));      // row_ror:4
+    v = op(v, dpp_move<0x122>(v));      // row_ror:2
+    v = op(v, dpp_move<0x121>(v));      // row_ror:1
+    return v;
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return wave_reduce(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+    return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float wave_min(float v) {
+    return wave_reduce(v, [](float a, float b) { return fminf(a, b); });
+}
+
+// Inclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);      // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);      // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);      // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // row_bcast:31 into rows 2 and 3
     return v;
 }
 

@@ -7,6 +7,7 @@
 
 #include "decode_kernels.h"
 #include "decode_persist.h"
+#include "decode_rows.h"
 #include "decode_select_gather.h"
 
 using namespace moc;
@@ -254,6 +255,48 @@ moc_status launch_select_gather(const Dims& D, const E* x, const E* wu, const E*
     return launch_select_gather_nch<E, 16>(D, x, wu, wd, g, idx, part, P, st);
 }
 
+// Selection + up projection, then the down projection, of row-wide decode (decode_rows.h).
+template <class E, int NCH>
+moc_status launch_select_up_nch(const Dims& D, const E* x, const E* wu, const float* g, const float* graw, int P, int32_t* idx,
+                                float* z, hipStream_t st) {
+    Span span("decode_select_up", st);
+    hipLaunchKernelGGL((decode_select_up_kernel<E, NCH>), dim3(P * D.T), dim3(kRowsNT), 0, st, x, wu, g, graw, (int64_t)D.ldF, D.F, D.d, D.K,
+                       P, D.T, idx, z);
+    HIP_TRY(hipGetLastError());
+    return MOC_OK;
+}
+template <class E>
+moc_status launch_down_cols(const Dims& D, const E* wd, const int32_t* idx, const float* z, E* y, hipStream_t st) {
+    Span span("decode_down", st);
+    const int slices = (D.d * (int)sizeof(E) + 63) / 64;
+    hipLaunchKernelGGL((decode_down_cols_kernel<E>), dim3(slices * D.T), dim3(1024), 0, st, wd, idx, z, D.d, D.F, D.K, slices, D.T, y);
+    HIP_TRY(hipGetLastError());
+    return MOC_OK;
+}
+template <class E>
+moc_status decode_rows(const Dims& D, const DecodeWs& W, const E* x, const E* wu, const E* wd, E* y, int32_t* idx, int key_mode,
+                       hipStream_t st) {
+    // ranges of channels: about five selected channels for the eight wavefronts of a workgroup, and one workgroup per compute unit over
+    // all tokens (two slow each other down: 25.0 against 23.8 us for three tokens at 2048 x 5461) unless the ranges would become too long
+    int P = std::min((D.K + 4) / 5, 256 / D.T);
+    P = std::max(P, (D.F + kRowsMaxRange - 1) / kRowsMaxRange);
+    if (P > 8) P = round_up(P, 8);
+    moc_status s;
+    const float* g = W.g;
+    if (key_mode != 0) {
+        if ((s = launch_key_transform(W.g, W.gkeys, (int64_t)D.T * D.ldF, key_mode, st)) != MOC_OK) return s;
+        g = W.gkeys;
+    }
+    const int nch = (D.F + 4 * kRowsNT - 1) / (4 * kRowsNT);
+    if (nch <= 1) s = launch_select_up_nch<E, 1>(D, x, wu, g, W.g, P, idx, W.z, st);
+    else if (nch <= 2) s = launch_select_up_nch<E, 2>(D, x, wu, g, W.g, P, idx, W.z, st);
+    else if (nch <= 3) s = launch_select_up_nch<E, 3>(D, x, wu, g, W.g, P, idx, W.z, st);
+    else if (nch <= 6) s = launch_select_up_nch<E, 6>(D, x, wu, g, W.g, P, idx, W.z, st);
+    else s = launch_select_up_nch<E, 16>(D, x, wu, g, W.g, P, idx, W.z, st);
+    if (s != MOC_OK) return s;
+    return launch_down_cols<E>(D, wd, idx, W.z, y, st);
+}
+
 template <class E>
 moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E* wd, E* y, int32_t* idx_out,
                        void* ws, hipStream_t st, int ga = 0, int gb = 0, int key_mode = 0) {
@@ -313,6 +356,7 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         else s = decode_gate_group_b<E, 16>(D, x, wg, ga, gb, idx, W.gsel, st);
     }
     if (s != MOC_OK) return s;
+    if (gb == 0 && B <= 4 && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
     const int P = decode_splits(B, D.K);
     if (gb == 0 && key_mode == 0 && gather_fused && options().decode_select_gather && (D.F + P - 1) / P <= kDsgMaxRange &&
         decode_select_gather_lds<E>(D.d) <= (size_t)kSelectGatherMaxLds) {

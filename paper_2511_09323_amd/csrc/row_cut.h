@@ -1,0 +1,306 @@
+// The cut of one row's Top-K, found by a workgroup that holds the row in registers: shared by the training forward's row
+// selection (topk.h) and by decode (decode_rows.h).
+//
+// Method: one histogram over 2048 bins of equal width between 0 and the row's maximum (a product, a conversion, a clamp and an LDS
+// atomic per value), a scan from the top for the bin that holds the K-th value, and a direct ranking of that bin's few values by
+// every wavefront.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
+// 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than K non-negative values, more than
+// 64 values in the bin (outliers, ties), ranges too small for the bin width -- goes on with the remaining range by the
+// general step until it is resolved.
+// What bounds it: instructions per value (one row occupies one workgroup, often one compute unit) and the dependent steps
+// between barriers; about nine instructions per value and six barriers.  The radix select it replaces (three histograms over key digits,
+// colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
+// 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
+#pragma once
+#include "common.h"
+
+namespace moc {
+
+constexpr int kCutBins = 2048;
+
+// Channel j with value v is selected iff v > tau, or v == tau and j <= last.
+struct RowCut {
+    float tau;
+    int last;      // INT_MAX: every value equal to tau is selected
+    int before;    // BEFORE: selected channels below c0
+    __device__ __forceinline__ bool in(float v, int j) const { return v > tau || (v == tau && j <= last); }
+};
+
+template <int NT> struct RowCutLds {
+    uint32_t below[64];      // where the counts of negative values go, a word per lane
+    uint32_t hist[kCutBins];
+    float cand_v[64];
+    int cand_j[64];
+    float red_f[2][NT / 64];
+    int red_i[NT / 64], red_b[NT / 64];
+    int bin, need, cnt, ncand;
+};
+
+// v[c][e] is the value of channel c * 4 NT + tid * 4 + e; what lies past the row's end holds -inf.  1 <= K <= row length.
+// BEFORE: also counts the selected channels below c0 (on the way, from the bins).
+// Deterministic; for non-finite values it ends, with some cut.  L may be overwritten after a barrier.
+template <int NT, int NCH, bool BEFORE>
+__device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCutLds<NT>& L, int c0 = 0) {
+    constexpr int NW = NT / 64, BPT = kCutBins / NT;
+    static_assert(BPT == 2 || BPT == 4 || BPT == 8, "256, 512 or 1024 threads");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float kInf = __builtin_inff();
+    // a copy the compiler does not recognise: channel numbers are formed where they are used instead of kept in registers
+    auto opaque = [](int t) {
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+
+    auto clear_bins = [&](int base) {
+        if (BPT == 2) *reinterpret_cast<u32x2_t*>(L.hist + base) = u32x2_t{0, 0};
+        else
+#pragma unroll
+            for (int q = 0; q < BPT; q += 4) *reinterpret_cast<u32x4_t*>(L.hist + base + q) = u32x4_t{0, 0, 0, 0};
+    };
+    float vmax = -kInf;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) vmax = max3_f32(max3_f32(vmax, v[c][0], v[c][1]), v[c][2], v[c][3]);
+    vmax = wave_max(vmax);
+    clear_bins(BPT * tid);
+    if (lane == 0) L.red_f[0][wave] = vmax;
+    if (tid == 0) { L.bin = 0; L.need = K; L.cnt = 0; L.ncand = 0; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) vmax = fmaxf(vmax, L.red_f[0][w]);
+
+    // Scans the bins from the top for the one in which the running count reaches `need`; L.bin, L.need (what is still wanted in
+    // that bin) and L.cnt (its size) are set, the bins are cleared and the total of all bins is returned.
+    auto scan = [&](int need) {
+        __syncthreads();
+        const int base = kCutBins - BPT * (tid + 1);         // thread order is descending bin order
+        uint32_t h[BPT];
+        if (BPT == 2) {
+            const u32x2_t t = *reinterpret_cast<const u32x2_t*>(L.hist + base);
+            h[0] = t[0]; h[1] = t[1];
+        } else {
+#pragma unroll
+            for (int q = 0; q < BPT; q += 4) {
+                const u32x4_t t = *reinterpret_cast<const u32x4_t*>(L.hist + base + q);
+                h[q] = t[0]; h[q + 1] = t[1]; h[q + 2] = t[2]; h[q + 3] = t[3];
+            }
+        }
+        int local = 0;
+#pragma unroll
+        for (int q = 0; q < BPT; ++q) local += (int)h[q];
+        int inc = wave_inclusive_sum(local);
+        if (lane == 63) L.red_i[wave] = inc;
+        clear_bins(base);                                    // (this thread's own, for a repetition)
+        __syncthreads();
+        int total = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            inc += w < wave ? L.red_i[w] : 0;
+            total += L.red_i[w];
+        }
+        int run = inc - local;
+        if (run < need && inc >= need) {                     // the bin is one of mine
+            int fb = -1, fneed = 0, fh = 0;
+#pragma unroll
+            for (int q = BPT - 1; q >= 0; --q) {
+                if (fb < 0 && run + (int)h[q] >= need) { fb = base + q; fneed = need - run; fh = (int)h[q]; }
+                run += (int)h[q];
+            }
+            L.bin = fb;
+            L.need = fneed;
+            L.cnt = fh;
+        }
+        __syncthreads();
+        return total;
+    };
+    auto keep = [&](float t, int j) {
+        const int p = atomicAdd(&L.ncand, 1);
+        if (p < 64) { L.cand_v[p] = t; L.cand_j[p] = j; }
+    };
+    // the cut among the cnt <= 64 kept values: the need-th in the order (value descending, channel ascending)
+    // (`above`: this thread's values above the kept ones with channels below c0)
+    auto rank_kept = [&](int cnt, int need, int above) {
+        if (BEFORE) {
+            above = (int)wave_sum((float)above);             // exact: counts are far below 2^24
+            if (lane == 0) L.red_b[wave] = above;
+        }
+        __syncthreads();
+        const int i = min(lane, max(cnt, 1) - 1);
+        const float cv = L.cand_v[i];
+        const int cj = L.cand_j[i];
+        int rank = 0;
+        for (int q = 0; q < cnt; ++q) {
+            const float ov = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cv), q));
+            const int oj = __builtin_amdgcn_readlane(cj, q);
+            rank += (ov > cv || (ov == cv && oj < cj)) ? 1 : 0;
+        }
+        const uint64_t m = __ballot(lane < cnt && rank == need - 1);
+        const int src = m ? __ffsll((unsigned long long)m) - 1 : 0;
+        const float tau = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cv), src));
+        const bool cut_ties = __ballot(lane < cnt && cv == tau && rank >= need) != 0;
+        int before = 0;
+        if (BEFORE) {
+            before = __popcll(__ballot(lane < cnt && rank < need && cj < c0));
+#pragma unroll
+            for (int w = 0; w < NW; ++w) before += L.red_b[w];
+        }
+        return RowCut{tau, cut_ties ? (int)__builtin_amdgcn_readlane(cj, src) : 0x7FFFFFFF, before};
+    };
+
+    int need = K, fb = 0;
+    float scale0 = 0.0f;
+    if (vmax > 1e-30f && vmax < 1e38f) {
+        scale0 = ((float)kCutBins - 1.0f) * __builtin_amdgcn_rcpf(vmax);      // v * scale0 < 2048 for every v <= vmax
+        // (no branch per value: negative ones count into the lane's own word in front of the bins; what truncates to bin 0 from
+        // below spoils that bin, which is therefore not used)
+        const int floor_bin = -1 - lane;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicAdd(L.hist + max((int)(v[c][e] * scale0), floor_bin), 1u);
+        const int total = scan(need);
+        fb = total >= need ? L.bin : 0;
+        const int cnt = L.cnt;
+        if (fb > 0) {
+            need = L.need;
+            if (cnt <= 64) {
+                asm volatile("" : "+v"(scale0));             // (keeps the compiler from holding every value's bin in a register)
+                uint32_t near = 1;
+                int above = 0;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    int x[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        x[e] = (int)(v[c][e] * scale0) - fb;
+                        near = min(near, (uint32_t)x[e]);
+                    }
+                    if (BEFORE && c * 4 * NT < c0) {         // (uniform; only the chunk that holds c0 needs the channel test)
+                        const int stop = c0 - (c * 4 * NT + tid * 4);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) above += (x[e] > 0 && e < stop) ? 1 : 0;
+                    }
+                }
+                if (near == 0) {
+                    const int jb = opaque(tid * 4);
+                    asm volatile("" : "+v"(scale0));
+#pragma unroll
+                    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if ((int)(v[c][e] * scale0) == fb) keep(v[c][e], c * 4 * NT + jb + e);
+                }
+                return rank_kept(cnt, need, above);
+            }
+        }
+    }
+    int npos = 0;
+    if (fb == 0) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) npos += v[c][e] >= 0.0f ? 1 : 0;
+        npos = (int)wave_sum((float)npos);                   // exact: counts are far below 2^24
+        if (lane == 0) L.red_i[wave] = npos;
+        __syncthreads();
+        npos = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) npos += L.red_i[w];
+        need = npos >= K ? K : K - npos;
+    }
+    // ---- general step on the closed range [lo, hi] of the values in question: every value above hi is selected, `need` of those
+    //      inside are.  A repetition takes at least the range's two ends apart, so it ends.
+    float lo, hi;
+    auto count_before = [&](RowCut cut) {
+        if (BEFORE) {
+            int n = 0;
+            const int jb = opaque(tid * 4);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int j = c * 4 * NT + jb + e;
+                    n += (j < c0 && cut.in(v[c][e], j)) ? 1 : 0;
+                }
+            n = (int)wave_sum((float)n);
+            __syncthreads();
+            if (lane == 0) L.red_b[wave] = n;
+            __syncthreads();
+            cut.before = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) cut.before += L.red_b[w];
+        }
+        return cut;
+    };
+    auto range_of = [&](const auto& in_question) {
+        float a = kInf, b = -kInf;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (in_question(v[c][e])) { a = fminf(a, v[c][e]); b = fmaxf(b, v[c][e]); }
+        a = wave_min(a);
+        b = wave_max(b);
+        __syncthreads();
+        if (lane == 0) { L.red_f[0][wave] = a; L.red_f[1][wave] = b; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { a = fminf(a, L.red_f[0][w]); b = fmaxf(b, L.red_f[1][w]); }
+        lo = a;
+        hi = b;
+    };
+    if (fb > 0) range_of([&](float t) { return (int)(t * scale0) == fb; });
+    else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
+    else range_of([&](float t) { return t < 0.0f && t > -kInf; });
+    for (int it = 0; it < 300; ++it) {
+        if (lo == hi) {
+            // all equal: the first `need` channels, by bisection over the channel index
+            int a = 0, b = NCH * 4 * NT - 1;
+            while (a < b) {
+                const int m = (a + b) >> 1;
+                int n = 0;
+                const int jb = opaque(tid * 4);
+#pragma unroll
+                for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) n += (v[c][e] == lo && c * 4 * NT + jb + e <= m) ? 1 : 0;
+                n = (int)wave_sum((float)n);
+                __syncthreads();
+                if (lane == 0) L.red_i[wave] = n;
+                __syncthreads();
+                n = 0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) n += L.red_i[w];
+                if (n >= need) b = m;
+                else a = m + 1;
+            }
+            return count_before(RowCut{lo, a, 0});
+        }
+        // monotonic in t, lo falls into bin 0 and hi into the last ones (`pre` keeps the factor finite for tiny ranges)
+        const float pre = hi - lo < 1e-30f ? 0x1p100f : 1.0f;
+        const float scale = (float)kCutBins / ((hi - lo) * pre);
+        auto bin_of = [&](float t) { return min(kCutBins - 1, (int)fminf((t - lo) * pre * scale, 4096.0f)); };
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (v[c][e] >= lo && v[c][e] <= hi) atomicAdd(&L.hist[bin_of(v[c][e])], 1u);
+        (void)scan(need);
+        fb = L.bin;
+        need = L.need;
+        const int cnt = L.cnt;
+        if (cnt <= 64) {
+            const int jb = opaque(tid * 4);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (v[c][e] >= lo && v[c][e] <= hi && bin_of(v[c][e]) == fb) keep(v[c][e], c * 4 * NT + jb + e);
+            return count_before(rank_kept(cnt, need, 0));
+        }
+        const float l0 = lo, h0 = hi;
+        range_of([&](float t) { return t >= l0 && t <= h0 && min(kCutBins - 1, (int)fminf((t - l0) * pre * scale, 4096.0f)) == fb; });
+    }
+    return RowCut{vmax, 0x7FFFFFFF, 0};
+}
+
+}  // namespace moc

@@ -1,0 +1,57 @@
+"""The row selection of row_cut.h on rows that its usual path (one histogram, a handful of values in the cut's bin) does not
+resolve: outliers that push everything else into one bin, more ties than a wavefront ranks, cuts at zero and among the negative
+values, powers of two over the whole exponent range.  Index sets are compared exactly; the values are exact by construction
+(given fp32 rows, or one-hot inputs that make the gate a column of W_gate)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2511_09323_amd as moc
+from oracle import moc_oracle as O
+from paper_2511_09323_amd import inputs
+from tests import parity as P
+from tests.test_gpu_parity import _topk_case
+
+pytestmark = pytest.mark.gpu
+
+
+def hard_rows(F, seed):
+    rng = np.random.default_rng(seed)
+    g = rng.standard_normal((8, F)).astype(np.float32)
+    g[0, F // 2] = 1e6                                                   # one outlier: all others share a bin
+    g[1] = np.sign(g[1]) * np.exp2(np.floor(rng.uniform(-120, 120, F)))  # geometric
+    g[2] = np.round(g[2] * 2) / 2                                        # hundreds of ties per value
+    g[3] = -np.abs(g[3]) - 1                                             # all negative
+    g[4] = np.where(rng.random(F) < 0.9, 0.0, g[4])                      # mostly (signed) zeros
+    g[4, ::3] *= -1
+    g[5] = np.where(rng.random(F) < 0.5, 1.0, np.nextafter(np.float32(1), np.float32(2)))
+    g[6] *= 1e-42                                                        # denormal
+    g[7, :] = -2.5
+    return g.astype(np.float32)
+
+
+@pytest.mark.parametrize("F", [5, 64, 1376, 5461, 11008])
+def test_rows_the_usual_path_does_not_resolve(F):
+    g = hard_rows(F, F)
+    for K in sorted({1, F // 8, F // 2, F - 1, F} - {0}):
+        _topk_case(g, K)
+
+
+@pytest.mark.parametrize("B,d,F", [(1, 64, 5), (1, 512, 1376), (3, 256, 5461), (4, 128, 11008), (2, 64, 32768)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_decode_selection_on_hard_rows(B, d, F, dtype):
+    L = inputs.make_layer(96, B, d, F, dtype)
+    rows = inputs.round_to_bf16(hard_rows(F, F + 1))                     # row r is the gate of a token whose input is one-hot at r
+    L["wg"][:, :8] = rows.T
+    for first in (0, 4):
+        L["x"] = np.zeros((B, d), dtype=np.float32)
+        for b in range(B):
+            L["x"][b, (first + b) % 8] = 1.0
+        G = {k: P.to_dev(v, dtype) for k, v in L.items()}
+        want = rows[[(first + b) % 8 for b in range(B)]]
+        for K in sorted({1, F // 8, F // 2, F} - {0}):
+            y, idx = moc.moc_ffn_decode(G["x"], G["wg"], G["wu"], G["wd"], K)
+            torch.cuda.synchronize()
+            ref = np.stack([np.flatnonzero(r) for r in O.topk_mask(want, K)])
+            np.testing.assert_array_equal(idx.cpu().numpy(), ref)
+            assert torch.isfinite(y).all()
