@@ -1,4 +1,8 @@
-"""ctypes binding of libmoc_ffn.so: argument marshalling only.
+"""Python binding of libmoc_ffn.so: argument marshalling only.
+
+The hot entry points hand their tensors to _marshal.so (csrc/marshal.cpp), which checks them and calls the C ABI in
+about a microsecond; whatever it does not take (another argument type, a wrong shape) goes through ctypes here, which
+names the error.
 
 Every function takes torch tensors that already live on the GPU, passes their data pointers and
 the current torch stream through the C ABI declared in include/moc.h, and raises MocError when the
@@ -36,11 +40,23 @@ class MocShape(ctypes.Structure):
 
 
 _lib = None
+_NOT_TAKEN = -1000
+
+
+class _NoMarshal:
+    """Stands in for _marshal.so until the library is loaded."""
+
+    def __getattr__(self, name):
+        load_library()
+        return getattr(_fast, name)
+
+
+_fast = _NoMarshal()
 
 
 def load_library():
     """Loads the in-tree library; raises if it has not been built."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -102,7 +118,13 @@ def load_library():
     lib.moc_last_error.argtypes = []
     lib.moc_version.restype = ctypes.c_char_p
     lib.moc_version.argtypes = []
-    _lib = lib
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise MocError("MOC_ERR_NOT_BUILT", "_marshal.so is missing or does not load (%s): run `python -m paper_2511_09323_amd.build`" % e)
+    if not _marshal.bind(LIB_PATH):
+        raise MocError("MOC_ERR_NOT_BUILT", "%s lacks an entry point" % LIB_PATH)
+    _lib, _fast = lib, _marshal
     return lib
 
 
@@ -165,6 +187,12 @@ def _workspace(ws, T, d, F, K, dtype, op, device):
 
 def moc_ffn_fwd(x, wg, wu, wd, K, ws=None, out=None):
     """Returns (y, idx, gvals, uvals).  x [T,d]; wg, wu, wd channel-major [F,d]."""
+    if out is not None and ws is not None:
+        y, idx, gvals, uvals = out
+        status = _fast.fwd(x, wg, wu, wd, K, y, idx, gvals, uvals, ws)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return y, idx, gvals, uvals
     lib = load_library()
     T, d = x.shape
     F = wg.shape[0]
@@ -188,6 +216,12 @@ def moc_ffn_fwd(x, wg, wu, wd, K, ws=None, out=None):
 
 def moc_ffn_bwd(x, wg, wu, wd, idx, gvals, uvals, dy, ws=None, out=None):
     """Returns (dx, dwg, dwu, dwd) from the stored set and the upstream gradient."""
+    if out is not None and ws is not None:
+        dx, dwg, dwu, dwd = out
+        status = _fast.bwd(x, wg, wu, wd, idx, gvals, uvals, dy, dx, dwg, dwu, dwd, ws, idx.shape[1])
+        if status != _NOT_TAKEN:
+            _check(status)
+            return dx, dwg, dwu, dwd
     lib = load_library()
     T, d = x.shape
     F = wg.shape[0]
@@ -214,6 +248,12 @@ def moc_ffn_bwd(x, wg, wu, wd, idx, gvals, uvals, dy, ws=None, out=None):
 
 def moc_ffn_decode(x, wg, wu, wd, K, ws=None, want_idx=True, out=None):
     """Returns (y, idx or None) for a decode batch x [B,d], B <= 16."""
+    if out is not None and ws is not None:
+        y, idx = out
+        status = _fast.decode(x, wg, wu, wd, K, y, idx, ws)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return y, idx
     lib = load_library()
     B, d = x.shape
     F = wg.shape[0]
@@ -326,6 +366,12 @@ def _offsets(offsets):
 def moc_ffn_fwd_experts(x, offsets, wg, wu, wd, K, ws=None, out=None):
     """MoC as the MLP of MoE experts.  x [A,d]: routed rows sorted by expert; offsets: n_experts + 1 host
     integers; wg, wu, wd [n_experts, F, d].  Returns (y, idx, gvals, uvals) for all rows."""
+    if out is not None and ws is not None:
+        y, idx, gvals, uvals = out
+        status = _fast.fwd_experts(x, offsets, wg, wu, wd, K, y, idx, gvals, uvals, ws)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return y, idx, gvals, uvals
     lib = load_library()
     T, d = x.shape
     E, F = wg.shape[0], wg.shape[1]
@@ -352,6 +398,12 @@ def moc_ffn_fwd_experts(x, offsets, wg, wu, wd, K, ws=None, out=None):
 
 def moc_ffn_bwd_experts(x, offsets, wg, wu, wd, idx, gvals, uvals, dy, ws=None, out=None):
     """Backward of moc_ffn_fwd_experts.  Returns (dx [A,d], dwg, dwu, dwd [n_experts, F, d])."""
+    if out is not None and ws is not None:
+        dx, dwg, dwu, dwd = out
+        status = _fast.bwd_experts(x, offsets, wg, wu, wd, idx, gvals, uvals, dy, dx, dwg, dwu, dwd, ws, idx.shape[1])
+        if status != _NOT_TAKEN:
+            _check(status)
+            return dx, dwg, dwu, dwd
     lib = load_library()
     T, d = x.shape
     E, F = wg.shape[0], wg.shape[1]
@@ -457,6 +509,12 @@ def _grouped_K(F, a, b):
 def moc_ffn_fwd_grouped(x, wg, wu, wd, a, b, ws=None, out=None):
     """MoC_{a:b} forward (a kept of every b consecutive channels).  Returns (y, idx, gvals, uvals)
     with K = a*F/b columns, usable by moc_ffn_bwd as they are."""
+    if out is not None and ws is not None:
+        y, idx, gvals, uvals = out
+        status = _fast.fwd_grouped(x, wg, wu, wd, _grouped_K(wg.shape[0], a, b), a, b, y, idx, gvals, uvals, ws)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return y, idx, gvals, uvals
     lib = load_library()
     T, d = x.shape
     F = wg.shape[0]
@@ -481,6 +539,12 @@ def moc_ffn_fwd_grouped(x, wg, wu, wd, a, b, ws=None, out=None):
 
 def moc_ffn_decode_grouped(x, wg, wu, wd, a, b, ws=None, want_idx=True, out=None):
     """MoC_{a:b} decode for a batch x [B,d], B <= 16.  Returns (y, idx or None)."""
+    if out is not None and ws is not None:
+        y, idx = out
+        status = _fast.decode_grouped(x, wg, wu, wd, _grouped_K(wg.shape[0], a, b), a, b, y, idx, ws)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return y, idx
     lib = load_library()
     B, d = x.shape
     F = wg.shape[0]
@@ -518,6 +582,11 @@ def moc_topk_grouped_rows(g, a, b):
 
 
 def moc_rmsnorm(h, gain, eps, out=None):
+    if out is not None:
+        status = _fast.rmsnorm(h, gain, eps, out)
+        if status != _NOT_TAKEN:
+            _check(status)
+            return out
     lib = load_library()
     T, d = h.shape
     if out is None:
@@ -528,6 +597,10 @@ def moc_rmsnorm(h, gain, eps, out=None):
 
 
 def moc_residual_add(h, y):
+    status = _fast.residual_add(h, y)
+    if status != _NOT_TAKEN:
+        _check(status)
+        return h
     lib = load_library()
     T, d = h.shape
     _check(lib.moc_residual_add(T, d, _dtype_code(h), _ptr(h, None, None, "h"), _ptr(y, h.dtype, (T, d), "y"),

@@ -1,18 +1,21 @@
-"""Builds the HIP library in-tree: paper_2511_09323_amd/libmoc_ffn.so (gfx950 only).
+"""Builds the HIP library in-tree: paper_2511_09323_amd/libmoc_ffn.so (gfx950 only), and _marshal.so beside it.
 
 The entry points are spread over four translation units that are compiled side by side and
-linked into one shared library.
+linked into one shared library.  _marshal.so is the host-only Python extension that hands torch tensors to
+that library (csrc/marshal.cpp); it is compiled against the installed torch's headers.
 """
 import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoc_ffn.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["moc_api.hip", "moc_fwd.hip", "moc_bwd.hip", "moc_decode.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -50,6 +53,17 @@ def _run(cmd, verbose):
         raise subprocess.CalledProcessError(r.returncode, cmd)
 
 
+def build_marshal(verbose):
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + sysconfig.get_paths()["include"],
+          "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
+          os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-Wl,--no-as-needed", "-L" + os.path.join(root, "lib"),
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose)
+
+
 def build(verbose=True, only=None):
     """Compiles every source (or the ones named in `only`, reusing the other objects) and links."""
     os.makedirs(OBJ, exist_ok=True)
@@ -57,8 +71,10 @@ def build(verbose=True, only=None):
     # moc_api.hip holds the version string with the source hash, so it is compiled every time
     todo = [(s, o) for s, o in zip(SOURCES, objs) if only is None or s in only or s == "moc_api.hip" or not os.path.exists(o)]
     define = ['-DMOC_SOURCE_HASH="%s"' % source_hash()]
-    with ThreadPoolExecutor(max_workers=4) as pool:
+    with ThreadPoolExecutor(max_workers=5) as pool:
         jobs = [pool.submit(_run, [HIPCC] + FLAGS + define + ["-c", os.path.join(CSRC, s), "-o", o], verbose) for s, o in todo]
+        if only is None or "marshal.cpp" in only or not os.path.exists(MARSHAL):
+            jobs.append(pool.submit(build_marshal, verbose))
         for j in jobs:
             j.result()
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
