@@ -288,7 +288,17 @@ PyObject* f_bind(PyObject*, PyObject* arg) {
     return PyBool_FromLong(ok);
 }
 
-#define FAST(name_, fn_) {name_, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(fn_)), METH_FASTCALL, nullptr}
+// torch throws where a tensor has no memory of its own (fake tensors and other subclasses under tracing): not taken.  The calls
+// into the library, made without the interpreter's lock, do not throw.
+template <PyObject* (*Fn)(PyObject*, PyObject* const*, Py_ssize_t)> PyObject* guarded(PyObject* self, PyObject* const* v, Py_ssize_t nargs) {
+    try {
+        return Fn(self, v, nargs);
+    } catch (...) {
+        return PyLong_FromLong(kNotTaken);
+    }
+}
+
+#define FAST(name_, fn_) {name_, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(guarded<fn_>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {{"bind", f_bind, METH_O, nullptr},
                          FAST("decode", f_decode),
                          FAST("decode_grouped", f_decode_grouped),

@@ -2,6 +2,7 @@
 ctypes path, which names the error.  Without a GPU nothing may be taken: the tensors are in host memory."""
 import pytest
 import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
 
 from paper_2511_09323_amd import binding as B
 
@@ -32,6 +33,15 @@ def test_errors_keep_their_names(fast):
         B.moc_ffn_decode(x, w, w, w, 16, ws=ws, out=(torch.zeros(4, 64), None))
     with pytest.raises(B.MocError, match="must be a GPU tensor"):
         B.moc_residual_add(x, x)
+
+
+def test_tensors_without_memory_raise(fast):
+    """A fake tensor says it is on the GPU and throws when asked for its address."""
+    with FakeTensorMode():
+        x, w = torch.empty(4, 64, device="cuda"), torch.empty(128, 64, device="cuda")
+        ws, idx = torch.empty(1 << 20, dtype=torch.uint8, device="cuda"), torch.empty(4, 16, dtype=torch.int32, device="cuda")
+        assert fast.decode(x, w, w, w, 16, x, idx, ws) == B._NOT_TAKEN
+        assert fast.residual_add(x, x) == B._NOT_TAKEN
 
 
 @pytest.mark.gpu
