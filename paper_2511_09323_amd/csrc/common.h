@@ -74,13 +74,6 @@ __device__ __forceinline__ int mbcnt(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// Largest of three (fmaxf would first quiet every operand, an instruction each).
-__device__ __forceinline__ float max3_f32(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // Wavefront reductions: lanes l and l ^ 32, then ^ 16, 8, 4, 2, 1 are combined; every lane gets the result.  The exchanges are register
 // moves (gfx950's half- and quarter-wavefront swaps, then rotations inside 16 lanes, which reach the xor partner because the values
 // repeat with the period of the step before); the same reduction through __shfl_xor costs six trips to LDS.

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kRowsNT, NCH <= 6 ? 4 : 2) void decode_select_up_ke
                 if (c * 4 * kRowsNT + tid * 4 + e >= F) v[c][e] = -__builtin_inff();
         }
     }
-    const RowCut cut = row_cut<kRowsNT, NCH, true>(v, K, L, c0);
+    const RowCut cut = row_cut<kRowsNT, NCH, true>(v, F, K, L, c0);
     const int below = cut.before;
     uint64_t mask[2];
 #pragma unroll

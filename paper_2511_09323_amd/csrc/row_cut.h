@@ -6,7 +6,8 @@
 // every wavefront.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
 // 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than K non-negative values, more than
 // 64 values in the bin (outliers, ties), ranges too small for the bin width -- goes on with the remaining range by the
-// general step until it is resolved.
+// general step until it is resolved.  Rows whose cut involves an infinity or a NaN are cut by a bisection over float_key
+// (+NaN above +inf, -NaN below -inf), the order of the radix select.
 // What bounds it: instructions per value (one row occupies one workgroup, often one compute unit) and the dependent steps
 // between barriers; about nine instructions per value and six barriers.  The radix select it replaces (three histograms over key digits,
 // colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
@@ -18,12 +19,18 @@ namespace moc {
 
 constexpr int kCutBins = 2048;
 
-// Channel j with value v is selected iff v > tau, or v == tau and j <= last.
+// Channel j with value v is selected iff v > tau, or v == tau and j <= last; with `end` set (non-finite rows, last < INT_MAX)
+// the same of keys, for the channels below end.
 struct RowCut {
     float tau;
     int last;      // INT_MAX: every value equal to tau is selected
     int before;    // BEFORE: selected channels below c0
-    __device__ __forceinline__ bool in(float v, int j) const { return v > tau || (v == tau && j <= last); }
+    int end = 0;
+    uint32_t key = 0;
+    __device__ __forceinline__ bool in(float v, int j) const {
+        if (end) return j < end && (float_key(v) > key || (float_key(v) == key && j <= last));
+        return v > tau || (v == tau && j <= last);
+    }
 };
 
 template <int NT> struct RowCutLds {
@@ -36,11 +43,11 @@ template <int NT> struct RowCutLds {
     int bin, need, cnt, ncand;
 };
 
-// v[c][e] is the value of channel c * 4 NT + tid * 4 + e; what lies past the row's end holds -inf.  1 <= K <= row length.
+// v[c][e] is the value of channel c * 4 NT + tid * 4 + e; what lies past the row's end (F) holds -inf.  1 <= K <= F.
 // BEFORE: also counts the selected channels below c0 (on the way, from the bins).
-// Deterministic; for non-finite values it ends, with some cut.  L may be overwritten after a barrier.
+// Exactly K channels are selected, whatever the values.  L may be overwritten after a barrier.
 template <int NT, int NCH, bool BEFORE>
-__device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCutLds<NT>& L, int c0 = 0) {
+__device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K, RowCutLds<NT>& L, int c0 = 0) {
     constexpr int NW = NT / 64, BPT = kCutBins / NT;
     static_assert(BPT == 2 || BPT == 4 || BPT == 8, "256, 512 or 1024 threads");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -57,16 +64,18 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCu
 #pragma unroll
             for (int q = 0; q < BPT; q += 4) *reinterpret_cast<u32x4_t*>(L.hist + base + q) = u32x4_t{0, 0, 0, 0};
     };
-    float vmax = -kInf;
+    // the maximum as an integer: the same as the floats' where one is not negative, and a NaN shows above infinity
+    auto bits_max = [](float a, float b) { return __int_as_float(max(__float_as_int(a), __float_as_int(b))); };
+    float vmax = __int_as_float((int)0x80000000);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) vmax = max3_f32(max3_f32(vmax, v[c][0], v[c][1]), v[c][2], v[c][3]);
-    vmax = wave_max(vmax);
+    for (int c = 0; c < NCH; ++c) vmax = bits_max(bits_max(bits_max(vmax, v[c][0]), v[c][1]), bits_max(v[c][2], v[c][3]));
+    vmax = wave_reduce(vmax, bits_max);
     clear_bins(BPT * tid);
     if (lane == 0) L.red_f[0][wave] = vmax;
     if (tid == 0) { L.bin = 0; L.need = K; L.cnt = 0; L.ncand = 0; }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) vmax = fmaxf(vmax, L.red_f[0][w]);
+    for (int w = 0; w < NW; ++w) vmax = bits_max(vmax, L.red_f[0][w]);
 
     // Scans the bins from the top for the one in which the running count reaches `need`; L.bin, L.need (what is still wanted in
     // that bin) and L.cnt (its size) are set, the bins are cleared and the total of all bins is returned.
@@ -171,13 +180,13 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCu
                     int x[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        x[e] = (int)(v[c][e] * scale0) - fb;
-                        near = min(near, (uint32_t)x[e]);
+                        x[e] = (int)(v[c][e] * scale0);      // (down to the lowest integer: no difference of it is formed)
+                        near = min(near, (uint32_t)x[e] ^ (uint32_t)fb);
                     }
                     if (BEFORE && c * 4 * NT < c0) {         // (uniform; only the chunk that holds c0 needs the channel test)
                         const int stop = c0 - (c * 4 * NT + tid * 4);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) above += (x[e] > 0 && e < stop) ? 1 : 0;
+                        for (int e = 0; e < 4; ++e) above += (x[e] > fb && e < stop) ? 1 : 0;
                     }
                 }
                 if (near == 0) {
@@ -193,44 +202,48 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCu
             }
         }
     }
-    int npos = 0;
-    if (fb == 0) {
+    // how many values (pred(value, channel)) there are in the row
+    auto count = [&](const auto& pred) {
+        int n = 0;
+        const int jb = opaque(tid * 4);
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) npos += v[c][e] >= 0.0f ? 1 : 0;
-        npos = (int)wave_sum((float)npos);                   // exact: counts are far below 2^24
-        if (lane == 0) L.red_i[wave] = npos;
+            for (int e = 0; e < 4; ++e) n += pred(v[c][e], c * 4 * NT + jb + e) ? 1 : 0;
+        n = (int)wave_sum((float)n);                         // exact: counts are far below 2^24
         __syncthreads();
-        npos = 0;
+        if (lane == 0) L.red_i[wave] = n;
+        __syncthreads();
+        n = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) npos += L.red_i[w];
+        for (int w = 0; w < NW; ++w) n += L.red_i[w];
+        return __builtin_amdgcn_readfirstlane(n);
+    };
+    // the channel of the n-th value in question
+    auto nth_channel = [&](int n, const auto& pred) {
+        int a = 0, b = NCH * 4 * NT - 1;
+#pragma unroll 1
+        while (a < b) {
+            const int m = (a + b) >> 1;
+            if (count([&](float t, int j) { return pred(t, j) && j <= m; }) >= n) b = m;
+            else a = m + 1;
+        }
+        return a;
+    };
+    auto count_before = [&](RowCut cut) {
+        if (BEFORE) cut.before = count([&](float t, int j) { return j < c0 && cut.in(t, j); });
+        return cut;
+    };
+    int npos = 0;
+    bool keyed = __float_as_int(vmax) >= 0x7F800000;         // +inf or +NaN
+    if (!keyed && fb == 0) {
+        npos = count([](float t, int) { return t >= 0.0f; });
         need = npos >= K ? K : K - npos;
+        if (npos < K) keyed = count([&](float t, int) { return t < 0.0f && t > -kInf; }) < need;
     }
     // ---- general step on the closed range [lo, hi] of the values in question: every value above hi is selected, `need` of those
     //      inside are.  A repetition takes at least the range's two ends apart, so it ends.
     float lo, hi;
-    auto count_before = [&](RowCut cut) {
-        if (BEFORE) {
-            int n = 0;
-            const int jb = opaque(tid * 4);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int j = c * 4 * NT + jb + e;
-                    n += (j < c0 && cut.in(v[c][e], j)) ? 1 : 0;
-                }
-            n = (int)wave_sum((float)n);
-            __syncthreads();
-            if (lane == 0) L.red_b[wave] = n;
-            __syncthreads();
-            cut.before = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) cut.before += L.red_b[w];
-        }
-        return cut;
-    };
     auto range_of = [&](const auto& in_question) {
         float a = kInf, b = -kInf;
 #pragma unroll
@@ -248,33 +261,13 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCu
         lo = a;
         hi = b;
     };
-    if (fb > 0) range_of([&](float t) { return (int)(t * scale0) == fb; });
+    if (keyed) lo = hi = 0.0f;
+    else if (fb > 0) range_of([&](float t) { return (int)(t * scale0) == fb; });
     else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
     else range_of([&](float t) { return t < 0.0f && t > -kInf; });
-    for (int it = 0; it < 300; ++it) {
-        if (lo == hi) {
-            // all equal: the first `need` channels, by bisection over the channel index
-            int a = 0, b = NCH * 4 * NT - 1;
-            while (a < b) {
-                const int m = (a + b) >> 1;
-                int n = 0;
-                const int jb = opaque(tid * 4);
-#pragma unroll
-                for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) n += (v[c][e] == lo && c * 4 * NT + jb + e <= m) ? 1 : 0;
-                n = (int)wave_sum((float)n);
-                __syncthreads();
-                if (lane == 0) L.red_i[wave] = n;
-                __syncthreads();
-                n = 0;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) n += L.red_i[w];
-                if (n >= need) b = m;
-                else a = m + 1;
-            }
-            return count_before(RowCut{lo, a, 0});
-        }
+    for (int it = 0; !keyed && it < 300; ++it) {
+        if (lo == hi)      // all equal: the first `need` channels
+            return count_before(RowCut{lo, nth_channel(need, [&](float t, int) { return t == lo; }), 0});
         // monotonic in t, lo falls into bin 0 and hi into the last ones (`pre` keeps the factor finite for tiny ranges)
         const float pre = hi - lo < 1e-30f ? 0x1p100f : 1.0f;
         const float scale = (float)kCutBins / ((hi - lo) * pre);
@@ -300,7 +293,17 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int K, RowCu
         const float l0 = lo, h0 = hi;
         range_of([&](float t) { return t >= l0 && t <= h0 && min(kCutBins - 1, (int)fminf((t - l0) * pre * scale, 4096.0f)) == fb; });
     }
-    return RowCut{vmax, 0x7FFFFFFF, 0};
+    // ---- by keys
+    uint32_t key = 0, top = 0xFFFFFFFFu;                   // the K-th largest key is the largest that K keys reach
+#pragma unroll 1
+    while (key < top) {
+        const uint32_t m = top - (top - key) / 2;
+        if (count([&](float t, int j) { return j < F && float_key(t) >= m; }) >= K) key = m;
+        else top = m - 1;
+    }
+    const int above = count([&](float t, int j) { return j < F && float_key(t) > key; });
+    const int last = nth_channel(K - above, [&](float t, int j) { return j < F && float_key(t) == key; });
+    return count_before(RowCut{0.0f, last, 0, F, key});
 }
 
 }  // namespace moc

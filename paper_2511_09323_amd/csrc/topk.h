@@ -324,7 +324,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
                 if (c * CHUNK + tid * 4 + e >= F) v[c][e] = -__builtin_inff();
         }
     }
-    const RowCut cut = row_cut<NT, NCH, false>(v, K, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
+    const RowCut cut = row_cut<NT, NCH, false>(v, F, K, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
     const bool straddle = cut.last != 0x7FFFFFFF;          // values equal to tau on both sides of the cut (uniform)
 
     // ---- one ballot sweep: per-lane prefixes in registers, per-wave totals to LDS

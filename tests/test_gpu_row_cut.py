@@ -55,3 +55,54 @@ def test_decode_selection_on_hard_rows(B, d, F, dtype):
             ref = np.stack([np.flatnonzero(r) for r in O.topk_mask(want, K)])
             np.testing.assert_array_equal(idx.cpu().numpy(), ref)
             assert torch.isfinite(y).all()
+
+
+def by_key(g, K):
+    """The K channels of each row with the largest float keys (+NaN above +inf, -NaN below -inf, -0.0 equal to +0.0), ties to
+    the lower channel, ascending."""
+    u = (g + np.float32(0)).view(np.uint32).astype(np.int64)
+    key = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)
+    return np.sort(np.argsort(-key, axis=1, kind="stable")[:, :K], axis=1)
+
+
+def nonfinite_rows(F, seed):
+    rng = np.random.default_rng(seed)
+    g = rng.standard_normal((8, F)).astype(np.float32)
+    inf = np.float32(np.inf)
+    g[0, rng.random(F) < 0.9] = -inf                                     # a mask
+    g[1] = -inf
+    g[2, rng.random(F) < 0.3] = inf
+    g[3, ::7], g[3, 1::7] = np.nan, -np.nan
+    g[4] = np.nan
+    g[5] = np.where(rng.random(F) < 0.5, -inf, -np.abs(g[5]))
+    g[6] = np.where(rng.random(F) < 0.5, -3e38, 1e-6 * np.abs(g[6]))     # far below what the bins can count
+    g[7, ::5], g[7, 2::5], g[7, 3::5] = -np.nan, inf, np.finfo(np.float32).min
+    return g
+
+
+@pytest.mark.parametrize("F", [5, 64, 1376, 5461, 11008])
+def test_rows_with_infinities_and_nans(F):
+    g = nonfinite_rows(F, F)
+    for K in sorted({1, F // 8, F // 2, F - 1, F} - {0}):
+        idx, gsel = moc.moc_topk_rows(torch.from_numpy(g).cuda(), K)
+        torch.cuda.synchronize()
+        want = by_key(g, K)
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+        np.testing.assert_array_equal(gsel.cpu().numpy(), np.take_along_axis(g, want, axis=1))
+
+
+@pytest.mark.parametrize("B,d,F", [(1, 64, 5), (3, 256, 1376), (4, 128, 11008)])
+def test_decode_selection_with_infinities(B, d, F):
+    rows = inputs.round_to_bf16(nonfinite_rows(F, F + 1)[[0, 1, 5, 6]])
+    if np.isinf(rows[3]).any():
+        rows[3] = np.where(np.isinf(rows[3]), np.float32(-1e38), rows[3])
+    L = inputs.make_layer(97, B, d, F, "f32")
+    for row in rows:                                                     # one-hot tokens: 0 * -inf would be a NaN, so one row at a time
+        L["x"] = np.zeros((B, d), dtype=np.float32)
+        L["x"][:, 0] = 1.0
+        L["wg"][:, 0] = row
+        G = {k: P.to_dev(v, "f32") for k, v in L.items()}
+        for K in sorted({1, F // 8, F // 2, F} - {0}):
+            _, idx = moc.moc_ffn_decode(G["x"], G["wg"], G["wu"], G["wd"], K)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(idx.cpu().numpy(), np.repeat(by_key(row[None], K), B, axis=0))
