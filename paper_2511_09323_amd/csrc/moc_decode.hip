@@ -273,6 +273,13 @@ moc_status launch_down_cols(const Dims& D, const E* wd, const int32_t* idx, cons
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }
+// The three launches save the selection's and the partial outputs' time; the gather of decode_updown_kernel, both rows of a channel in
+// flight together, streams faster.  At d 4096, F 11008, bf16 (bytes of the tokens' selected rows; this / gather): one token 22.5 MB 35.6 /
+// 43.0 us, 180 MB (K = F) 93.5 / 71.0; four tokens 90 MB 56.5 / 57.7, 721 MB 153.5 / 113.  The lines meet near 64 and 108 MB.
+template <class E> bool decode_rows_pays(const Dims& D) {
+    const int64_t bytes = (int64_t)2 * D.T * D.K * D.d * (int64_t)sizeof(E);
+    return D.T <= 4 && bytes <= (D.T == 1 ? 60000000 : 100000000);
+}
 template <class E>
 moc_status decode_rows(const Dims& D, const DecodeWs& W, const E* x, const E* wu, const E* wd, E* y, int32_t* idx, int key_mode,
                        hipStream_t st) {
@@ -356,7 +363,7 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         else s = decode_gate_group_b<E, 16>(D, x, wg, ga, gb, idx, W.gsel, st);
     }
     if (s != MOC_OK) return s;
-    if (gb == 0 && B <= 4 && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
+    if (gb == 0 && decode_rows_pays<E>(D) && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
     const int P = decode_splits(B, D.K);
     if (gb == 0 && key_mode == 0 && gather_fused && options().decode_select_gather && (D.F + P - 1) / P <= kDsgMaxRange &&
         decode_select_gather_lds<E>(D.d) <= (size_t)kSelectGatherMaxLds) {
