@@ -20,6 +20,7 @@
 #pragma once
 #include "common.h"
 #include "gemm_generic.h"
+#include "gemm_plan.h"
 #include "kernel_attrs.h"
 
 namespace moc {
@@ -83,8 +84,8 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
         const int k0 = (seg ? kt - nk0 : kt) * BK, left = (seg ? pr.Kc2 : pr.Kc) - k0;      // left >= 1
         const float* pa = (seg ? pr.A.p2 : pr.A.p) + (AKM ? k0 * pr.A.ld : (int64_t)k0);
         const float* pb = (seg ? pr.B.p2 : pr.B.p) + (BKM ? k0 * pr.B.ld : (int64_t)k0);
-        const int a_last = AKM ? (left - 1) * (int)pr.A.ld : ((left + 3) & ~3) - 4;
-        const int b_last = BKM ? (left - 1) * (int)pr.B.ld : ((left + 3) & ~3) - 4;
+        const int a_last = AKM ? last_row_offset(left, BK, (int)pr.A.ld) : ((left + 3) & ~3) - 4;
+        const int b_last = BKM ? last_row_offset(left, BK, (int)pr.B.ld) : ((left + 3) & ~3) - 4;
 #pragma unroll
         for (int i = 0; i < LA; ++i) ga[buf][i] = *reinterpret_cast<const f32x4_t*>(pa + (uint32_t)(a_off[i] + min(a_koff[i], a_last)));
 #pragma unroll
