@@ -35,6 +35,7 @@
 
 #include "common.h"
 #include "gemm_generic.h"
+#include "gemm_plan.h"
 #include "kernel_attrs.h"
 
 namespace moc {
@@ -281,7 +282,8 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
         const int klen = seg ? t.Kc2 : t.Kc;
         const int kwant = (seg ? kt - t.nk0 : kt) * BK;                                  // first k still to accumulate
         const int kfrom = TAILMODE == 1 ? min(kwant, ((klen + 7) & ~7) - BK) : kwant;   // first k read
-        const int klast = klen - 1 - kfrom;                                              // last valid k row of this slice
+        [[maybe_unused]] const int a_last = last_row_offset(klen - kfrom, BK, t.lda);    // last valid k row of this slice
+        [[maybe_unused]] const int b_last = last_row_offset(klen - kfrom, BK, t.ldb);
         // TAILMODE 1: the chunks of this slice that lie before the part still to accumulate or past the end are
         // zeroed when the slice goes to LDS, not here: a select on a value just loaded would make the wavefront
         // wait for the load at once and undo the prefetch
@@ -291,7 +293,7 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             int off = t.a_off[i];
-            if (AKM) off += (TAILMODE == 1 ? min(a_k[i] * t.lda, klast * t.lda) : a_k[i] * t.lda);
+            if (AKM) off += (TAILMODE == 1 ? min(a_k[i] * t.lda, a_last) : a_k[i] * t.lda);
             // uniform base + unsigned 32-bit byte offset: the load takes the base from scalar registers
             ga[buf][i] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(ap) + (uint32_t)off * 2u);
             if (TAILMODE == 1) {
@@ -302,7 +304,7 @@ __device__ __forceinline__ void gemm_bf16_mfma_tiles(const MfmaProblem* prs, con
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             int off = t.b_off[i];
-            if (BKM) off += (TAILMODE ? min(b_k[i] * t.ldb, klast * t.ldb) : b_k[i] * t.ldb);
+            if (BKM) off += (TAILMODE ? min(b_k[i] * t.ldb, b_last) : b_k[i] * t.ldb);
             gb[buf][i] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(bp) + (uint32_t)off * 2u);
             if (TAILMODE == 1) {
                 const int k = kfrom + b_k[i];
