@@ -284,9 +284,9 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
 
 // Up to NB products that differ only in their row counts (and, for weight gradients, in their
 // contraction lengths) in one launch: one per expert of an MoE layer.  Problems with M = 0 are
-// skipped.  Falls back to one run_gemm per problem when the MFMA kernel cannot take all of them.
+// skipped.  Falls back to one run_gemm per problem when the MFMA kernel cannot take all of them (`ascending` see launch_gemm_f32).
 template <class E, bool AKM, bool BKM, class Epi, int NB>
-moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* pr, const Epi* epi, hipStream_t st) {
+moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* pr, const Epi* epi, hipStream_t st, bool ascending = false) {
     if constexpr (std::is_same<E, bf16_t>::value) {
         bool ok = !options().force_generic && nprob <= NB;
         bool tail = false, padded = true;
@@ -328,7 +328,7 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
     }
     for (int z = 0; z < nprob; ++z) {
         if (pr[z].M == 0) continue;
-        moc_status s = run_gemm<E, AKM, BKM>(name, pr[z], epi[z], st);
+        moc_status s = run_gemm<E, AKM, BKM>(name, pr[z], epi[z], st, nullptr, ascending);
         if (s != MOC_OK) return s;
     }
     return MOC_OK;

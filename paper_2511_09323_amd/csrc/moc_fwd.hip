@@ -83,7 +83,7 @@ moc_status fwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
         pr[e] = GemmProblem<E>{kc_operand<E>(x + r0 * D.d, D.d), kc_operand<E>(wg + e * wsz, D.d), off[e + 1] - off[e], D.F, D.d, 0, false};
         eg[e] = EpiStore<float>{W.G + r0 * D.ldF, D.ldF, Fs, 0};
     }
-    if ((s = run_gemm_grouped<E, false, false, EpiStore<float>, kMaxExperts>("gemm_gate_experts", n_exp, pr, eg, st)) != MOC_OK) return s;
+    if ((s = run_gemm_grouped<E, false, false, EpiStore<float>, kMaxExperts>("gemm_gate_experts", n_exp, pr, eg, st, true)) != MOC_OK) return s;
     for (int e = 0; e < n_exp; ++e) {
         const int64_t r0 = off[e];
         pr[e].B = kc_operand<E>(wu + e * wsz, D.d);

@@ -92,6 +92,23 @@ def test_one_expert_is_the_plain_layer():
     assert torch.equal(idx, idx0) and torch.equal(y, y0) and torch.equal(gv, gv0) and torch.equal(uv, uv0)
 
 
+def test_f32_expert_gates_do_not_depend_on_the_number_of_rows():
+    """The fp32 gate is one sum over ascending k, whatever tiles a product of that many rows takes: an expert's stored set is that of
+    the plain layer on its rows, bit for bit (so that a near-tied row selects the same channels)."""
+    counts, d, F, K = (3, 40, 0, 700), 132, 520, 65
+    W = make_experts(720, 4, d, F, "f32")
+    offsets = [0, 3, 43, 43, 743]
+    x = P.to_dev(inputs.normal((offsets[-1], d), 820, 1.0, "f32"), "f32")
+    Wd_ = {k: P.to_dev(v, "f32") for k, v in W.items()}
+    _, idx, gv, _ = moc.moc_ffn_fwd_experts(x, offsets, Wd_["wg"], Wd_["wu"], Wd_["wd"], K)
+    for e in range(4):
+        rows = slice(offsets[e], offsets[e + 1])
+        if counts[e]:
+            _, idx0, gv0, _ = moc.moc_ffn_fwd(x[rows].contiguous(), Wd_["wg"][e], Wd_["wu"][e], Wd_["wd"][e], K)
+            torch.cuda.synchronize()
+            assert torch.equal(idx[rows], idx0) and torch.equal(gv[rows], gv0), e
+
+
 @pytest.mark.parametrize("counts,d,F,K,dtype", [
     ((40, 0, 33, 200, 7, 64, 90, 50), 128, 520, 65, "bf16"),       # ragged, one empty, one below 32 rows
     ((64, 96, 160), 96, 200, 25, "f32"),
