@@ -67,6 +67,13 @@ __device__ __forceinline__ float key_float(uint32_t k) {
     return __uint_as_float(u);
 }
 
+// Towards zero; values outside the integer range give its nearest end, NaN gives 0 (a cast leaves both undefined).
+__device__ __forceinline__ int cvt_i32(float f) {
+    int r;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(f));
+    return r;
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Number of set bits of `mask` below this lane.

@@ -34,8 +34,7 @@ struct RowCut {
 };
 
 template <int NT> struct RowCutLds {
-    uint32_t below[64];      // where the counts of negative values go, a word per lane
-    uint32_t hist[kCutBins];
+    uint32_t count[64 + kCutBins];      // a word per lane for what lies below the bins, then the bins
     float cand_v[64];
     int cand_j[64];
     float red_f[2][NT / 64];
@@ -52,6 +51,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     static_assert(BPT == 2 || BPT == 4 || BPT == 8, "256, 512 or 1024 threads");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float kInf = __builtin_inff();
+    uint32_t* const hist = L.count + 64;
     // a copy the compiler does not recognise: channel numbers are formed where they are used instead of kept in registers
     auto opaque = [](int t) {
         asm volatile("" : "+v"(t));
@@ -59,10 +59,10 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     };
 
     auto clear_bins = [&](int base) {
-        if (BPT == 2) *reinterpret_cast<u32x2_t*>(L.hist + base) = u32x2_t{0, 0};
+        if (BPT == 2) *reinterpret_cast<u32x2_t*>(hist + base) = u32x2_t{0, 0};
         else
 #pragma unroll
-            for (int q = 0; q < BPT; q += 4) *reinterpret_cast<u32x4_t*>(L.hist + base + q) = u32x4_t{0, 0, 0, 0};
+            for (int q = 0; q < BPT; q += 4) *reinterpret_cast<u32x4_t*>(hist + base + q) = u32x4_t{0, 0, 0, 0};
     };
     // the maximum as an integer: the same as the floats' where one is not negative, and a NaN shows above infinity
     auto bits_max = [](float a, float b) { return __int_as_float(max(__float_as_int(a), __float_as_int(b))); };
@@ -84,12 +84,12 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         const int base = kCutBins - BPT * (tid + 1);         // thread order is descending bin order
         uint32_t h[BPT];
         if (BPT == 2) {
-            const u32x2_t t = *reinterpret_cast<const u32x2_t*>(L.hist + base);
+            const u32x2_t t = *reinterpret_cast<const u32x2_t*>(hist + base);
             h[0] = t[0]; h[1] = t[1];
         } else {
 #pragma unroll
             for (int q = 0; q < BPT; q += 4) {
-                const u32x4_t t = *reinterpret_cast<const u32x4_t*>(L.hist + base + q);
+                const u32x4_t t = *reinterpret_cast<const u32x4_t*>(hist + base + q);
                 h[q] = t[0]; h[q + 1] = t[1]; h[q + 2] = t[2]; h[q + 3] = t[3];
             }
         }
@@ -165,7 +165,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) atomicAdd(L.hist + max((int)(v[c][e] * scale0), floor_bin), 1u);
+            for (int e = 0; e < 4; ++e) atomicAdd(hist + max(cvt_i32(v[c][e] * scale0), floor_bin), 1u);
         const int total = scan(need);
         fb = total >= need ? L.bin : 0;
         const int cnt = L.cnt;
@@ -180,7 +180,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
                     int x[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        x[e] = (int)(v[c][e] * scale0);      // (down to the lowest integer: no difference of it is formed)
+                        x[e] = cvt_i32(v[c][e] * scale0);      // (down to the lowest integer: no difference of it is formed)
                         near = min(near, (uint32_t)x[e] ^ (uint32_t)fb);
                     }
                     if (BEFORE && c * 4 * NT < c0) {         // (uniform; only the chunk that holds c0 needs the channel test)
@@ -196,7 +196,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
                     for (int c = 0; c < NCH; ++c)
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            if ((int)(v[c][e] * scale0) == fb) keep(v[c][e], c * 4 * NT + jb + e);
+                            if (cvt_i32(v[c][e] * scale0) == fb) keep(v[c][e], c * 4 * NT + jb + e);
                 }
                 return rank_kept(cnt, need, above);
             }
@@ -262,7 +262,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         hi = b;
     };
     if (keyed) lo = hi = 0.0f;
-    else if (fb > 0) range_of([&](float t) { return (int)(t * scale0) == fb; });
+    else if (fb > 0) range_of([&](float t) { return cvt_i32(t * scale0) == fb; });
     else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
     else range_of([&](float t) { return t < 0.0f && t > -kInf; });
     for (int it = 0; !keyed && it < 300; ++it) {
@@ -276,7 +276,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (v[c][e] >= lo && v[c][e] <= hi) atomicAdd(&L.hist[bin_of(v[c][e])], 1u);
+                if (v[c][e] >= lo && v[c][e] <= hi) atomicAdd(&hist[bin_of(v[c][e])], 1u);
         (void)scan(need);
         fb = L.bin;
         need = L.need;
