@@ -74,6 +74,13 @@ __device__ __forceinline__ int cvt_i32(float f) {
     return r;
 }
 
+// min(max(x, lo), hi) for lo <= hi in one instruction; hi uniform.
+__device__ __forceinline__ int clamp_i32(int x, int lo, int hi) {
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "s"(hi));
+    return r;
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
 // Number of set bits of `mask` below this lane.

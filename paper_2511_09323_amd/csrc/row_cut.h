@@ -1,17 +1,19 @@
 // The cut of one row's Top-K, found by a workgroup that holds the row in registers: shared by the training forward's row
 // selection (topk.h) and by decode (decode_rows.h).
 //
-// Method: one histogram over 2048 bins of equal width between 0 and the row's maximum (a product, a conversion, a clamp and an LDS
-// atomic per value), a scan from the top for the bin that holds the K-th value, and a direct ranking of that bin's few values by
-// every wavefront.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
+// Method: one histogram over 2048 bins of equal width between 0 and the row's maximum, or a bound on the K-th value where outliers lie
+// far above it (a product, a conversion, a clamp and an LDS atomic per value), a scan from the top for the bin that holds the K-th value,
+// and a direct ranking of that bin's few values by every wavefront.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
 // 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than K non-negative values, more than
-// 64 values in the bin (outliers, ties), ranges too small for the bin width -- goes on with the remaining range by the
+// 64 values in the bin (ties), ranges too small for the bin width -- goes on with the remaining range by the
 // general step until it is resolved.  Rows whose cut involves an infinity or a NaN are cut by a bisection over float_key
 // (+NaN above +inf, -NaN below -inf), the order of the radix select.
 // What bounds it: instructions per value (one row occupies one workgroup, often one compute unit) and the dependent steps
 // between barriers; about nine instructions per value and six barriers.  The radix select it replaces (three histograms over key digits,
 // colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
+// Outliers (one value of 1000 standard deviations a row, 8192 rows of 11008, K 1376, forward at d 64): 180 us as for rows without, 240 with
+// bins up to the maximum, 220 with the radix select.
 #pragma once
 #include "common.h"
 
@@ -70,12 +72,19 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
 #pragma unroll
     for (int c = 0; c < NCH; ++c) vmax = bits_max(bits_max(bits_max(vmax, v[c][0]), v[c][1]), bits_max(v[c][2], v[c][3]));
     vmax = wave_reduce(vmax, bits_max);
+    float pos = 0.0f;                                        // sum of the positive values, from a quarter of the row
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) pos += __int_as_float(max(__float_as_int(v[c][0]), 0));
+    pos = wave_sum(pos);
     clear_bins(BPT * tid);
-    if (lane == 0) L.red_f[0][wave] = vmax;
+    if (lane == 0) { L.red_f[0][wave] = vmax; L.red_f[1][wave] = pos; }
     if (tid == 0) { L.bin = 0; L.need = K; L.cnt = 0; L.ncand = 0; }
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) vmax = bits_max(vmax, L.red_f[0][w]);
+    pos = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) pos += L.red_f[1][w];
 
     // Scans the bins from the top for the one in which the running count reaches `need`; L.bin, L.need (what is still wanted in
     // that bin) and L.cnt (its size) are set, the bins are cleared and the total of all bins is returned.
@@ -158,20 +167,25 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     int need = K, fb = 0;
     float scale0 = 0.0f;
     if (vmax > 1e-30f && vmax < 1e38f) {
-        scale0 = ((float)kCutBins - 1.0f) * __builtin_amdgcn_rcpf(vmax);      // v * scale0 < 2048 for every v <= vmax
+        // The bins end at the maximum or, where outliers lie above the rest, at 1.5 / K of the sum S of the positive values (the K-th
+        // value is at most S / K; 1.5 because S comes from a quarter of the row) or ten times their mean over the row, whichever is larger: what
+        // lies above shares the last bin.
+        const float far = pos * fmaxf(6.0f * __builtin_amdgcn_rcpf((float)K), 40.0f * __builtin_amdgcn_rcpf((float)F));
+        const float range = far > 1e-30f ? fminf(far, vmax) : vmax;
+        scale0 = ((float)kCutBins - 2.0f) * __builtin_amdgcn_rcpf(range);      // v * scale0 < 2047 for every v <= range
         // (no branch per value: negative ones count into the lane's own word in front of the bins; what truncates to bin 0 from
         // below spoils that bin, which is therefore not used)
         const int floor_bin = -1 - lane;
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) atomicAdd(hist + max(cvt_i32(v[c][e] * scale0), floor_bin), 1u);
+            for (int e = 0; e < 4; ++e) atomicAdd(hist + clamp_i32(cvt_i32(v[c][e] * scale0), floor_bin, kCutBins - 1), 1u);
         const int total = scan(need);
         fb = total >= need ? L.bin : 0;
         const int cnt = L.cnt;
         if (fb > 0) {
             need = L.need;
-            if (cnt <= 64) {
+            if (cnt <= 64 && fb < kCutBins - 1) {
                 asm volatile("" : "+v"(scale0));             // (keeps the compiler from holding every value's bin in a register)
                 uint32_t near = 1;
                 int above = 0;
@@ -262,7 +276,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         hi = b;
     };
     if (keyed) lo = hi = 0.0f;
-    else if (fb > 0) range_of([&](float t) { return cvt_i32(t * scale0) == fb; });
+    else if (fb > 0) range_of([&](float t) { return min(cvt_i32(t * scale0), kCutBins - 1) == fb; });
     else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
     else range_of([&](float t) { return t < 0.0f && t > -kInf; });
     for (int it = 0; !keyed && it < 300; ++it) {

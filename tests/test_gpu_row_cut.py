@@ -37,6 +37,28 @@ def test_rows_the_usual_path_does_not_resolve(F):
         _topk_case(g, K)
 
 
+def outlier_rows(F, seed):
+    """Rows whose bins end far below the maximum: one outlier, outliers that share the last bin with and without the cut among them,
+    positive values so few that the sampled quarter of the row may hold none."""
+    rng = np.random.default_rng(seed)
+    g = rng.standard_normal((6, F)).astype(np.float32)
+    g[0, F // 3] = 1000.0
+    n = max(1, F // 20)
+    g[1, rng.permutation(F)[:n]] = 1000.0 + np.arange(n)                 # distinct
+    g[2, rng.permutation(F)[:n]] = 1000.0                                # equal
+    g[3] = rng.standard_t(1.5, F)
+    g[4] = np.where(np.arange(F) % 4 == 1, np.abs(g[4]), -np.abs(g[4]))  # nothing positive in the sampled quarter
+    g[5] = np.where(np.arange(F) % 4 == 0, 1e37 * np.abs(g[5]), g[5])    # all of the sampled quarter far above the rest
+    return g.astype(np.float32)
+
+
+@pytest.mark.parametrize("F", [64, 1376, 5461, 11008, 14336])
+def test_rows_with_outliers(F):
+    g = outlier_rows(F, F)
+    for K in sorted({1, F // 40, F // 20, F // 20 + 1, F // 8, F // 5, F // 3} - {0}):
+        _topk_case(g, K)
+
+
 @pytest.mark.parametrize("B,d,F", [(1, 64, 5), (1, 512, 1376), (3, 256, 5461), (4, 128, 11008), (2, 64, 32768)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_decode_selection_on_hard_rows(B, d, F, dtype):
