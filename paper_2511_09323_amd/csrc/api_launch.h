@@ -364,6 +364,13 @@ moc_status launch_topk_reg(const char* name, const TopkArgs<E>& a, int T, hipStr
 // registers; everything else goes through the LDS-resident kernel.
 template <class E, int NT, bool FUSED>
 moc_status run_topk(const char* name, const TopkArgs<E>& a, int T, hipStream_t st) {
+    if (a.K == a.F) {
+        Span span(name, st);
+        const unsigned parts = (unsigned)(((FUSED ? a.ldz : a.F) + kAllSpan - 1) / kAllSpan);
+        hipLaunchKernelGGL((select_all_kernel<E, FUSED>), dim3(T, parts), dim3(256), 0, st, a);
+        HIP_TRY(hipGetLastError());
+        return MOC_OK;
+    }
     const bool aligned = a.ldg % 4 == 0 && aligned16(a.g);
     const int cover = FUSED ? (int)std::max<int64_t>(a.F, a.ldz) : a.F;
     const int nch = (cover + NT * 4 - 1) / (NT * 4);

@@ -3,7 +3,8 @@
 //
 // Method: one histogram over 2048 bins of equal width between 0 and the row's maximum, or a bound on the K-th value where outliers lie
 // far above it (a product, a conversion, a clamp and an LDS atomic per value), a scan from the top for the bin that holds the K-th value,
-// and a direct ranking of that bin's few values by every wavefront.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
+// and a direct ranking of that bin's few values by every wavefront.  Where more than a third of the row is selected, half of the
+// bins lie below zero.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
 // 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than K non-negative values, more than
 // 64 values in the bin (ties), ranges too small for the bin width -- goes on with the remaining range by the
 // general step until it is resolved.  Rows whose cut involves an infinity or a NaN are cut by a bisection over float_key
@@ -12,6 +13,7 @@
 // between barriers; about nine instructions per value and six barriers.  The radix select it replaces (three histograms over key digits,
 // colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
+// K 5504 of those rows: 372 us, 429 without bins below zero, 467 with the radix select.
 // Outliers (one value of 1000 standard deviations a row, 8192 rows of 11008, K 1376, forward at d 64): 180 us as for rows without, 240 with
 // bins up to the maximum, 220 with the radix select.
 #pragma once
@@ -59,6 +61,8 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         asm volatile("" : "+v"(t));
         return t;
     };
+
+    if (K == F) return RowCut{0.0f, F - 1, min(c0, F), F, 0u};      // (every key is above or equal to 0)
 
     auto clear_bins = [&](int base) {
         if (BPT == 2) *reinterpret_cast<u32x2_t*>(hist + base) = u32x2_t{0, 0};
@@ -165,21 +169,24 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     };
 
     int need = K, fb = 0;
-    float scale0 = 0.0f;
+    float scale0 = 0.0f, zero_bin = 0.0f;
+    auto bin_at = [&](float t) { return cvt_i32(fmaf(t, scale0, zero_bin)); };
     if (vmax > 1e-30f && vmax < 1e38f) {
         // The bins end at the maximum or, where outliers lie above the rest, at 1.5 / K of the sum S of the positive values (the K-th
         // value is at most S / K; 1.5 because S comes from a quarter of the row) or ten times their mean over the row, whichever is larger: what
         // lies above shares the last bin.
         const float far = pos * fmaxf(6.0f * __builtin_amdgcn_rcpf((float)K), 40.0f * __builtin_amdgcn_rcpf((float)F));
         const float range = far > 1e-30f ? fminf(far, vmax) : vmax;
-        scale0 = ((float)kCutBins - 2.0f) * __builtin_amdgcn_rcpf(range);      // v * scale0 < 2047 for every v <= range
-        // (no branch per value: negative ones count into the lane's own word in front of the bins; what truncates to bin 0 from
+        // From zero upwards, or from -range upwards where more than a third of the row is selected and the cut may lie below zero.
+        zero_bin = 3 * K > F ? kCutBins / 2 : 0.0f;
+        scale0 = ((float)kCutBins - 2.0f - zero_bin) * __builtin_amdgcn_rcpf(range);      // bin_at(v) < 2047 for every v <= range
+        // (no branch per value: those below count into the lane's own word in front of the bins; what truncates to bin 0 from
         // below spoils that bin, which is therefore not used)
         const int floor_bin = -1 - lane;
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) atomicAdd(hist + clamp_i32(cvt_i32(v[c][e] * scale0), floor_bin, kCutBins - 1), 1u);
+            for (int e = 0; e < 4; ++e) atomicAdd(hist + clamp_i32(bin_at(v[c][e]), floor_bin, kCutBins - 1), 1u);
         const int total = scan(need);
         fb = total >= need ? L.bin : 0;
         const int cnt = L.cnt;
@@ -194,7 +201,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
                     int x[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        x[e] = cvt_i32(v[c][e] * scale0);      // (down to the lowest integer: no difference of it is formed)
+                        x[e] = bin_at(v[c][e]);      // (down to the lowest integer: no difference of it is formed)
                         near = min(near, (uint32_t)x[e] ^ (uint32_t)fb);
                     }
                     if (BEFORE && c * 4 * NT < c0) {         // (uniform; only the chunk that holds c0 needs the channel test)
@@ -210,7 +217,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
                     for (int c = 0; c < NCH; ++c)
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            if (cvt_i32(v[c][e] * scale0) == fb) keep(v[c][e], c * 4 * NT + jb + e);
+                            if (bin_at(v[c][e]) == fb) keep(v[c][e], c * 4 * NT + jb + e);
                 }
                 return rank_kept(cnt, need, above);
             }
@@ -276,7 +283,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         hi = b;
     };
     if (keyed) lo = hi = 0.0f;
-    else if (fb > 0) range_of([&](float t) { return min(cvt_i32(t * scale0), kCutBins - 1) == fb; });
+    else if (fb > 0) range_of([&](float t) { return min(bin_at(t), kCutBins - 1) == fb; });
     else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
     else range_of([&](float t) { return t < 0.0f && t > -kInf; });
     for (int it = 0; !keyed && it < 300; ++it) {

@@ -276,6 +276,36 @@ __global__ __launch_bounds__(NT) void topk_rows_lds_kernel(TopkArgs<E> a) {
     }
 }
 
+// ---------------------------------------------------------------- K = F: nothing to select
+// Bound by its stores; workgroup (t, p) writes channels p * kAllSpan .. of row t, padding of Z' included.  8192 rows of 5461: 193 us (297
+// with a radix select, 465 with a cut and the gather of the row kernel).
+constexpr int kAllSpan = 1024;
+template <class E, bool FUSED>
+__global__ __launch_bounds__(256) void select_all_kernel(TopkArgs<E> a) {
+    constexpr int U = kAllSpan / 256;
+    const int64_t row = blockIdx.x;
+    const float* grow = (a.g_raw ? a.g_raw : a.g) + row * a.ldg;
+    const int j0 = blockIdx.y * kAllSpan + threadIdx.x;
+    float g[U], u[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int j = min(j0 + q * 256, a.F - 1);
+        g[q] = a.g_raw ? grow[j] : grow[j] + 0.0f;           // (-0.0 is stored as +0.0)
+        if (FUSED) u[q] = Elem<E>::load(a.u + row * a.ldu + j);
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        const int j = j0 + q * 256;
+        if (j < a.F) {
+            a.idx[row * a.F + j] = j;
+            if (a.gsel_f32) a.gsel_f32[row * a.F + j] = g[q];
+            if (a.gvals) Elem<E>::store(a.gvals + row * a.F + j, g[q]);
+            if (FUSED) Elem<E>::store(a.uvals + row * a.F + j, u[q]);
+        }
+        if (FUSED && j < a.ldz) Elem<E>::store(a.zd + row * a.ldz + j, j < a.F ? silu_f32(g[q]) * u[q] : 0.0f);
+    }
+}
+
 // ---------------------------------------------------------------- register-resident variant
 // The selected set without the index list: a channel j with key k belongs to it iff k > tau, or k == tau and j <= cut
 // (cut = INT_MAX when every key equal to tau is in).
@@ -324,6 +354,9 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
                 if (c * CHUNK + tid * 4 + e >= F) v[c][e] = -__builtin_inff();
         }
     }
+    // ---- slot lists and the dense row; they take over the LDS of the cut
+    u32x2_t* rec = reinterpret_cast<u32x2_t*>(topk_dyn);              // [K] records {channel, value}
+    E* zrow = reinterpret_cast<E*>(topk_dyn + ((size_t)2 * K * 4 + 15) / 16 * 16);   // [ldz] (FUSED)
     const RowCut cut = row_cut<NT, NCH, false>(v, F, K, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
     const bool straddle = cut.last != 0x7FFFFFFF;          // values equal to tau on both sides of the cut (uniform)
 
@@ -364,15 +397,10 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
                 run += tab[c * NW + w];
             }
     }
-    // ---- slot lists and the dense row take over the LDS of the cut (dead since the last barrier)
-    u32x2_t* rec = reinterpret_cast<u32x2_t*>(topk_dyn);              // [K] records {channel, value}
-    E* zrow = reinterpret_cast<E*>(topk_dyn + ((size_t)2 * K * 4 + 15) / 16 * 16);   // [ldz] (FUSED)
-    const int ldz = FUSED ? (int)a.ldz : 0;
-    if (FUSED) {
+    if (FUSED) {                                            // (the cut's LDS is dead since the last barrier)
         constexpr int PER = 16 / (int)sizeof(E);
-        for (int i = tid * PER; i < ldz; i += NT * PER) *reinterpret_cast<u32x4_t*>(zrow + i) = u32x4_t{0, 0, 0, 0};
+        for (int i = tid * PER; i < (int)a.ldz; i += NT * PER) *reinterpret_cast<u32x4_t*>(zrow + i) = u32x4_t{0, 0, 0, 0};
     }
-
     asm volatile("" : "+v"(jb));
     // ---- rank: every selected channel drops (channel, gate value) into LDS at its
     //      output slot (number of selected channels before it)
@@ -391,25 +419,42 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
         }
     }
     __syncthreads();
-    // ---- write the compact outputs slot by slot (coalesced) and scatter z' into the dense row
-    for (int sl = tid; sl < K; sl += NT) {
-        const u32x2_t r = rec[sl];
-        const int j = (int)min(r[0], (uint32_t)(F - 1));  // the clamp only matters for non-finite input
-        const float g = a.g_raw ? a.g_raw[row * a.ldg + j] : __uint_as_float(r[1]) + 0.0f;      // (-0.0 is stored as +0.0)
-        a.idx[row * K + sl] = j;
-        if (a.gsel_f32) a.gsel_f32[row * K + sl] = g;
-        if (a.gvals) Elem<E>::store(a.gvals + row * K + sl, g);
-        if (FUSED) {
-            const float u = Elem<E>::load(a.u + row * a.ldu + j);
-            Elem<E>::store(a.uvals + row * K + sl, u);
-            Elem<E>::store(zrow + j, silu_f32(g) * u);
+    // ---- write the compact outputs slot by slot (coalesced) and scatter z' into the dense row; the gathered loads of up to four slots of a
+    //      thread go out together (8192 rows of 5461: K 4000 255 us, 280 with a slot at a time, K 683 88.8 and 90.3)
+    auto write_slots = [&](auto slots_c) {
+        constexpr int NS = decltype(slots_c)::value;
+        for (int s0 = tid; s0 < K; s0 += NS * NT) {
+            int j[NS];
+            float g[NS], u[NS];
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const u32x2_t r = rec[min(s0 + q * NT, K - 1)];
+                j[q] = (int)min(r[0], (uint32_t)(F - 1));     // (every slot holds a channel: the bound only guards the loads)
+                g[q] = a.g_raw ? a.g_raw[row * a.ldg + j[q]] : __uint_as_float(r[1]) + 0.0f;      // (-0.0 is stored as +0.0)
+                if (FUSED) u[q] = Elem<E>::load(a.u + row * a.ldu + j[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const int sl = s0 + q * NT;
+                if (sl >= K) break;
+                a.idx[row * K + sl] = j[q];
+                if (a.gsel_f32) a.gsel_f32[row * K + sl] = g[q];
+                if (a.gvals) Elem<E>::store(a.gvals + row * K + sl, g[q]);
+                if (FUSED) {
+                    Elem<E>::store(a.uvals + row * K + sl, u[q]);
+                    Elem<E>::store(zrow + j[q], silu_f32(g[q]) * u[q]);
+                }
+            }
         }
-    }
+    };
+    if (K <= NT) write_slots(std::integral_constant<int, 1>{});
+    else if (K <= 2 * NT) write_slots(std::integral_constant<int, 2>{});
+    else write_slots(std::integral_constant<int, 4>{});
     if (FUSED) {
         __syncthreads();
         constexpr int PER = 16 / (int)sizeof(E);
         E* zout = a.zd + row * a.ldz;
-        for (int i = tid * PER; i < ldz; i += NT * PER)
+        for (int i = tid * PER; i < (int)a.ldz; i += NT * PER)
             *reinterpret_cast<u32x4_t*>(zout + i) = *reinterpret_cast<const u32x4_t*>(zrow + i);
     }
 }

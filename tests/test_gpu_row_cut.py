@@ -59,6 +59,16 @@ def test_rows_with_outliers(F):
         _topk_case(g, K)
 
 
+@pytest.mark.parametrize("F", [9, 1376, 5461, 11008])
+def test_cuts_below_zero(F):
+    """More than a third of the row: bins on both sides of zero; K on both sides of that line, of the slots a thread writes at a time
+    (256 and 512), and the whole row."""
+    g = np.concatenate([outlier_rows(F, F + 2), hard_rows(F, F + 2)])
+    g[0] -= 0.5
+    for K in sorted({F // 3, F // 3 + 1, F // 2 + 3, 3 * F // 4, F - 1, F, min(F, 256), min(F, 257), min(F, 513)}):
+        _topk_case(g, K)
+
+
 @pytest.mark.parametrize("B,d,F", [(1, 64, 5), (1, 512, 1376), (3, 256, 5461), (4, 128, 11008), (2, 64, 32768)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_decode_selection_on_hard_rows(B, d, F, dtype):
@@ -71,7 +81,7 @@ def test_decode_selection_on_hard_rows(B, d, F, dtype):
             L["x"][b, (first + b) % 8] = 1.0
         G = {k: P.to_dev(v, dtype) for k, v in L.items()}
         want = rows[[(first + b) % 8 for b in range(B)]]
-        for K in sorted({1, F // 8, F // 2, F} - {0}):
+        for K in sorted({1, F // 8, F // 2, 3 * F // 4, F} - {0}):
             y, idx = moc.moc_ffn_decode(G["x"], G["wg"], G["wu"], G["wd"], K)
             torch.cuda.synchronize()
             ref = np.stack([np.flatnonzero(r) for r in O.topk_mask(want, K)])
