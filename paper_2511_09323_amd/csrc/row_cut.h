@@ -14,6 +14,7 @@
 // colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
 // K 5504 of those rows: 372 us, 429 without bins below zero, 467 with the radix select.
+// Hundreds of ties at the cut: 202 us, 385 with a bisection over the channels, 260 with the radix select.
 // Outliers (one value of 1000 standard deviations a row, 8192 rows of 11008, K 1376, forward at d 64): 180 us as for rows without, 240 with
 // bins up to the maximum, 220 with the radix select.
 #pragma once
@@ -58,6 +59,11 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     uint32_t* const hist = L.count + 64;
     // a copy the compiler does not recognise: channel numbers are formed where they are used instead of kept in registers
     auto opaque = [](int t) {
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    // the same of a value, so that what is formed from it is not kept from one pass to the next
+    auto opaque_value = [](float t) {
         asm volatile("" : "+v"(t));
         return t;
     };
@@ -240,16 +246,56 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         for (int w = 0; w < NW; ++w) n += L.red_i[w];
         return __builtin_amdgcn_readfirstlane(n);
     };
-    // the channel of the n-th value in question
+    // the channel of the n-th value in question, in one pass: the values of every (chunk, wavefront) are counted, the one that holds the
+    // n-th is found from the counts, and its wavefront looks the channel up.  (The counts take the place of the bins.)
     auto nth_channel = [&](int n, const auto& pred) {
-        int a = 0, b = NCH * 4 * NT - 1;
-#pragma unroll 1
-        while (a < b) {
-            const int m = (a + b) >> 1;
-            if (count([&](float t, int j) { return pred(t, j) && j <= m; }) >= n) b = m;
-            else a = m + 1;
+        constexpr int NG = NCH * NW;
+        const int jb = opaque(tid * 4);
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            int m = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m += __popcll(__ballot(pred(v[c][e], c * 4 * NT + jb + e)));
+            if (lane == 0) hist[c * NW + wave] = (uint32_t)m;
         }
-        return a;
+        if (tid == 0) L.bin = F - 1;
+        __syncthreads();
+        int group = -1, left = n;                            // the group and what is still wanted in it
+#pragma unroll
+        for (int q = 0; q < NG; q += 64) {
+            const int m = q + lane < NG ? (int)hist[q + lane] : 0;
+            const int inc = wave_inclusive_sum(m);
+            const uint64_t reached = __ballot(inc >= left);
+            if (group < 0) {
+                if (reached) {
+                    const int at = __ffsll((unsigned long long)reached) - 1;
+                    left -= __builtin_amdgcn_readlane(inc - m, at);
+                    group = q + at;
+                } else {
+                    left -= __builtin_amdgcn_readlane(inc, 63);
+                }
+            }
+        }
+        if (group >= 0 && group % NW == wave) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                if (c == group / NW) {
+                    const int j0 = c * 4 * NT + opaque(tid * 4);
+                    bool in[4];
+                    int rank = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        in[e] = pred(opaque_value(v[c][e]), j0 + e);
+                        rank += mbcnt(__ballot(in[e]));
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (in[e] && ++rank == left) L.bin = j0 + e;
+                }
+        }
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(L.bin);
     };
     auto count_before = [&](RowCut cut) {
         if (BEFORE) cut.before = count([&](float t, int j) { return j < c0 && cut.in(t, j); });

@@ -358,7 +358,17 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
     u32x2_t* rec = reinterpret_cast<u32x2_t*>(topk_dyn);              // [K] records {channel, value}
     E* zrow = reinterpret_cast<E*>(topk_dyn + ((size_t)2 * K * 4 + 15) / 16 * 16);   // [ldz] (FUSED)
     const RowCut cut = row_cut<NT, NCH, false>(v, F, K, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
-    const bool straddle = cut.last != 0x7FFFFFFF;          // values equal to tau on both sides of the cut (uniform)
+    // values equal to tau on both sides of the cut, or NaN (uniform): decided once, a value that is out becomes a NaN
+    const bool keyed = cut.end != 0;
+    if (cut.last != 0x7FFFFFFF && !keyed) {
+        int jv = tid * 4;
+        asm volatile("" : "+v"(jv));
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (v[c][e] == cut.tau && c * CHUNK + jv + e > cut.last) v[c][e] = __builtin_nanf("");
+    }
 
     // ---- one ballot sweep: per-lane prefixes in registers, per-wave totals to LDS
     int pg[NCH];
@@ -370,7 +380,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             bool in = v[c][e] >= cut.tau;
-            if (straddle) in = cut.in(v[c][e], c * CHUNK + jb + e);
+            if (keyed) in = cut.in(v[c][e], c * CHUNK + jb + e);
             const uint64_t bg = __ballot(in);
             lg += mbcnt(bg);
             ngt += __popcll(bg);
@@ -411,7 +421,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             bool in = v[c][e] >= cut.tau;
-            if (straddle) in = cut.in(v[c][e], j0 + e);
+            if (keyed) in = cut.in(v[c][e], j0 + e);
             if (in) {
                 rec[min(slot, K - 1)] = u32x2_t{(uint32_t)(j0 + e), __float_as_uint(v[c][e])};
                 ++slot;

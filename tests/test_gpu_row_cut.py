@@ -69,6 +69,16 @@ def test_cuts_below_zero(F):
         _topk_case(g, K)
 
 
+@pytest.mark.parametrize("F", [64, 1376, 5461, 11008, 32768])
+def test_ties_at_the_ends_of_a_thread_wavefront_and_chunk(F):
+    """Two values only: the cut's channel is the K-th of the equal ones, at every kind of place."""
+    g = np.full((3, F), 1.0, dtype=np.float32)
+    g[1, ::3] = 2.0
+    g[2, F // 2:] = 2.0
+    for K in sorted({k for k in (1, 4, 5, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 4097, F // 2, F // 2 + 1, F - 1) if 1 <= k <= F}):
+        _topk_case(g, K)
+
+
 @pytest.mark.parametrize("B,d,F", [(1, 64, 5), (1, 512, 1376), (3, 256, 5461), (4, 128, 11008), (2, 64, 32768)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_decode_selection_on_hard_rows(B, d, F, dtype):
