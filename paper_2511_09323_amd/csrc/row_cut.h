@@ -5,18 +5,17 @@
 // far above it (a product, a conversion, a clamp and an LDS atomic per value), a scan from the top for the bin that holds the K-th value,
 // and a direct ranking of that bin's few values by every wavefront.  Where more than a third of the row is selected, half of the
 // bins lie below zero.  Values spread over linear bins, so the atomics hardly collide and the bin of the cut holds a handful of values: at the
-// 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than K non-negative values, more than
-// 64 values in the bin (ties), ranges too small for the bin width -- goes on with the remaining range by the
-// general step until it is resolved.  Rows whose cut involves an infinity or a NaN are cut by a bisection over float_key
-// (+NaN above +inf, -NaN below -inf), the order of the radix select.
+// 7B shape (11008 gates around zero, K = 1376) about five.  Everything else -- fewer than
+// K non-negative values, more than 64 values in the bin (ties), infinities -- goes on with what holds the cut (a bin, the positive ones,
+// zeros, the negative ones, an infinity) by up to two general steps.  Rows that these do not resolve (values spread over many
+// powers of two) or whose cut lies among NaN (+NaN above +inf, -NaN below -inf) are cut by a radix select on float_key.
 // What bounds it: instructions per value (one row occupies one workgroup, often one compute unit) and the dependent steps
 // between barriers; about nine instructions per value and six barriers.  The radix select it replaces (three histograms over key digits,
 // colliding atomics on the exponent digit, thirteen barriers) took 8.8 us for one decode row of 11008 as a launch of its own and
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
-// K 5504 of those rows: 372 us, 429 without bins below zero, 467 with the radix select.
-// Hundreds of ties at the cut: 202 us, 385 with a bisection over the channels, 260 with the radix select.
-// Outliers (one value of 1000 standard deviations a row, 8192 rows of 11008, K 1376, forward at d 64): 180 us as for rows without, 240 with
-// bins up to the maximum, 220 with the radix select.
+// Other rows, 8192 of 11008, K 1376, in a forward at d 64 (this / the radix select; 182 / 229 us for Gaussian rows): one value of 1000
+// standard deviations 180 / 220, hundreds of ties at the cut 202 / 260, all zero 176 / 1013, all negative 225 / 334, 95 % -inf 211 / 999,
+// K 5504 372 / 467.  Slower than it: values spread evenly over 200 powers of two, 551 / 225.
 #pragma once
 #include "common.h"
 
@@ -24,7 +23,7 @@ namespace moc {
 
 constexpr int kCutBins = 2048;
 
-// Channel j with value v is selected iff v > tau, or v == tau and j <= last; with `end` set (non-finite rows, last < INT_MAX)
+// Channel j with value v is selected iff v > tau, or v == tau and j <= last; with `end` set (rows with NaN, or K = F; last < INT_MAX)
 // the same of keys, for the channels below end.
 struct RowCut {
     float tau;
@@ -229,23 +228,31 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
             }
         }
     }
-    // how many values (pred(value, channel)) there are in the row
-    auto count = [&](const auto& pred) {
-        int n = 0;
+    // f(value, channel) for this thread's values; every pass of the steps below forms what it needs anew
+    auto each = [&](const auto& f) {
         const int jb = opaque(tid * 4);
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) n += pred(v[c][e], c * 4 * NT + jb + e) ? 1 : 0;
-        n = (int)wave_sum((float)n);                         // exact: counts are far below 2^24
+            for (int e = 0; e < 4; ++e) f(opaque_value(v[c][e]), c * 4 * NT + jb + e);
+    };
+    // how many values of the row satisfy p, and how many q (each at most 32768): first * 2^16 + second
+    auto count2 = [&](const auto& p, const auto& q) {
+        uint32_t np = 0, n = 0;
+        each([&](float t, int j) {
+            np += p(t, j) ? 1u : 0u;
+            n += q(t, j) ? 1u : 0u;
+        });
+        n = (uint32_t)wave_inclusive_sum((int)(n + (np << 16)));
         __syncthreads();
-        if (lane == 0) L.red_i[wave] = n;
+        if (lane == 63) L.red_i[wave] = (int)n;
         __syncthreads();
         n = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) n += L.red_i[w];
-        return __builtin_amdgcn_readfirstlane(n);
+        for (int w = 0; w < NW; ++w) n += (uint32_t)L.red_i[w];
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
     };
+    auto count = [&](const auto& p) { return (int)count2([](float, int) { return false; }, p); };
     // the channel of the n-th value in question, in one pass: the values of every (chunk, wavefront) are counted, the one that holds the
     // n-th is found from the counts, and its wavefront looks the channel up.  (The counts take the place of the bins.)
     auto nth_channel = [&](int n, const auto& pred) {
@@ -297,27 +304,24 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(L.bin);
     };
-    auto count_before = [&](RowCut cut) {
+    const bool nan = __float_as_int(vmax) > 0x7F800000;      // +NaN lies above +inf
+    auto finish = [&](RowCut cut) {
+        if (nan) {
+            cut.end = F;
+            cut.key = float_key(cut.tau);
+            cut.last = min(cut.last, F - 1);
+        }
         if (BEFORE) cut.before = count([&](float t, int j) { return j < c0 && cut.in(t, j); });
         return cut;
     };
-    int npos = 0;
-    bool keyed = __float_as_int(vmax) >= 0x7F800000;         // +inf or +NaN
-    if (!keyed && fb == 0) {
-        npos = count([](float t, int) { return t >= 0.0f; });
-        need = npos >= K ? K : K - npos;
-        if (npos < K) keyed = count([&](float t, int) { return t < 0.0f && t > -kInf; }) < need;
-    }
     // ---- general step on the closed range [lo, hi] of the values in question: every value above hi is selected, `need` of those
     //      inside are.  A repetition takes at least the range's two ends apart, so it ends.
     float lo, hi;
     auto range_of = [&](const auto& in_question) {
         float a = kInf, b = -kInf;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (in_question(v[c][e])) { a = fminf(a, v[c][e]); b = fmaxf(b, v[c][e]); }
+        each([&](float t, int) {
+            if (in_question(t)) { a = fminf(a, t); b = fmaxf(b, t); }
+        });
         a = wave_min(a);
         b = wave_max(b);
         __syncthreads();
@@ -328,49 +332,80 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         lo = a;
         hi = b;
     };
-    if (keyed) lo = hi = 0.0f;
-    else if (fb > 0) range_of([&](float t) { return min(bin_at(t), kCutBins - 1) == fb; });
-    else if (npos >= K) range_of([&](float t) { return t >= 0.0f; });
-    else range_of([&](float t) { return t < 0.0f && t > -kInf; });
-    for (int it = 0; !keyed && it < 300; ++it) {
-        if (lo == hi)      // all equal: the first `need` channels
-            return count_before(RowCut{lo, nth_channel(need, [&](float t, int) { return t == lo; }), 0});
+    // ---- the values in question: those of the cut's bin or, without one, +inf, the positive ones, zeros, the negative ones or -inf, whichever
+    //      hold the cut once +NaN and what lies above are selected
+    bool found = fb > 0;
+    lo = hi = 0.0f;
+    if (found) {
+        range_of([&](float t) { return min(bin_at(t), kCutBins - 1) == fb; });
+    } else {
+        need = K;
+        if (nan) need -= count([](float t, int) { return __float_as_int(t) > 0x7F800000; });
+        if (__float_as_int(vmax) >= 0x7F800000 && need > 0) {
+            const int n = count([&](float t, int) { return t == kInf; });
+            found = need <= n;
+            if (found) lo = hi = kInf;
+            else need -= n;
+        }
+        const bool below = __float_as_int(vmax) < 0;         // no value above -0.0, which is one of the negative ones then
+#pragma unroll 1
+        for (int q = below ? 1 : 0; q < 2 && !found && need > 0; ++q) {
+            const float a = q ? -kInf : 0.0f, b = q ? (below ? 0x1p-149f : 0.0f) : kInf;
+            const uint32_t n = count2([&](float t, int) { return t > a && t < b; }, [&](float t, int j) { return t == a && j < F; });
+            const int inside = (int)(n >> 16), equal = (int)(n & 0xFFFF);
+            if (need <= inside) {
+                if (q == 0 && scale0 != 0.0f) break;         // positive ones that the bins did not tell apart: by keys
+                found = true;
+                range_of([&](float t) { return t > a && t < b; });
+            } else {
+                need -= inside;
+                found = need <= equal;
+                if (found) lo = hi = a;
+                else need -= equal;
+            }
+        }
+    }
+#pragma unroll 1
+    for (int it = 0; found && it < 3; ++it) {
+        if (lo == hi) return finish(RowCut{lo, nth_channel(need, [&](float t, int j) { return t == lo && j < F; }), 0});
+        if (it == 2) break;
         // monotonic in t, lo falls into bin 0 and hi into the last ones (`pre` keeps the factor finite for tiny ranges)
         const float pre = hi - lo < 1e-30f ? 0x1p100f : 1.0f;
         const float scale = (float)kCutBins / ((hi - lo) * pre);
         auto bin_of = [&](float t) { return min(kCutBins - 1, (int)fminf((t - lo) * pre * scale, 4096.0f)); };
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (v[c][e] >= lo && v[c][e] <= hi) atomicAdd(&hist[bin_of(v[c][e])], 1u);
+        each([&](float t, int) {
+            if (t >= lo && t <= hi) atomicAdd(hist + bin_of(t), 1u);
+        });
         (void)scan(need);
         fb = L.bin;
         need = L.need;
         const int cnt = L.cnt;
         if (cnt <= 64) {
-            const int jb = opaque(tid * 4);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (v[c][e] >= lo && v[c][e] <= hi && bin_of(v[c][e]) == fb) keep(v[c][e], c * 4 * NT + jb + e);
-            return count_before(rank_kept(cnt, need, 0));
+            each([&](float t, int j) {
+                if (t >= lo && t <= hi && bin_of(t) == fb) keep(t, j);
+            });
+            return finish(rank_kept(cnt, need, 0));
         }
         const float l0 = lo, h0 = hi;
         range_of([&](float t) { return t >= l0 && t <= h0 && min(kCutBins - 1, (int)fminf((t - l0) * pre * scale, 4096.0f)) == fb; });
     }
-    // ---- by keys
-    uint32_t key = 0, top = 0xFFFFFFFFu;                   // the K-th largest key is the largest that K keys reach
+    // ---- values that two more steps do not tell apart (spread over many powers of two), a cut among NaN: by the digits of their keys
+    uint32_t key = 0;
+    need = K;
 #pragma unroll 1
-    while (key < top) {
-        const uint32_t m = top - (top - key) / 2;
-        if (count([&](float t, int j) { return j < F && float_key(t) >= m; }) >= K) key = m;
-        else top = m - 1;
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0, bits = pass == 2 ? 10 : 11;
+        each([&](float t, int j) {
+            const uint32_t k = float_key(t);
+            if (j < F && (pass == 0 || k >> (shift + bits) == key)) atomicAdd(hist + (k >> shift & ((1u << bits) - 1)), 1u);
+        });
+        (void)scan(need);
+        key = key << bits | (uint32_t)L.bin;
+        need = L.need;
     }
-    const int above = count([&](float t, int j) { return j < F && float_key(t) > key; });
-    const int last = nth_channel(K - above, [&](float t, int j) { return j < F && float_key(t) == key; });
-    return count_before(RowCut{0.0f, last, 0, F, key});
+    RowCut cut{0.0f, nth_channel(need, [&](float t, int j) { return j < F && float_key(t) == key; }), 0, F, key};
+    if (BEFORE) cut.before = count([&](float t, int j) { return j < c0 && cut.in(t, j); });
+    return cut;
 }
 
 }  // namespace moc

@@ -473,7 +473,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
 // selected channels (instead of the whole row in registers) that costs five spilled registers in the rare general step.  Rows of 11008,
 // K 1376, 8192 of them: 205 us with four wavefronts, 155 with eight (5.2 TB/s, the rate of a copy); 5461 / 683: 102 and 92.
 template <class E, int NT, int NCH, bool FUSED>
-__global__ __launch_bounds__(NT, NT == 1024 ? 4 : NCH <= 6 ? 8 : 4) void topk_rows_kernel(TopkArgs<E> a) {
+__global__ __launch_bounds__(NT, NT == 1024 ? 4 : NCH <= 6 ? 8 : NCH <= 8 ? 6 : 4) void topk_rows_kernel(TopkArgs<E> a) {
     extern __shared__ __align__(16) unsigned char topk_dyn[];
     topk_row_body<E, NT, NCH, FUSED>(a, blockIdx.x, topk_dyn);
 }

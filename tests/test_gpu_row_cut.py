@@ -109,7 +109,7 @@ def by_key(g, K):
 
 def nonfinite_rows(F, seed):
     rng = np.random.default_rng(seed)
-    g = rng.standard_normal((8, F)).astype(np.float32)
+    g = rng.standard_normal((12, F)).astype(np.float32)
     inf = np.float32(np.inf)
     g[0, rng.random(F) < 0.9] = -inf                                     # a mask
     g[1] = -inf
@@ -119,6 +119,11 @@ def nonfinite_rows(F, seed):
     g[5] = np.where(rng.random(F) < 0.5, -inf, -np.abs(g[5]))
     g[6] = np.where(rng.random(F) < 0.5, -3e38, 1e-6 * np.abs(g[6]))     # far below what the bins can count
     g[7, ::5], g[7, 2::5], g[7, 3::5] = -np.nan, inf, np.finfo(np.float32).min
+    g[8, 1::9], g[8, 4::9] = np.nan, inf                                 # the cut among finite values below both
+    g[9] = np.where(rng.random(F) < 0.5, np.float32(0), -inf)            # among zeros, among -inf
+    g[9, ::17] = np.nan
+    g[10] = np.where(rng.random(F) < 0.6, np.where(rng.random(F) < 0.5, np.float32(-0.0), np.float32(0)), -np.abs(g[10]))
+    g[11] = np.exp2(rng.uniform(-120, 120, F)) * np.where(rng.random(F) < 0.5, -1, 1)     # by the digits of the keys
     return g
 
 
@@ -135,7 +140,7 @@ def test_rows_with_infinities_and_nans(F):
 
 @pytest.mark.parametrize("B,d,F", [(1, 64, 5), (3, 256, 1376), (4, 128, 11008)])
 def test_decode_selection_with_infinities(B, d, F):
-    rows = inputs.round_to_bf16(nonfinite_rows(F, F + 1)[[0, 1, 5, 6]])
+    rows = inputs.round_to_bf16(nonfinite_rows(F, F + 1)[[0, 1, 5, 6, 8, 9, 10, 11]])
     if np.isinf(rows[3]).any():
         rows[3] = np.where(np.isinf(rows[3]), np.float32(-1e38), rows[3])
     L = inputs.make_layer(97, B, d, F, "f32")
