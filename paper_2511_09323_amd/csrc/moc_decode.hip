@@ -273,12 +273,19 @@ moc_status launch_down_cols(const Dims& D, const E* wd, const int32_t* idx, cons
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }
-// The three launches save the selection's and the partial outputs' time; the gather of decode_updown_kernel, both rows of a channel in
-// flight together, streams faster.  At d 4096, F 11008, bf16 (bytes of the tokens' selected rows; this / gather): one token 22.5 MB 35.6 /
-// 43.0 us, 180 MB (K = F) 93.5 / 71.0; four tokens 90 MB 56.5 / 57.7, 721 MB 153.5 / 113.  The lines meet near 64 and 108 MB.
-template <class E> bool decode_rows_pays(const Dims& D) {
-    const int64_t bytes = (int64_t)2 * D.T * D.K * D.d * (int64_t)sizeof(E);
-    return D.T <= 4 && bytes <= (D.T == 1 ? 60000000 : 100000000);
+// Whether up to four tokens take the three launches: they save the selection's and the partial outputs' time, while the gather of
+// decode_updown_kernel, both rows of a channel in flight together, streams faster and serves a channel that several tokens selected from L2.
+// Measured over d 512, 1024, 2048, 4096, 8192 (F of 8/3 d, 8192 at the last), both types, one to four tokens, K/F of 1/50 .. 1, as time of
+// this / gather: one token K/F 1/4 0.83 .. 0.93 (fused gather), 1/2 0.84 .. 1.00, 3/4 0.86 .. 1.23; two to four tokens 1/4 0.83 .. 1.01,
+// 1/2 0.87 .. 1.21, 3/4 0.85 .. 1.38.  Below 8.5 MB of selected rows the launches decide (0.78 .. 0.98 up to 3/4; K = F has a selection
+// of its own, 1.02 .. 1.10).  Against the gather in two launches (rows too long for the fused one): 0.75 .. 1.05 up to 16 KB a row, for
+// longer rows 0.84 .. 1.03 at 1/8 and 0.98 .. 1.13 at 1/4.
+template <class E> bool decode_rows_pays(const Dims& D, bool gather_fused) {
+    const int64_t row = D.d * (int64_t)sizeof(E);
+    if (D.T > 4) return false;
+    if (!gather_fused) return row <= 16384 || 5 * D.K <= D.F;
+    if (2 * D.T * D.K * row <= 8500000 && D.K < D.F) return true;
+    return D.T == 1 ? 2 * D.K <= D.F : 3 * D.K <= D.F;
 }
 template <class E>
 moc_status decode_rows(const Dims& D, const DecodeWs& W, const E* x, const E* wu, const E* wd, E* y, int32_t* idx, int key_mode,
@@ -363,7 +370,7 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         else s = decode_gate_group_b<E, 16>(D, x, wg, ga, gb, idx, W.gsel, st);
     }
     if (s != MOC_OK) return s;
-    if (gb == 0 && decode_rows_pays<E>(D) && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
+    if (gb == 0 && decode_rows_pays<E>(D, gather_fused) && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
     const int P = decode_splits(B, D.K);
     if (gb == 0 && key_mode == 0 && gather_fused && options().decode_select_gather && (D.F + P - 1) / P <= kDsgMaxRange &&
         decode_select_gather_lds<E>(D.d) <= (size_t)kSelectGatherMaxLds) {

@@ -155,10 +155,13 @@ def test_decode_selection_with_infinities(B, d, F):
             np.testing.assert_array_equal(idx.cpu().numpy(), np.repeat(by_key(row[None], K), B, axis=0))
 
 
-@pytest.mark.parametrize("B,K", [(1, 3662), (1, 3663), (1, 8192), (4, 1525), (4, 1526), (4, 8192)])
-def test_decode_on_both_sides_of_the_three_launch_line(B, K):
-    """Two rows of 4096 bf16 per selected channel: 60 MB for one token, 100 MB for four."""
-    d, F = 4096, 8192
+@pytest.mark.parametrize("B,K,d", [(1, 3662, 4096), (1, 3663, 4096), (1, 4096, 4096), (1, 4097, 4096), (1, 8192, 4096), (2, 2730, 4096),
+                                   (2, 2731, 4096), (4, 1525, 4096), (4, 1526, 4096), (4, 2730, 4096), (4, 2731, 4096), (4, 8192, 4096),
+                                   (1, 4150, 512), (1, 4151, 512), (3, 2730, 1024), (3, 2731, 1024), (4, 5000, 4608), (2, 8192, 4608)])
+def test_decode_on_both_sides_of_the_three_launch_line(B, K, d):
+    """Half of F for one token, a third for more; below 8.5 MB of selected rows (two rows of d bf16 per selected channel) and where the
+    rows are too long for the fused gather always."""
+    F = 8192
     gen = torch.Generator(device="cuda").manual_seed(K)
     x = torch.randn((B, d), generator=gen, device="cuda").bfloat16()
     wg, wu, wd = [(torch.randn((F, d), generator=gen, device="cuda") * 0.02).bfloat16() for _ in range(3)]
