@@ -174,8 +174,14 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
                     constexpr GemmTile t = kGemmTile[C];
                     return launch_gemm_bf16_mfma<t.bm, t.bn, AKM, BKM, BKM ? 2 : 1, Epi, 4, t.sets>(pr, epi, st, tile_workgroups<C>());
                 });
-            else      // a contraction tail without padding: only d % 32 != 0, which no model has
-                e = launch_gemm_bf16_mfma<128, 128, AKM, BKM, 1, Epi, 4, 3>(pr, epi, st);
+            else {    // a contraction tail without padding (d % 32 != 0); the smaller shapes were measured without one only
+                const int basic = choose_tile<kTilesBasic>([&](const GemmTile& t) { return tile_count(pr.M, pr.N, t); }, nk);
+                e = with_tile<kTilesBasic>(basic, [&](auto c) {
+                    constexpr int C = decltype(c)::value;
+                    constexpr GemmTile t = kGemmTile[C];
+                    return launch_gemm_bf16_mfma<t.bm, t.bn, AKM, BKM, 1, Epi, 4, t.sets>(pr, epi, st, tile_workgroups<C>());
+                });
+            }
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -300,11 +306,13 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
             slices += (int64_t)pr[z].M * slice_count(pr[z].Kc, pr[z].Kc2);
         }
         if (ok && total_m > 0 && !(BKM && tail && !padded)) {
-            const int best = choose_tile<kTilesGroup>([&](const GemmTile& t) {
+            const int nk = (int)(slices / total_m);
+            auto tiles_of = [&](const GemmTile& t) {
                 int64_t tiles = 0;
                 for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
                 return tiles;
-            }, (int)(slices / total_m));
+            };
+            const int best = choose_tile<kTilesGroup>(tiles_of, nk);
             MfmaGroup<Epi, NB> g;
             for (int z = 0; z < nprob; ++z) { g.pr[z] = pr[z]; g.epi[z] = epi[z]; }
             Span span(name, st);
@@ -316,7 +324,10 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
                     return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 2, Epi, NB, 4, t.sets>(g, nprob, st);
                 });
             } else {
-                e = tail ? launch_gemm_bf16_mfma_group<128, 128, AKM, BKM, 1, Epi, NB, 4, 3>(g, nprob, st)
+                e = tail ? with_tile<kTilesBasic>(choose_tile<kTilesBasic>(tiles_of, nk), [&](auto c) {
+                               constexpr GemmTile t = kGemmTile[decltype(c)::value];
+                               return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 1, Epi, NB, 4, t.sets>(g, nprob, st);
+                           })
                          : with_tile<kTilesGroup>(best, [&](auto c) {
                                constexpr GemmTile t = kGemmTile[decltype(c)::value];
                                return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 0, Epi, NB, 4, t.sets>(g, nprob, st);

@@ -2,6 +2,10 @@
 tokens (64-row tiles, down and dX products cut into shares), a last share with fewer slices than the others, token counts
 one short of and one past a k-slice, experts with fewer rows than a slice.  Against the float64 oracle at the bf16 tolerance
 of the other parity tests."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 from tests.test_gpu_experts import run_experts_case
@@ -22,3 +26,18 @@ def test_tiles_shares_and_padded_rows(T, d, F, K):
 
 def test_experts_with_fewer_rows_than_a_slice():
     run_experts_case("few rows", 980, [1, 0, 31, 33, 64, 5, 100, 2], 128, 333, 41, "bf16")
+
+
+@pytest.mark.parametrize("tile", ["256", "192", "128"])
+def test_contraction_tails_without_padding_on_every_tile(tile):
+    """d % 32 != 0: gate, up and dZ' end inside a k-slice that nothing pads.  The environment (read once per process, hence the child
+    process) names the tile; ragged rows and columns, several tiles, experts with and without rows."""
+    code = ("from tests.test_gpu_experts import run_experts_case\n"
+            "from tests.test_gpu_parity import run_fwd_bwd_case\n"
+            "run_fwd_bwd_case('tails', 99, 300, 104, 530, 66, 'bf16')\n"
+            "run_fwd_bwd_case('tails', 99, 777, 264, 1031, 129, 'bf16')\n"
+            "run_experts_case('tails', 990, [300, 0, 40, 65], 104, 530, 66, 'bf16')\n"
+            "print('ok')\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, MOC_GEMM_TILE=tile), capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-3000:] + r.stderr[-3000:]
