@@ -21,50 +21,11 @@ using namespace moc;
 // or 0 (one workgroup per tile) with MOC_GEMM_PERSISTENT=0.
 inline int persistent_workgroups() { return options().gemm_persistent ? device_cu_count() : 0; }
 
-// Tile shapes of the bf16 matrix-core kernel and what a launch of each costs, in microseconds: `o` once per round of
-// tiles (launch, first loads, epilogue), `lo` .. `hi` per 32-k slice with few .. all compute units busy (the chip is
-// power-limited with the large tiles, so a full round runs slower), `co` per slice and workgroup where several
-// workgroups share a compute unit (`resident` of them; 1 = one persistent workgroup per compute unit).
-// Measured with 64 .. 768 tiles at contractions of 768, 2048 and 5472; the three operand layouts agree within 5 %.
-struct GemmTile {
-    int bm, bn, sets, resident;      // sets: k-slices in flight in registers
-    double o, lo, hi, co;
-};
-constexpr int kGemmTiles = 8;
-constexpr GemmTile kGemmTile[kGemmTiles] = {
-    {256, 256, 3, 1, 12.0, 0.592, 0.851, 0.0}, {256, 192, 3, 1, 11.5, 0.457, 0.680, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
-    {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.283, 0.378, 0.0},  {192, 128, 3, 1, 7.0, 0.290, 0.385, 0.0},
-    {128, 128, 3, 3, 5.7, 0.222, 0.275, 0.275}, {64, 128, 5, 4, 4.7, 0.216, 0.225, 0.200}};
-constexpr unsigned kTilesAll = 0xFF, kTilesBasic = 0x43 /* 256x256, 256x192, 128x128 */, kTilesGroup = 0xCB /* and 256x128, 64x128 */;
-constexpr int kTile128 = 6;
-
-inline double gemm_cost(const GemmTile& t, int64_t tiles, int nk, int cus) {
-    const int64_t n = tiles % cus;
-    const double f = std::max(0.0, ((double)n / cus - 0.25) / 0.75);
-    const double partial = n ? t.o + nk * (t.lo + (t.hi - t.lo) * f * f) : 0.0;      // a round that leaves compute units idle
-    if (t.resident == 1 || tiles <= cus) return (double)(tiles / cus) * (t.o + nk * t.hi) + partial;
-    const double w = 0.6 * tiles / cus + 0.4 * ((tiles + cus - 1) / cus);             // workgroups on the busiest compute unit, softened
-    return 1.5 + t.o * ((tiles + (int64_t)cus * t.resident - 1) / ((int64_t)cus * t.resident)) + nk * t.co * w;
-}
-
-// The cheapest of the tile shapes in MASK; tiles_of(tile) counts the tiles of the launch.
+// The cheapest of the tile shapes in MASK on this device (gemm_plan.h); MOC_GEMM_TILE forces one.
 template <unsigned MASK, class TilesOf> int choose_tile(const TilesOf& tiles_of, int nk, double* cost_out = nullptr) {
     const int forced = options().tile == 256 ? 0 : options().tile == 192 ? 1 : options().tile == 128 ? kTile128 : -1;
-    const int cus = std::max(1, device_cu_count());
-    int best = -1;
-    double best_cost = 0.0;
-    for (int c = 0; c < kGemmTiles; ++c) {
-        if (!((MASK >> c) & 1u) || (forced >= 0 && c != forced)) continue;
-        const double cost = gemm_cost(kGemmTile[c], tiles_of(kGemmTile[c]), nk, cus);
-        if (best < 0 || cost < best_cost) { best = c; best_cost = cost; }
-    }
-    if (cost_out) *cost_out = best_cost;
-    return best;
+    return cheapest_tile(MASK, tiles_of, nk, std::max(1, device_cu_count()), forced, cost_out);
 }
-inline int64_t tile_count(int M, int N, const GemmTile& t) {
-    return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-}
-inline int slice_count(int Kc, int Kc2) { return (Kc + kMfmaBK - 1) / kMfmaBK + (Kc2 + kMfmaBK - 1) / kMfmaBK; }
 
 // f(tile index as a compile-time constant) for the tile shape `t` of MASK.
 template <unsigned MASK, int C = 0, class F> hipError_t with_tile(int t, const F& f) {
@@ -105,20 +66,12 @@ moc_status run_gemm_shares(const char* name, const GemmProblem<E>& pr, const Epi
                            double whole_cost, bool* done) {
     *done = false;
     if (!sc.p || epi.ldc != epi.N || epi.N != pr.N || epi.N % 4 != 0 || options().tile != 0 || !gemm_padded(pr)) return MOC_OK;
-    const int nk = slice_count(pr.Kc, pr.Kc2), cus = std::max(1, device_cu_count());
     const int64_t out = (int64_t)pr.M * pr.N;
-    constexpr unsigned kMask = 0xE0;      // 192x128, 128x128, 64x128
-    int best = -1, shares = 0;
-    double best_cost = 0.95 * whole_cost;
-    for (int c = 5; c < kGemmTiles; ++c)
-        for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= sc.bytes; ++z) {
-            const double cost = gemm_cost(kGemmTile[c], z * tile_count(pr.M, pr.N, kGemmTile[c]), (nk + z - 1) / z, cus) + 3.5 +
-                                (8.0 * z + sizeof(E)) * out / 4.0e6;
-            if (cost < best_cost) { best = c; best_cost = cost; shares = z; }
-        }
-    if (best < 0) return MOC_OK;
+    const SharePlan plan = plan_shares(pr.M, pr.N, slice_count(pr.Kc, pr.Kc2), sizeof(E), sc.bytes, std::max(1, device_cu_count()), whole_cost);
+    if (plan.tile < 0) return MOC_OK;
+    const int shares = plan.shares;
     const EpiShare es{sc.p, pr.N, out, pr.N};
-    hipError_t e = with_tile<kMask>(best, [&](auto c) {
+    hipError_t e = with_tile<kTilesShares>(plan.tile, [&](auto c) {
         constexpr GemmTile t = kGemmTile[decltype(c)::value];
         return launch_gemm_bf16_mfma_split<t.bm, t.bn, false, true, 2, EpiShare, 4, t.sets>(pr, es, shares, st);
     });

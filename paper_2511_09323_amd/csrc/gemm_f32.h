@@ -4,7 +4,7 @@
 //
 // Same operand layouts as the bf16 kernel (k-contiguous or k-major, gemm_generic.h), staged as they lie in
 // memory: k-contiguous tiles as [row][BK + 4] floats, k-major tiles as [k][ROWS + 16] floats.  Both pitches
-// put the 16 rows x 4 k that one fragment read touches on 64 different banks.
+// put the 16 rows x 4 k that one fragment read touches on 64 different banks (k-major tiles of 16 rows: on 32, twice each).
 //
 // What bounds it: at the sizes fp32 is used for (a few hundred tokens, d of 512 to 768) a product has less than
 // one GFLOP, 2 to 5 us of matrix-core time for the chip, so the launch, the load latency and the length of a
@@ -243,21 +243,16 @@ inline hipError_t launch_gemm_f32_tile(const F32Batch<Epi, NB>& b, hipStream_t s
     return hipGetLastError();
 }
 
-// Tile shape: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
-// fragment reads); below that 32 x 32, with the k-slices split over the wavefronts when the contraction is long (several
-// 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate product, so
-// that the selection does not depend on the tile choice).
+// Tile shape by f32_tile (gemm_plan.h).
 template <bool AKM, bool BKM, class Epi, int NB>
 inline hipError_t launch_gemm_f32(const F32Batch<Epi, NB>& b, bool ascending, int num_cu, hipStream_t st) {
     const GemmProblem<float>& p = b.pr[0];
-    const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) * NB;
-    const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32) * NB;
-    if (t64 >= num_cu) return launch_gemm_f32_tile<64, 64, 1, AKM, BKM, Epi, NB>(b, st);
-    if (!ascending && (t32 < num_cu || p.Kc + p.Kc2 > 1024)) {
-        if (t32 < num_cu) return launch_gemm_f32_tile<16, 32, 4, AKM, BKM, Epi, NB>(b, st);
-        return launch_gemm_f32_tile<32, 32, 4, AKM, BKM, Epi, NB>(b, st);
+    switch (f32_tile(p.M, p.N, NB, (int64_t)p.Kc + p.Kc2, ascending, num_cu)) {
+        case F32Tile::k64x64: return launch_gemm_f32_tile<64, 64, 1, AKM, BKM, Epi, NB>(b, st);
+        case F32Tile::k32x32: return launch_gemm_f32_tile<32, 32, 1, AKM, BKM, Epi, NB>(b, st);
+        case F32Tile::k32x32Split: return launch_gemm_f32_tile<32, 32, 4, AKM, BKM, Epi, NB>(b, st);
+        default: return launch_gemm_f32_tile<16, 32, 4, AKM, BKM, Epi, NB>(b, st);
     }
-    return launch_gemm_f32_tile<32, 32, 1, AKM, BKM, Epi, NB>(b, st);
 }
 
 }  // namespace moc

@@ -42,7 +42,6 @@ namespace moc {
 
 typedef GemmProblem<bf16_t> MfmaProblem;
 
-constexpr int kMfmaBK = 32;
 constexpr int kMfmaStages = 3;
 
 // LDS byte offset of the 16-byte chunk `ch` (8 k) of row `row` in a k-contiguous tile: rows of 64

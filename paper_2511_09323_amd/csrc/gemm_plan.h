@@ -1,6 +1,9 @@
 // Arithmetic shared by the matrix-core kernels and their launchers that depends on sizes only: plain C++, so that it can be
 // checked on a CPU at sizes no test would allocate.
 #pragma once
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
 
 #if defined(__HIPCC__)
 #define MOC_HOST_DEVICE __host__ __device__ __forceinline__
@@ -14,5 +17,85 @@ namespace moc {
 // contraction: the k-row offsets of a slice are clamped to it.  The rows are clamped before the product is formed: left * ld does not
 // fit 32 bits for contractions over a few hundred thousand tokens, bk * ld does (checked on the host).
 MOC_HOST_DEVICE int last_row_offset(int left, int bk, int ld) { return ((left < bk ? left : bk) - 1) * ld; }
+
+constexpr int kMfmaBK = 32;      // k-slice of the bf16 kernel
+
+// Tile shapes of the bf16 matrix-core kernel and what a launch of each costs, in microseconds: `o` once per round of
+// tiles (launch, first loads, epilogue), `lo` .. `hi` per 32-k slice with few .. all compute units busy (the chip is
+// power-limited with the large tiles, so a full round runs slower), `co` per slice and workgroup where several
+// workgroups share a compute unit (`resident` of them; 1 = one persistent workgroup per compute unit).
+// Measured with 64 .. 768 tiles at contractions of 768, 2048 and 5472; the three operand layouts agree within 5 %.
+struct GemmTile {
+    int bm, bn, sets, resident;      // sets: k-slices in flight in registers
+    double o, lo, hi, co;
+};
+constexpr int kGemmTiles = 8;
+constexpr GemmTile kGemmTile[kGemmTiles] = {
+    {256, 256, 3, 1, 12.0, 0.592, 0.851, 0.0}, {256, 192, 3, 1, 11.5, 0.457, 0.680, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
+    {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.283, 0.378, 0.0},  {192, 128, 3, 1, 7.0, 0.290, 0.385, 0.0},
+    {128, 128, 3, 3, 5.7, 0.222, 0.275, 0.275}, {64, 128, 5, 4, 4.7, 0.216, 0.225, 0.200}};
+// every shape; 256x256, 256x192, 128x128; and 256x128, 64x128; 192x128, 128x128, 64x128
+constexpr unsigned kTilesAll = 0xFF, kTilesBasic = 0x43, kTilesGroup = 0xCB, kTilesShares = 0xE0;
+constexpr int kTile128 = 6;
+
+inline int64_t tile_count(int M, int N, const GemmTile& t) {
+    return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+}
+inline int slice_count(int Kc, int Kc2) { return (Kc + kMfmaBK - 1) / kMfmaBK + (Kc2 + kMfmaBK - 1) / kMfmaBK; }
+
+inline double gemm_cost(const GemmTile& t, int64_t tiles, int nk, int cus) {
+    const int64_t n = tiles % cus;
+    const double f = std::max(0.0, ((double)n / cus - 0.25) / 0.75);
+    const double partial = n ? t.o + nk * (t.lo + (t.hi - t.lo) * f * f) : 0.0;      // a round that leaves compute units idle
+    if (t.resident == 1 || tiles <= cus) return (double)(tiles / cus) * (t.o + nk * t.hi) + partial;
+    const double w = 0.6 * tiles / cus + 0.4 * ((tiles + cus - 1) / cus);             // workgroups on the busiest compute unit, softened
+    return 1.5 + t.o * ((tiles + (int64_t)cus * t.resident - 1) / ((int64_t)cus * t.resident)) + nk * t.co * w;
+}
+
+// The cheapest of the tile shapes in `mask` (the one named by `forced` if that is not negative); tiles_of(tile) counts the tiles of
+// the launch.
+template <class TilesOf> int cheapest_tile(unsigned mask, const TilesOf& tiles_of, int nk, int cus, int forced = -1, double* cost_out = nullptr) {
+    int best = -1;
+    double best_cost = 0.0;
+    for (int c = 0; c < kGemmTiles; ++c) {
+        if (!((mask >> c) & 1u) || (forced >= 0 && c != forced)) continue;
+        const double cost = gemm_cost(kGemmTile[c], tiles_of(kGemmTile[c]), nk, cus);
+        if (best < 0 || cost < best_cost) { best = c; best_cost = cost; }
+    }
+    if (cost_out) *cost_out = best_cost;
+    return best;
+}
+
+// Shares of a split contraction (run_gemm_shares): tile -1 where the whole product, of `whole_cost`, is not dearer.  The shares' way
+// through memory, written and read once at about 4 TB/s, and the second launch are counted.
+struct SharePlan {
+    int tile, shares;
+};
+inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost) {
+    const int64_t out = (int64_t)M * N;
+    SharePlan best{-1, 0};
+    double best_cost = 0.95 * whole_cost;
+    for (int c = 0; c < kGemmTiles; ++c) {
+        if (!((kTilesShares >> c) & 1u)) continue;
+        for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
+            const double cost = gemm_cost(kGemmTile[c], z * tile_count(M, N, kGemmTile[c]), (nk + z - 1) / z, cus) + 3.5 +
+                                (8.0 * z + elem) * out / 4.0e6;
+            if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
+        }
+    }
+    return best;
+}
+
+// fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
+// fragment reads); below that 32 x 32, with the k-slices split over the wavefronts (16 x 32 or 32 x 32) when the contraction is long
+// (several 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate
+// product, so that the selection does not depend on the tile choice).
+enum class F32Tile { k64x64, k32x32, k32x32Split, k16x32Split };
+inline F32Tile f32_tile(int M, int N, int batch, int64_t contraction, bool ascending, int cus) {
+    const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch, t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
+    if (t64 >= cus) return F32Tile::k64x64;
+    if (ascending || (t32 >= cus && contraction <= 1024)) return F32Tile::k32x32;
+    return t32 < cus ? F32Tile::k16x32Split : F32Tile::k32x32Split;
+}
 
 }  // namespace moc

@@ -10,13 +10,20 @@ from tests.test_gpu_parity import run_fwd_bwd_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,d,F,K", [
-    (1, 4, 5, 2),              # smaller than every tile and slice
-    (17, 36, 33, 9),           # one row and one column past a tile
-    (64, 128, 127, 16),        # contraction over F ends inside a chunk
-    (65, 132, 1025, 128),      # split k-slices, nine slices of the down product, the last one k long
-    (300, 260, 1000, 100),     # weight gradients on 64 x 64 tiles, T ends inside a slice
-    (1100, 260, 1031, 100),    # gate and up on 64 x 64 tiles
-])
-def test_f32_products_at_tile_edges(T, d, F, K):
-    run_fwd_bwd_case("f32-tiles", 97, T, d, F, K, "f32")
+# T, d, F, K, and kernels of interest that the launchers take (s: k-slices split over wavefronts; test_gemm_plan.py checks them)
+CASES = [
+    (1, 4, 5, 2, "gate_up=32x32 down=16x32s dw=16x32s"),               # smaller than every tile and slice
+    (17, 36, 33, 9, "gate_up=32x32 dz=16x32s dx=16x32s"),              # one row and one column past a tile
+    (64, 128, 127, 16, "down=16x32s"),                                 # contraction over F ends inside a chunk
+    (65, 132, 1025, 128, "down=16x32s dw=32x32"),                      # nine slices of the down product, the last one k long
+    (300, 260, 1000, 100, "dw=32x32 dz=32x32"),                        # T ends inside a slice
+    (300, 260, 1100, 100, "dw=64x64"),                                 # the same on the larger tiles, cut in d and F
+    (1100, 260, 500, 60, "down=32x32 dx=32x32"),
+    (1100, 260, 1031, 100, "gate_up=64x64 dz=64x64 down=32x32s dx=32x32s dw=32x32s"),
+    (2100, 516, 200, 25, "down=64x64 dx=64x64"),                       # k-contiguous x k-major, two segments, cut in T and d
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,kernels", CASES)
+def test_f32_products_at_tile_edges(T, d, F, K, kernels):
+    run_fwd_bwd_case("f32-tiles " + kernels, 97, T, d, F, K, "f32")

@@ -1,5 +1,5 @@
-"""bf16 products at the sizes where the choice of tile, the padded token rows and the split contraction can go wrong: few
-tokens (64-row tiles, down and dX products cut into shares), a last share with fewer slices than the others, token counts
+"""bf16 products at the sizes where the choice of tile, the padded token rows and the split contraction can go wrong: every tile
+shape at ragged edges, few tokens (64-row tiles, down and dX products cut into shares), shares of different lengths, token counts
 one short of and one past a k-slice, experts with fewer rows than a slice.  Against the float64 oracle at the bf16 tolerance
 of the other parity tests."""
 import os
@@ -14,14 +14,33 @@ from tests.test_gpu_parity import run_fwd_bwd_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,d,F,K", [
-    (17, 512, 1365, 170),      # fewer tokens than a k-slice; shares of a contraction with a tail
-    (33, 1024, 2736, 342),     # one token past a slice
-    (129, 256, 5461, 682),     # one row past a tile, 171 slices that no number of shares divides
-    (1999, 768, 2048, 409),    # token rows padded by 17
-])
-def test_tiles_shares_and_padded_rows(T, d, F, K):
-    run_fwd_bwd_case("tiles", 98, T, d, F, K, "bf16")
+# T, d, F, K, and kernels of interest that the launchers take (product=tile or product=tile/shares; test_gemm_plan.py checks them)
+CASES = [
+    (17, 512, 1365, 170, "gate_up=64x128 dx=64x128/2"),                # fewer tokens than a k-slice; shares of a contraction with a tail
+    (33, 1024, 2736, 342, "gate_up=64x128 down=64x128/4"),             # one token past a slice
+    (129, 256, 5461, 682, "dw=192x128 down=64x128/8 dx=64x128/8"),     # one row past a tile; 171 slices in shares of 21 and 22
+    (1999, 768, 2048, 409, "gate_up=128x128 dw=128x192 down=64x128"),  # token rows padded by 17
+    (17, 64, 1030, 128, "gate_up=64x128 dw=64x128 down=64x128/4 dx=64x128/8"),
+    (65, 64, 8200, 1025, "gate_up=128x128 dw=128x128"),
+    (97, 544, 2736, 342, "dw=128x192"),
+    (33, 768, 5461, 682, "dw=256x256"),
+    (2100, 128, 1365, 170, "gate_up=192x128"),
+    (4100, 128, 520, 65, "gate_up=128x192"),
+    (2600, 64, 2736, 342, "gate_up=256x256"),
+    (4100, 64, 2736, 342, "down=128x128/6 dx=128x128/7"),
+    (900, 512, 5461, 682, "dw=192x256"),
+    (1537, 288, 5461, 682, "dw=256x128"),
+    (1100, 288, 8200, 1025, "dw=256x192"),
+    (513, 768, 8200, 1025, "gate_up=192x256"),
+    (400, 1024, 8200, 1025, "gate_up=256x192"),
+    (700, 1536, 4100, 512, "gate_up=256x128"),
+    (1300, 1024, 8200, 1025, "gate=192x256 dz=192x256 down=192x128/4 dx=192x128/4"),
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,kernels", CASES)
+def test_tiles_shares_and_padded_rows(T, d, F, K, kernels):
+    run_fwd_bwd_case("tiles " + kernels, 98, T, d, F, K, "bf16")
 
 
 def test_experts_with_fewer_rows_than_a_slice():
