@@ -121,7 +121,7 @@ def load_library():
     try:
         from . import _marshal
     except ImportError as e:
-        raise MocError("MOC_ERR_NOT_BUILT", "_marshal.so is missing or does not load (%s): run `python -m paper_2511_09323_amd.build`" % e)
+        raise MocError("MOC_ERR_NOT_BUILT", "the _marshal extension is missing or does not load (%s): run `python -m paper_2511_09323_amd.build`" % e)
     if not _marshal.bind(LIB_PATH):
         raise MocError("MOC_ERR_NOT_BUILT", "%s lacks an entry point" % LIB_PATH)
     _lib, _fast = lib, _marshal

@@ -1,7 +1,7 @@
-"""Builds the HIP library in-tree: paper_2511_09323_amd/libmoc_ffn.so (gfx950 only), and _marshal.so beside it.
+"""Builds the HIP library in-tree: paper_2511_09323_amd/libmoc_ffn.so (gfx950 only), and the _marshal extension beside it.
 
 The entry points are spread over four translation units that are compiled side by side and
-linked into one shared library.  _marshal.so is the host-only Python extension that hands torch tensors to
+linked into one shared library.  _marshal is the host-only Python extension that hands torch tensors to
 that library (csrc/marshal.cpp); it is compiled against the installed torch's headers.
 """
 import hashlib
@@ -15,7 +15,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoc_ffn.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+# (named for the interpreter it was built for: another one does not find it, and says so)
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+HEADER = os.path.join(os.path.dirname(HERE), "include", "moc.h")
 SOURCES = ["moc_api.hip", "moc_fwd.hip", "moc_bwd.hip", "moc_decode.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -25,12 +27,12 @@ FLAGS = [
 
 
 def source_hash():
-    """Content hash of the kernel sources (csrc/*.h, csrc/*.hip, include/moc.h).  The library carries the
+    """Content hash of the native sources (csrc/*.h, csrc/*.hip, csrc/*.cpp, include/moc.h).  The library carries the
     hash it was built from in moc_version(), so a measurement taken on one build can be told from a
     measurement taken on another."""
     h = hashlib.sha256()
-    files = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".hip")))
-    files.append(os.path.join(os.path.dirname(HERE), "include", "moc.h"))
+    files = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".hip", ".cpp")))
+    files.append(HEADER)
     for f in files:
         h.update(os.path.basename(f).encode() + b"\0")
         with open(f, "rb") as fh:
@@ -53,6 +55,14 @@ def _run(cmd, verbose):
         raise subprocess.CalledProcessError(r.returncode, cmd)
 
 
+def marshal_is_stale():
+    """Whether _marshal is missing or older than what it is built from."""
+    if not os.path.exists(MARSHAL):
+        return True
+    built = os.path.getmtime(MARSHAL)
+    return any(os.path.getmtime(f) > built for f in (os.path.join(CSRC, "marshal.cpp"), HEADER))
+
+
 def build_marshal(verbose):
     import torch
     root = os.path.dirname(torch.__file__)
@@ -73,7 +83,7 @@ def build(verbose=True, only=None):
     define = ['-DMOC_SOURCE_HASH="%s"' % source_hash()]
     with ThreadPoolExecutor(max_workers=5) as pool:
         jobs = [pool.submit(_run, [HIPCC] + FLAGS + define + ["-c", os.path.join(CSRC, s), "-o", o], verbose) for s, o in todo]
-        if only is None or "marshal.cpp" in only or not os.path.exists(MARSHAL):
+        if only is None or "marshal.cpp" in only or marshal_is_stale():
             jobs.append(pool.submit(build_marshal, verbose))
         for j in jobs:
             j.result()

@@ -44,6 +44,40 @@ def test_tensors_without_memory_raise(fast):
         assert fast.residual_add(x, x) == B._NOT_TAKEN
 
 
+def test_hash_and_rebuild_cover_the_extension(tmp_path, monkeypatch):
+    """The hash that tells builds apart covers marshal.cpp, and a build of single files does not leave an extension behind that is
+    older than its sources."""
+    import os
+    import shutil
+
+    from paper_2511_09323_amd import build as b
+    csrc = tmp_path / "csrc"
+    shutil.copytree(b.CSRC, csrc)
+    monkeypatch.setattr(b, "CSRC", str(csrc))
+    before = b.source_hash()
+    with open(csrc / "marshal.cpp", "a") as f:
+        f.write("// changed\n")
+    assert b.source_hash() != before
+    ran = []
+    ext = tmp_path / "ext.so"
+    monkeypatch.setattr(b, "MARSHAL", str(ext))
+    monkeypatch.setattr(b, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(b, "_run", lambda cmd, verbose: ran.append(cmd[-3:] if "-c" in cmd else cmd))
+    built = lambda: any("marshal.cpp" in a for cmd in ran for a in cmd)
+    b.build(verbose=False, only=["moc_fwd.hip"])
+    assert built()                                                             # missing
+    ext.write_bytes(b"")
+    newer = os.path.getmtime(csrc / "marshal.cpp") + 10
+    os.utime(ext, (newer, newer))
+    ran.clear()
+    b.build(verbose=False, only=["moc_fwd.hip"])
+    assert not built()
+    os.utime(csrc / "marshal.cpp", (newer + 10, newer + 10))
+    ran.clear()
+    b.build(verbose=False, only=["moc_fwd.hip"])
+    assert built()
+
+
 @pytest.mark.gpu
 def test_both_ways_give_the_same_call():
     x, w = torch.randn(3, 64, device="cuda").bfloat16(), [torch.randn(200, 64, device="cuda").bfloat16() for _ in range(3)]
