@@ -128,7 +128,7 @@ __global__ __launch_bounds__(1024) void decode_down_cols_kernel(const E* __restr
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int r = r0 + u * 256;
-            j[u] = min((uint32_t)ib[min(r, K - 1)], (uint32_t)(F - 1));      // (the clamp only matters for non-finite input)
+            j[u] = min((uint32_t)ib[min(r, K - 1)], (uint32_t)(F - 1));      // (every slot holds a channel: the bound only guards the loads)
             zz[u] = r < K ? zb[min(r, K - 1)] : 0.0f;
         }
         u32x4_t w[U];

@@ -320,8 +320,8 @@ __device__ __forceinline__ bool topk_member(uint32_t key, int j, TopkThreshold t
 
 // Row of up to NCH * NT * 4 channels; thread t holds channels c*NT*4 + t*4 .. +3 of every chunk c.
 // Bound by vector instructions as long as a value costs more than about 25 of them, then by memory.  The cut comes from
-// row_cut.h; channels are ranked with one ballot sweep (one compare per value; the index test only where equal values straddle
-// the cut) whose per-lane prefixes stay in registers.  Selected channels are staged in LDS at their output slot, so that the
+// row_cut.h; channels are ranked with one ballot sweep (one compare per value; where equal values straddle the cut, those past it are
+// marked before) whose per-lane prefixes stay in registers.  Selected channels are staged in LDS at their output slot, so that the
 // compact outputs are written slot by slot (coalesced, SiLU evaluated K times instead of under divergence for every channel)
 // and the dense Z' row is assembled in LDS and streamed out with 16-byte stores.  Dynamic LDS: topk_reg_dyn_lds().
 template <class E, int NT, int NCH, bool FUSED>
@@ -470,7 +470,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
 }
 
 // Eight wavefronts per SIMD up to six chunks: rows come and go, and what one waits for the others compute.  With U gathered at the
-// selected channels (instead of the whole row in registers) that costs five spilled registers in the rare general step.  Rows of 11008,
+// selected channels (instead of the whole row in registers) that costs up to four spilled registers in the rare general step.  Rows of 11008,
 // K 1376, 8192 of them: 205 us with four wavefronts, 155 with eight (5.2 TB/s, the rate of a copy); 5461 / 683: 102 and 92.
 template <class E, int NT, int NCH, bool FUSED>
 __global__ __launch_bounds__(NT, NT == 1024 ? 4 : NCH <= 6 ? 8 : NCH <= 8 ? 6 : 4) void topk_rows_kernel(TopkArgs<E> a) {
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : NCH <= 6 ? 8 : NCH <= 8 ? 6 : 
     topk_row_body<E, NT, NCH, FUSED>(a, blockIdx.x, topk_dyn);
 }
 
-// Dynamic LDS of topk_rows_kernel: the bins and lists of the cut, reused for the three slot lists and, in
+// Dynamic LDS of topk_rows_kernel: the bins and lists of the cut, reused for the slot records and, in
 // the fused forward, the dense row.
 inline size_t topk_reg_dyn_lds(int K, int64_t ldz, size_t elem, bool fused) {
     size_t lists = (size_t)2 * K * 4;
