@@ -194,7 +194,7 @@ def main():
     # rate stands beside them.  HBM traffic per launch comes from the committed rocprofv3 counter
     # summary, and only when that summary was taken on the sources this library was built from.
     traffic_keys = {"gemm_gate": "gemm_bf16_mfma<256,256,KC,KC,tail0,EpiStore<float>>",
-                    "gemm_dw3": "gemm_bf16_mfma_batch3<256,192,KM,KM,tail0,EpiStore<bf16>>"}
+                    "gemm_dw3": "gemm_bf16_mfma_batch3<192,256,KM,KM,tail0,EpiStore<bf16>>"}
 
     def roofline_entry(row):
         name = row["kernel"]

@@ -1,6 +1,6 @@
 """Python binding of libmoc_ffn.so: argument marshalling only.
 
-The hot entry points hand their tensors to _marshal.so (csrc/marshal.cpp), which checks them and calls the C ABI in
+The hot entry points hand their tensors to _marshal (csrc/marshal.cpp), which checks them and calls the C ABI in
 about a microsecond; whatever it does not take (another argument type, a wrong shape) goes through ctypes here, which
 names the error.
 
@@ -44,7 +44,7 @@ _NOT_TAKEN = -1000
 
 
 class _NoMarshal:
-    """Stands in for _marshal.so until the library is loaded."""
+    """Stands in for _marshal until the library is loaded."""
 
     def __getattr__(self, name):
         load_library()

@@ -1,4 +1,4 @@
-"""_marshal.so takes a call only if every argument is exactly what the entry point wants and leaves everything else to the
+"""_marshal takes a call only if every argument is exactly what the entry point wants and leaves everything else to the
 ctypes path, which names the error.  Without a GPU nothing may be taken: the tensors are in host memory."""
 import pytest
 import torch
