@@ -319,7 +319,9 @@ moc_status launch_topk_reg(const char* name, const TopkArgs<E>& a, int T, hipStr
     auto kern = topk_rows_kernel<E, NT, NCH, FUSED>;
     LdsAttr<topk_rows_kernel<E, NT, NCH, FUSED>, (int)kTopkRegDynMax>::use();
     Span span(name, st);
-    hipLaunchKernelGGL(kern, dim3(T), dim3(NT), dyn, st, a);
+    TopkArgs<E> args = a;
+    args.far = cut_far(a.F, a.K);
+    hipLaunchKernelGGL(kern, dim3(T), dim3(NT), dyn, st, args);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }

@@ -119,6 +119,19 @@ __device__ __forceinline__ float wave_min(float v) {
     return wave_reduce(v, [](float a, float b) { return fminf(a, b); });
 }
 
+// Reductions whose result only the last lane holds: six instructions instead of about twelve.  Not the order of wave_reduce.
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_or(int v, int identity) {
+    return __builtin_amdgcn_update_dpp(identity, v, CTRL, ROWS, 0xF, false);
+}
+template <class Op> __device__ __forceinline__ int wave_reduce_last(int v, int identity, const Op& op) {
+    v = op(v, dpp_or<0x111, 0xF>(v, identity));      // row_shr:1, 2, 4, 8: the last lane of every 16 has its row's result
+    v = op(v, dpp_or<0x112, 0xF>(v, identity));
+    v = op(v, dpp_or<0x114, 0xF>(v, identity));
+    v = op(v, dpp_or<0x118, 0xF>(v, identity));
+    v = op(v, dpp_or<0x142, 0xA>(v, identity));      // row_bcast:15 into rows 1 and 3
+    return op(v, dpp_or<0x143, 0xC>(v, identity));   // row_bcast:31 into rows 2 and 3
+}
+
 // Inclusive prefix sum over the lanes of a wavefront.
 __device__ __forceinline__ int wave_inclusive_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr:1

@@ -21,7 +21,7 @@ constexpr int kRowsMaxRange = 128;           // channels of one workgroup's shar
 template <class E, int NCH>
 __global__ __launch_bounds__(kRowsNT, NCH <= 6 ? 4 : 2) void decode_select_up_kernel(const E* __restrict__ x, const E* __restrict__ wu,
                                                                    const float* __restrict__ g, const float* __restrict__ graw,
-                                                                   int64_t ldg, int F, int d, int K, int P, int B,
+                                                                   int64_t ldg, int F, int d, int K, float far, int P, int B,
                                                                    int32_t* __restrict__ idx, float* __restrict__ z) {
     constexpr int CN = Chunk<E>::N, NIT = 8, NW = kRowsNT / 64;
     __shared__ RowCutLds<kRowsNT> L;
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kRowsNT, NCH <= 6 ? 4 : 2) void decode_select_up_ke
                 if (c * 4 * kRowsNT + tid * 4 + e >= F) v[c][e] = -__builtin_inff();
         }
     }
-    const RowCut cut = row_cut<kRowsNT, NCH, true>(v, F, K, L, c0);
+    const RowCut cut = row_cut<kRowsNT, NCH, true>(v, F, K, far, L, c0);
     const int below = cut.before;
     uint64_t mask[2];
 #pragma unroll

@@ -261,7 +261,7 @@ moc_status launch_select_up_nch(const Dims& D, const E* x, const E* wu, const fl
                                 float* z, hipStream_t st) {
     Span span("decode_select_up", st);
     hipLaunchKernelGGL((decode_select_up_kernel<E, NCH>), dim3(P * D.T), dim3(kRowsNT), 0, st, x, wu, g, graw, (int64_t)D.ldF, D.F, D.d, D.K,
-                       P, D.T, idx, z);
+                       cut_far(D.F, D.K), P, D.T, idx, z);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }

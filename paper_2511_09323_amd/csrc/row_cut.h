@@ -15,7 +15,8 @@
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
 // Other rows, 8192 of 11008, K 1376, in a forward at d 64 (this / the radix select; 182 / 229 us for Gaussian rows): one value of 1000
 // standard deviations 180 / 220, hundreds of ties at the cut 202 / 260, all zero 176 / 1013, all negative 225 / 334, 95 % -inf 211 / 999,
-// K 5504 372 / 467.  Slower than it: values spread evenly over 200 powers of two, 551 / 225.
+// K 5504 372 / 467.  The bound on the K-th value costs rows that need none about 25 instructions a thread: nothing where U is gathered,
+// 45.0 -> 47.5 us for 16384 rows of 2048 on their own (67 with the radix select).  Slower than it: values spread evenly over 200 powers of two, 551 / 225.
 #pragma once
 #include "common.h"
 
@@ -46,11 +47,16 @@ template <int NT> struct RowCutLds {
     int bin, need, cnt, ncand;
 };
 
+// The bins end at the maximum or, where outliers lie above the rest, at 1.5 / K of the sum S of the positive values (the K-th value is at most
+// S / K; 1.5 because S comes from a quarter of the row) or ten times their mean over the row, whichever is larger: what lies above shares
+// the last bin.  This is the factor for the sum of that quarter.
+inline float cut_far(int F, int K) { return fmaxf(6.0f / (float)K, 40.0f / (float)F); }
+
 // v[c][e] is the value of channel c * 4 NT + tid * 4 + e; what lies past the row's end (F) holds -inf.  1 <= K <= F.
-// BEFORE: also counts the selected channels below c0 (on the way, from the bins).
+// far: cut_far(F, K).  BEFORE: also counts the selected channels below c0 (on the way, from the bins).
 // Exactly K channels are selected, whatever the values.  L may be overwritten after a barrier.
 template <int NT, int NCH, bool BEFORE>
-__device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K, RowCutLds<NT>& L, int c0 = 0) {
+__device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K, float far, RowCutLds<NT>& L, int c0 = 0) {
     constexpr int NW = NT / 64, BPT = kCutBins / NT;
     static_assert(BPT == 2 || BPT == 4 || BPT == 8, "256, 512 or 1024 threads");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -80,13 +86,13 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     float vmax = __int_as_float((int)0x80000000);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) vmax = bits_max(bits_max(bits_max(vmax, v[c][0]), v[c][1]), bits_max(v[c][2], v[c][3]));
-    vmax = wave_reduce(vmax, bits_max);
+    vmax = __int_as_float(wave_reduce_last(__float_as_int(vmax), (int)0x80000000, [](int a, int b) { return max(a, b); }));
     float pos = 0.0f;                                        // sum of the positive values, from a quarter of the row
 #pragma unroll
     for (int c = 0; c < NCH; ++c) pos += __int_as_float(max(__float_as_int(v[c][0]), 0));
-    pos = wave_sum(pos);
+    pos = __int_as_float(wave_reduce_last(__float_as_int(pos), 0, [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }));
     clear_bins(BPT * tid);
-    if (lane == 0) { L.red_f[0][wave] = vmax; L.red_f[1][wave] = pos; }
+    if (lane == 63) { L.red_f[0][wave] = vmax; L.red_f[1][wave] = pos; }
     if (tid == 0) { L.bin = 0; L.need = K; L.cnt = 0; L.ncand = 0; }
     __syncthreads();
 #pragma unroll
@@ -177,11 +183,8 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     float scale0 = 0.0f, zero_bin = 0.0f;
     auto bin_at = [&](float t) { return cvt_i32(fmaf(t, scale0, zero_bin)); };
     if (vmax > 1e-30f && vmax < 1e38f) {
-        // The bins end at the maximum or, where outliers lie above the rest, at 1.5 / K of the sum S of the positive values (the K-th
-        // value is at most S / K; 1.5 because S comes from a quarter of the row) or ten times their mean over the row, whichever is larger: what
-        // lies above shares the last bin.
-        const float far = pos * fmaxf(6.0f * __builtin_amdgcn_rcpf((float)K), 40.0f * __builtin_amdgcn_rcpf((float)F));
-        const float range = far > 1e-30f ? fminf(far, vmax) : vmax;
+        const float end = pos * far;
+        const float range = end > 1e-30f ? fminf(end, vmax) : vmax;      // (nothing positive in that quarter: up to the maximum)
         // From zero upwards, or from -range upwards where more than a third of the row is selected and the cut may lie below zero.
         zero_bin = 3 * K > F ? kCutBins / 2 : 0.0f;
         scale0 = ((float)kCutBins - 2.0f - zero_bin) * __builtin_amdgcn_rcpf(range);      // bin_at(v) < 2047 for every v <= range

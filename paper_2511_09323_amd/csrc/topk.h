@@ -43,6 +43,7 @@ template <class E> struct TopkArgs {
     // Keyed selection (Top-K position variants): g then holds the transformed keys the ranking is
     // done on, and the gate values themselves are fetched from here ([T, ldg] like g); null otherwise.
     const float* g_raw;
+    float far = 0.0f;   // cut_far(F, K), set by the launcher of the register-resident kernel
 };
 
 // Selection keys of the Top-K position variants: mode 1 ranks SiLU(g) (ablation row "After SiLU"),
@@ -357,7 +358,7 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
     // ---- slot lists and the dense row; they take over the LDS of the cut
     u32x2_t* rec = reinterpret_cast<u32x2_t*>(topk_dyn);              // [K] records {channel, value}
     E* zrow = reinterpret_cast<E*>(topk_dyn + ((size_t)2 * K * 4 + 15) / 16 * 16);   // [ldz] (FUSED)
-    const RowCut cut = row_cut<NT, NCH, false>(v, F, K, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
+    const RowCut cut = row_cut<NT, NCH, false>(v, F, K, a.far, *reinterpret_cast<RowCutLds<NT>*>(topk_dyn));
     // values equal to tau on both sides of the cut, or NaN (uniform): decided once, a value that is out becomes a NaN
     const bool keyed = cut.end != 0;
     if (cut.last != 0x7FFFFFFF && !keyed) {
