@@ -15,8 +15,9 @@
 // 225 us for 8192 such rows in the training forward, against 4.9 us inside the decode gather and 155 us here.
 // Other rows, 8192 of 11008, K 1376, in a forward at d 64 (this / the radix select; 182 / 229 us for Gaussian rows): one value of 1000
 // standard deviations 180 / 220, hundreds of ties at the cut 202 / 260, all zero 176 / 1013, all negative 225 / 334, 95 % -inf 211 / 999,
-// K 5504 372 / 467.  The bound on the K-th value costs rows that need none about 25 instructions a thread: nothing where U is gathered,
-// 45.0 -> 47.5 us for 16384 rows of 2048 on their own (67 with the radix select).  Slower than it: values spread evenly over 200 powers of two, 551 / 225.
+// K 5504 372 / 467.  The paths for these cost Gaussian rows an eighth more scalar instructions and
+// branches (the vector instructions are as many): nothing in the forward, 45.0 -> 47.5 us for 16384 rows of 2048 on their own (67 with the
+// radix select).  Slower than it: values spread evenly over 200 powers of two, 551 / 225.
 #pragma once
 #include "common.h"
 
