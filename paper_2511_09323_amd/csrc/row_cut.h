@@ -98,6 +98,8 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) vmax = bits_max(vmax, L.red_f[0][w]);
+    // (decisions are taken on scalar copies of what all lanes hold: branches instead of lane masks)
+    vmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(vmax)));
     pos = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) pos += L.red_f[1][w];
@@ -183,7 +185,7 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
     int need = K, fb = 0;
     float scale0 = 0.0f, zero_bin = 0.0f;
     auto bin_at = [&](float t) { return cvt_i32(fmaf(t, scale0, zero_bin)); };
-    if (vmax > 1e-30f && vmax < 1e38f) {
+    if (__float_as_int(vmax) > __float_as_int(1e-30f) && __float_as_int(vmax) < __float_as_int(1e38f)) {
         const float end = pos * far;
         const float range = end > 1e-30f ? fminf(end, vmax) : vmax;      // (nothing positive in that quarter: up to the maximum)
         // From zero upwards, or from -range upwards where more than a third of the row is selected and the cut may lie below zero.
@@ -196,11 +198,11 @@ __device__ __forceinline__ RowCut row_cut(const float (&v)[NCH][4], int F, int K
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
             for (int e = 0; e < 4; ++e) atomicAdd(hist + clamp_i32(bin_at(v[c][e]), floor_bin, kCutBins - 1), 1u);
-        const int total = scan(need);
-        fb = total >= need ? L.bin : 0;
-        const int cnt = L.cnt;
+        const int total = __builtin_amdgcn_readfirstlane(scan(need)), bin = __builtin_amdgcn_readfirstlane(L.bin);
+        fb = total >= need ? bin : 0;
+        const int cnt = __builtin_amdgcn_readfirstlane(L.cnt);
         if (fb > 0) {
-            need = L.need;
+            need = __builtin_amdgcn_readfirstlane(L.need);
             if (cnt <= 64 && fb < kCutBins - 1) {
                 asm volatile("" : "+v"(scale0));             // (keeps the compiler from holding every value's bin in a register)
                 uint32_t near = 1;
