@@ -9,6 +9,7 @@
 #include "gemm_f32.h"
 #include "gemm_generic.h"
 #include "gemm_mfma.h"
+#include "gemm_pingpong.h"
 #include "group_select.h"
 #include "kernel_attrs.h"
 #include "topk.h"
@@ -21,10 +22,11 @@ using namespace moc;
 // or 0 (one workgroup per tile) with MOC_GEMM_PERSISTENT=0.
 inline int persistent_workgroups() { return options().gemm_persistent ? device_cu_count() : 0; }
 
+inline int forced_tile() { return options().tile == 256 ? 0 : options().tile == 192 ? 1 : options().tile == 128 ? kTile128 : -1; }
+
 // The cheapest of the tile shapes in MASK on this device (gemm_plan.h); MOC_GEMM_TILE forces one.
 template <unsigned MASK, class TilesOf> int choose_tile(const TilesOf& tiles_of, int nk, double* cost_out = nullptr) {
-    const int forced = options().tile == 256 ? 0 : options().tile == 192 ? 1 : options().tile == 128 ? kTile128 : -1;
-    return cheapest_tile(MASK, tiles_of, nk, std::max(1, device_cu_count()), forced, cost_out);
+    return cheapest_tile(MASK, tiles_of, nk, std::max(1, device_cu_count()), forced_tile(), cost_out);
 }
 
 // f(tile index as a compile-time constant) for the tile shape `t` of MASK.
@@ -57,29 +59,64 @@ struct ShareScratch {
     size_t bytes = 0;
 };
 
-// C = A B^T with A k-contiguous and padded, B k-major, stored contiguously: where the tiles leave most of the chip idle and
-// the contraction is long, every tile's k-slices are cut into shares that run as workgroups of their own and are summed
-// afterwards.  Worth it when the cost model says so including the shares' way through memory (written and read once at
-// about 4 TB/s) and the second launch; fills `done`.
+// f(tile index as a compile-time constant) for the large tile `t`.
+template <int C = 0, class F> hipError_t with_pp_tile(int t, const F& f) {
+    if constexpr (C < kPpTiles) {
+        if (t == C) return f(std::integral_constant<int, C>{});
+        return with_pp_tile<C + 1>(t, f);
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+template <class T> PpOut pp_out(const EpiStore<T>& e) { return PpOut{e.C, e.ldc, 0, e.N, std::is_same<T, float>::value}; }
+// Whether the kernel of gemm_pingpong.h takes the problem (a tile shape named by the environment is one of gemm_mfma.h).
+template <class Epi> bool pp_takes(const MfmaProblem&, const Epi&) { return false; }
+template <class T> bool pp_takes(const MfmaProblem& pr, const EpiStore<T>& epi) {
+    return !options().force_generic && options().tile == 0 && epi.pad_to == 0 && pp_problem_ok(pr, pp_out(epi));
+}
+
+// One product (its contraction in `shares` shares) on large tiles.
+template <bool AKM, bool BKM, bool F32> hipError_t launch_pp(int tile, const MfmaProblem& pr, const PpOut& out, int shares, hipStream_t st) {
+    PpWork<1> w;
+    w.pr[0] = pr;
+    w.out[0] = out;
+    w.nprob = 1;
+    w.nsplit = shares;
+    return with_pp_tile(tile, [&](auto c) {
+        constexpr PpTile t = kPpTile[decltype(c)::value];
+        return launch_gemm_bf16_pp<t.bm, t.bn, AKM, BKM, F32 ? 1 : 0, 1>(w, persistent_workgroups(), st);
+    });
+}
+
+// Can the product be cut into shares: A k-contiguous and padded, B k-major, stored contiguously, memory for the shares.
+template <class E> bool can_share(const GemmProblem<E>& pr, const EpiStore<E>& epi, const ShareScratch& sc) {
+    return sc.p && epi.ldc == epi.N && epi.N == pr.N && epi.N % 4 == 0 && options().tile == 0 && gemm_padded(pr);
+}
+
+// Bytes of scratch the shares of a product may take, 0 if it cannot be cut.
+template <class E, class Epi> size_t share_bytes(const GemmProblem<E>& pr, const Epi& epi, const ShareScratch& sc) {
+    if constexpr (std::is_same<Epi, EpiStore<E>>::value) return can_share(pr, epi, sc) ? sc.bytes : 0;
+    return 0;
+}
+
 template <class E>
 moc_status run_gemm_shares(const char* name, const GemmProblem<E>& pr, const EpiStore<E>& epi, hipStream_t st, const ShareScratch& sc,
-                           double whole_cost, bool* done) {
-    *done = false;
-    if (!sc.p || epi.ldc != epi.N || epi.N != pr.N || epi.N % 4 != 0 || options().tile != 0 || !gemm_padded(pr)) return MOC_OK;
+                           const GemmRoute& r) {
     const int64_t out = (int64_t)pr.M * pr.N;
-    const SharePlan plan = plan_shares(pr.M, pr.N, slice_count(pr.Kc, pr.Kc2), sizeof(E), sc.bytes, std::max(1, device_cu_count()), whole_cost);
-    if (plan.tile < 0) return MOC_OK;
-    const int shares = plan.shares;
-    const EpiShare es{sc.p, pr.N, out, pr.N};
-    hipError_t e = with_tile<kTilesShares>(plan.tile, [&](auto c) {
-        constexpr GemmTile t = kGemmTile[decltype(c)::value];
-        return launch_gemm_bf16_mfma_split<t.bm, t.bn, false, true, 2, EpiShare, 4, t.sets>(pr, es, shares, st);
-    });
+    hipError_t e;
+    if (r.pp) {
+        e = launch_pp<false, true, true>(r.tile, pr, PpOut{sc.p, pr.N, out, pr.N, 1}, r.shares, st);
+    } else {
+        const EpiShare es{sc.p, pr.N, out, pr.N};
+        e = with_tile<kTilesShares>(r.tile, [&](auto c) {
+            constexpr GemmTile t = kGemmTile[decltype(c)::value];
+            return launch_gemm_bf16_mfma_split<t.bm, t.bn, false, true, 2, EpiShare, 4, t.sets>(pr, es, r.shares, st);
+        });
+    }
     if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
     const int64_t n4 = out / 4;
-    hipLaunchKernelGGL((reduce_shares_kernel<E>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, sc.p, shares, out, n4, epi.C);
+    hipLaunchKernelGGL((reduce_shares_kernel<E>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, sc.p, r.shares, out, n4, epi.C);
     HIP_TRY(hipGetLastError());
-    *done = true;
     return MOC_OK;
 }
 
@@ -107,13 +144,19 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
             }
             constexpr bool kStore = std::is_same<Epi, EpiStore<bf16_t>>::value || std::is_same<Epi, EpiStore<float>>::value;
             constexpr unsigned kMask = kStore ? kTilesAll : kTilesBasic;
-            double cost = 0.0;
-            const int best = choose_tile<kMask>([&](const GemmTile& t) { return tile_count(pr.M, pr.N, t); }, nk, &cost);
-            if constexpr (!AKM && BKM && std::is_same<Epi, EpiStore<E>>::value) {
-                bool done;
-                moc_status s = run_gemm_shares<E>(name, pr, epi, st, scratch, cost, &done);
-                if (s != MOC_OK || done) return s;
+            constexpr bool kShares = !AKM && BKM && std::is_same<Epi, EpiStore<E>>::value;
+            const GemmRoute route = gemm_route(kMask, pr.M, pr.N, pr.Kc, pr.Kc2, sizeof(E), pp_takes(pr, epi), kShares ? share_bytes(pr, epi, scratch) : 0,
+                                               std::max(1, device_cu_count()), forced_tile());
+            if constexpr (kShares)
+                if (route.shares > 1) return run_gemm_shares<E>(name, pr, epi, st, scratch, route);
+            if constexpr (kStore) {
+                if (route.pp) {
+                    const hipError_t e = launch_pp<AKM, BKM, std::is_same<Epi, EpiStore<float>>::value>(route.tile, pr, pp_out(epi), 1, st);
+                    if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                    return MOC_OK;
+                }
             }
+            const int best = route.tile;
             hipError_t e;
             if (!tail)
                 e = with_tile<kMask>(best, [&](auto c) {
@@ -151,6 +194,20 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
     return MOC_OK;
 }
 
+// Several products in one launch on large tiles: they agree in their columns and leading dimensions, and the kernel takes every one of them.
+template <class T> bool pp_group_takes(int n, const MfmaProblem* pr, const EpiStore<T>* epi) {
+    for (int z = 0; z < n; ++z)
+        if (pr[z].M != 0 && !(pp_takes(pr[z], epi[z]) && pr[z].N == pr[0].N && pr[z].A.ld == pr[0].A.ld && pr[z].B.ld == pr[0].B.ld)) return false;
+    return true;
+}
+template <bool AKM, bool BKM, int F32, int NB> hipError_t launch_pp_group(int tile, PpWork<NB>& w, hipStream_t st) {
+    w.nsplit = 1;
+    return with_pp_tile(tile, [&](auto c) {
+        constexpr PpTile t = kPpTile[decltype(c)::value];
+        return launch_gemm_bf16_pp<t.bm, t.bn, AKM, BKM, F32, NB>(w, persistent_workgroups(), st);
+    });
+}
+
 // Three independent products of one shape (both operands k-major, plain stores) in one launch when
 // a matrix-core kernel takes them; otherwise one run_gemm each.  Same tile choice as run_gemm, over the
 // tiles of all three.
@@ -164,7 +221,21 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
         const bool padded = gemm_padded(pr[0]) && gemm_padded(pr[1]) && gemm_padded(pr[2]);
         if (same && (!tail || padded) && !options().force_generic && mfma_problem_ok(pr[0]) && mfma_problem_ok(pr[1]) && mfma_problem_ok(pr[2])) {
             const int nk = slice_count(pr[0].Kc, 0);
-            const int best = choose_tile<kTilesAll>([&](const GemmTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); }, nk);
+            double cost = 0.0;
+            const bool pp = pp_group_takes(3, pr, epi) && !(sk && sk->part && options().gemm_streamk);
+            const GemmRoute route = group_route(kTilesAll, [&](const GemmTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); },
+                                                [&](const PpTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); }, nk, pp_slice_count(pr[0].Kc, 0), pp,
+                                                std::max(1, device_cu_count()), forced_tile(), &cost);
+            if (route.pp) {
+                Span span(name, st);
+                PpWork<3> w;
+                for (int i = 0; i < 3; ++i) { w.pr[i] = pr[i]; w.out[i] = pp_out(epi[i]); }
+                w.nprob = 3;
+                const hipError_t e = launch_pp_group<true, true, 0, 3>(route.tile, w, st);
+                if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                return MOC_OK;
+            }
+            const int best = route.tile;
             MfmaBatch<EpiStore<E>, 3> b;
             for (int i = 0; i < 3; ++i) { b.pr[i] = pr[i]; b.epi[i] = epi[i]; }
             Span span(name, st);
@@ -214,10 +285,28 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
         if (same && !options().force_generic && mfma_problem_ok(pa) && mfma_problem_ok(pb)) {
             const int nk = slice_count(pa.Kc, 0);
             double cost = 0.0, single = 0.0;
-            const int best = choose_tile<kTilesAll>([&](const GemmTile& t) { return 2 * tile_count(pa.M, pa.N, t); }, nk, &cost);
+            constexpr bool kGateUp = std::is_same<EpiA, EpiStore<float>>::value && std::is_same<EpiB, EpiStore<bf16_t>>::value;
+            const bool pp = kGateUp && pp_takes(pa, ea) && pp_takes(pb, eb) && pa.A.ld == pb.A.ld && pa.B.ld == pb.B.ld &&
+                            !(sk && sk->part && options().gemm_streamk);
+            const GemmRoute route = group_route(kTilesAll, [&](const GemmTile& t) { return 2 * tile_count(pa.M, pa.N, t); },
+                                                [&](const PpTile& t) { return 2 * tile_count(pa.M, pa.N, t); }, nk, pp_slice_count(pa.Kc, 0), pp,
+                                                std::max(1, device_cu_count()), forced_tile(), &cost);
             (void)choose_tile<kTilesAll>([&](const GemmTile& t) { return tile_count(pa.M, pa.N, t); }, nk, &single);
+            if constexpr (kGateUp) {
+                if (route.pp && cost < 2.0 * single) {
+                    Span span(name, st);
+                    PpWork<2> w;
+                    w.pr[0] = pa; w.out[0] = pp_out(ea);
+                    w.pr[1] = pb; w.out[1] = pp_out(eb);
+                    w.nprob = 2;
+                    const hipError_t e = launch_pp_group<false, false, 2, 2>(route.tile, w, st);
+                    if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                    return MOC_OK;
+                }
+            }
+            const int best = route.tile;
             // one launch when the two together cost less than apart, which they do unless both fill whole rounds of tiles
-            if (cost < 2.0 * single) {
+            if (!route.pp && cost < 2.0 * single) {
                 Span span(name, st);
                 const hipError_t e = with_tile<kTilesAll>(best, [&](auto c) {
                     constexpr GemmTile t = kGemmTile[decltype(c)::value];
@@ -265,7 +354,26 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
                 for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
                 return tiles;
             };
-            const int best = choose_tile<kTilesGroup>(tiles_of, nk);
+            int64_t slices64 = 0;
+            for (int z = 0; z < nprob; ++z) slices64 += (int64_t)pr[z].M * pp_slice_count(pr[z].Kc, pr[z].Kc2);
+            auto pp_tiles_of = [&](const PpTile& t) {
+                int64_t tiles = 0;
+                for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
+                return tiles;
+            };
+            double cost = 0.0;
+            const GemmRoute route = group_route(kTilesGroup, tiles_of, pp_tiles_of, nk, (int)(slices64 / total_m), pp_group_takes(nprob, pr, epi),
+                                                std::max(1, device_cu_count()), forced_tile(), &cost);
+            if (route.pp) {
+                Span span(name, st);
+                PpWork<NB> w;
+                for (int z = 0; z < nprob; ++z) { w.pr[z] = pr[z]; w.out[z] = pp_out(epi[z]); }
+                w.nprob = nprob;
+                const hipError_t e = launch_pp_group<AKM, BKM, std::is_same<Epi, EpiStore<float>>::value ? 1 : 0, NB>(route.tile, w, st);
+                if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                return MOC_OK;
+            }
+            const int best = route.tile;
             MfmaGroup<Epi, NB> g;
             for (int z = 0; z < nprob; ++z) { g.pr[z] = pr[z]; g.epi[z] = epi[z]; }
             Span span(name, st);
@@ -295,6 +403,42 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
         moc_status s = run_gemm<E, AKM, BKM>(name, pr[z], epi[z], st, nullptr, ascending);
         if (s != MOC_OK) return s;
     }
+    return MOC_OK;
+}
+
+// The gate (fp32 result) and up projection of all experts in one launch on large tiles, an expert's two products next to each other
+// because they share its rows of x; fills `done` unless the kernel does not take them or single launches are cheaper.
+template <int NB>
+moc_status run_gate_up_grouped(const char* name, int nprob, const MfmaProblem* gate, const EpiStore<float>* eg, const MfmaProblem* up,
+                               const EpiStore<bf16_t>* eu, hipStream_t st, bool* done) {
+    *done = false;
+    bool ok = nprob <= NB && pp_group_takes(nprob, gate, eg) && pp_group_takes(nprob, up, eu) && gate[0].A.ld == up[0].A.ld && gate[0].B.ld == up[0].B.ld;
+    int64_t rows = 0;
+    for (int z = 0; z < nprob; ++z) {
+        ok = ok && gate[z].M == up[z].M && gate[z].N == up[z].N && gate[z].Kc == gate[0].Kc && up[z].Kc == gate[0].Kc && gate[z].Kc2 == 0 && up[z].Kc2 == 0;
+        rows += gate[z].M;
+    }
+    if (!ok || rows == 0) return MOC_OK;
+    const int cus = std::max(1, device_cu_count());
+    auto tiles_of = [&](const auto& t) {
+        int64_t tiles = 0;
+        for (int z = 0; z < nprob; ++z) tiles += tile_count(gate[z].M, gate[0].N, t);
+        return tiles;
+    };
+    double single = 0.0, both = 0.0;
+    (void)group_route(kTilesGroup, tiles_of, tiles_of, slice_count(gate[0].Kc, 0), pp_slice_count(gate[0].Kc, 0), true, cus, forced_tile(), &single);
+    const int t = cheapest_pp_tile([&](const PpTile& p) { return 2 * tiles_of(p); }, pp_slice_count(gate[0].Kc, 0), cus, &both);
+    if (both >= 2.0 * single) return MOC_OK;
+    Span span(name, st);
+    PpWork<2 * NB> w;
+    for (int z = 0; z < nprob; ++z) {
+        w.pr[2 * z] = gate[z]; w.out[2 * z] = pp_out(eg[z]);
+        w.pr[2 * z + 1] = up[z]; w.out[2 * z + 1] = pp_out(eu[z]);
+    }
+    w.nprob = 2 * nprob;
+    const hipError_t e = launch_pp_group<false, false, 2, 2 * NB>(t, w, st);
+    if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+    *done = true;
     return MOC_OK;
 }
 

@@ -71,19 +71,107 @@ template <class TilesOf> int cheapest_tile(unsigned mask, const TilesOf& tiles_o
 struct SharePlan {
     int tile, shares;
 };
-inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost) {
+inline double shares_traffic_cost(int64_t out, int shares, int elem) { return 3.5 + (8.0 * shares + elem) * out / 4.0e6; }
+inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out = nullptr) {
     const int64_t out = (int64_t)M * N;
     SharePlan best{-1, 0};
     double best_cost = 0.95 * whole_cost;
     for (int c = 0; c < kGemmTiles; ++c) {
         if (!((kTilesShares >> c) & 1u)) continue;
         for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
-            const double cost = gemm_cost(kGemmTile[c], z * tile_count(M, N, kGemmTile[c]), (nk + z - 1) / z, cus) + 3.5 +
-                                (8.0 * z + elem) * out / 4.0e6;
+            const double cost = gemm_cost(kGemmTile[c], z * tile_count(M, N, kGemmTile[c]), (nk + z - 1) / z, cus) +
+                                shares_traffic_cost(out, z, elem);
             if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
         }
     }
+    if (cost_out && best.tile >= 0) *cost_out = best_cost;
     return best;
+}
+
+// The large tiles of gemm_pingpong.h and their cost in microseconds: kPpLaunch once, `o` per round of tiles, `lo` .. `hi` per 64-k slice
+// with few .. all compute units busy.  Measured with 64 .. 704 tiles at contractions of 512, 2048 and 8192; the operand layouts agree
+// within 5 %, the formula with the measurements within 6 %.
+constexpr int kPpBK = 64;
+struct PpTile {
+    int bm, bn;
+    double o, lo, hi;
+};
+constexpr int kPpTiles = 5;
+constexpr double kPpLaunch = 6.8;
+constexpr PpTile kPpTile[kPpTiles] = {
+    {256, 256, 3.2, 1.04, 1.37}, {192, 256, 1.8, 0.84, 1.05}, {256, 192, 2.0, 0.86, 1.07}, {128, 256, 1.4, 0.69, 0.79}, {256, 128, 1.4, 0.68, 0.78}};
+
+inline int64_t tile_count(int M, int N, const PpTile& t) { return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+inline int pp_slice_count(int Kc, int Kc2) { return (Kc + kPpBK - 1) / kPpBK + (Kc2 + kPpBK - 1) / kPpBK; }
+inline double pp_cost(const PpTile& t, int64_t tiles, int nk, int cus) {
+    const int64_t n = tiles % cus;
+    const double f = std::max(0.0, ((double)n / cus - 0.25) / 0.75);
+    return kPpLaunch + (double)(tiles / cus) * (t.o + nk * t.hi) + (n ? t.o + nk * (t.lo + (t.hi - t.lo) * f * f) : 0.0);
+}
+template <class TilesOf> int cheapest_pp_tile(const TilesOf& tiles_of, int nk, int cus, double* cost_out) {
+    int best = 0;
+    for (int c = 0; c < kPpTiles; ++c) {
+        const double cost = pp_cost(kPpTile[c], tiles_of(kPpTile[c]), nk, cus);
+        if (c == 0 || cost < *cost_out) { best = c; *cost_out = cost; }
+    }
+    return best;
+}
+// As plan_shares, for the large tiles; at least four slices to a share.
+inline SharePlan plan_pp_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out) {
+    const int64_t out = (int64_t)M * N;
+    SharePlan best{-1, 0};
+    double best_cost = 0.95 * whole_cost;
+    for (int c = 0; c < kPpTiles; ++c)
+        for (int z = 2; z <= 16 && nk / z >= 4 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
+            const double cost = pp_cost(kPpTile[c], z * tile_count(M, N, kPpTile[c]), (nk + z - 1) / z, cus) + shares_traffic_cost(out, z, elem);
+            if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
+        }
+    if (best.tile >= 0) *cost_out = best_cost;
+    return best;
+}
+
+// How a product runs: whole on a tile of gemm_mfma.h (`mask`; `forced` see cheapest_tile) or, with pp, of gemm_pingpong.h, or, with scratch
+// for it, with every tile's k-slices cut into shares that run as workgroups of their own and are summed afterwards.  The cheapest
+// by the cost models.
+struct GemmRoute {
+    bool pp = false;
+    int tile = 0, shares = 1;
+};
+inline GemmRoute gemm_route(unsigned mask, int M, int N, int Kc, int Kc2, int elem, bool pp, size_t scratch_bytes, int cus, int forced = -1) {
+    const int nk = slice_count(Kc, Kc2), nk64 = pp_slice_count(Kc, Kc2);
+    GemmRoute r;
+    double cost = 0.0;
+    r.tile = cheapest_tile(mask, [&](const GemmTile& t) { return tile_count(M, N, t); }, nk, cus, forced, &cost);
+    if (scratch_bytes) {
+        const SharePlan p = plan_shares(M, N, nk, elem, scratch_bytes, cus, cost, &cost);
+        if (p.tile >= 0) r = GemmRoute{false, p.tile, p.shares};
+    }
+    if (!pp) return r;
+    double pp_whole = 0.0;
+    const int t = cheapest_pp_tile([&](const PpTile& p) { return tile_count(M, N, p); }, nk64, cus, &pp_whole);
+    if (pp_whole < cost) {
+        r = GemmRoute{true, t, 1};
+        cost = pp_whole;
+    }
+    if (scratch_bytes) {
+        const SharePlan p = plan_pp_shares(M, N, nk64, elem, scratch_bytes, cus, cost, &cost);
+        if (p.tile >= 0) r = GemmRoute{true, p.tile, p.shares};
+    }
+    return r;
+}
+// The same for several products in one launch, `tiles_of(tile)` tiles altogether; never in shares.
+template <class TilesOf, class PpTilesOf>
+GemmRoute group_route(unsigned mask, const TilesOf& tiles_of, const PpTilesOf& pp_tiles_of, int nk, int nk64, bool pp, int cus, int forced, double* cost) {
+    GemmRoute r;
+    r.tile = cheapest_tile(mask, tiles_of, nk, cus, forced, cost);
+    if (!pp) return r;
+    double pp_cost = 0.0;
+    const int t = cheapest_pp_tile(pp_tiles_of, nk64, cus, &pp_cost);
+    if (pp_cost < *cost) {
+        r = GemmRoute{true, t, 1};
+        *cost = pp_cost;
+    }
+    return r;
 }
 
 // fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four

@@ -29,7 +29,7 @@ moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
                     hipStream_t st) {
     BwdWs<E> W(ws, D, DENSE);
     moc_status s;
-    const int Fs = round_up(D.F, 4);      // whole 4-column groups into the padded [T, ldF] array (its padding is never read)
+    const int Fs = round_up(D.F, 8);      // whole 16-byte pieces into the padded [T, ldF] array (its padding is never read)
     GemmProblem<E> pz{kc_operand<E>(dy, D.d), kc_operand<E>(wd, D.d), D.T, D.F, D.d, 0, false};
     const size_t expand_lds = (size_t)3 * D.ldF * sizeof(E);
     if (!DENSE && expand_lds <= 160 * 1024 - 64 && !options().bwd_epilogue) {
@@ -88,7 +88,7 @@ moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
                             void* ws, hipStream_t st) {
     BwdWs<E> W(ws, D, false);
     const int64_t wsz = (int64_t)D.F * D.d;
-    const int Fs = round_up(D.F, 4);      // whole 4-column groups into the padded [T, ldF] array (its padding is never read)
+    const int Fs = round_up(D.F, 8);      // whole 16-byte pieces into the padded [T, ldF] array (its padding is never read)
     const size_t expand_lds = (size_t)3 * D.ldF * sizeof(E);
     if (expand_lds > 160 * 1024 - 64) return fail(MOC_ERR_UNSUPPORTED, "F = %d too large for the expert backward", D.F);
     GemmProblem<E> pr[3 * kMaxExperts];

@@ -15,10 +15,10 @@ moc_status fwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
                     E* uvals, void* ws, hipStream_t st, int ga = 0, int gb = 0, int key_mode = 0) {
     FwdWs<E> W(ws, D, false, key_mode != 0);
     moc_status s;
-    // Columns stored by the products that fill [T, ldF] scratch arrays: F rounded up to a whole 4-column group.
-    // The up to three extra columns land in the arrays' padding, which nothing reads; without them every
+    // Columns stored by the products that fill [T, ldF] scratch arrays: F rounded up to whole 16-byte pieces of bf16.
+    // The up to seven extra columns land in the arrays' padding, which nothing reads; without them every
     // row would end in a partly filled group, whose element-wise stores cost about 10 us per product at the 1B shape.
-    const int Fs = round_up(D.F, 4);
+    const int Fs = round_up(D.F, 8);
     // G = X W_gate, kept in fp32 for the selection (Eq. MoC-1)
     // and U = X W_up (Eq. MoC-1): one launch for both when possible
     GemmProblem<E> pg{kc_operand<E>(x, D.d), kc_operand<E>(wg, D.d), D.T, D.F, D.d, 0, false};
@@ -73,8 +73,8 @@ moc_status fwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
                             E* y, int32_t* idx, E* gvals, E* uvals, void* ws, hipStream_t st) {
     FwdWs<E> W(ws, D, false);
     const int64_t wsz = (int64_t)D.F * D.d;
-    const int Fs = round_up(D.F, 4);      // see fwd_impl
-    GemmProblem<E> pr[kMaxExperts];
+    const int Fs = round_up(D.F, 8);      // see fwd_impl
+    GemmProblem<E> pr[kMaxExperts], pu[kMaxExperts];
     EpiStore<float> eg[kMaxExperts];
     EpiStore<E> ee[kMaxExperts];
     moc_status s;
@@ -82,14 +82,17 @@ moc_status fwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const 
         const int64_t r0 = off[e];
         pr[e] = GemmProblem<E>{kc_operand<E>(x + r0 * D.d, D.d), kc_operand<E>(wg + e * wsz, D.d), off[e + 1] - off[e], D.F, D.d, 0, false};
         eg[e] = EpiStore<float>{W.G + r0 * D.ldF, D.ldF, Fs, 0};
-    }
-    if ((s = run_gemm_grouped<E, false, false, EpiStore<float>, kMaxExperts>("gemm_gate_experts", n_exp, pr, eg, st, true)) != MOC_OK) return s;
-    for (int e = 0; e < n_exp; ++e) {
-        const int64_t r0 = off[e];
-        pr[e].B = kc_operand<E>(wu + e * wsz, D.d);
+        pu[e] = pr[e];
+        pu[e].B = kc_operand<E>(wu + e * wsz, D.d);
         ee[e] = EpiStore<E>{W.U + r0 * D.ldF, D.ldF, Fs, 0};
     }
-    if ((s = run_gemm_grouped<E, false, false, EpiStore<E>, kMaxExperts>("gemm_up_experts", n_exp, pr, ee, st)) != MOC_OK) return s;
+    bool done = false;
+    if constexpr (std::is_same<E, bf16_t>::value)
+        if ((s = run_gate_up_grouped<kMaxExperts>("gemm_gate_up_experts", n_exp, pr, eg, pu, ee, st, &done)) != MOC_OK) return s;
+    if (!done) {
+        if ((s = run_gemm_grouped<E, false, false, EpiStore<float>, kMaxExperts>("gemm_gate_experts", n_exp, pr, eg, st, true)) != MOC_OK) return s;
+        if ((s = run_gemm_grouped<E, false, false, EpiStore<E>, kMaxExperts>("gemm_up_experts", n_exp, pu, ee, st)) != MOC_OK) return s;
+    }
     TopkArgs<E> a{W.G, D.ldF, D.F, D.K, idx, nullptr, gvals, W.U, D.ldF, uvals, W.Zd, D.ldF, nullptr};
     s = D.ldF > 6144 ? run_topk<E, 512, true>("topk_select_act", a, D.T, st) : run_topk<E, 256, true>("topk_select_act", a, D.T, st);
     if (s != MOC_OK) return s;

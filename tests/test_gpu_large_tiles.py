@@ -1,0 +1,72 @@
+"""bf16 products on the large tiles of gemm_pingpong.h where they can go wrong: every tile shape with ragged rows and columns, one and two
+slices (the pipeline is deeper than that), odd numbers of slices, contraction ends inside a slice and inside the second operand pair, several
+tiles to a workgroup, shares of different lengths, experts with no and few rows; and the products they leave to gemm_mfma.h (d % 64
+== 32).  Against the float64 oracle at the bf16 tolerance of the other parity tests."""
+import pytest
+import torch
+
+import paper_2511_09323_amd as moc
+from paper_2511_09323_amd import inputs
+from tests import parity as P
+from tests.test_gpu_experts import run_experts_case
+from tests.test_gpu_parity import run_fwd_bwd_case
+
+pytestmark = pytest.mark.gpu
+
+# T, d, F, K, and kernels of interest that the launchers take (product=tile or product=tile/shares, pp: gemm_pingpong.h;
+# test_gemm_routes.py checks them)
+CASES = [
+    (513, 64, 11008, 1376, "gate_up=pp128x256"),               # one row past a tile; a single slice, several tiles to a workgroup
+    (700, 64, 11008, 1376, "gate_up=pp192x256"),
+    (1025, 64, 5461, 682, "gate_up=pp256x128"),
+    (5000, 192, 1030, 128, "gate_up=pp256x192"),               # three slices: an odd one at the end of every tile
+    (1025, 128, 5461, 682, "gate_up=pp256x256"),
+    (1025, 64, 11008, 1376, "dz=pp128x256"),
+    (3000, 64, 4100, 512, "dz=pp256x128"),
+    (65, 768, 5461, 682, "dw=pp256x256"),                      # one token past a slice
+    (17, 320, 11008, 1376, "dw=pp256x128"),                    # fewer tokens than a slice
+    (17, 576, 11008, 1376, "dw=pp256x192"),
+    (300, 1536, 1365, 170, "dw=pp128x256"),
+    (17, 320, 16001, 2000, "dw=pp192x256"),
+    (6100, 2048, 200, 25, "down=pp192x256 dx=pp192x256"),      # a contraction of four slices that ends inside the last
+    (4100, 1536, 520, 65, "down=pp256x128"),
+    (5000, 1536, 200, 25, "dx=pp256x128"),                     # two operand pairs of four slices each
+    (17, 64, 16001, 2000, "dx=pp256x128/16"),                  # 502 slices in shares of 31 and 32, one of them across both operand pairs
+    (1025, 96, 5461, 682, "gate_up=256x256"),
+    (513, 800, 8200, 1025, "gate_up=192x256"),
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,kernels", CASES)
+def test_large_tiles(T, d, F, K, kernels):
+    run_fwd_bwd_case("large tiles " + kernels, 97, T, d, F, K, "bf16")
+
+
+@pytest.mark.parametrize("counts,d,F,K", [([700, 0, 1, 513, 300, 64, 257, 900], 128, 2736, 342), ([2000, 33], 192, 1030, 128)])
+def test_experts_on_large_tiles(counts, d, F, K):
+    """Gate and up projection of all experts in one launch; row counts one short of and past a tile, experts with no and one row."""
+    run_experts_case("large tiles", 970, counts, d, F, K, "bf16")
+
+
+@pytest.mark.parametrize("T,d,F,K", [(513, 64, 2731, 341), (1025, 128, 5461, 682), (2047, 1536, 200, 25)])
+def test_nothing_outside_the_operands_counts(T, d, F, K):
+    """Every operand lies between NaN: what a tile loads past an edge must not reach a result."""
+    L = inputs.make_layer(96, T, d, F, "bf16", with_dy=True)
+
+    def between_nan(a):
+        t = P.to_dev(a, "bf16")
+        buf = torch.full((t.numel() + 2 * 65536,), float("nan"), dtype=t.dtype, device="cuda")
+        inner = buf[65536:65536 + t.numel()].view(t.shape)
+        inner.copy_(t)
+        return inner
+
+    def run(place):
+        x, wg, wu, wd, dy = (place(L[n]) for n in ("x", "wg", "wu", "wd", "dy"))
+        ws = [torch.full((moc.workspace_bytes(T, d, F, K, torch.bfloat16, op) // 2 + 1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+              .view(torch.uint8) for op in (0, 1)]
+        y, idx, gv, uv = moc.moc_ffn_fwd(x, wg, wu, wd, K, ws=ws[0])
+        return (y, idx, gv, uv) + tuple(moc.moc_ffn_bwd(x, wg, wu, wd, idx, gv, uv, dy, ws=ws[1]))
+
+    for a, b in zip(run(between_nan), run(lambda a: P.to_dev(a, "bf16"))):
+        assert torch.isfinite(a.float()).all()
+        assert torch.equal(a, b)
