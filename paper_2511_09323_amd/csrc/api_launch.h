@@ -367,7 +367,10 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
             if (route.pp) {
                 Span span(name, st);
                 PpWork<NB> w;
-                for (int z = 0; z < nprob; ++z) { w.pr[z] = pr[z]; w.out[z] = pp_out(epi[z]); }
+                int order[NB];
+                for (int z = 0; z < nprob; ++z) order[z] = z;
+                std::stable_sort(order, order + nprob, [&](int a, int b) { return pr[a].Kc + pr[a].Kc2 > pr[b].Kc + pr[b].Kc2; });
+                for (int z = 0; z < nprob; ++z) { w.pr[z] = pr[order[z]]; w.out[z] = pp_out(epi[order[z]]); }
                 w.nprob = nprob;
                 const hipError_t e = launch_pp_group<AKM, BKM, std::is_same<Epi, EpiStore<float>>::value ? 1 : 0, NB>(route.tile, w, st);
                 if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));

@@ -143,13 +143,21 @@ struct PpOut {
     int f32;
 };
 
-// Up to NB problems in one launch that agree in N, both leading dimensions and the layouts; problem z has the tiles cum[z] ..
-// cum[z + 1] - 1, tiles_n to a row of tiles.  With nsplit > 1 (one problem) item i is share i / tiles of tile i % tiles: the shares are
-// ranges of whole slices.
+// Up to NB problems in one launch that agree in N, both leading dimensions and the layouts; problem z has tiles[z] tiles, tiles_n to a
+// row of tiles.  With nsplit > 1 (one problem) item i is share i / tiles of tile i % tiles: the shares are ranges of whole slices.
+//
+// The items are the tiles, dealt to the XCDs as follows; an XCD's workgroups take its items in turn.
+//   NB <= 3: the tiles of all problems in a row, XCD x takes the x-th eighth (neighbouring tiles share operand panels in its L2).
+//   NB > 3 (experts, whose row counts differ): XCD x takes the x-th eighth of EVERY problem, in the order of the problems, which the host
+//     sorts by the length of the contraction, and every second round of its workgroups goes backwards, so that long and short
+//     contractions add up alike.  Eight experts of 768 x 2048 with 2000 to 6000 rows each (24 weight gradients): 370 us with
+//     the whole list cut into eighths, where one XCD got one expert.
 template <int NB> struct PpWork {
+    static constexpr bool kSpread = NB > 3;
     MfmaProblem pr[NB];
     PpOut out[NB];
-    int cum[NB + 1];
+    int tiles[NB];
+    int cum[kSpread ? 8 : 1][NB + 1];      // items before problem z: of XCD x, or of all
     int nprob, tiles_n, nsplit;
 };
 
@@ -163,7 +171,10 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / C::WGN, wn = wave % C::WGN;
     const int group = wave >> 2;
-    const int tiles = w.cum[w.nprob], total = tiles * (NB == 1 ? w.nsplit : 1);
+    constexpr bool kSpread = PpWork<NB>::kSpread;
+    const int xcd = blockIdx.x & 7;
+    const int* const cum = w.cum[kSpread ? xcd : 0];
+    const int tiles = cum[NB], total = tiles * (NB == 1 ? w.nsplit : 1);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
     const uint32_t lda = (uint32_t)w.pr[0].A.ld, ldb = (uint32_t)w.pr[0].B.ld;
 
     const uint32_t lds_a = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem);
@@ -185,9 +196,18 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     struct Item {
         int z, share, m0, n0;
     };
-    auto item_at = [&](int item) {
+    // position of this workgroup's item number r in the list that cum counts, or -1 after its last
+    auto position = [&](int r) {
+        if (kSpread) {
+            const int width = (int)gridDim.x >> 3, local = (int)blockIdx.x >> 3;
+            const int p = r * width + ((r & 1) ? width - 1 - local : local);
+            return p < total ? p : -1;      // (only the last round is part-filled)
+        }
+        const int item = (int)blockIdx.x + r * (int)gridDim.x;
+        return item < total ? xcd_contiguous_index(item, total) : -1;
+    };
+    auto item_at = [&](int mapped) {
         Item t;
-        int mapped = xcd_contiguous_index(item, total);
         t.share = 0;
         if (NB == 1 && w.nsplit > 1) {
             t.share = mapped / tiles;
@@ -195,9 +215,10 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
         }
         t.z = 0;
 #pragma unroll
-        for (int z = 1; z < NB; ++z) t.z += mapped >= w.cum[z];      // (cum is the total past the last problem)
-        const int logical = mapped - w.cum[t.z];
-        const int tiles_m = (w.cum[t.z + 1] - w.cum[t.z]) / w.tiles_n;
+        for (int z = 1; z < NB; ++z) t.z += mapped >= cum[z];
+        int logical = mapped - cum[t.z];
+        if (kSpread) logical += w.tiles[t.z] * xcd / 8;
+        const int tiles_m = w.tiles[t.z] / w.tiles_n;
         const int height = w.tiles_n >= 32 ? 8 : 4;      // band height, see gemm_bf16_mfma_tiles
         const int band = logical / (height * w.tiles_n);
         const int first_m = band * height;
@@ -307,8 +328,8 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
                 }
     };
 
-    int item = blockIdx.x;
-    if (item >= total) return;
+    int turn = 0, item = position(0);
+    if (item < 0) return;
     int slices, next_slices = 0;
     Item cur = item_at(item), nxt = cur;
     Stream st = begin(cur, slices);
@@ -328,8 +349,8 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     int stores = 0;                              // of the tile before, still among the counted
     if (group == 1) pp_barrier();                // half a phase behind
     for (;;) {
-        const int next_item = item + (int)gridDim.x;
-        const bool more = next_item < total;
+        const int next_item = position(++turn);
+        const bool more = next_item >= 0;
         const int pairs = (slices + 1) >> 1;
         // Two slices.  In a tile's first pair the products start from zero and, as the previous tile's stores went out after the loads
         // that phases 1 .. 6 wait for, these waits let the stores be.
@@ -447,15 +468,21 @@ inline bool pp_problem_ok(const MfmaProblem& p, const PpOut& o) {
            256 * o.ldc * es < (1ll << 31);
 }
 
-// w.cum and w.tiles_n are filled in here; `wgs` workgroups at most (a multiple of 8), each walking over its tiles.
+// w.tiles, w.cum and w.tiles_n are filled in here; `wgs` workgroups at most (a multiple of 8; 0: one per item), each walking over its items.
 template <int BM, int BN, bool AKM, bool BKM, int F32, int NB> inline hipError_t launch_gemm_bf16_pp(PpWork<NB>& w, int wgs, hipStream_t st) {
     using C = PpCfg<BM, BN>;
     auto kern = gemm_bf16_pp_kernel<BM, BN, AKM, BKM, F32, NB>;
     LdsAttr<gemm_bf16_pp_kernel<BM, BN, AKM, BKM, F32, NB>, C::kLds>::use();
     w.tiles_n = (w.pr[0].N + BN - 1) / BN;
-    w.cum[0] = 0;
-    for (int z = 0; z < NB; ++z) w.cum[z + 1] = w.cum[z] + (z < w.nprob ? (w.pr[z].M + BM - 1) / BM * w.tiles_n : 0);
-    const int total = w.cum[w.nprob] * w.nsplit;
+    for (int z = 0; z < NB; ++z) w.tiles[z] = z < w.nprob ? (w.pr[z].M + BM - 1) / BM * w.tiles_n : 0;
+    constexpr int kLists = PpWork<NB>::kSpread ? 8 : 1;
+    int longest = 0;
+    for (int x = 0; x < kLists; ++x) {
+        w.cum[x][0] = 0;
+        for (int z = 0; z < NB; ++z) w.cum[x][z + 1] = w.cum[x][z] + (w.tiles[z] * (x + 1) / kLists - w.tiles[z] * x / kLists);
+        longest = std::max(longest, w.cum[x][NB]);
+    }
+    const int total = kLists * longest * w.nsplit;
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(kern, dim3(mfma_grid(total, wgs)), dim3(kPpThreads), C::kLds, st, w);
     return hipGetLastError();
