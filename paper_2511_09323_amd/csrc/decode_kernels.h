@@ -7,6 +7,8 @@
 #pragma once
 #include "common.h"
 #include "group_select.h"
+#include "kernel_attrs.h"
+#include "lds_dma.h"
 
 namespace moc {
 
@@ -221,117 +223,166 @@ __global__ __launch_bounds__(256) void decode_gate_group_kernel(const E* __restr
 
 // Gate projection for batches of 2..16 tokens on the matrix cores (bf16 only):
 //   g[b, j] = x[b] . wg[j]  as D[row j][token b] tiles of v_mfma_f32_16x16x32_bf16.
-// A workgroup of RG * KS wavefronts owns 16 RG consecutive channel rows: wave w works on row group
-// w / KS (16 rows) and on share w % KS of the contraction, UN steps of 64 k (8 KB at UN = 4) in
-// flight per wave.  Lane l of a wave reads 32 contiguous bytes of row l % 16 per step (4 lanes cover
-// a 128-byte line); x[BTOK, d] sits in LDS (rows padded by 16 bytes) and supplies the second MFMA
-// input with the same k assignment (token slots from BTOK up are zero).  The KS partial tiles of a
-// row group are summed through LDS.  Needs d % (64 KS UN) == 0.
-// Two shapes are used: (RG 3, KS 4, BTOK 16, UN 4), 768 threads, 48 rows, one workgroup per CU because
-// x fills most of the LDS; and for at most four tokens (RG 1, KS 8, BTOK 4, UN 8), 512 threads, 16
-// rows, every load of a wave in flight at once and several workgroups per CU.
-// GB = 0 writes the gate rows g[B, ldg]; GB = 4, 8, 16 selects the a largest of every GB channels
-// instead (MoC_{a:b}; the rows of a workgroup are a whole number of groups) and writes idx / gsel
-// [B, K] only.
+// Bound: the stream of W_gate, which every compute unit must keep full from its first to its last cycle.  So
+//  - the rows are dealt evenly to one workgroup per compute unit (in units of four rows, or of a group), which walks over them
+//    16 at a time;
+//  - the eight wavefronts of a workgroup each have an eighth of the contraction (at most NS steps of 64 k), so that x stays in
+//    registers, MFMA-ready, and nothing is staged before the first product;
+//  - W_gate goes to LDS directly (lds_load16), in pieces of 16 rows x P steps, two pieces of every wavefront under way: one instruction
+//    reads 512 bytes of a row where d allows, while loads in the order the MFMA wants would read 64 bytes of each of 16 rows.
+//    A wavefront reads only what it loaded, so nothing but its own counter orders the two;
+//  - rows past the workgroup's last, steps past d and tokens from B up are zeros of the buffer's range check, not branches.
+// The partial tiles meet in LDS, one barrier per 16 rows; the wavefronts take turns in adding them.
+// 4096 x 11008 (90 MB), kernel alone: 16 tokens 22.0 -> 17.8 us (5.1 TB/s), 2:8 with 4 tokens 25.6 -> 17.5; before, one workgroup per 48
+// (16) rows staged x in LDS and read W_gate in MFMA order.  The same walk with loads to registers, 64 bytes of a row each: 20.8.
+// GB = 0 writes the gate rows g[B, ldg]; GB = 4, 8, 16 selects the a largest of every GB channels instead (MoC_{a:b}; a workgroup's
+// rows are a whole number of groups) and writes idx / gsel [B, K] only.  Needs d % 64 == 0, d <= 512 NS, 16-byte aligned operands.
 typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
-template <int GB, int RG, int KS, int BTOK, int UN>
-__global__ __launch_bounds__(RG * KS * 64) void decode_gate_mfma_kernel(const bf16_t* __restrict__ x,
-                                                                         const bf16_t* __restrict__ wg, int B, int d, int F,
-                                                                         float* __restrict__ g, int64_t ldg, int ga, int K,
-                                                                         int32_t* __restrict__ idx, float* __restrict__ gsel) {
-    constexpr int NT = RG * KS * 64, ROWS = RG * 16;
-    static_assert(GB == 0 || ROWS % GB == 0, "a workgroup's rows must be whole groups");
+constexpr int kGateStreamWaves = 8, kGateStreamMaxD = 8 * 64 * kGateStreamWaves;
+template <int GB, int NS> struct GateStreamCfg {
+    static constexpr int P = NS < 4 ? NS : 4;                // steps of a piece
+    static constexpr int PB = NS / P;                        // pieces of a block of 16 rows
+    static constexpr int kPiece = 16 * P * 128;              // bytes
+    static constexpr int kRing = kGateStreamWaves * 2 * kPiece, kRed = 2 * kGateStreamWaves * 256 * 4;
+    static constexpr int kLds = kRing + kRed + (GB == 0 ? 0 : 16 * 17 * 4);
+    static_assert(PB <= 2 && kLds <= kMaxDynLds, "");
+};
+template <int GB, int NS>
+__global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int B, int d, int F, float* __restrict__ g, int64_t ldg, int ga,
+    int K, int32_t* __restrict__ idx, float* __restrict__ gsel) {
+    using C = GateStreamCfg<GB, NS>;
+    constexpr int NW = kGateStreamWaves, P = C::P, PB = C::PB;
+    constexpr int UNIT = GB == 0 ? 4 : GB;
+    // Large layers do not stay in the last-level cache until the next token (4096 x 11008, 16 tokens, call with / without the hint: 75.4 /
+    // 76.4 us; 2:8, 4 tokens 49.9 / 51.6); smaller ones may, and the hint would undo that (2048 x 5461, 3 tokens, three layers in turn: 24.1 / 22.7).
+    constexpr bool kNonTemporal = NS == 8;
     extern __shared__ __align__(16) unsigned char dec_smem[];
-    const int xpitch = d * 2 + 16;                                   // bytes per staged token row
-    float* red = reinterpret_cast<float*>(dec_smem + BTOK * xpitch); // [RG row groups][KS shares][256]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int rg = wave / KS, ks = wave % KS;
-    const int row0 = blockIdx.x * ROWS + rg * 16;
-    const int kq = d / KS;                                           // contraction share of this wave
-    const int q = lane >> 4;                                         // 16-element k sub-block of a 64-wide step
-    const bf16_t* wrow = wg + (int64_t)min(row0 + (lane & 15), F - 1) * d + ks * kq + q * 16;
-    // first weights in flight before x is staged
-    u32x4_t w0[UN], w1[UN];
+    float (*red)[NW][256] = reinterpret_cast<float (*)[NW][256]>(dec_smem + C::kRing);
+    float* tile = reinterpret_cast<float*>(dec_smem + C::kRing + C::kRed);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t units = (F + UNIT - 1) / UNIT;
+    const int row0 = (int)(units * blockIdx.x / gridDim.x) * UNIT;
+    const int rows = min(F, (int)(units * (blockIdx.x + 1) / gridDim.x) * UNIT) - row0;
+    // this wavefront's steps of 64 k
+    const int steps = d / 64, per = (steps + NW - 1) / NW;
+    const int first = min(wave * per, steps), mine = min(per, steps - first);
+    constexpr uint32_t kNowhere = 0xF0000000u;      // past the end of every buffer: zeros
+    const uint32_t pitch = (uint32_t)d * 2u;
+    u32x4_t xf[NS][2];
+    {
+        const auto xbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(x), 0, (uint32_t)B * pitch, 0x00020000);
+        const uint32_t off = (uint32_t)(lane & 15) * pitch + (uint32_t)first * 128u + (uint32_t)(lane >> 4) * 16u;
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
-        w0[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wrow + u * 64));
-        w1[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wrow + u * 64 + 8));
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t o = s < mine ? off : kNowhere;
+            xf[s][0] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, o + s * 128, 0, 0);
+            xf[s][1] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, o + s * 128 + 64, 0, 0);
+        }
     }
-    for (int i = tid * 8; i < BTOK * d; i += NT * 8) {
-        const int b = i / d, k = i - b * d;
-        u32x4_t v = {0, 0, 0, 0};
-        if (b < B) v = *reinterpret_cast<const u32x4_t*>(x + i);
-        *reinterpret_cast<u32x4_t*>(dec_smem + b * xpitch + k * 2) = v;
+    __builtin_amdgcn_sched_barrier(0);
+    // A piece in LDS: [16 rows][8 P chunks of 16 bytes], the position of a chunk XORed with the row, so that the 16 rows that an LDS
+    // read takes one chunk of lie in different banks.
+    const auto chunk_xor = [](int row) { return P == 1 ? (row >> 1) & 7 : row & 15; };
+    uint32_t src[PB][2 * P];
+#pragma unroll
+    for (int i = 0; i < 2 * P; ++i) {
+        const int c = i * 64 + lane, row = c / (8 * P), chunk = (c % (8 * P)) ^ chunk_xor(row);
+#pragma unroll
+        for (int part = 0; part < PB; ++part)
+            src[part][i] = part * P + chunk / 8 < mine ? (uint32_t)row * pitch + (uint32_t)(first + part * P) * 128u + (uint32_t)chunk * 16u : kNowhere;
     }
-    __syncthreads();
-    const bool tok = (lane & 15) < BTOK;                             // this lane's token slot holds a token
-    const unsigned char* xl = dec_smem + (tok ? (lane & 15) : 0) * xpitch + (ks * kq + q * 16) * 2;
+    const uint32_t ring = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)dec_smem) +
+                          (uint32_t)wave * 2 * C::kPiece;
+    auto request = [&](int block, int part, int slot) {      // blocks past the last: no bytes to read, zeros
+        const int left = max(rows - block * 16, 0);
+        const u32x4_t desc = buffer_desc(wg + (int64_t)(row0 + block * 16) * d, (uint32_t)left * pitch);
+#pragma unroll
+        for (int i = 0; i < 2 * P; ++i) lds_load16<kNonTemporal>(src[part][i], desc, ring + slot * C::kPiece + i * 1024);
+    };
+    typedef __attribute__((address_space(3))) const u32x4_t* frag_ptr;
     f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    const int nstep = kq / 64;
-    for (int s0 = 0; s0 < nstep; s0 += UN) {
-        u32x4_t c0[UN], c1[UN];
+    // Products of one piece; the ring slot is requested again as soon as its fragments are in registers.
+    auto consume = [&](int part, int slot, int next_block) {
+        wait_counts<2 * P, false>();                // (all but the other slot's requests have arrived)
+        u32x4_t f[P][2];
+        const int row = lane & 15;
 #pragma unroll
-        for (int u = 0; u < UN; ++u) { c0[u] = w0[u]; c1[u] = w1[u]; }
-        if (s0 + UN < nstep) {
-            const int nxt = min(s0 + UN, nstep - UN);                // clamped prefetch of the next UN steps
+        for (int s = 0; s < P; ++s)
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                w0[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wrow + (nxt + u) * 64));
-                w1[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(wrow + (nxt + u) * 64 + 8));
-            }
-        }
+            for (int h = 0; h < 2; ++h)
+                f[s][h] = *reinterpret_cast<frag_ptr>(ring + slot * C::kPiece + row * P * 128 +
+                                                      (((s * 8 + h * 4 + (lane >> 4)) ^ chunk_xor(row)) << 4));
+        wait_counts<63, true>();
+        request(next_block, part, slot);
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            if (s0 + u < nstep) {
-                u32x4_t x0 = {0, 0, 0, 0}, x1 = {0, 0, 0, 0};
-                if (BTOK == 16 || tok) {
-                    x0 = *reinterpret_cast<const u32x4_t*>(xl + (s0 + u) * 128);
-                    x1 = *reinterpret_cast<const u32x4_t*>(xl + (s0 + u) * 128 + 16);
-                }
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8_t, c0[u]),
-                                                              __builtin_bit_cast(dec_bf16x8_t, x0), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8_t, c1[u]),
-                                                              __builtin_bit_cast(dec_bf16x8_t, x1), acc, 0, 0, 0);
-            }
-        }
-    }
-    // acc[r] = D[row 4*(lane/16) + r][token lane % 16] over this wave's share of k
-    *reinterpret_cast<f32x4_t*>(red + ((rg * KS + ks) * 64 + lane) * 4) = acc;
-    __syncthreads();
-    float* tile = red + RG * KS * 256;                               // [ROWS][17], grouped selection only
-    if (ks == 0) {
-        f32x4_t s = acc;
+        for (int s = 0; s < P; ++s)
 #pragma unroll
-        for (int o = 1; o < KS; ++o) s += *reinterpret_cast<const f32x4_t*>(red + ((rg * KS + o) * 64 + lane) * 4);
-        const int b = lane & 15, r = row0 + 4 * (lane >> 4);
-        if (GB == 0) {
+            for (int h = 0; h < 2; ++h)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(dec_bf16x8_t, f[s][h]),
+                                                              __builtin_bit_cast(dec_bf16x8_t, xf[part * P + s][h]), acc, 0, 0, 0);
+    };
+    // acc[e] = D[row 4 (lane / 16) + e][token lane % 16] over this wavefront's share of k
+    auto finish = [&](int block) {
+        float (&part)[NW][256] = red[block & 1];
+        *reinterpret_cast<f32x4_t*>(&part[wave][lane * 4]) = acc;
+        acc = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        wait_counts<63, true>();
+        __builtin_amdgcn_s_barrier();               // (the requests stay under way)
+        asm volatile("" ::: "memory");
+        // Until the next block's barrier the adding wavefront has `part`, and `tile`, to itself.
+        if (wave != (block & (NW - 1))) return;
+        f32x4_t s = *reinterpret_cast<const f32x4_t*>(&part[0][lane * 4]);
+#pragma unroll
+        for (int o = 1; o < NW; ++o) s += *reinterpret_cast<const f32x4_t*>(&part[o][lane * 4]);
+        const int b = lane & 15, in_block = 4 * (lane >> 4);
+        if constexpr (GB == 0) {
+            const int r = block * 16 + in_block;
+            float* q = g + (int64_t)b * ldg + row0 + r;
             if (b < B) {
-                if (r + 3 < F) *reinterpret_cast<f32x4_t*>(g + (int64_t)b * ldg + r) = s;
+                if (r + 3 < rows) *reinterpret_cast<f32x4_t*>(q) = s;
                 else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (r + e < F) g[(int64_t)b * ldg + r + e] = s[e];
+                        if (r + e < rows) q[e] = s[e];
                 }
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tile[(rg * 16 + 4 * (lane >> 4) + e) * 17 + b] = s[e];
+            for (int e = 0; e < 4; ++e) tile[(in_block + e) * 17 + b] = s[e];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int group = lane >> 4, r = block * 16 + group * GB;
+            if (group < 16 / GB && b < B && r < rows)
+                decode_group_select<GB>(tile + group * GB * 17 + b, 17, row0 + r, (row0 + r) / GB, ga, idx + (int64_t)b * K,
+                                        gsel + (int64_t)b * K);
+        }
+    };
+    request(0, 0, 0);
+    if (PB == 2) request(0, PB - 1, 1);
+    else request(1, 0, 1);
+    // x has arrived before the loop: the compiler, which does not count the requests, would wait for them inside it
+#pragma unroll
+    for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(xf[s][0]), "+v"(xf[s][1]));
+    const int blocks = (rows + 15) / 16;
+    if constexpr (PB == 2) {
+        for (int block = 0; block < blocks; ++block) {
+            consume(0, 0, block + 1);
+            consume(1, 1, block + 1);
+            finish(block);
+        }
+    } else {
+        for (int block = 0; block < blocks; block += 2) {
+            consume(0, 0, block + 2);
+            finish(block);
+            if (block + 1 == blocks) break;
+            consume(0, 1, block + 3);
+            finish(block + 1);
         }
     }
-    if (GB != 0) {
-        __syncthreads();
-        constexpr int GBS = GB == 0 ? 8 : GB;
-        const int grp = tid >> 4, b = tid & 15;                     // group of this workgroup's rows, token
-        const int c0 = blockIdx.x * ROWS + grp * GBS;
-        if (grp < ROWS / GBS && b < B && c0 < F)
-            decode_group_select<GBS>(tile + grp * GBS * 17 + b, 17, c0, c0 / GBS, ga, idx + (int64_t)b * K,
-                                     gsel + (int64_t)b * K);
-    }
-}
-
-// LDS bytes of decode_gate_mfma_kernel.
-inline size_t decode_gate_mfma_lds(int d, int RG, int KS, int BTOK) {
-    return (size_t)BTOK * (d * 2 + 16) + (size_t)RG * KS * 256 * sizeof(float) + (size_t)RG * 16 * 17 * sizeof(float);
+    wait_counts<0, true>();                         // nothing may still be on its way to LDS when the workgroup ends
 }
 
 // z[b, s] = SiLU(gsel[b, s]) * (x[b] . wu[idx[b, s]])  for every selected (token, channel) pair.

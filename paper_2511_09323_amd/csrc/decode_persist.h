@@ -922,8 +922,8 @@ __global__ __launch_bounds__(NT) void decode_persistent_kernel(DecArgs<E> a) {
 }
 
 // ------------------------------------------------------------------------- MFMA variant (5..16 tokens)
-// bf16, 768 threads = 3 row groups x 4 shares of the contraction (the gate phase is that of
-// decode_gate_mfma_kernel<0, 3, 4, 16, 4>); a workgroup owns blocks of 48 consecutive channels.
+// bf16, 768 threads = 3 row groups x 4 shares of the contraction (gate phase: a wavefront reads
+// 32 bytes of each of 16 rows per 64 k, four steps ahead); a workgroup owns blocks of 48 consecutive channels.
 // LDS: x [16, d] with rows padded by 16 bytes at 0; own gate tiles [rmax][48][17] floats at off_own;
 // the phase-overlaid area (MFMA partial tiles, selection) at off_over.
 template <int NCH>

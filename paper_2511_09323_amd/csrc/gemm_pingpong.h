@@ -38,6 +38,7 @@
 #include "gemm_mfma.h"
 #include "gemm_plan.h"
 #include "kernel_attrs.h"
+#include "lds_dma.h"
 
 namespace moc {
 
@@ -58,22 +59,6 @@ template <int BM, int BN> struct PpCfg {
     static_assert(4 * kA <= 65536 && 4 * kB <= 65536 && kLds <= 160 * 1024, "");
 };
 
-// 16 bytes per lane from memory to LDS (lane l to lds + 16 l).  Has no register result; the caller counts it in vmcnt.  (As the
-// builtin, the compiler would wait for all of them before every LDS read, which it cannot tell apart.)
-__device__ __forceinline__ void lds_load16(uint32_t off, u32x4_t rsrc, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(rsrc) : "memory");
-}
-__device__ __forceinline__ u32x4_t buffer_desc(const void* p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    return u32x4_t{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
-}
-// At most VM of this wavefront's vector memory instructions still under way (and no LDS reads, with LDS).
-template <int VM, bool LDS> __device__ __forceinline__ void wait_counts() {
-    static_assert(VM >= 0 && VM < 64, "");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | ((LDS ? 0 : 15) << 8) | ((VM >> 4) << 14));
-    asm volatile("" ::: "memory");
-}
 __device__ __forceinline__ void pp_barrier() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);

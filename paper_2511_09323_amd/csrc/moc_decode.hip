@@ -53,27 +53,27 @@ moc_status decode_gate_group_b(const Dims& D, const E* x, const E* wg, int ga, i
     return decode_gate_group<E, BT, 16>(D, x, wg, ga, idx, gsel, st);
 }
 
-template <int GB, int RG, int KS, int BTOK, int UN>
-moc_status launch_decode_gate_mfma_shape(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx,
-                                         float* gsel, hipStream_t st) {
-    const size_t lds = decode_gate_mfma_lds(D.d, RG, KS, BTOK);
-    auto kern = decode_gate_mfma_kernel<GB, RG, KS, BTOK, UN>;
-    LdsAttr<decode_gate_mfma_kernel<GB, RG, KS, BTOK, UN>, kMaxDynLds>::use();
+template <int GB, int NS>
+moc_status launch_decode_gate_stream_ns(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
+                                        hipStream_t st) {
+    auto kern = decode_gate_stream_kernel<GB, NS>;
+    constexpr int lds = GateStreamCfg<GB, NS>::kLds;
+    LdsAttr<decode_gate_stream_kernel<GB, NS>, lds>::use();
     Span span(GB == 0 ? "decode_gate" : "decode_gate_select", st);
-    const int rows = RG * 16;
-    hipLaunchKernelGGL(kern, dim3((D.F + rows - 1) / rows), dim3(RG * KS * 64), lds, st, x, wg, D.T, D.d, D.F, g,
-                       (int64_t)D.ldF, ga, D.K, idx, gsel);
+    const int unit = GB == 0 ? 4 : GB;
+    hipLaunchKernelGGL(kern, dim3(std::min(256, (D.F + unit - 1) / unit)), dim3(kGateStreamWaves * 64), lds, st,
+                       x, wg, D.T, D.d, D.F, g, (int64_t)D.ldF, ga, D.K, idx, gsel);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }
-
-// small = true: at most four tokens, d a multiple of 4096 (16 rows per workgroup, eight shares of the
-// contraction); otherwise up to 16 tokens, d a multiple of 1024 (48 rows, four shares).
 template <int GB>
-moc_status launch_decode_gate_mfma(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx,
-                                   float* gsel, bool small, hipStream_t st) {
-    if (small) return launch_decode_gate_mfma_shape<GB, 1, 8, 4, 8>(D, x, wg, g, ga, idx, gsel, st);
-    return launch_decode_gate_mfma_shape<GB, 3, 4, 16, 4>(D, x, wg, g, ga, idx, gsel, st);
+moc_status launch_decode_gate_stream(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
+                                     hipStream_t st) {
+    const int steps = (D.d / 64 + kGateStreamWaves - 1) / kGateStreamWaves;
+    if (steps <= 1) return launch_decode_gate_stream_ns<GB, 1>(D, x, wg, g, ga, idx, gsel, st);
+    if (steps <= 2) return launch_decode_gate_stream_ns<GB, 2>(D, x, wg, g, ga, idx, gsel, st);
+    if (steps <= 4) return launch_decode_gate_stream_ns<GB, 4>(D, x, wg, g, ga, idx, gsel, st);
+    return launch_decode_gate_stream_ns<GB, 8>(D, x, wg, g, ga, idx, gsel, st);
 }
 
 template <class E, int BT, int GA>
@@ -346,20 +346,21 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         HIP_TRY(hipGetLastError());
         return MOC_OK;
     }
-    const bool bf16_mfma = std::is_same<E, bf16_t>::value && !options().force_generic;
-    // two to four tokens: the MFMA kernel's strided row reads stream slower than the row-per-wavefront
-    // GEMV (26.7 against 24.8 us at the 7B shape), but with the selection fused in it beats the
-    // workgroup-per-group GEMV (28.3 against 30.8 us), so it serves the grouped variant only
-    const bool mfma_small = bf16_mfma && gb != 0 && B >= 2 && B <= 4 && D.d % 4096 == 0 &&
-                            decode_gate_mfma_lds(D.d, 1, 8, 4) <= 64 * 1024;
-    const bool mfma_large = bf16_mfma && B > 4 && D.d % 1024 == 0 && decode_gate_mfma_lds(D.d, 3, 4, 16) <= 160 * 1024 - 64;
-    if (mfma_small || mfma_large) {
+    // bf16 from two tokens on: the streamed gate on the matrix cores, against the row-per-wavefront dot products (grouped: workgroup per
+    // group).  Cold weights, F = 8/3 d, K/F = 1/8, whole call, that / this in us.  Two and four tokens: d 512 12.7 / 12.4 and 13.2 / 12.7,
+    // 768 14.0 / 13.6 and 14.3 / 13.8, 1024 15.2 / 14.9 and 15.8 / 15.8, 4096 40.0 / 37.4 and 48.7 / 45.5; but 1536 17.4 / 17.6 and 18.8 / 19.3,
+    // 2048 20.2 / 21.3 and 22.5 / 24.6: a workgroup has less than two blocks of rows there, all requested at once, and nothing to overlap
+    // the last arrivals with.  Sixteen tokens: 512 18.5 / 15.5, 768 21.4 / 17.7, 1536 36.6 / 26.1 (eight: 29.9 / 22.9).
+    const bool small_batch_pays = D.d <= 1024 || D.d > 2048;
+    const bool gate_stream = std::is_same<E, bf16_t>::value && !options().force_generic && D.d % 64 == 0 && D.d <= kGateStreamMaxD &&
+                             (B > 4 || (B >= 2 && small_batch_pays));
+    if (gate_stream) {
         const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
         const bf16_t* wb = reinterpret_cast<const bf16_t*>(wg);
-        if (gb == 0) s = launch_decode_gate_mfma<0>(D, xb, wb, W.g, 0, idx, W.gsel, mfma_small, st);
-        else if (gb == 4) s = launch_decode_gate_mfma<4>(D, xb, wb, W.g, ga, idx, W.gsel, mfma_small, st);
-        else if (gb == 8) s = launch_decode_gate_mfma<8>(D, xb, wb, W.g, ga, idx, W.gsel, mfma_small, st);
-        else s = launch_decode_gate_mfma<16>(D, xb, wb, W.g, ga, idx, W.gsel, mfma_small, st);
+        if (gb == 0) s = launch_decode_gate_stream<0>(D, xb, wb, W.g, 0, idx, W.gsel, st);
+        else if (gb == 4) s = launch_decode_gate_stream<4>(D, xb, wb, W.g, ga, idx, W.gsel, st);
+        else if (gb == 8) s = launch_decode_gate_stream<8>(D, xb, wb, W.g, ga, idx, W.gsel, st);
+        else s = launch_decode_gate_stream<16>(D, xb, wb, W.g, ga, idx, W.gsel, st);
     } else if (gb == 0) {
         if (B == 1) s = decode_gate<E, 1>(D, x, wg, W.g, st);
         else if (B <= 4) s = decode_gate<E, 4>(D, x, wg, W.g, st);
