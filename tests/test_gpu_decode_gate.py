@@ -29,6 +29,12 @@ def test_streamed_gate_with_grouped_selection(B, d, F, a, b):
     run_grouped_decode("streamed gate", 87, B, d, F, a, b, "bf16")
 
 
+@pytest.mark.parametrize("K", [8191, 8192, 8200, 8312, 9000])
+def test_gather_with_more_slots_than_lanes(K):
+    """16 tokens, 16 shares of the channels: a wavefront of the gather has 64, 65 and up to 71 slots, and reads the channels of 64 at a time."""
+    run_decode_case("gather", 86, 16, 64, 9000, K, "bf16")
+
+
 @pytest.mark.parametrize("B,d,F,K", [(3, 576, 1030, 128), (16, 4096, 523, 65)])
 def test_nothing_outside_the_operands_counts(B, d, F, K):
     """x and W_gate lie between NaN: what is requested past a row, a token or a workgroup's rows must not reach a result."""
