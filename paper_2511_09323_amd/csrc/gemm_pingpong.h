@@ -435,22 +435,11 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     wait_counts<0, true>();      // nothing may still be on its way to LDS when the workgroup ends
 }
 
-// What the kernel takes beyond mfma_problem_ok: contraction ends that the range check or A's zeros cover, offsets in 32 bits, whole
-// 16-byte pieces of output rows.
+inline PpSizes pp_sizes(const MfmaProblem& p, const PpOut& o) {
+    return PpSizes{p.M, p.N, p.Kc, p.Kc2, p.A.ld, p.B.ld, p.A.km, p.B.km, p.a_zero_padded, o.N, o.ldc, o.stride, o.f32 ? 4 : 2};
+}
 inline bool pp_problem_ok(const MfmaProblem& p, const PpOut& o) {
-    if (!mfma_problem_ok(p)) return false;
-    // both k-contiguous: the slice past the end would be the next rows' values
-    if (!p.A.km && !p.B.km && (p.Kc % kPpBK != 0 || p.Kc2 % kPpBK != 0)) return false;
-    if (!p.A.km && p.B.km && (p.Kc % kPpBK != 0 || p.Kc2 % kPpBK != 0) &&
-        !(p.a_zero_padded && p.A.ld >= round_up(std::max(p.Kc, p.Kc2), kPpBK))) return false;
-    if (p.A.km && !p.B.km) return false;
-    const int64_t lim = (1ll << 32) - 65536;
-    const int64_t k = std::max(p.Kc, p.Kc2) + 2 * kPpBK;
-    const auto bytes = [&](const GemmOperand<bf16_t>& q, int rows) { return ((q.km ? k : (int64_t)rows + 256) * q.ld + 256 + k) * 2; };
-    if (bytes(p.A, p.M) >= lim || bytes(p.B, p.N) >= lim) return false;
-    const int es = o.f32 ? 4 : 2;
-    return (reinterpret_cast<uintptr_t>(o.p) & 15) == 0 && o.N * es % 16 == 0 && o.ldc * es % 16 == 0 && o.stride * es % 16 == 0 &&
-           256 * o.ldc * es < (1ll << 31);
+    return mfma_problem_ok(p) && (reinterpret_cast<uintptr_t>(o.p) & 15) == 0 && pp_sizes_ok(pp_sizes(p, o));
 }
 
 // w.tiles, w.cum and w.tiles_n are filled in here; `wgs` workgroups at most (a multiple of 8; 0: one per item), each walking over its items.

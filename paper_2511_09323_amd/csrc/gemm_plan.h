@@ -101,6 +101,31 @@ constexpr double kPpLaunch = 6.8;
 constexpr PpTile kPpTile[kPpTiles] = {
     {256, 256, 3.2, 1.04, 1.37}, {192, 256, 1.8, 0.84, 1.05}, {256, 192, 2.0, 0.86, 1.07}, {128, 256, 1.4, 0.69, 0.79}, {256, 128, 1.4, 0.68, 0.78}};
 
+// A product as the kernel of gemm_pingpong.h sees it: leading dimensions, layouts (km: k-major) and zero padding of the operands as in
+// GemmProblem, and its result: columns stored, row pitch, distance of the shares of a split contraction, bytes of an element.
+struct PpSizes {
+    int M, N, Kc, Kc2;
+    int64_t lda, ldb;
+    bool akm, bkm, a_zero_padded;
+    int64_t out_n, ldc, stride;
+    int elem;
+};
+// Whether sizes let the kernel take it: contraction ends that the range check or A's zeros cover; byte offsets within an operand in 32 bits,
+// to the end of the last tile (256 rows or columns) and slice; whole 16-byte pieces of output rows.
+inline bool pp_sizes_ok(const PpSizes& s) {
+    const auto whole = [](int k) { return k % kPpBK == 0; };
+    // both k-contiguous: the slice past the end would be the next rows' values
+    if (!s.akm && !s.bkm && !(whole(s.Kc) && whole(s.Kc2))) return false;
+    const int longest = std::max(s.Kc, s.Kc2);
+    if (!s.akm && s.bkm && !(whole(s.Kc) && whole(s.Kc2)) &&
+        !(s.a_zero_padded && s.lda >= ((int64_t)longest + kPpBK - 1) / kPpBK * kPpBK)) return false;
+    if (s.akm && !s.bkm) return false;
+    const int64_t k = (int64_t)longest + 2 * kPpBK, lim = (1ll << 32) - 65536;
+    const auto bytes = [&](bool km, int rows, int64_t ld) { return ((km ? k : (int64_t)rows + 256) * ld + 256 + k) * 2; };
+    if (bytes(s.akm, s.M, s.lda) >= lim || bytes(s.bkm, s.N, s.ldb) >= lim) return false;
+    return s.out_n * s.elem % 16 == 0 && s.ldc * s.elem % 16 == 0 && s.stride * s.elem % 16 == 0 && 256 * s.ldc * s.elem < (1ll << 31);
+}
+
 inline int64_t tile_count(int M, int N, const PpTile& t) { return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
 inline int pp_slice_count(int Kc, int Kc2) { return (Kc + kPpBK - 1) / kPpBK + (Kc2 + kPpBK - 1) / kPpBK; }
 inline double pp_cost(const PpTile& t, int64_t tiles, int nk, int cus) {

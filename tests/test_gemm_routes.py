@@ -61,8 +61,79 @@ static void routes() {
                 }
     std::puts("ok");
 }
+// Byte offsets that gemm_bf16_pp_kernel forms in 32 bits: within an operand of `rows` rows (k-contiguous) or columns (k-major), to the
+// end of the last tile and of the last slice; its readable bytes; within a tile's rows of the result.
+static int64_t last_offset(bool km, int64_t rows, int64_t ld, int64_t k) {
+    const int64_t row = (rows + 255) / 256 * 256 - 1, last_k = (k + kPpBK - 1) / kPpBK * kPpBK - 1;
+    return 2 * (km ? last_k * ld + row : row * ld + last_k);
+}
+static int64_t readable(bool km, int64_t rows, int64_t ld, int64_t k) { return 2 * ld * (km ? k : rows); }
+static void check_offsets(const PpSizes& s) {
+    const int64_t lim = 1ll << 32;
+    for (int k : {s.Kc, s.Kc2}) {
+        if (k == 0) continue;
+        EXPECT(last_offset(s.akm, s.M, s.lda, k) + 16 <= lim && readable(s.akm, s.M, s.lda, k) < lim);
+        EXPECT(last_offset(s.bkm, s.N, s.ldb, k) + 16 <= lim && readable(s.bkm, s.N, s.ldb, k) < lim);
+    }
+    EXPECT(256 * s.ldc * s.elem <= 1ll << 31);      // (0xFFFFFF00, where columns past the last go, is out of range)
+}
+// The largest value of one size that is taken, as the kernel's limit is approached; nothing that passes 4 GiB is.
+template <class Set> static int64_t largest(const PpSizes& base, int64_t hi, int64_t step, const Set& set) {
+    int64_t best = 0;
+    for (int64_t lo = 1, up = hi / step; lo <= up;) {
+        const int64_t mid = (lo + up) / 2;
+        PpSizes s = base;
+        set(s, mid * step);
+        if (pp_sizes_ok(s)) { best = mid * step; lo = mid + 1; check_offsets(s); }
+        else up = mid - 1;
+    }
+    return best;
+}
+static void sizes() {
+    const int64_t lim = 1ll << 32;
+    for (int64_t ld : {64, 512, 4096, 5504, 11008, 32768, 1 << 20}) {
+        // x W^T: rows of x
+        const PpSizes kc{256, 256, 64, 0, ld, 64, false, false, false, 256, 256, 0, 4};
+        const int64_t m = largest(kc, 1ll << 30, 1, [](PpSizes& s, int64_t v) { s.M = (int)v; });
+        EXPECT(m > 0 && m * ld * 2 < lim && (m + 300) * ld * 2 >= lim - 131072);
+        // down and dX: the contraction over B's rows, ragged, A's rows padded
+        const PpSizes km{256, (int)std::min<int64_t>(ld, 256), 64, 0, 0, ld, false, true, true, 256, 256, 0, 2};
+        for (int add : {0, 1, 33}) {
+            const int64_t k = largest(km, (1ll << 30) / 64, 64, [&](PpSizes& s, int64_t v) {
+                s.Kc = (int)v + add;
+                s.lda = (v + add + 63) / 64 * 64;
+            });
+            EXPECT(k > 0 && k * ld * 2 < lim);
+        }
+        // weight gradients: the contraction over the tokens
+        const PpSizes kk{(int)std::min<int64_t>(ld, 300), 64, 64, 0, ld, 64, true, true, true, 256, 256, 0, 2};
+        const int64_t t = largest(kk, 1ll << 30, 1, [](PpSizes& s, int64_t v) { s.Kc = (int)v; });
+        EXPECT(t > 0 && t * ld * 2 < lim && (t + 300) * (ld + 1) * 2 >= lim - 131072);
+        // pitch of the result
+        for (int elem : {2, 4}) {
+            const int64_t c = largest(kc, 1ll << 30, 16 / elem, [&](PpSizes& s, int64_t v) { s.ldc = v; s.elem = elem; });
+            EXPECT(256 * c * elem < 1ll << 31 && 256 * (c + 16) * elem >= 1ll << 31);
+        }
+    }
+    const PpSizes good{256, 256, 64, 0, 64, 256, false, true, true, 256, 256, 0, 2};
+    EXPECT(pp_sizes_ok(good));
+    const auto refused = [&](auto change) {
+        PpSizes s = good;
+        change(s);
+        return !pp_sizes_ok(s);
+    };
+    EXPECT(refused([](PpSizes& s) { s.Kc = 63; s.a_zero_padded = false; }));      // a ragged contraction that nothing covers
+    EXPECT(refused([](PpSizes& s) { s.Kc = 65; }));                              // rows of A end before the slice
+    EXPECT(refused([](PpSizes& s) { s.Kc = 63; s.bkm = false; }));
+    EXPECT(refused([](PpSizes& s) { s.akm = true; s.bkm = false; }));
+    EXPECT(refused([](PpSizes& s) { s.out_n = 252; }));                          // half a 16-byte piece
+    EXPECT(refused([](PpSizes& s) { s.ldc = 260; }));
+    EXPECT(refused([](PpSizes& s) { s.stride = 4; }));
+    std::puts("ok");
+}
 int main(int argc, char** argv) {
     if (argc == 1) routes();
+    else if (argc == 2) sizes();
     else if (argc == 4) products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
@@ -79,6 +150,12 @@ def plan(tmp_path_factory):
 
 def test_routes_stay_within_what_the_launchers_take(plan):
     r = plan()
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_sizes_that_large_tiles_take(plan):
+    """Every 32-bit offset of gemm_bf16_pp_kernel, up to the largest operands that pp_sizes_ok admits (near 4 GiB)."""
+    r = plan("sizes")
     assert r.returncode == 0, r.stdout + r.stderr
 
 
