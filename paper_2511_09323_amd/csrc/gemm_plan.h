@@ -119,7 +119,7 @@ inline bool pp_sizes_ok(const PpSizes& s) {
     const int longest = std::max(s.Kc, s.Kc2);
     if (!s.akm && s.bkm && !(whole(s.Kc) && whole(s.Kc2)) &&
         !(s.a_zero_padded && s.lda >= ((int64_t)longest + kPpBK - 1) / kPpBK * kPpBK)) return false;
-    if (s.akm && !s.bkm) return false;
+    if (s.akm && (!s.bkm || s.Kc2 != 0)) return false;      // (the kernel has one count of A's readable bytes, which with k-major rows depends on the contraction)
     const int64_t k = (int64_t)longest + 2 * kPpBK, lim = (1ll << 32) - 65536;
     const auto bytes = [&](bool km, int rows, int64_t ld) { return ((km ? k : (int64_t)rows + 256) * ld + 256 + k) * 2; };
     if (bytes(s.akm, s.M, s.lda) >= lim || bytes(s.bkm, s.N, s.ldb) >= lim) return false;

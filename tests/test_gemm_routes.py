@@ -126,6 +126,10 @@ static void sizes() {
     EXPECT(refused([](PpSizes& s) { s.Kc = 65; }));                              // rows of A end before the slice
     EXPECT(refused([](PpSizes& s) { s.Kc = 63; s.bkm = false; }));
     EXPECT(refused([](PpSizes& s) { s.akm = true; s.bkm = false; }));
+    // weight gradients over two operand pairs: the kernel knows the readable bytes of A's first only
+    EXPECT(!refused([](PpSizes& s) { s.akm = true; }));
+    EXPECT(refused([](PpSizes& s) { s.akm = true; s.Kc2 = 32; }));
+    EXPECT(!refused([](PpSizes& s) { s.Kc2 = 32; }));
     EXPECT(refused([](PpSizes& s) { s.out_n = 252; }));                          // half a 16-byte piece
     EXPECT(refused([](PpSizes& s) { s.ldc = 260; }));
     EXPECT(refused([](PpSizes& s) { s.stride = 4; }));
