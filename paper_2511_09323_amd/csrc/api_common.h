@@ -12,6 +12,7 @@
 
 #include "../../include/moc.h"
 #include "common.h"
+#include "gemm_plan.h"
 
 namespace mocapi {
 using namespace moc;
@@ -125,7 +126,7 @@ struct Dims {
     int T, d, F, K;
     int ldF, nw;
     explicit Dims(const moc_shape& s) : T(s.T), d(s.d), F(s.F), K(s.K) {
-        ldF = round_up(F, 64);
+        ldF = round_up(F, kColPad);
         nw = ldF / 32;
     }
 };
@@ -174,7 +175,7 @@ template <class E> struct FwdWs {      // dense scratch of the forward: fp32 gat
 };
 
 constexpr int kMaxExperts = 8;
-constexpr int kRowPad = 32;      // k-slice of the weight-gradient products, which contract over the rows below
+constexpr int kRowPad = kMfmaBK;      // rows of the weight-gradient products' operands below, which contract over them: whole k-slices
 
 // Rows of the dense backward operands: every expert's rows (one "expert" for the plain layer) are followed by zero rows up
 // to a whole k-slice, so that the weight-gradient products need no handling of contraction tails.

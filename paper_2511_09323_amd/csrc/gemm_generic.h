@@ -8,6 +8,7 @@
 // at p[k * ld + r]).
 #pragma once
 #include "common.h"
+#include "gemm_plan.h"
 
 namespace moc {
 
@@ -24,7 +25,9 @@ template <class E> struct GemmProblem {
     GemmOperand<E> A, B;
     int M, N;
     int Kc, Kc2;    // contraction lengths of segment 0 and 1 (Kc2 = 0: single segment)
-    bool a_zero_padded;    // operand A reads as zero for k from Kc up to the next multiple of 32 (both segments)
+    // Operand A (both segments) is readable and zero for k from the end of the contraction on: k-contiguous, up to the next multiple of kColPad (64); k-major,
+    // up to the next multiple of kMfmaBK (32).
+    bool a_zero_padded;
 };
 
 template <class E> inline GemmOperand<E> kc_operand(const E* p, int64_t ld, const E* p2 = nullptr) {

@@ -92,6 +92,10 @@ inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_byte
 // with few .. all compute units busy.  Measured with 64 .. 704 tiles at contractions of 512, 2048 and 8192; the operand layouts agree
 // within 5 %, the formula with the measurements within 6 %.
 constexpr int kPpBK = 64;
+// The library's dense operands [rows, F] are laid out in rows of a multiple of this and are zero from column F on, so that contractions
+// over the columns may run to the end of the last slice of any kernel (GemmProblem::a_zero_padded).
+constexpr int kColPad = 64;
+static_assert(kColPad % kMfmaBK == 0 && kColPad % kPpBK == 0, "whole slices");
 struct PpTile {
     int bm, bn;
     double o, lo, hi;
@@ -118,7 +122,7 @@ inline bool pp_sizes_ok(const PpSizes& s) {
     if (!s.akm && !s.bkm && !(whole(s.Kc) && whole(s.Kc2))) return false;
     const int longest = std::max(s.Kc, s.Kc2);
     if (!s.akm && s.bkm && !(whole(s.Kc) && whole(s.Kc2)) &&
-        !(s.a_zero_padded && s.lda >= ((int64_t)longest + kPpBK - 1) / kPpBK * kPpBK)) return false;
+        !(s.a_zero_padded && s.lda >= ((int64_t)longest + kColPad - 1) / kColPad * kColPad)) return false;
     if (s.akm && (!s.bkm || s.Kc2 != 0)) return false;      // (the kernel has one count of A's readable bytes, which with k-major rows depends on the contraction)
     const int64_t k = (int64_t)longest + 2 * kPpBK, lim = (1ll << 32) - 65536;
     const auto bytes = [&](bool km, int rows, int64_t ld) { return ((km ? k : (int64_t)rows + 256) * ld + 256 + k) * 2; };

@@ -70,3 +70,42 @@ def test_nothing_outside_the_operands_counts(T, d, F, K):
     for a, b in zip(run(between_nan), run(lambda a: P.to_dev(a, "bf16"))):
         assert torch.isfinite(a.float()).all()
         assert torch.equal(a, b)
+
+
+def _fwd_bwd(kind, L, F, K, fill):
+    """Outputs of one forward and backward of a kind of layer on workspaces that hold `fill`."""
+    x, wg, wu, wd, dy = (L[n] for n in ("x", "wg", "wu", "wd", "dy"))
+    T, d = x.shape
+
+    def ws(op):
+        return torch.full((moc.workspace_bytes(T, d, F, K, torch.bfloat16, op) // 2 + 1,), fill, dtype=torch.bfloat16, device="cuda").view(torch.uint8)
+
+    if kind == "dense":
+        y, g, u = moc.moc_swiglu_fwd(x, wg, wu, wd, ws=ws(3))
+        return (y, g, u) + tuple(moc.moc_swiglu_bwd(x, wg, wu, wd, g, u, dy, ws=ws(4)))
+    if kind == "experts":
+        off = [0, T // 2 + 13, T]
+        w = [torch.stack([t, t.flip(0)]) for t in (wg, wu, wd)]
+        y, idx, gv, uv = moc.moc_ffn_fwd_experts(x, off, *w, K, ws=ws(0))
+        return (y, idx, gv, uv) + tuple(moc.moc_ffn_bwd_experts(x, off, *w, idx, gv, uv, dy, ws=ws(1)))
+    if kind == "grouped":
+        y, idx, gv, uv = moc.moc_ffn_fwd_grouped(x, wg, wu, wd, 2, 8, ws=ws(0))
+    elif kind == "keyed":
+        y, idx, gv, uv = moc.moc_ffn_fwd_keyed(x, wg, wu, wd, K, "abs_silu", ws=ws(5))
+    else:
+        y, idx, gv, uv = moc.moc_ffn_fwd(x, wg, wu, wd, K, ws=ws(0))
+    return (y, idx, gv, uv) + tuple(moc.moc_ffn_bwd(x, wg, wu, wd, idx, gv, uv, dy, ws=ws(1)))
+
+
+@pytest.mark.parametrize("kind,T,d,F,K", [
+    ("rows", 6100, 2048, 200, 25), ("all", 6100, 2048, 200, 200), ("grouped", 6100, 2048, 200, 50), ("keyed", 6100, 2048, 200, 25),
+    ("dense", 6100, 2048, 200, 200), ("experts", 12000, 2048, 200, 25),
+    ("rows", 520, 1024, 29990, 25000),                         # lists too long for the registers: topk_rows_lds_kernel
+])
+def test_dense_operands_are_zero_to_the_end_of_their_rows(kind, T, d, F, K):
+    """Slices of the large tiles are 64 wide, those of gemm_mfma.h 32: with F % 64 in 1 .. 32 only the former read the last 32 columns of Z', dG and dU,
+    which everything that writes those arrays has to clear, whatever the workspace held."""
+    L = {n: P.to_dev(a, "bf16") for n, a in inputs.make_layer(95, T, d, F, "bf16", with_dy=True).items()}
+    for a, b in zip(_fwd_bwd(kind, L, F, K, float("nan")), _fwd_bwd(kind, L, F, K, 0.0)):
+        assert torch.isfinite(a.float()).all()
+        assert torch.equal(a, b)
