@@ -236,7 +236,8 @@ __global__ __launch_bounds__(256) void decode_gate_group_kernel(const E* __restr
 // 4096 x 11008 (90 MB), kernel alone: 16 tokens 22.0 -> 17.8 us (5.1 TB/s), 2:8 with 4 tokens 25.6 -> 17.5; before, one workgroup per 48
 // (16) rows staged x in LDS and read W_gate in MFMA order.  The same walk with loads to registers, 64 bytes of a row each: 20.8.
 // GB = 0 writes the gate rows g[B, ldg]; GB = 4, 8, 16 selects the a largest of every GB channels instead (MoC_{a:b}; a workgroup's
-// rows are a whole number of groups) and writes idx / gsel [B, K] only.  Needs d % 64 == 0, d <= 512 NS, 16-byte aligned operands.
+// rows are a whole number of groups) and writes idx / gsel [B, K] only.  NT: see gate_stream_nontemporal.  Needs d % 64 == 0, d <= 512 NS,
+// 16-byte aligned operands.
 typedef __bf16 dec_bf16x8_t __attribute__((ext_vector_type(8)));
 constexpr int kGateStreamWaves = 8, kGateStreamMaxD = 8 * 64 * kGateStreamWaves;
 template <int GB, int NS> struct GateStreamCfg {
@@ -247,16 +248,13 @@ template <int GB, int NS> struct GateStreamCfg {
     static constexpr int kLds = kRing + kRed + (GB == 0 ? 0 : 16 * 17 * 4);
     static_assert(PB <= 2 && kLds <= kMaxDynLds, "");
 };
-template <int GB, int NS>
+template <int GB, int NS, bool NT>
 __global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int B, int d, int F, float* __restrict__ g, int64_t ldg, int ga,
     int K, int32_t* __restrict__ idx, float* __restrict__ gsel) {
     using C = GateStreamCfg<GB, NS>;
     constexpr int NW = kGateStreamWaves, P = C::P, PB = C::PB;
     constexpr int UNIT = GB == 0 ? 4 : GB;
-    // Large layers do not stay in the last-level cache until the next token (4096 x 11008, 16 tokens, call with / without the hint: 75.4 /
-    // 76.4 us; 2:8, 4 tokens 49.9 / 51.6); smaller ones may, and the hint would undo that (2048 x 5461, 3 tokens, three layers in turn: 24.1 / 22.7).
-    constexpr bool kNonTemporal = NS == 8;
     extern __shared__ __align__(16) unsigned char dec_smem[];
     float (*red)[NW][256] = reinterpret_cast<float (*)[NW][256]>(dec_smem + C::kRing);
     float* tile = reinterpret_cast<float*>(dec_smem + C::kRing + C::kRed);
@@ -299,7 +297,7 @@ __global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_k
         const int left = max(rows - block * 16, 0);
         const u32x4_t desc = buffer_desc(wg + (int64_t)(row0 + block * 16) * d, (uint32_t)left * pitch);
 #pragma unroll
-        for (int i = 0; i < 2 * P; ++i) lds_load16<kNonTemporal>(src[part][i], desc, ring + slot * C::kPiece + i * 1024);
+        for (int i = 0; i < 2 * P; ++i) lds_load16<NT>(src[part][i], desc, ring + slot * C::kPiece + i * 1024);
     };
     typedef __attribute__((address_space(3))) const u32x4_t* frag_ptr;
     f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -203,6 +203,28 @@ GemmRoute group_route(unsigned mask, const TilesOf& tiles_of, const PpTilesOf& p
     return r;
 }
 
+// The streamed gate of bf16 decode (decode_gate_stream_kernel), whose workgroups have ceil(F / workgroups) rows each, in blocks of 16.
+//
+// Non-temporal loads where the layers of a model do not stay in the 256 MB last-level cache until the next token: from 24 MB of W_gate on for
+// certain (twelve matrices, four layers), with the hint / without, whole call: weights from memory 34 MB 0.93 to 0.98, 67 MB and more 0.85 to 0.97;
+// three layers in turn 34 MB 0.97 to 1.06, more as above.  Between 12 and 24 MB what three layers in turn lose weighs against what a
+// model's weights win: d > 2048 1.00 to 1.03 and 0.96 to 0.97, shorter rows 1.01 to 1.06 and 0.95 to 0.99.  Below: 1.00 to 1.07 and 0.96 to 1.02.
+inline bool gate_stream_nontemporal(int d, int F) { return 2ll * d * F >= (d > 2048 ? 12000000 : 24000000); }
+// From five tokens on it takes 0.44 to 0.93 of the dot products' time (d 512 .. 4096, F d/4 .. 8 d).  For two to four tokens, against one row
+// (grouped: one group) to a wavefront (workgroup), weights from memory, d 512 .. 4096, F 512 .. 12288, mean over two, three and four:
+//   row-wide: 0.89 to 1.02 with the hint.  Otherwise a compute unit's share of W_gate is requested at once by either kernel, and the dot products
+//     are as fast or faster (d > 1024: 0.98 to 1.10) except where their sums over a wavefront weigh most, in short rows: d <= 1024
+//     0.95 to 1.03 from five rows a workgroup on, below 1.01 to 1.04.
+//   grouped: 0.87 to 0.98 where a workgroup has one block of rows (up to 2048 x 4096: 1.01); with part of a second one 0.97 to 1.04 for
+//     d <= 1024 and d > 2048, 1.00 to 1.08 in between.
+inline bool gate_stream_pays(int B, int d, int F, bool grouped, int workgroups) {
+    if (B < 2) return false;
+    if (B > 4) return true;
+    const int rows = (F + workgroups - 1) / workgroups;
+    if (grouped) return d <= 1024 || d > 2048 || rows <= 16;
+    return gate_stream_nontemporal(d, F) || (d <= 1024 && rows >= 5);
+}
+
 // fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
 // fragment reads); below that 32 x 32, with the k-slices split over the wavefronts (16 x 32 or 32 x 32) when the contraction is long
 // (several 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate

@@ -53,18 +53,24 @@ moc_status decode_gate_group_b(const Dims& D, const E* x, const E* wg, int ga, i
     return decode_gate_group<E, BT, 16>(D, x, wg, ga, idx, gsel, st);
 }
 
-template <int GB, int NS>
-moc_status launch_decode_gate_stream_ns(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
+template <int GB, int NS, bool NT>
+moc_status launch_decode_gate_stream_nt(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
                                         hipStream_t st) {
-    auto kern = decode_gate_stream_kernel<GB, NS>;
+    auto kern = decode_gate_stream_kernel<GB, NS, NT>;
     constexpr int lds = GateStreamCfg<GB, NS>::kLds;
-    LdsAttr<decode_gate_stream_kernel<GB, NS>, lds>::use();
+    LdsAttr<decode_gate_stream_kernel<GB, NS, NT>, lds>::use();
     Span span(GB == 0 ? "decode_gate" : "decode_gate_select", st);
     const int unit = GB == 0 ? 4 : GB;
     hipLaunchKernelGGL(kern, dim3(std::min(256, (D.F + unit - 1) / unit)), dim3(kGateStreamWaves * 64), lds, st,
                        x, wg, D.T, D.d, D.F, g, (int64_t)D.ldF, ga, D.K, idx, gsel);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
+}
+template <int GB, int NS>
+moc_status launch_decode_gate_stream_ns(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
+                                        hipStream_t st) {
+    return gate_stream_nontemporal(D.d, D.F) ? launch_decode_gate_stream_nt<GB, NS, true>(D, x, wg, g, ga, idx, gsel, st)
+                                             : launch_decode_gate_stream_nt<GB, NS, false>(D, x, wg, g, ga, idx, gsel, st);
 }
 template <int GB>
 moc_status launch_decode_gate_stream(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
@@ -346,14 +352,9 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         HIP_TRY(hipGetLastError());
         return MOC_OK;
     }
-    // bf16 from two tokens on: the streamed gate on the matrix cores, against the row-per-wavefront dot products (grouped: workgroup per
-    // group).  Cold weights, F = 8/3 d, K/F = 1/8, whole call, that / this in us.  Two and four tokens: d 512 12.7 / 12.4 and 13.2 / 12.7,
-    // 768 14.0 / 13.6 and 14.3 / 13.8, 1024 15.2 / 14.9 and 15.8 / 15.8, 4096 40.0 / 37.4 and 48.7 / 45.5; but 1536 17.4 / 17.6 and 18.8 / 19.3,
-    // 2048 20.2 / 21.3 and 22.5 / 24.6: a workgroup has less than two blocks of rows there, all requested at once, and nothing to overlap
-    // the last arrivals with.  Sixteen tokens: 512 18.5 / 15.5, 768 21.4 / 17.7, 1536 36.6 / 26.1 (eight: 29.9 / 22.9).
-    const bool small_batch_pays = D.d <= 1024 || D.d > 2048;
+    // bf16 from two tokens on: the streamed gate on the matrix cores where gate_stream_pays says so.
     const bool gate_stream = std::is_same<E, bf16_t>::value && !options().force_generic && D.d % 64 == 0 && D.d <= kGateStreamMaxD &&
-                             (B > 4 || (B >= 2 && small_batch_pays));
+                             gate_stream_pays(B, D.d, D.F, gb != 0, 256);
     if (gate_stream) {
         const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
         const bf16_t* wb = reinterpret_cast<const bf16_t*>(wg);

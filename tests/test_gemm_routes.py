@@ -135,9 +135,26 @@ static void sizes() {
     EXPECT(refused([](PpSizes& s) { s.stride = 4; }));
     std::puts("ok");
 }
+static void gate() {
+    struct Row { int B, d, F; bool grouped, pays; };
+    for (const Row& r : {Row{1, 4096, 11008, false, false}, Row{2, 4096, 11008, false, true}, Row{4, 4096, 11008, true, true},
+                         // few rows a workgroup: the dot products, at any width
+                         Row{2, 2560, 640, false, false}, Row{4, 3072, 768, false, false}, Row{3, 4096, 1024, false, false}, Row{2, 1024, 1024, false, false},
+                         Row{2, 512, 512, false, false}, Row{4, 512, 1376, false, true}, Row{4, 1024, 2736, false, true},
+                         // the bytes of W_gate decide, not the width
+                         Row{3, 2048, 5461, false, false}, Row{3, 2048, 16384, false, true}, Row{3, 1536, 8192, false, true}, Row{3, 3072, 1900, false, false}, Row{3, 3072, 2000, false, true},
+                         Row{3, 2048, 2048, true, true}, Row{3, 1536, 4096, true, true}, Row{4, 2048, 5464, true, false}, Row{4, 2560, 6824, true, true},
+                         Row{5, 2048, 5461, false, true}, Row{16, 64, 8, true, true}, Row{5, 2560, 640, false, true}}) {
+        if (gate_stream_pays(r.B, r.d, r.F, r.grouped, kCus) != r.pays) std::printf("%d tokens, %d x %d\n", r.B, r.d, r.F);
+        EXPECT(gate_stream_pays(r.B, r.d, r.F, r.grouped, kCus) == r.pays);
+    }
+    EXPECT(!gate_stream_nontemporal(2048, 5464) && gate_stream_nontemporal(2048, 5860) && gate_stream_nontemporal(1024, 16384));
+    EXPECT(!gate_stream_nontemporal(4096, 1024) && gate_stream_nontemporal(4096, 1536) && gate_stream_nontemporal(4096, 11008) && gate_stream_nontemporal(4096, 32768));
+    std::puts("ok");
+}
 int main(int argc, char** argv) {
     if (argc == 1) routes();
-    else if (argc == 2) sizes();
+    else if (argc == 2) (std::strcmp(argv[1], "gate") ? sizes : gate)();
     else if (argc == 4) products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
@@ -160,6 +177,12 @@ def test_routes_stay_within_what_the_launchers_take(plan):
 def test_sizes_that_large_tiles_take(plan):
     """Every 32-bit offset of gemm_bf16_pp_kernel, up to the largest operands that pp_sizes_ok admits (near 4 GiB)."""
     r = plan("sizes")
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_decodes_that_take_the_streamed_gate(plan):
+    """By rows per workgroup and bytes of W_gate (gate_stream_pays, gate_stream_nontemporal)."""
+    r = plan("gate")
     assert r.returncode == 0, r.stdout + r.stderr
 
 

@@ -19,12 +19,17 @@ pytestmark = pytest.mark.gpu
     (7, 1536, 333, 40), (15, 2048, 12345, 1543),  # three steps of four; 48 and 49 rows
     (2, 2112, 700, 87), (16, 4096, 4100, 512),    # 33 steps in fives; eight each
     (16, 96, 300, 37), (2, 4160, 300, 37), (1, 4096, 300, 37),
+    (5, 64, 5, 2), (6, 2112, 700, 87),            # as with two tokens above, which few rows send to the dot products
+    (5, 512, 23440, 2930), (2, 1024, 11720, 1465), (3, 2048, 5860, 732), (2, 4096, 1465, 183),      # the first F with non-temporal loads
+    (5, 512, 23434, 2930), (3, 1024, 11716, 1465), (5, 2048, 5859, 732), (5, 4096, 1464, 183),      # and without
 ])
 def test_streamed_gate(B, d, F, K):
     run_decode_case("streamed gate", 88, B, d, F, K, "bf16")
 
 
-@pytest.mark.parametrize("B,d,F,a,b", [(2, 64, 8, 2, 8), (16, 512, 4104, 2, 8), (5, 1024, 12304, 3, 16), (4, 4096, 2052, 1, 4), (9, 576, 3000, 4, 8)])
+@pytest.mark.parametrize("B,d,F,a,b", [(2, 64, 8, 2, 8), (16, 512, 4104, 2, 8), (5, 1024, 12304, 3, 16), (4, 4096, 2052, 1, 4), (9, 576, 3000, 4, 8),
+                                       (3, 1536, 4096, 2, 8), (2, 2048, 2052, 1, 4), (4, 2048, 5464, 2, 8),      # one block a workgroup, and more
+                                       (5, 2048, 8192, 2, 8), (2, 4096, 3008, 3, 16)])                           # non-temporal
 def test_streamed_gate_with_grouped_selection(B, d, F, a, b):
     run_grouped_decode("streamed gate", 87, B, d, F, a, b, "bf16")
 
