@@ -53,6 +53,8 @@ moc_status decode_gate_group_b(const Dims& D, const E* x, const E* wg, int ga, i
     return decode_gate_group<E, BT, 16>(D, x, wg, ga, idx, gsel, st);
 }
 
+int gate_stream_workgroups() { return std::max(1, device_cu_count()); }
+
 template <int GB, int NS, bool NT>
 moc_status launch_decode_gate_stream_nt(const Dims& D, const bf16_t* x, const bf16_t* wg, float* g, int ga, int32_t* idx, float* gsel,
                                         hipStream_t st) {
@@ -61,7 +63,7 @@ moc_status launch_decode_gate_stream_nt(const Dims& D, const bf16_t* x, const bf
     LdsAttr<decode_gate_stream_kernel<GB, NS, NT>, lds>::use();
     Span span(GB == 0 ? "decode_gate" : "decode_gate_select", st);
     const int unit = GB == 0 ? 4 : GB;
-    hipLaunchKernelGGL(kern, dim3(std::min(256, (D.F + unit - 1) / unit)), dim3(kGateStreamWaves * 64), lds, st,
+    hipLaunchKernelGGL(kern, dim3(std::min(gate_stream_workgroups(), (D.F + unit - 1) / unit)), dim3(kGateStreamWaves * 64), lds, st,
                        x, wg, D.T, D.d, D.F, g, (int64_t)D.ldF, ga, D.K, idx, gsel);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
@@ -354,7 +356,7 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
     }
     // bf16 from two tokens on: the streamed gate on the matrix cores where gate_stream_pays says so.
     const bool gate_stream = std::is_same<E, bf16_t>::value && !options().force_generic && D.d % 64 == 0 && D.d <= kGateStreamMaxD &&
-                             gate_stream_pays(B, D.d, D.F, gb != 0, 256);
+                             gate_stream_pays(B, D.d, D.F, gb != 0, gate_stream_workgroups());
     if (gate_stream) {
         const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
         const bf16_t* wb = reinterpret_cast<const bf16_t*>(wg);
