@@ -221,11 +221,8 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
         const bool padded = gemm_padded(pr[0]) && gemm_padded(pr[1]) && gemm_padded(pr[2]);
         if (same && (!tail || padded) && !options().force_generic && mfma_problem_ok(pr[0]) && mfma_problem_ok(pr[1]) && mfma_problem_ok(pr[2])) {
             const int nk = slice_count(pr[0].Kc, 0);
-            double cost = 0.0;
             const bool pp = pp_group_takes(3, pr, epi) && !(sk && sk->part && options().gemm_streamk);
-            const GemmRoute route = group_route(kTilesAll, [&](const GemmTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); },
-                                                [&](const PpTile& t) { return 3 * tile_count(pr[0].M, pr[0].N, t); }, nk, pp_slice_count(pr[0].Kc, 0), pp,
-                                                std::max(1, device_cu_count()), forced_tile(), &cost);
+            const GemmRoute route = batch3_route(pr[0].M, pr[0].N, pr[0].Kc, pp, std::max(1, device_cu_count()), forced_tile());
             if (route.pp) {
                 Span span(name, st);
                 PpWork<3> w;
@@ -283,17 +280,13 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
     if constexpr (std::is_same<E, bf16_t>::value) {
         const bool same = pa.M == pb.M && pa.N == pb.N && pa.Kc == pb.Kc && pa.Kc % kMfmaBK == 0 && pa.Kc2 == 0 && pb.Kc2 == 0;
         if (same && !options().force_generic && mfma_problem_ok(pa) && mfma_problem_ok(pb)) {
-            const int nk = slice_count(pa.Kc, 0);
-            double cost = 0.0, single = 0.0;
             constexpr bool kGateUp = std::is_same<EpiA, EpiStore<float>>::value && std::is_same<EpiB, EpiStore<bf16_t>>::value;
             const bool pp = kGateUp && pp_takes(pa, ea) && pp_takes(pb, eb) && pa.A.ld == pb.A.ld && pa.B.ld == pb.B.ld &&
                             !(sk && sk->part && options().gemm_streamk);
-            const GemmRoute route = group_route(kTilesAll, [&](const GemmTile& t) { return 2 * tile_count(pa.M, pa.N, t); },
-                                                [&](const PpTile& t) { return 2 * tile_count(pa.M, pa.N, t); }, nk, pp_slice_count(pa.Kc, 0), pp,
-                                                std::max(1, device_cu_count()), forced_tile(), &cost);
-            (void)choose_tile<kTilesAll>([&](const GemmTile& t) { return tile_count(pa.M, pa.N, t); }, nk, &single);
+            const PairRoute pair = pair_route(pa.M, pa.N, pa.Kc, pp, std::max(1, device_cu_count()), forced_tile());
+            const GemmRoute route = pair.route;
             if constexpr (kGateUp) {
-                if (route.pp && cost < 2.0 * single) {
+                if (pair.together && route.pp) {
                     Span span(name, st);
                     PpWork<2> w;
                     w.pr[0] = pa; w.out[0] = pp_out(ea);
@@ -305,8 +298,7 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
                 }
             }
             const int best = route.tile;
-            // one launch when the two together cost less than apart, which they do unless both fill whole rounds of tiles
-            if (!route.pp && cost < 2.0 * single) {
+            if (pair.together && !route.pp) {
                 Span span(name, st);
                 const hipError_t e = with_tile<kTilesAll>(best, [&](auto c) {
                     constexpr GemmTile t = kGemmTile[decltype(c)::value];
@@ -338,32 +330,20 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
     if constexpr (std::is_same<E, bf16_t>::value) {
         bool ok = !options().force_generic && nprob <= NB;
         bool tail = false, padded = true;
-        int64_t total_m = 0, slices = 0;
+        int64_t total_m = 0;
+        int rows[NB], k[NB], k2[NB];
         for (int z = 0; z < nprob && ok; ++z) {
+            rows[z] = pr[z].M; k[z] = pr[z].Kc; k2[z] = pr[z].Kc2;
             if (pr[z].M == 0) continue;
             ok = mfma_problem_ok(pr[z]) && pr[z].N == pr[0].N && (pr[z].Kc2 == 0) == (pr[0].Kc2 == 0);
             tail = tail || gemm_has_tail(pr[z]);
             padded = padded && gemm_padded(pr[z]);
             total_m += pr[z].M;
-            slices += (int64_t)pr[z].M * slice_count(pr[z].Kc, pr[z].Kc2);
         }
         if (ok && total_m > 0 && !(BKM && tail && !padded)) {
-            const int nk = (int)(slices / total_m);
-            auto tiles_of = [&](const GemmTile& t) {
-                int64_t tiles = 0;
-                for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
-                return tiles;
-            };
-            int64_t slices64 = 0;
-            for (int z = 0; z < nprob; ++z) slices64 += (int64_t)pr[z].M * pp_slice_count(pr[z].Kc, pr[z].Kc2);
-            auto pp_tiles_of = [&](const PpTile& t) {
-                int64_t tiles = 0;
-                for (int z = 0; z < nprob; ++z) tiles += tile_count(pr[z].M, pr[0].N, t);
-                return tiles;
-            };
+            const int cus = std::max(1, device_cu_count());
             double cost = 0.0;
-            const GemmRoute route = group_route(kTilesGroup, tiles_of, pp_tiles_of, nk, (int)(slices64 / total_m), pp_group_takes(nprob, pr, epi),
-                                                std::max(1, device_cu_count()), forced_tile(), &cost);
+            const GemmRoute route = grouped_route(kTilesGroup, nprob, rows, pr[0].N, k, k2, pp_group_takes(nprob, pr, epi), cus, forced_tile(), &cost);
             if (route.pp) {
                 Span span(name, st);
                 PpWork<NB> w;
@@ -388,7 +368,7 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
                     return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 2, Epi, NB, 4, t.sets>(g, nprob, st);
                 });
             } else {
-                e = tail ? with_tile<kTilesBasic>(choose_tile<kTilesBasic>(tiles_of, nk), [&](auto c) {
+                e = tail ? with_tile<kTilesBasic>(grouped_route(kTilesBasic, nprob, rows, pr[0].N, k, k2, false, cus, forced_tile(), &cost).tile, [&](auto c) {
                                constexpr GemmTile t = kGemmTile[decltype(c)::value];
                                return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 1, Epi, NB, 4, t.sets>(g, nprob, st);
                            })
@@ -417,21 +397,15 @@ moc_status run_gate_up_grouped(const char* name, int nprob, const MfmaProblem* g
     *done = false;
     bool ok = nprob <= NB && pp_group_takes(nprob, gate, eg) && pp_group_takes(nprob, up, eu) && gate[0].A.ld == up[0].A.ld && gate[0].B.ld == up[0].B.ld;
     int64_t rows = 0;
-    for (int z = 0; z < nprob; ++z) {
+    int m[NB];
+    for (int z = 0; z < nprob && ok; ++z) {
+        m[z] = gate[z].M;
         ok = ok && gate[z].M == up[z].M && gate[z].N == up[z].N && gate[z].Kc == gate[0].Kc && up[z].Kc == gate[0].Kc && gate[z].Kc2 == 0 && up[z].Kc2 == 0;
         rows += gate[z].M;
     }
     if (!ok || rows == 0) return MOC_OK;
-    const int cus = std::max(1, device_cu_count());
-    auto tiles_of = [&](const auto& t) {
-        int64_t tiles = 0;
-        for (int z = 0; z < nprob; ++z) tiles += tile_count(gate[z].M, gate[0].N, t);
-        return tiles;
-    };
-    double single = 0.0, both = 0.0;
-    (void)group_route(kTilesGroup, tiles_of, tiles_of, slice_count(gate[0].Kc, 0), pp_slice_count(gate[0].Kc, 0), true, cus, forced_tile(), &single);
-    const int t = cheapest_pp_tile([&](const PpTile& p) { return 2 * tiles_of(p); }, pp_slice_count(gate[0].Kc, 0), cus, &both);
-    if (both >= 2.0 * single) return MOC_OK;
+    const int t = grouped_pair_tile(nprob, m, gate[0].N, gate[0].Kc, std::max(1, device_cu_count()), forced_tile());
+    if (t < 0) return MOC_OK;
     Span span(name, st);
     PpWork<2 * NB> w;
     for (int z = 0; z < nprob; ++z) {

@@ -203,6 +203,57 @@ GemmRoute group_route(unsigned mask, const TilesOf& tiles_of, const PpTilesOf& p
     return r;
 }
 
+// Two products of one shape, both operands k-contiguous: in one launch where the two together cost less than apart, which they do unless both
+// fill whole rounds of tiles.
+struct PairRoute {
+    bool together;
+    GemmRoute route;      // of the one launch
+};
+inline PairRoute pair_route(int M, int N, int Kc, bool pp, int cus, int forced = -1) {
+    double cost = 0.0, single = 0.0;
+    PairRoute r;
+    r.route = group_route(kTilesAll, [&](const GemmTile& t) { return 2 * tile_count(M, N, t); }, [&](const PpTile& t) { return 2 * tile_count(M, N, t); },
+                          slice_count(Kc, 0), pp_slice_count(Kc, 0), pp, cus, forced, &cost);
+    (void)cheapest_tile(kTilesAll, [&](const GemmTile& t) { return tile_count(M, N, t); }, slice_count(Kc, 0), cus, forced, &single);
+    r.together = cost < 2.0 * single;
+    return r;
+}
+// Three products of one shape in one launch.
+inline GemmRoute batch3_route(int M, int N, int Kc, bool pp, int cus, int forced = -1) {
+    double cost = 0.0;
+    return group_route(kTilesAll, [&](const GemmTile& t) { return 3 * tile_count(M, N, t); }, [&](const PpTile& t) { return 3 * tile_count(M, N, t); },
+                       slice_count(Kc, 0), pp_slice_count(Kc, 0), pp, cus, forced, &cost);
+}
+// Products of M[z] x N with contractions Kc[z], Kc2[z] (experts) in one launch; those without rows count for nothing.
+inline GemmRoute grouped_route(unsigned mask, int n, const int* M, int N, const int* Kc, const int* Kc2, bool pp, int cus, int forced, double* cost) {
+    int64_t rows = 0, slices = 0, slices64 = 0;
+    for (int z = 0; z < n; ++z) {
+        if (M[z] == 0) continue;
+        rows += M[z];
+        slices += (int64_t)M[z] * slice_count(Kc[z], Kc2[z]);
+        slices64 += (int64_t)M[z] * pp_slice_count(Kc[z], Kc2[z]);
+    }
+    if (rows == 0) return GemmRoute{};
+    const auto tiles_of = [&](const auto& t) {
+        int64_t tiles = 0;
+        for (int z = 0; z < n; ++z) tiles += tile_count(M[z], N, t);
+        return tiles;
+    };
+    return group_route(mask, tiles_of, tiles_of, (int)(slices / rows), (int)(slices64 / rows), pp, cus, forced, cost);
+}
+// Two products per expert with the same contraction in one launch on large tiles: the tile, or -1 where two launches are not dearer.
+inline int grouped_pair_tile(int n, const int* M, int N, int Kc, int cus, int forced = -1) {
+    const auto tiles_of = [&](const auto& t) {
+        int64_t tiles = 0;
+        for (int z = 0; z < n; ++z) tiles += tile_count(M[z], N, t);
+        return tiles;
+    };
+    double single = 0.0, both = 0.0;
+    (void)group_route(kTilesGroup, tiles_of, tiles_of, slice_count(Kc, 0), pp_slice_count(Kc, 0), true, cus, forced, &single);
+    const int t = cheapest_pp_tile([&](const PpTile& p) { return 2 * tiles_of(p); }, pp_slice_count(Kc, 0), cus, &both);
+    return both < 2.0 * single ? t : -1;
+}
+
 // The streamed gate of bf16 decode (decode_gate_stream_kernel), whose workgroups have ceil(F / workgroups) rows each, in blocks of 16.
 //
 // Non-temporal loads where the layers of a model do not stay in the 256 MB last-level cache until the next token: from 24 MB of W_gate on for

@@ -1,13 +1,12 @@
 """The size arithmetic of the matrix-core products (csrc/gemm_plan.h), compiled for the CPU with overflow checks: offsets at sizes at which
-a GPU test would need hundreds of gigabytes, and which kernel each case of the GPU tests takes, so that those tests reach what they
-say."""
+a GPU test would need hundreds of gigabytes, and which kernel each case of the fp32 GPU tests takes, so that those tests reach what they
+say (bf16: test_gemm_routes.py)."""
 import os
 import subprocess
 
 import pytest
 
 from tests.test_gpu_f32_gemm import CASES as F32_CASES
-from tests.test_gpu_gemm_tiles import CASES as BF16_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -16,7 +15,6 @@ PROGRAM = r"""
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
-#include <cstring>
 #include "gemm_plan.h"
 using namespace moc;
 #define EXPECT(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
@@ -34,31 +32,6 @@ static void offsets() {
     std::puts("ok");
 }
 
-static void say(const char* what, int tile, int shares = 0) {
-    std::printf("%s=%dx%d", what, kGemmTile[tile].bm, kGemmTile[tile].bn);
-    if (shares) std::printf("/%d", shares);
-    std::printf(" ");
-}
-// the products of one forward + backward, d a multiple of 32
-static void bf16(int T, int d, int F) {
-    double both, one;
-    const int nk = slice_count(d, 0);
-    const int pair = cheapest_tile(kTilesAll, [&](const GemmTile& t) { return 2 * tile_count(T, F, t); }, nk, kCus, -1, &both);
-    const int alone = cheapest_tile(kTilesAll, [&](const GemmTile& t) { return tile_count(T, F, t); }, nk, kCus, -1, &one);
-    if (both < 2.0 * one) say("gate_up", pair);
-    else say("gate", alone);
-    say("dz", alone);
-    say("dw", cheapest_tile(kTilesAll, [&](const GemmTile& t) { return 3 * tile_count(F, d, t); }, slice_count(T, 0), kCus));
-    const size_t ldf = (F + 63) / 64 * 64;
-    for (int two = 0; two < 2; ++two) {
-        const int n = slice_count(F, two ? F : 0);
-        double whole;
-        const int tile = cheapest_tile(kTilesAll, [&](const GemmTile& t) { return tile_count(T, d, t); }, n, kCus, -1, &whole);
-        const SharePlan p = plan_shares(T, d, n, 2, (size_t)T * ldf * (two ? 4 : 6), kCus, whole);
-        say(two ? "dx" : "down", p.tile >= 0 ? p.tile : tile, p.tile >= 0 ? p.shares : 0);
-    }
-    std::puts("");
-}
 static void f32(int T, int d, int F) {
     static const char* const names[4] = {"64x64", "32x32", "32x32s", "16x32s"};
     auto tile = [&](int M, int N, int batch, int64_t k, bool ascending) { return names[(int)f32_tile(M, N, batch, k, ascending, kCus)]; };
@@ -67,7 +40,7 @@ static void f32(int T, int d, int F) {
 }
 int main(int argc, char** argv) {
     if (argc == 1) offsets();
-    else if (argc == 5) (std::strcmp(argv[1], "f32") ? bf16 : f32)(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
+    else if (argc == 4) f32(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
 
@@ -86,19 +59,13 @@ def test_row_offsets_of_long_contractions(plan):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("dtype,cases", [("bf16", BF16_CASES), ("f32", F32_CASES)])
-def test_cases_take_the_kernels_they_name(plan, dtype, cases):
-    for T, d, F, _, want in cases:
-        got = plan(dtype, T, d, F).stdout.split()
+def test_cases_take_the_kernels_they_name(plan):
+    for T, d, F, _, want in F32_CASES:
+        got = plan(T, d, F).stdout.split()
         assert set(want.split()) <= set(got), (T, d, F, want, got)
 
 
 def test_cases_reach_every_tile():
-    named = " ".join(c[4] for c in BF16_CASES).split()
-    shapes = ("256x256", "256x192", "192x256", "256x128", "128x192", "192x128", "128x128", "64x128")
-    for product, wanted in (("gate_up", shapes), ("dw", shapes), ("down", ("192x128/4", "128x128/6", "64x128/4")),
-                            ("dx", ("192x128/4", "128x128/7", "64x128/8"))):
-        assert {"%s=%s" % (product, s) for s in wanted} <= set(named)
     named = " ".join(c[4] for c in F32_CASES).split()
     for product, wanted in (("gate_up", ("64x64", "32x32")), ("down", ("64x64", "32x32", "32x32s", "16x32s")),
                             ("dz", ("64x64", "32x32", "16x32s")), ("dw", ("64x64", "32x32", "16x32s")), ("dx", ("64x64", "32x32", "32x32s", "16x32s"))):

@@ -1,11 +1,14 @@
-"""Which kernel every bf16 product takes (csrc/gemm_plan.h: gemm_route, group_route), compiled for the CPU: the cases of
-test_gpu_large_tiles.py reach the tiles they name, and the routes keep to what the launchers can run."""
+"""Which kernel every bf16 product takes, by the functions of csrc/gemm_plan.h that the launchers call, compiled for the CPU: the cases of
+test_gpu_large_tiles.py and test_gpu_gemm_tiles.py reach the tiles they name, and the routes keep to what the launchers can run."""
 import os
+import re
 import subprocess
 
 import pytest
 
-from tests.test_gpu_large_tiles import CASES
+from tests.test_gpu_experts import MIXTRAL_180M
+from tests.test_gpu_gemm_tiles import CASES as TILE_CASES
+from tests.test_gpu_large_tiles import CASES, EXPERT_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -13,6 +16,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 #include "gemm_plan.h"
 using namespace moc;
 #define EXPECT(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
@@ -24,24 +28,56 @@ static void say(const char* what, const GemmRoute& r) {
     if (r.shares > 1) std::printf("/%d", r.shares);
     std::printf(" ");
 }
-static GemmRoute several(int n, int M, int N, int K, bool pp, double* cost) {
-    return group_route(kTilesAll, [&](const GemmTile& t) { return n * tile_count(M, N, t); }, [&](const PpTile& t) { return n * tile_count(M, N, t); },
-                       slice_count(K, 0), pp_slice_count(K, 0), pp, kCus, -1, cost);
-}
-// the products of one forward + backward, d a multiple of 32; x W^T products go to the large tiles for multiples of 64 only
+static int ldf(int F) { return (F + kColPad - 1) / kColPad * kColPad; }
+static int fs(int F) { return (F + 7) / 8 * 8; }
+// the operands of x W^T products to [T, F], of products over the channels to [T, d], and of weight gradients
+static PpSizes to_channels(int T, int d, int F, int elem) { return PpSizes{T, F, d, 0, d, d, false, false, false, fs(F), ldf(F), 0, elem}; }
+static PpSizes to_model(int T, int d, int F, int F2) { return PpSizes{T, d, F, F2, ldf(F), d, false, true, true, d, d, 0, 2}; }
+static PpSizes to_weights(int T, int d, int F) { return PpSizes{F, d, T, 0, ldf(F), d, true, true, true, d, d, 0, 2}; }
+// the products of one forward + backward, d a multiple of 32
 static void products(int T, int d, int F) {
-    double cost, single;
-    const bool kc = d % 64 == 0;
-    const GemmRoute both = several(2, T, F, d, kc, &cost);
-    cheapest_tile(kTilesAll, [&](const GemmTile& t) { return tile_count(T, F, t); }, slice_count(d, 0), kCus, -1, &single);
-    const GemmRoute one = gemm_route(kTilesAll, T, F, d, 0, 2, kc, 0, kCus);
-    if (cost < 2.0 * single) say("gate_up", both);
-    else say("gate", one);
-    say("dz", one);
-    say("dw", several(3, F, d, T, true, &cost));
-    const size_t ldf = (F + 63) / 64 * 64;
-    say("down", gemm_route(kTilesAll, T, d, F, 0, 2, true, T * ldf * 6, kCus));
-    say("dx", gemm_route(kTilesAll, T, d, F, F, 2, true, T * ldf * 4, kCus));
+    const bool kc = pp_sizes_ok(to_channels(T, d, F, 4)) && pp_sizes_ok(to_channels(T, d, F, 2));
+    const PairRoute pair = pair_route(T, F, d, kc, kCus);
+    if (pair.together) say("gate_up", pair.route);
+    else say("gate", gemm_route(kTilesAll, T, F, d, 0, 2, kc, 0, kCus));
+    say("dz", gemm_route(kTilesAll, T, F, d, 0, 2, kc, 0, kCus));
+    say("dw", batch3_route(F, d, T, pp_sizes_ok(to_weights(T, d, F)), kCus));
+    say("down", gemm_route(kTilesAll, T, d, F, 0, 2, pp_sizes_ok(to_model(T, d, F, 0)), (size_t)T * ldf(F) * 6, kCus));
+    say("dx", gemm_route(kTilesAll, T, d, F, F, 2, pp_sizes_ok(to_model(T, d, F, F)), (size_t)T * ldf(F) * 4, kCus));
+    std::puts("");
+}
+// of experts with `counts` rows
+static void experts(int d, int F, int n, const int* counts) {
+    const std::vector<int> rows(counts, counts + n), ks(n, d), kf(n, F), no(n, 0);
+    bool channels = true, model = true, two = true, weights = true;
+    std::vector<int> wm, wk, wno;
+    for (int c : rows) {
+        if (c == 0) continue;
+        channels = channels && pp_sizes_ok(to_channels(c, d, F, 4)) && pp_sizes_ok(to_channels(c, d, F, 2));
+        model = model && pp_sizes_ok(to_model(c, d, F, 0));
+        two = two && pp_sizes_ok(to_model(c, d, F, F));
+        weights = weights && pp_sizes_ok(to_weights(c, d, F));
+        for (int k = 0; k < 3; ++k) { wm.push_back(F); wk.push_back(c); wno.push_back(0); }
+    }
+    double cost;
+    const int t = channels ? grouped_pair_tile(n, rows.data(), F, d, kCus) : -1;
+    if (t >= 0) say("gate_up", GemmRoute{true, t, 1});
+    else say("gate", grouped_route(kTilesGroup, n, rows.data(), F, ks.data(), no.data(), channels, kCus, -1, &cost));
+    const auto rounds = [&](const GemmRoute& r, int m, const int* M, int N) {      // rounds of the busiest XCD's workgroups
+        if (!r.pp) return;
+        int64_t tiles = 0;
+        for (int z = 0; z < m; ++z) tiles += tile_count(M[z], N, kPpTile[r.tile]);
+        std::printf("x%d ", (int)((tiles + kCus - 1) / kCus));
+    };
+    const GemmRoute dz = grouped_route(kTilesGroup, n, rows.data(), F, ks.data(), no.data(), channels, kCus, -1, &cost);
+    say("dz", dz);
+    const GemmRoute dw = grouped_route(kTilesGroup, (int)wm.size(), wm.data(), d, wk.data(), wno.data(), weights, kCus, -1, &cost);
+    say("dw", dw);
+    rounds(dw, (int)wm.size(), wm.data(), d);
+    const GemmRoute down = grouped_route(kTilesGroup, n, rows.data(), d, kf.data(), no.data(), model, kCus, -1, &cost);
+    say("down", down);
+    rounds(down, n, rows.data(), d);
+    say("dx", grouped_route(kTilesGroup, n, rows.data(), d, kf.data(), kf.data(), two, kCus, -1, &cost));
     std::puts("");
 }
 static void routes() {
@@ -155,7 +191,11 @@ static void gate() {
 int main(int argc, char** argv) {
     if (argc == 1) routes();
     else if (argc == 2) (std::strcmp(argv[1], "gate") ? sizes : gate)();
-    else if (argc == 4) products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
+    else if (!std::strcmp(argv[1], "experts")) {
+        std::vector<int> counts;
+        for (int i = 4; i < argc; ++i) counts.push_back(std::atoi(argv[i]));
+        experts(std::atoi(argv[2]), std::atoi(argv[3]), (int)counts.size(), counts.data());
+    } else products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
 
@@ -187,9 +227,19 @@ def test_decodes_that_take_the_streamed_gate(plan):
 
 
 def test_cases_take_the_kernels_they_name(plan):
-    for T, d, F, _, want in CASES:
+    for T, d, F, _, want in CASES + TILE_CASES:
         got = plan(T, d, F).stdout.split()
         assert set(want.split()) <= set(got), (T, d, F, want, got)
+
+
+def test_expert_cases_take_the_kernels_they_name(plan):
+    # (the Mixtral shape: weight gradients of 24 problems in two rounds)
+    for counts, d, F, _, want in EXPERT_CASES + [(MIXTRAL_180M, 512, 1376, 256, "gate_up=pp256x256 dz=pp256x128 dw=pp192x256 x2")]:
+        got = plan("experts", d, F, *counts).stdout
+        at = 0
+        for word in want.split():                        # (in order: xN belongs to the product before it)
+            at = got.find(word + " ", at)
+            assert at >= 0, (counts, d, F, want, got)
 
 
 def test_cases_reach_every_large_tile():
@@ -200,3 +250,17 @@ def test_cases_reach_every_large_tile():
     for product in ("dz", "down", "dx"):
         assert any(n.startswith(product + "=pp") and "/" not in n for n in named), product
     assert any(n.startswith("dx=pp") and "/" in n for n in named)
+    experts = " ".join(c[4] for c in EXPERT_CASES)
+    for product in ("gate_up", "dz", "dw", "down", "dx"):
+        assert product + "=pp" in experts, product
+    assert re.search(r"down=pp\S+ x2", experts)
+
+
+def test_cases_reach_every_basic_tile():
+    """Every tile of gemm_mfma.h by a product that takes it without MOC_GEMM_TILE."""
+    named = set(" ".join(c[4] for c in TILE_CASES).split())
+    small = ("128x192", "192x128", "128x128", "64x128")
+    for product, wanted in (("gate_up", ("256x256", "256x192", "192x256", "256x128") + small), ("gate", ("256x256", "256x192", "192x256")),
+                            ("dz", ("256x128", "128x192", "192x128", "64x128")), ("dw", small),
+                            ("down", ("192x128/4", "128x128/6", "64x128/4")), ("dx", ("192x128/4", "128x128/7", "64x128/8"))):
+        assert {"%s=%s" % (product, s) for s in wanted} <= named, product

@@ -119,9 +119,12 @@ def test_experts_small_shapes(counts, d, F, K, dtype):
     run_experts_case("small", 600, counts, d, F, K, dtype)
 
 
+# 8 experts, 2 per token: 2048 tokens -> 4096 routed rows with an uneven split
+MIXTRAL_180M = (700, 420, 512, 384, 650, 330, 600, 500)
+
+
 def test_experts_mixtral_180m_shape():
-    # 8 experts, 2 per token: 2048 tokens -> 4096 routed rows with an uneven split
-    counts = (700, 420, 512, 384, 650, 330, 600, 500)
+    counts = MIXTRAL_180M
     run_experts_case("mixtral-180M", 610, counts, 512, 1376, 256, "bf16")
 
 

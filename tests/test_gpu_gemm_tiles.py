@@ -14,27 +14,36 @@ from tests.test_gpu_parity import run_fwd_bwd_case
 pytestmark = pytest.mark.gpu
 
 
-# T, d, F, K, and kernels of interest that the launchers take (product=tile or product=tile/shares; test_gemm_plan.py checks them)
+# T, d, F, K, and kernels of interest that the launchers take (product=tile or product=tile/shares; test_gemm_routes.py checks them)
 CASES = [
     (17, 512, 1365, 170, "gate_up=64x128 dx=64x128/2"),                # fewer tokens than a k-slice; shares of a contraction with a tail
     (33, 1024, 2736, 342, "gate_up=64x128 down=64x128/4"),             # one token past a slice
     (129, 256, 5461, 682, "dw=192x128 down=64x128/8 dx=64x128/8"),     # one row past a tile; 171 slices in shares of 21 and 22
-    (1999, 768, 2048, 409, "gate_up=128x128 dw=128x192 down=64x128"),  # token rows padded by 17
+    (1999, 768, 2048, 409, "dw=128x192 down=64x128"),  # token rows padded by 17
     (17, 64, 1030, 128, "gate_up=64x128 dw=64x128 down=64x128/4 dx=64x128/8"),
     (65, 64, 8200, 1025, "gate_up=128x128 dw=128x128"),
     (97, 544, 2736, 342, "dw=128x192"),
-    (33, 768, 5461, 682, "dw=256x256"),
+    (33, 768, 5461, 682, "down=64x128/8 dx=64x128/7"),
     (2100, 128, 1365, 170, "gate_up=192x128"),
     (4100, 128, 520, 65, "gate_up=128x192"),
-    (2600, 64, 2736, 342, "gate_up=256x256"),
+    (2600, 64, 2736, 342, "dz=64x128 down=64x128/6"),
     (4100, 64, 2736, 342, "down=128x128/6 dx=128x128/7"),
-    (900, 512, 5461, 682, "dw=192x256"),
-    (1537, 288, 5461, 682, "dw=256x128"),
-    (1100, 288, 8200, 1025, "dw=256x192"),
-    (513, 768, 8200, 1025, "gate_up=192x256"),
-    (400, 1024, 8200, 1025, "gate_up=256x192"),
-    (700, 1536, 4100, 512, "gate_up=256x128"),
-    (1300, 1024, 8200, 1025, "gate=192x256 dz=192x256 down=192x128/4 dx=192x128/4"),
+    (900, 512, 5461, 682, "dz=192x128 dx=128x128/7"),
+    (1537, 288, 5461, 682, "gate_up=128x128 down=128x128/6"),
+    (1100, 288, 8200, 1025, "down=128x128/7 dx=128x128/8"),
+    (513, 768, 8200, 1025, "dz=192x128"),
+    (400, 1024, 8200, 1025, "dz=128x192"),
+    (700, 1536, 4100, 512, "down=128x128/3 dx=128x128/2"),
+    (1300, 1024, 8200, 1025, "down=192x128/4 dx=192x128/4"),
+    # d % 64 == 32, which the large tiles of gemm_pingpong.h leave to these
+    (700, 96, 8200, 1025, "gate_up=256x256"),
+    (400, 1056, 8200, 1025, "gate_up=256x192"),
+    (300, 992, 11008, 1376, "gate_up=192x256"),
+    (1200, 1056, 2736, 342, "gate_up=256x128"),
+    (900, 800, 11008, 1376, "gate=192x256"),
+    (2200, 544, 5461, 682, "gate=256x256"),
+    (1200, 1056, 8200, 1025, "gate=256x192"),
+    (1700, 992, 4100, 512, "dz=256x128"),
 ]
 
 

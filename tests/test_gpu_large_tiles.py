@@ -42,10 +42,19 @@ def test_large_tiles(T, d, F, K, kernels):
     run_fwd_bwd_case("large tiles " + kernels, 97, T, d, F, K, "bf16")
 
 
-@pytest.mark.parametrize("counts,d,F,K", [([700, 0, 1, 513, 300, 64, 257, 900], 128, 2736, 342), ([2000, 33], 192, 1030, 128)])
-def test_experts_on_large_tiles(counts, d, F, K):
-    """Gate and up projection of all experts in one launch; row counts one short of and past a tile, experts with no and one row."""
-    run_experts_case("large tiles", 970, counts, d, F, K, "bf16")
+# rows of the experts, d, F, K, kernels (a large tile of dw and down with its rounds of the workgroups: xN)
+EXPERT_CASES = [
+    ([700, 0, 1, 513, 300, 64, 257, 900], 128, 2736, 342, "gate_up=pp192x256 dz=128x128 dw=pp256x128"),      # one short of and past a tile, no and one row
+    ([2000, 33], 192, 1030, 128, "gate_up=pp256x128"),
+    # contractions over the channels, ragged (330 % 64 = 10), in two rounds, the second of which goes backwards
+    ([2600, 2100, 0, 9, 4300, 2250, 1900, 3000], 1024, 330, 41, "gate_up=pp256x128 dz=pp256x128 dw=pp128x256 x1 down=pp192x256 x2 dx=pp192x256"),
+]
+
+
+@pytest.mark.parametrize("counts,d,F,K,kernels", EXPERT_CASES)
+def test_experts_on_large_tiles(counts, d, F, K, kernels):
+    """All products of the experts, as far as `kernels` says so: gate and up in one launch, down and dX (two operand pairs) with unequal row counts."""
+    run_experts_case("large tiles " + kernels, 970, counts, d, F, K, "bf16")
 
 
 @pytest.mark.parametrize("T,d,F,K", [(513, 64, 2731, 341), (1025, 128, 5461, 682), (2047, 1536, 200, 25)])
