@@ -143,7 +143,7 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
                 }
             }
             constexpr bool kStore = std::is_same<Epi, EpiStore<bf16_t>>::value || std::is_same<Epi, EpiStore<float>>::value;
-            constexpr unsigned kMask = kStore ? kTilesAll : kTilesBasic;
+            constexpr unsigned kMask = !kStore ? kTilesBasic : BKM ? kTilesKm : kTilesAll;
             constexpr bool kShares = !AKM && BKM && std::is_same<Epi, EpiStore<E>>::value;
             const GemmRoute route = gemm_route(kMask, pr.M, pr.N, pr.Kc, pr.Kc2, sizeof(E), pp_takes(pr, epi), kShares ? share_bytes(pr, epi, scratch) : 0,
                                                std::max(1, device_cu_count()), forced_tile());
@@ -245,7 +245,7 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
                 }
             }
             auto launch = [&](auto mode) {
-                return with_tile<kTilesAll>(best, [&](auto c) {
+                return with_tile<kTilesKm>(best, [&](auto c) {
                     constexpr int C = decltype(c)::value;
                     constexpr GemmTile t = kGemmTile[C];
                     return launch_gemm_bf16_mfma_batch<t.bm, t.bn, true, true, decltype(mode)::value, EpiStore<E>, 3, 4, t.sets>(b, st, tile_workgroups<C>());
@@ -342,8 +342,9 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
         }
         if (ok && total_m > 0 && !(BKM && tail && !padded)) {
             const int cus = std::max(1, device_cu_count());
+            constexpr unsigned kMask = BKM ? kTilesKmGroup : kTilesGroup;
             double cost = 0.0;
-            const GemmRoute route = grouped_route(kTilesGroup, nprob, rows, pr[0].N, k, k2, pp_group_takes(nprob, pr, epi), cus, forced_tile(), &cost);
+            const GemmRoute route = grouped_route(kMask, nprob, rows, pr[0].N, k, k2, pp_group_takes(nprob, pr, epi), cus, forced_tile(), &cost);
             if (route.pp) {
                 Span span(name, st);
                 PpWork<NB> w;
@@ -363,7 +364,7 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
             hipError_t e;
             if constexpr (BKM) {
                 // (the padded mode also serves contractions without a tail: one set of kernels)
-                e = with_tile<kTilesGroup>(best, [&](auto c) {
+                e = with_tile<kMask>(best, [&](auto c) {
                     constexpr GemmTile t = kGemmTile[decltype(c)::value];
                     return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 2, Epi, NB, 4, t.sets>(g, nprob, st);
                 });
@@ -372,7 +373,7 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
                                constexpr GemmTile t = kGemmTile[decltype(c)::value];
                                return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 1, Epi, NB, 4, t.sets>(g, nprob, st);
                            })
-                         : with_tile<kTilesGroup>(best, [&](auto c) {
+                         : with_tile<kMask>(best, [&](auto c) {
                                constexpr GemmTile t = kGemmTile[decltype(c)::value];
                                return launch_gemm_bf16_mfma_group<t.bm, t.bn, AKM, BKM, 0, Epi, NB, 4, t.sets>(g, nprob, st);
                            });

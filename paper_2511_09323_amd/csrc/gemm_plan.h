@@ -36,6 +36,9 @@ constexpr GemmTile kGemmTile[kGemmTiles] = {
     {128, 128, 3, 3, 5.7, 0.222, 0.275, 0.275}, {64, 128, 5, 4, 4.7, 0.216, 0.225, 0.200}};
 // every shape; 256x256, 256x192, 128x128; and 256x128, 64x128; 192x128, 128x128, 64x128
 constexpr unsigned kTilesAll = 0xFF, kTilesBasic = 0x43, kTilesGroup = 0xCB, kTilesShares = 0xE0;
+// With a k-major B, the large tiles of gemm_pingpong.h take every product that 192x256 or 256x128 would be chosen for but those of operands
+// past 4 GiB, which 256x256 and 256x192 serve as well (and which MOC_GEMM_TILE names): not built.
+constexpr unsigned kTilesKm = kTilesAll & ~0x0Cu, kTilesKmGroup = kTilesGroup & ~0x0Cu;
 constexpr int kTile128 = 6;
 
 inline int64_t tile_count(int M, int N, const GemmTile& t) {
@@ -218,10 +221,10 @@ inline PairRoute pair_route(int M, int N, int Kc, bool pp, int cus, int forced =
     r.together = cost < 2.0 * single;
     return r;
 }
-// Three products of one shape in one launch.
+// Three products of one shape, k-major, in one launch.
 inline GemmRoute batch3_route(int M, int N, int Kc, bool pp, int cus, int forced = -1) {
     double cost = 0.0;
-    return group_route(kTilesAll, [&](const GemmTile& t) { return 3 * tile_count(M, N, t); }, [&](const PpTile& t) { return 3 * tile_count(M, N, t); },
+    return group_route(kTilesKm, [&](const GemmTile& t) { return 3 * tile_count(M, N, t); }, [&](const PpTile& t) { return 3 * tile_count(M, N, t); },
                        slice_count(Kc, 0), pp_slice_count(Kc, 0), pp, cus, forced, &cost);
 }
 // Products of M[z] x N with contractions Kc[z], Kc2[z] (experts) in one launch; those without rows count for nothing.

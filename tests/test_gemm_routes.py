@@ -42,8 +42,8 @@ static void products(int T, int d, int F) {
     else say("gate", gemm_route(kTilesAll, T, F, d, 0, 2, kc, 0, kCus));
     say("dz", gemm_route(kTilesAll, T, F, d, 0, 2, kc, 0, kCus));
     say("dw", batch3_route(F, d, T, pp_sizes_ok(to_weights(T, d, F)), kCus));
-    say("down", gemm_route(kTilesAll, T, d, F, 0, 2, pp_sizes_ok(to_model(T, d, F, 0)), (size_t)T * ldf(F) * 6, kCus));
-    say("dx", gemm_route(kTilesAll, T, d, F, F, 2, pp_sizes_ok(to_model(T, d, F, F)), (size_t)T * ldf(F) * 4, kCus));
+    say("down", gemm_route(kTilesKm, T, d, F, 0, 2, pp_sizes_ok(to_model(T, d, F, 0)), (size_t)T * ldf(F) * 6, kCus));
+    say("dx", gemm_route(kTilesKm, T, d, F, F, 2, pp_sizes_ok(to_model(T, d, F, F)), (size_t)T * ldf(F) * 4, kCus));
     std::puts("");
 }
 // of experts with `counts` rows
@@ -71,13 +71,13 @@ static void experts(int d, int F, int n, const int* counts) {
     };
     const GemmRoute dz = grouped_route(kTilesGroup, n, rows.data(), F, ks.data(), no.data(), channels, kCus, -1, &cost);
     say("dz", dz);
-    const GemmRoute dw = grouped_route(kTilesGroup, (int)wm.size(), wm.data(), d, wk.data(), wno.data(), weights, kCus, -1, &cost);
+    const GemmRoute dw = grouped_route(kTilesKmGroup, (int)wm.size(), wm.data(), d, wk.data(), wno.data(), weights, kCus, -1, &cost);
     say("dw", dw);
     rounds(dw, (int)wm.size(), wm.data(), d);
-    const GemmRoute down = grouped_route(kTilesGroup, n, rows.data(), d, kf.data(), no.data(), model, kCus, -1, &cost);
+    const GemmRoute down = grouped_route(kTilesKmGroup, n, rows.data(), d, kf.data(), no.data(), model, kCus, -1, &cost);
     say("down", down);
     rounds(down, n, rows.data(), d);
-    say("dx", grouped_route(kTilesGroup, n, rows.data(), d, kf.data(), kf.data(), two, kCus, -1, &cost));
+    say("dx", grouped_route(kTilesKmGroup, n, rows.data(), d, kf.data(), kf.data(), two, kCus, -1, &cost));
     std::puts("");
 }
 static void routes() {
@@ -87,6 +87,10 @@ static void routes() {
                 for (size_t scratch : {(size_t)0, (size_t)1 << 20, (size_t)1 << 28}) {
                     const GemmRoute r = gemm_route(kTilesAll, M, N, K, 0, 2, true, scratch, kCus), plain = gemm_route(kTilesAll, M, N, K, 0, 2, false, 0, kCus);
                     EXPECT(r.tile >= 0 && r.tile < (r.pp ? kPpTiles : kGemmTiles));
+                    // where both may run, the large tiles leave no product to the same shapes of gemm_mfma.h: with a k-major B two of them are not built
+                    EXPECT(r.pp || r.tile > 3);
+                    const GemmRoute km = gemm_route(kTilesKm, M, N, K, 0, 2, true, scratch, kCus);
+                    EXPECT(km.pp == r.pp && km.tile == r.tile && km.shares == r.shares);
                     EXPECT(!plain.pp && plain.shares == 1);
                     EXPECT(r.shares == 1 || (size_t)r.shares * M * N * 4 <= scratch);
                     // no share without a slice
