@@ -49,6 +49,10 @@ def parse():
     return ap.parse_args()
 
 
+# kernels of the headline step whose HBM traffic the committed counter summary holds, by the library's name of the launch
+TRAFFIC_KEYS = {"gemm_gate_up": "gemm_bf16_pp<256,256,KC,KC>, gate and up", "gemm_dw3": "gemm_bf16_pp<192,256,KM,KM>, three products"}
+
+
 def source_hash():
     from paper_2511_09323_amd.build import source_hash as h
     return h()
@@ -193,15 +197,12 @@ def main():
     # FLOP/s (2 d K per token and product for the gathered contractions); the executed (dense-tile)
     # rate stands beside them.  HBM traffic per launch comes from the committed rocprofv3 counter
     # summary, and only when that summary was taken on the sources this library was built from.
-    traffic_keys = {"gemm_gate": "gemm_bf16_mfma<256,256,KC,KC,tail0,EpiStore<float>>",
-                    "gemm_dw3": "gemm_bf16_mfma_batch3<192,256,KM,KM,tail0,EpiStore<bf16>>"}
-
     def roofline_entry(row):
         name = row["kernel"]
         ex, al = flops[name]
         traffic, note = (None, "not measured for this kernel")
-        if args.workload == "cfg2" and name in traffic_keys:
-            traffic, note = committed_traffic(traffic_keys[name], moc.version())
+        if args.workload == "cfg2" and name in TRAFFIC_KEYS:
+            traffic, note = committed_traffic(TRAFFIC_KEYS[name], moc.version())
         return {"kernel": name, "bound": "mfma", "achieved": row["algorithmic_tflops"], "peak": PEAK_BF16_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(row["algorithmic_tflops"] / PEAK_BF16_TFLOPS, 4),
                 "achieved_executed": row["executed_tflops"], "frac_executed": row["frac_executed"],

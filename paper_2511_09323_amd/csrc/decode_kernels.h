@@ -233,8 +233,9 @@ __global__ __launch_bounds__(256) void decode_gate_group_kernel(const E* __restr
 //    A wavefront reads only what it loaded, so nothing but its own counter orders the two;
 //  - rows past the workgroup's last, steps past d and tokens from B up are zeros of the buffer's range check, not branches.
 // The partial tiles meet in LDS, one barrier per 16 rows; the wavefronts take turns in adding them.
-// 4096 x 11008 (90 MB), kernel alone: 16 tokens 22.0 -> 17.8 us (5.1 TB/s), 2:8 with 4 tokens 25.6 -> 17.5; before, one workgroup per 48
-// (16) rows staged x in LDS and read W_gate in MFMA order.  The same walk with loads to registers, 64 bytes of a row each: 20.8.
+// 4096 x 11008 (90 MB), averages of a profile with eight sets of weights in turn: 16 tokens 22.3 -> 19.2 us (4.8 TB/s), with the selection of a:8
+// and four tokens 25.8, 16 tokens 23.2 -> 19.9 over both; before, one workgroup per 48 (16) rows staged x in LDS and read W_gate in MFMA
+// order.  The same walk with loads to registers, 64 bytes of a row each, against this, the least of the launches: 20.8 / 17.8.
 // GB = 0 writes the gate rows g[B, ldg]; GB = 4, 8, 16 selects the a largest of every GB channels instead (MoC_{a:b}; a workgroup's
 // rows are a whole number of groups) and writes idx / gsel [B, K] only.  NT: see gate_stream_nontemporal.  Needs d % 64 == 0, d <= 512 NS,
 // 16-byte aligned operands.

@@ -4,9 +4,11 @@
 //
 // Operands as in gemm_mfma.h: k-contiguous (KC) or k-major (KM), in the layout they have in memory.
 //
-// Bound: the matrix cores, at the clock the power limit leaves them.  What the kernel of gemm_mfma.h loses against that is the
-// way of the operands: one wavefront per SIMD has to fit the global loads, the writes to LDS and the fragment reads between
-// its own MFMAs.  Here
+// Bound: the matrix cores, as far as the hand-over and the rounds of tiles let them work, at the clock the power limit leaves (2.0 to
+// 2.15 GHz).  Counted (SQ_VALU_MFMA_BUSY_CYCLES of all SIMD cycles): 0.70 for one full round of 256 tiles, 8192 x 2048 x 5461 and 2 * 5461;
+// 0.61 and 0.59 for 2.75 and 5.5 rounds, 8192 x 5461 x 2048 to bf16 and as gate + up; 0.54 for three products 5461 x 2048 x 8192 on 192 x 256
+// tiles.  What the kernel of gemm_mfma.h (0.47 to 0.61) loses against that is the way of the operands: one wavefront per SIMD has to fit the
+// global loads, the writes to LDS and the fragment reads between its own MFMAs.  Here
 //  - operands go from memory to LDS without passing through registers (buffer_load ... lds, 1 KB per instruction), so there are no
 //    staging registers and no LDS writes to issue; what lies past the end of an operand is delivered as zeros by the buffer's range
 //    check, so ragged rows, columns and contraction ends need no code;
@@ -71,7 +73,8 @@ __device__ __forceinline__ void pp_barrier() {
 //   KC: [row][64 k], 128 bytes a row, the position of a 16-byte chunk XORed with bits 1..3 of the row;
 //   KM: [k][HR rows] as in memory, the position of a 64-byte piece XORed with the k row and of a 32-byte piece with bit 3 of the k row
 //       (96 rows: 192 bytes a k row, which spreads the 64-byte pieces by itself).
-// Both so that the lanes that an LDS read serves together meet different banks (counted: no conflicts).
+// Both so that the lanes that an LDS read serves together meet different banks.  (Counted: 2 to 15 % of the LDS cycles are conflicts, in inverse
+// proportion to the number of slices: they are the epilogue's.)
 template <bool KM, int HR, int TR> struct PpHalf {
     static constexpr int kPitch = HR * 2;                 // KM
     static constexpr int kAddrs = KM ? TR : 2;

@@ -24,7 +24,8 @@ constexpr int kMfmaBK = 32;      // k-slice of the bf16 kernel
 // tiles (launch, first loads, epilogue), `lo` .. `hi` per 32-k slice with few .. all compute units busy (the chip is
 // power-limited with the large tiles, so a full round runs slower), `co` per slice and workgroup where several
 // workgroups share a compute unit (`resident` of them; 1 = one persistent workgroup per compute unit).
-// Measured with 64 .. 768 tiles at contractions of 768, 2048 and 5472; the three operand layouts agree within 5 %.
+// Measured with 64 .. 768 tiles at contractions of 768, 2048 and 5472; the three operand layouts agree within 5 %.  Longer contractions are
+// underestimated: 2047 x 2048 over 2 * 5464 on 128 x 128 tiles takes 126 us, the formula says 100 (over 5464: 68, 53).
 struct GemmTile {
     int bm, bn, sets, resident;      // sets: k-slices in flight in registers
     double o, lo, hi, co;
