@@ -20,8 +20,6 @@ def normal(*shape):
 
 def kernels_of(call):
     """Names of the library's kernels that `call` launches, in their order."""
-    call()
-    torch.cuda.synchronize()
     with profile(activities=[ProfilerActivity.CUDA]) as p:
         call()
         torch.cuda.synchronize()
@@ -29,9 +27,14 @@ def kernels_of(call):
     return [e.name for e in sorted(events, key=lambda e: e.time_range.start)]
 
 
-def products(names):
+def products_of(call):
     """product=tile of the products of one forward and backward; shares end in /."""
-    tiles = []
+    call()
+    torch.cuda.synchronize()
+    names = kernels_of(call)
+    if not any("bwd_expand" in n for n in names):      # the profiler's first use in a process may come too late for it
+        names = kernels_of(call)
+    tiles, before = [], None
     for n in names:
         m = re.search(r"gemm_bf16_(pp|mfma)(?:_[a-z]+)?_kernel<(\d+), (\d+),", n)
         if m:
@@ -57,7 +60,7 @@ def test_layers_run_the_kernels_they_name(T, d, F, K, kernels):
         _, idx, gv, uv = moc.moc_ffn_fwd(x, *w, K)
         moc.moc_ffn_bwd(x, *w, idx, gv, uv, dy)
 
-    got = products(kernels_of(call))
+    got = products_of(call)
     assert wanted(kernels) <= set(got), got
 
 
@@ -71,5 +74,5 @@ def test_experts_run_the_kernels_they_name(counts, d, F, K, kernels):
         _, idx, gv, uv = moc.moc_ffn_fwd_experts(x, off, *w, K)
         moc.moc_ffn_bwd_experts(x, off, *w, idx, gv, uv, dy)
 
-    got = products(kernels_of(call))
+    got = products_of(call)
     assert wanted(kernels) <= set(got), got
