@@ -219,7 +219,9 @@ struct DecodeWs {
     // channel [F, 1 + token slots], partial outputs of its down projection, its flag words
     uint64_t *g2, *zt;
     float* part2;
+    float *sd, *ud;      // both projections as streams: SiLU(g) or kNotSelected and u of every channel, [T, ldF] each (in the place of g2)
     void* sync;
+    uint32_t* arrived;   // counters of the down projection's slices, cleared in the launch before it (in the place of sync)
     size_t bytes;
     DecodeWs(void* ws, const Dims& D) {
         Carver c(ws);
@@ -233,9 +235,12 @@ struct DecodeWs {
         part = c.take<float>((size_t)shares * D.T * D.d);
         const int slots = D.T == 1 ? 1 : (D.T <= 4 ? 4 : 16);
         g2 = c.take<uint64_t>((size_t)D.T * D.ldF);
+        sd = reinterpret_cast<float*>(g2);
+        ud = sd + (g2 ? (size_t)D.T * D.ldF : 0);
         zt = c.take<uint64_t>((size_t)D.F * (1 + slots));
         part2 = c.take<float>(kDecodePartBudget / sizeof(float));
         sync = c.take<unsigned char>(kDecodeSyncBytes);
+        arrived = static_cast<uint32_t*>(sync);
         bytes = c.off;
     }
 };

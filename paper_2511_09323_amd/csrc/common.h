@@ -43,6 +43,8 @@ template <> struct Elem<bf16_t> {
 // SiLU(x) = x / (1 + exp(-x))  (paper Eq. 3) and the logistic function it is built from.
 __device__ __forceinline__ float sigmoid_f32(float x) { return 1.0f / (1.0f + expf(-x)); }
 __device__ __forceinline__ float silu_f32(float x) { return x * sigmoid_f32(x); }
+// What a dense row of SiLU(g) holds on channels that are not selected: SiLU is never below -0.279 (and NaN at -inf).
+constexpr float kNotSelected = -1.0f;
 
 // Given the stored g and u of one selected channel and the incoming dz' (Eqs. bp-2, bp-3):
 //   s = SiLU(g), z' = s u, du = s dz', dg = u dz' SiLU'(g), SiLU'(g) = sig (1 + g (1 - sig)).

@@ -249,21 +249,21 @@ template <int GB, int NS> struct GateStreamCfg {
     static constexpr int kLds = kRing + kRed + (GB == 0 ? 0 : 16 * 17 * 4);
     static_assert(PB <= 2 && kLds <= kMaxDynLds, "");
 };
+// (workgroup wgi of wgn: the same walk also computes u over W_up, decode_dense.h)
 template <int GB, int NS, bool NT>
-__global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_kernel(
-    const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int B, int d, int F, float* __restrict__ g, int64_t ldg, int ga,
-    int K, int32_t* __restrict__ idx, float* __restrict__ gsel) {
+__device__ __forceinline__ void decode_stream_rows(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int B, int d, int F,
+                                                   float* __restrict__ g, int64_t ldg, int ga, int K, int32_t* __restrict__ idx,
+                                                   float* __restrict__ gsel, int wgi, int wgn, unsigned char* dec_smem) {
     using C = GateStreamCfg<GB, NS>;
     constexpr int NW = kGateStreamWaves, P = C::P, PB = C::PB;
     constexpr int UNIT = GB == 0 ? 4 : GB;
-    extern __shared__ __align__(16) unsigned char dec_smem[];
     float (*red)[NW][256] = reinterpret_cast<float (*)[NW][256]>(dec_smem + C::kRing);
     float* tile = reinterpret_cast<float*>(dec_smem + C::kRing + C::kRed);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t units = (F + UNIT - 1) / UNIT;
-    const int row0 = (int)(units * blockIdx.x / gridDim.x) * UNIT;
-    const int rows = min(F, (int)(units * (blockIdx.x + 1) / gridDim.x) * UNIT) - row0;
+    const int row0 = (int)(units * wgi / wgn) * UNIT;
+    const int rows = min(F, (int)(units * (wgi + 1) / wgn) * UNIT) - row0;
     // this wavefront's steps of 64 k
     const int steps = d / 64, per = (steps + NW - 1) / NW;
     const int first = min(wave * per, steps), mine = min(per, steps - first);
@@ -382,6 +382,13 @@ __global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_k
         }
     }
     wait_counts<0, true>();                         // nothing may still be on its way to LDS when the workgroup ends
+}
+template <int GB, int NS, bool NT>
+__global__ __launch_bounds__(kGateStreamWaves * 64, 2) void decode_gate_stream_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ wg, int B, int d, int F, float* __restrict__ g, int64_t ldg, int ga,
+    int K, int32_t* __restrict__ idx, float* __restrict__ gsel) {
+    extern __shared__ __align__(16) unsigned char dec_smem[];
+    decode_stream_rows<GB, NS, NT>(x, wg, B, d, F, g, ldg, ga, K, idx, gsel, blockIdx.x, gridDim.x, dec_smem);
 }
 
 // z[b, s] = SiLU(gsel[b, s]) * (x[b] . wu[idx[b, s]])  for every selected (token, channel) pair.

@@ -280,6 +280,22 @@ inline bool gate_stream_pays(int B, int d, int F, bool grouped, int workgroups) 
     return gate_stream_nontemporal(d, F) || (d <= 1024 && rows >= 5);
 }
 
+// bf16 decode with both projections as streams (decode_dense.h) instead of gathers, by what the gathers would request of a matrix, B K / F
+// times its rows.  Whole call, this / gather, weights from memory, B 2 .. 16, K/F 1/8, 1/5 and 1:
+//   row-wide, from five tokens: 1536 x 4096 to 4096 x 11008 1.2 times 0.92 to 0.97 (3072 x 8192 1.06), 1.6 times 0.83 to 1.00, 3.2 times 0.75 to
+//     0.85; 0.8 times 1.02 to 1.11.  Long columns (F > 4 d), whose values every slice reads: 1.2 times 0.97 to 1.13, 2 times 0.86 to 0.96.
+//     Fewer tokens, whose gathers repeat less: 2 times 0.93 to 1.08, 4 times 0.73 to 0.86.
+//   grouped, where no selection runs beside it: 2.5 times 0.94 to 1.05, 3.25 times 0.60 to 0.98.
+//   layers below 12 MB a matrix, where the launches weigh: 512 x 1376 to 1024 x 2752 3.2 times 1.01 to 1.02, 6 times 0.88 to 0.99; wide rows (2560
+//     x 640) gain nothing.
+inline bool decode_dense_pays(int B, int d, int F, int K, bool grouped) {
+    const int64_t requested = (int64_t)B * K, bytes = 2ll * d * F;
+    if (bytes < 12000000) return B > 4 && d <= 2048 && requested >= 6ll * F;
+    if (B <= 4) return !grouped && bytes >= 24000000 && requested >= 3ll * F;
+    if (grouped) return requested >= 3ll * F;
+    return F > 4 * d ? requested >= 2ll * F : 5 * requested >= 6ll * F;
+}
+
 // fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
 // fragment reads); below that 32 x 32, with the k-slices split over the wavefronts (16 x 32 or 32 x 32) when the contraction is long
 // (several 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate

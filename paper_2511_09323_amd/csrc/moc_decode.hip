@@ -5,6 +5,7 @@
 #include <atomic>
 #include <random>
 
+#include "decode_dense.h"
 #include "decode_kernels.h"
 #include "decode_persist.h"
 #include "decode_rows.h"
@@ -82,6 +83,72 @@ moc_status launch_decode_gate_stream(const Dims& D, const bf16_t* x, const bf16_
     if (steps <= 2) return launch_decode_gate_stream_ns<GB, 2>(D, x, wg, g, ga, idx, gsel, st);
     if (steps <= 4) return launch_decode_gate_stream_ns<GB, 4>(D, x, wg, g, ga, idx, gsel, st);
     return launch_decode_gate_stream_ns<GB, 8>(D, x, wg, g, ga, idx, gsel, st);
+}
+
+// ------------------------------------------------- both projections as streams (decode_dense.h)
+constexpr int kSelectUpMaxLds = 156 * 1024;      // (the kernel has up to 512 bytes of static LDS)
+template <int NCH, int NS, bool NT>
+moc_status launch_select_up_stream(const Dims& D, const TopkArgs<float>& a, const bf16_t* x, const bf16_t* wu, float* u, uint32_t* arrived, hipStream_t st) {
+    auto kern = decode_select_up_stream_kernel<NCH, NS, NT>;
+    LdsAttr<decode_select_up_stream_kernel<NCH, NS, NT>, kSelectUpMaxLds>::use();
+    const size_t lds = std::max((size_t)GateStreamCfg<0, NS>::kLds, NCH > 0 ? topk_reg_dyn_lds(D.K, 0, sizeof(float), false) : 0);
+    Span span("decode_select_up_stream", st);
+    hipLaunchKernelGGL(kern, dim3(D.T + std::min(std::max(1, gate_stream_workgroups() - D.T), (D.F + 3) / 4)), dim3(kGateStreamWaves * 64), lds, st,
+                       a, x, wu, D.T, D.d, u, arrived);
+    HIP_TRY(hipGetLastError());
+    return MOC_OK;
+}
+template <int NCH, int NS>
+moc_status launch_select_up_stream_nt(const Dims& D, const TopkArgs<float>& a, const bf16_t* x, const bf16_t* wu, float* u, uint32_t* arrived, hipStream_t st) {
+    return gate_stream_nontemporal(D.d, D.F) ? launch_select_up_stream<NCH, NS, true>(D, a, x, wu, u, arrived, st)
+                                             : launch_select_up_stream<NCH, NS, false>(D, a, x, wu, u, arrived, st);
+}
+template <int NCH>
+moc_status launch_select_up_stream_ns(const Dims& D, const TopkArgs<float>& a, const bf16_t* x, const bf16_t* wu, float* u, uint32_t* arrived, hipStream_t st) {
+    const int steps = (D.d / 64 + kGateStreamWaves - 1) / kGateStreamWaves;
+    if (steps <= 1) return launch_select_up_stream_nt<NCH, 1>(D, a, x, wu, u, arrived, st);
+    if (steps <= 2) return launch_select_up_stream_nt<NCH, 2>(D, a, x, wu, u, arrived, st);
+    if (steps <= 4) return launch_select_up_stream_nt<NCH, 4>(D, a, x, wu, u, arrived, st);
+    return launch_select_up_stream_nt<NCH, 8>(D, a, x, wu, u, arrived, st);
+}
+// Ranges of channels: as many workgroups as the device has compute units, at least a step of 32 channels for every wavefront.
+template <int CT, bool NT>
+moc_status launch_down_stream(const Dims& D, const DecodeWs& W, const bf16_t* wd, bf16_t* y, hipStream_t st) {
+    auto kern = decode_down_stream_kernel<CT, NT>;
+    LdsAttr<decode_down_stream_kernel<CT, NT>, DownStreamCfg<CT>::kLds>::use();
+    Span span("decode_down_stream", st);
+    const int slices = (D.d + 16 * CT - 1) / (16 * CT);
+    int P = std::min({std::max(1, gate_stream_workgroups() / slices), (D.F + 127) / 128, decode_splits(D.T, D.K)});
+    if (P > 8) P = P / 8 * 8;                 // (a range on one XCD: 1536 x 4096 23.0 us with 8 ranges, 24.0 with the 10 that fill the chip)
+    const int per = round_up((D.F + 4 * P - 1) / (4 * P), 4);
+    hipLaunchKernelGGL(kern, dim3(P, slices), dim3(256), DownStreamCfg<CT>::kLds, st, W.sd, W.ud, (int64_t)D.ldF, wd, D.T, D.d, D.F, per, W.part,
+                       W.arrived, y);
+    HIP_TRY(hipGetLastError());
+    return MOC_OK;
+}
+// After the gate: selection (row-wide; grouped selection happened in the gate) and up projection, down projection, sum of the shares.
+moc_status decode_dense(const Dims& D, const DecodeWs& W, const bf16_t* x, const bf16_t* wu, const bf16_t* wd, bf16_t* y, int32_t* idx, int gb,
+                        int key_mode, hipStream_t st) {
+    moc_status s;
+    TopkArgs<float> a{W.g, D.ldF, D.F, D.K, idx, W.gsel, nullptr, nullptr, 0, nullptr, nullptr, 0, nullptr, cut_far(D.F, D.K), W.sd};
+    if (gb != 0) {
+        s = launch_select_up_stream_ns<0>(D, a, x, wu, W.ud, W.arrived, st);
+    } else {
+        if (key_mode != 0) {
+            if ((s = launch_key_transform(W.g, W.gkeys, (int64_t)D.T * D.ldF, key_mode, st)) != MOC_OK) return s;
+            a.g = W.gkeys;
+            a.g_raw = W.g;
+        }
+        constexpr int kChunk = 4 * kGateStreamWaves * 64;
+        if (D.F <= 3 * kChunk) s = launch_select_up_stream_ns<3>(D, a, x, wu, W.ud, W.arrived, st);
+        else if (D.F <= 6 * kChunk) s = launch_select_up_stream_ns<6>(D, a, x, wu, W.ud, W.arrived, st);
+        else s = launch_select_up_stream_ns<16>(D, a, x, wu, W.ud, W.arrived, st);
+    }
+    if (s != MOC_OK) return s;
+    // (slices of 64 columns where those of 128 would need many ranges, whose shares are added: d 512 6.8 us against 9.2, 2048 12.3 against 15.1;
+    // at 4096 the twice as many slices read SiLU(g) and u twice as often, 30.0 against 24.8)
+    if (D.d <= 2048) return gate_stream_nontemporal(D.d, D.F) ? launch_down_stream<4, true>(D, W, wd, y, st) : launch_down_stream<4, false>(D, W, wd, y, st);
+    return gate_stream_nontemporal(D.d, D.F) ? launch_down_stream<8, true>(D, W, wd, y, st) : launch_down_stream<8, false>(D, W, wd, y, st);
 }
 
 template <class E, int BT, int GA>
@@ -357,6 +424,8 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
     // bf16 from two tokens on: the streamed gate on the matrix cores where gate_stream_pays says so.
     const bool gate_stream = std::is_same<E, bf16_t>::value && !options().force_generic && D.d % 64 == 0 && D.d <= kGateStreamMaxD &&
                              gate_stream_pays(B, D.d, D.F, gb != 0, gate_stream_workgroups());
+    const bool dense = gate_stream && !options().decode_select_gather && decode_dense_pays(B, D.d, D.F, D.K, gb != 0) &&
+                       (gb != 0 || topk_reg_dyn_lds(D.K, 0, sizeof(float), false) <= (size_t)kSelectUpMaxLds);
     if (gate_stream) {
         const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
         const bf16_t* wb = reinterpret_cast<const bf16_t*>(wg);
@@ -374,6 +443,8 @@ moc_status decode_impl(const Dims& D, const E* x, const E* wg, const E* wu, cons
         else s = decode_gate_group_b<E, 16>(D, x, wg, ga, gb, idx, W.gsel, st);
     }
     if (s != MOC_OK) return s;
+    if constexpr (std::is_same<E, bf16_t>::value)
+        if (dense) return decode_dense(D, W, x, wu, wd, y, idx, gb, key_mode, st);
     if (gb == 0 && decode_rows_pays<E>(D, gather_fused) && !options().decode_select_gather) return decode_rows<E>(D, W, x, wu, wd, y, idx, key_mode, st);
     const int P = decode_splits(B, D.K);
     if (gb == 0 && key_mode == 0 && gather_fused && options().decode_select_gather && (D.F + P - 1) / P <= kDsgMaxRange &&

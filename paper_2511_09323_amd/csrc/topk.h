@@ -44,6 +44,7 @@ template <class E> struct TopkArgs {
     // done on, and the gate values themselves are fetched from here ([T, ldg] like g); null otherwise.
     const float* g_raw;
     float far = 0.0f;   // cut_far(F, K), set by the launcher of the register-resident kernel
+    float* sd = nullptr;      // DENSE only: [T, ldg], SiLU(g) of selected channels, kNotSelected elsewhere and on the padding of the row
 };
 
 // Selection keys of the Top-K position variants: mode 1 ranks SiLU(g) (ablation row "After SiLU"),
@@ -325,7 +326,7 @@ __device__ __forceinline__ bool topk_member(uint32_t key, int j, TopkThreshold t
 // marked before) whose per-lane prefixes stay in registers.  Selected channels are staged in LDS at their output slot, so that the
 // compact outputs are written slot by slot (coalesced, SiLU evaluated K times instead of under divergence for every channel)
 // and the dense Z' row is assembled in LDS and streamed out with 16-byte stores.  Dynamic LDS: topk_reg_dyn_lds().
-template <class E, int NT, int NCH, bool FUSED>
+template <class E, int NT, int NCH, bool FUSED, bool DENSE = false>
 __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row, unsigned char* topk_dyn) {
     constexpr int NW = NT / 64;
     constexpr int CHUNK = NT * 4;
@@ -388,6 +389,21 @@ __device__ __forceinline__ void topk_row_body(const TopkArgs<E>& a, int64_t row,
         }
         pg[c] = lg;
         if (lane == 0) tab[c * NW + wave] = ngt;
+    }
+    if constexpr (DENSE) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int j0 = c * CHUNK + jb;
+            if (j0 >= a.ldg) break;                         // (ldg is a multiple of 4)
+            f32x4_t g = a.g_raw ? *reinterpret_cast<const f32x4_t*>(a.g_raw + row * a.ldg + j0) : f32x4_t{v[c][0], v[c][1], v[c][2], v[c][3]};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                bool in = v[c][e] >= cut.tau;
+                if (keyed) in = cut.in(v[c][e], j0 + e);
+                g[e] = in ? silu_f32(g[e]) : kNotSelected;
+            }
+            *reinterpret_cast<f32x4_t*>(a.sd + row * a.ldg + j0) = g;
+        }
     }
     __syncthreads();
     // exclusive prefix of the totals in (chunk, wavefront) order: the first n lanes of every wavefront hold one total each
