@@ -184,6 +184,19 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
     }
     if constexpr (std::is_same<E, float>::value) {
         if (!options().force_generic && f32_problem_ok(pr)) {
+            if constexpr (!AKM && BKM && std::is_same<Epi, EpiStore<float>>::value) {
+                if (!ascending && scratch.p && epi.ldc == epi.N && epi.N == pr.N && epi.N % 4 == 0 && epi.pad_to == 0) {
+                    const F32Shares plan = f32_shares(pr.M, pr.N, pr.Kc, pr.Kc2, scratch.bytes, std::max(1, device_cu_count()));
+                    const int64_t out = (int64_t)pr.M * pr.N, n4 = out / 4;
+                    if (plan.shares > 1) {
+                        const hipError_t e = launch_gemm_f32_shares(pr, EpiShare{scratch.p, pr.N, out, pr.N}, plan, st);
+                        if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
+                        hipLaunchKernelGGL((reduce_shares_kernel<float>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, scratch.p, plan.shares, out, n4, epi.C);
+                        HIP_TRY(hipGetLastError());
+                        return MOC_OK;
+                    }
+                }
+            }
             hipError_t e = launch_gemm_f32<AKM, BKM, Epi, 1>(F32Batch<Epi, 1>{{pr}, {epi}}, ascending, device_cu_count(), st);
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;

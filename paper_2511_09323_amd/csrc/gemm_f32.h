@@ -13,8 +13,10 @@
 // and the contraction is long, KW = 4: the four wavefronts of a workgroup take a quarter of every k-slice each and
 // their tiles are added through LDS in a fixed order.  With KW = 1 a result is one sum over ascending k from zero.
 //
-// Measured at T 256, d 512, F 1376 (forward + backward, ten products in five launches): gate + up 15.6 us, down 10.4, dZ' 10.0,
-// three weight gradients 19.7, dX 18.0, against 125, 222, 63, 143 and 424 us on the fp32-FMA kernel of gemm_generic.h, which has 32
+// Contractions whose tiles leave compute units idle run in shares (f32_shares).
+//
+// Measured at T 256, d 512, F 1376 (forward + backward, ten products in five launches): gate + up 15.6 us, down 10.0, dZ' 10.0,
+// three weight gradients 18.0, dX 15.4, against 125, 222, 63, 143 and 424 us on the fp32-FMA kernel of gemm_generic.h, which has 32
 // to 88 workgroups and waits for every 16-k slice; about 72 TFLOP/s at the margin (142 on a large library product), the rest launch
 // and first loads.
 #pragma once
@@ -42,7 +44,8 @@ template <int BM, int BN, int KW, bool AKM, bool BKM> struct F32Cfg {
 };
 
 // (three workgroups per compute unit for the small-slice tiles: the weight-gradient launch then runs in one round)
-template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB>
+// With SPLIT (one problem) blockIdx.y is a share of the tile's k-slices, whose sums go to epi.share(blockIdx.y).
+template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB, bool SPLIT = false>
 __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32Batch<Epi, NB> batch, int tiles_n) {
     using Cfg = F32Cfg<BM, BN, KW, AKM, BKM>;
     static_assert(KW == 1 || KW == 4, "the wavefronts split the tile 2 x 2 or the k-slice in four");
@@ -52,13 +55,18 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
     constexpr int LA = BM * BK / 4 / NT, LB = BN * BK / 4 / NT;      // 16-byte chunks per thread and slice
     extern __shared__ __align__(16) float f32_smem[];
     const GemmProblem<float>& pr = batch.pr[NB == 1 ? 0 : blockIdx.y];
-    const Epi& epi = batch.epi[NB == 1 ? 0 : blockIdx.y];
+    static_assert(!SPLIT || NB == 1, "");
+    const Epi epi = [&] {
+        if constexpr (SPLIT) return batch.epi[0].share(blockIdx.y);
+        else return batch.epi[NB == 1 ? 0 : blockIdx.y];
+    }();
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int M = pr.M, N = pr.N;
     const int m0 = (blockIdx.x / tiles_n) * BM, n0 = (blockIdx.x % tiles_n) * BN;
     const int wm0 = KW == 1 ? (wave >> 1) * WM : 0, wn0 = KW == 1 ? (wave & 1) * WN : 0;
     const int k_wave = KW == 1 ? 0 : wave * (BK / KW);               // first k of this wavefront inside a slice
-    const int nk0 = (pr.Kc + BK - 1) / BK, nk = nk0 + (pr.Kc2 + BK - 1) / BK;
+    const int nk0 = (pr.Kc + BK - 1) / BK, nk_all = nk0 + (pr.Kc2 + BK - 1) / BK;
+    const int ks = SPLIT ? nk_all * (int)blockIdx.y / (int)gridDim.y : 0, nk = SPLIT ? nk_all * ((int)blockIdx.y + 1) / (int)gridDim.y : nk_all;      // slices ks .. nk - 1
 
     f32x4_t ga[kF32Sets][LA], gb[kF32Sets][LB];
     // one operand's chunks of k-slice kt -> registers.  Branch-free: rows and k past the end are clamped to readable
@@ -77,6 +85,11 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
     };
     offsets(std::integral_constant<bool, AKM>{}, std::integral_constant<int, BM>{}, pr.A, m0, M, a_off, a_koff);
     offsets(std::integral_constant<bool, BKM>{}, std::integral_constant<int, BN>{}, pr.B, n0, N, b_off, b_koff);
+    int a_all[LA], b_all[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) a_all[i] = a_off[i] + a_koff[i];
+#pragma unroll
+    for (int i = 0; i < LB; ++i) b_all[i] = b_off[i] + b_koff[i];
     auto fetch = [&](auto buf_c, int kt) {
         constexpr int buf = decltype(buf_c)::value;
         kt = min(kt, nk - 1);
@@ -86,10 +99,15 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
         const float* pb = (seg ? pr.B.p2 : pr.B.p) + (BKM ? k0 * pr.B.ld : (int64_t)k0);
         const int a_last = AKM ? last_row_offset(left, BK, (int)pr.A.ld) : ((left + 3) & ~3) - 4;
         const int b_last = BKM ? last_row_offset(left, BK, (int)pr.B.ld) : ((left + 3) & ~3) - 4;
+        auto load = [&](auto cut_c) {                                // (whole slices: nothing to compute per chunk)
+            constexpr bool CUT = decltype(cut_c)::value;
 #pragma unroll
-        for (int i = 0; i < LA; ++i) ga[buf][i] = *reinterpret_cast<const f32x4_t*>(pa + (uint32_t)(a_off[i] + min(a_koff[i], a_last)));
+            for (int i = 0; i < LA; ++i) ga[buf][i] = *reinterpret_cast<const f32x4_t*>(pa + (uint32_t)(CUT ? a_off[i] + min(a_koff[i], a_last) : a_all[i]));
 #pragma unroll
-        for (int i = 0; i < LB; ++i) gb[buf][i] = *reinterpret_cast<const f32x4_t*>(pb + (uint32_t)(b_off[i] + min(b_koff[i], b_last)));
+            for (int i = 0; i < LB; ++i) gb[buf][i] = *reinterpret_cast<const f32x4_t*>(pb + (uint32_t)(CUT ? b_off[i] + min(b_koff[i], b_last) : b_all[i]));
+        };
+        if (left >= BK) load(std::false_type{});
+        else load(std::true_type{});
     };
     // `left`: k of the slice that count, the rest is zeroed (CUT is the uniform "left < BK")
     auto stash_operand = [&](auto km_c, auto rows_c, auto pitch_c, auto cut_c, float* base, const f32x4_t* g, int left) {
@@ -120,13 +138,20 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
         else both(std::true_type{});
     };
 
-    f32x4_t acc[TM][TN];
+    // (a share's products may be two sums, of every other group of four k, which halves the chain of dependent instructions)
+    constexpr int NACC = SPLIT && KW == 1 ? 2 : 1;
+    f32x4_t accs[NACC][TM][TN];
+    f32x4_t (&acc)[TM][TN] = accs[0];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int n = 0; n < NACC; ++n)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) accs[n][i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     // fragment of 16 rows x 4 k: lane l gets row l % 16, k = l / 16
-    auto compute = [&](auto stage_c) {
+    // `between`: what the next slices need (LDS writes, loads and their addresses), put behind the first fragment reads so that the matrix
+    // instructions hide it.  Before the products it took 8 to 12 % of a slice (64 x 64 tiles 0.83 -> 0.76 us, 16 x 32 0.75 -> 0.67).
+    auto compute = [&](auto stage_c, const auto& between) {
         constexpr int stage = decltype(stage_c)::value;
         const float* a = f32_smem + stage * Cfg::kStage;
         const float* b = a + Cfg::kFloatsA;
@@ -148,36 +173,37 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
             }
         };
         read(0, 0);
+        between();
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             if (g + 1 < NG) read(g + 1, (g + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < GK; ++q)
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
                     for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[g & 1][q][j], fa[g & 1][q][i], acc[i][j], 0, 0, 0);
+                        accs[q % NACC][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[g & 1][q][j], fa[g & 1][q][i], accs[q % NACC][i][j], 0, 0, 0);
         }
     };
-    fetch(std::integral_constant<int, 0>{}, 0);
-    fetch(std::integral_constant<int, 1>{}, 1);
-    fetch(std::integral_constant<int, 2>{}, 2);
-    fetch(std::integral_constant<int, 3>{}, 3);
-    stash(std::integral_constant<int, 0>{}, 0);
-    fetch(std::integral_constant<int, 0>{}, 4);
+    fetch(std::integral_constant<int, 0>{}, ks);
+    fetch(std::integral_constant<int, 1>{}, ks + 1);
+    fetch(std::integral_constant<int, 2>{}, ks + 2);
+    fetch(std::integral_constant<int, 3>{}, ks + 3);
+    stash(std::integral_constant<int, 0>{}, ks);
+    fetch(std::integral_constant<int, 0>{}, ks + 4);
     __syncthreads();
     // slice kt is in LDS stage kt % 2, slices kt + 1 .. kt + 4 are in or on their way to registers
     auto step = [&](auto set_c, int kt) {
         constexpr int set = decltype(set_c)::value, nxt = (set + 1) % kF32Sets;
         // the other stage was last read in the slice before this one, a barrier ago (past the end: zeros nobody multiplies)
-        stash(std::integral_constant<int, nxt>{}, kt + 1);
-        fetch(std::integral_constant<int, nxt>{}, kt + 5);
-        compute(std::integral_constant<int, set & 1>{});
+        compute(std::integral_constant<int, set & 1>{}, [&] {
+            stash(std::integral_constant<int, nxt>{}, kt + 1);
+            fetch(std::integral_constant<int, nxt>{}, kt + 5);
+        });
         __syncthreads();
     };
-    int kt = 0;
+    int kt = ks;
     for (; kt + 4 <= nk; kt += 4) {
         step(std::integral_constant<int, 0>{}, kt);
         step(std::integral_constant<int, 1>{}, kt + 1);
@@ -188,6 +214,12 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
     if (kt + 1 < nk) step(std::integral_constant<int, 1>{}, kt + 1);
     if (kt + 2 < nk) step(std::integral_constant<int, 2>{}, kt + 2);
 
+    if constexpr (NACC == 2) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] += accs[1][i][j];
+    }
     // acc[i][j][r] is C[m0 + wm0 + 16 i + lane % 16, n0 + wn0 + 16 j + 4 (lane / 16) + r]
     if (KW == 1) {
 #pragma unroll
@@ -233,13 +265,13 @@ inline bool f32_problem_ok(const GemmProblem<float>& p) {
     return p.M >= 1 && p.N >= 1 && p.Kc >= 1 && operand_ok(p.A, p.M) && operand_ok(p.B, p.N);
 }
 
-template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB>
-inline hipError_t launch_gemm_f32_tile(const F32Batch<Epi, NB>& b, hipStream_t st) {
+template <int BM, int BN, int KW, bool AKM, bool BKM, class Epi, int NB, bool SPLIT = false>
+inline hipError_t launch_gemm_f32_tile(const F32Batch<Epi, NB>& b, hipStream_t st, int shares = 1) {
     using Cfg = F32Cfg<BM, BN, KW, AKM, BKM>;
-    auto kern = gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB>;
-    LdsAttr<gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB>, Cfg::kLds>::use();
+    auto kern = gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB, SPLIT>;
+    LdsAttr<gemm_f32_mfma_kernel<BM, BN, KW, AKM, BKM, Epi, NB, SPLIT>, Cfg::kLds>::use();
     const int tiles_m = (b.pr[0].M + BM - 1) / BM, tiles_n = (b.pr[0].N + BN - 1) / BN;
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n, NB), dim3(256), Cfg::kLds, st, b, tiles_n);
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n, SPLIT ? shares : NB), dim3(256), Cfg::kLds, st, b, tiles_n);
     return hipGetLastError();
 }
 
@@ -253,6 +285,13 @@ inline hipError_t launch_gemm_f32(const F32Batch<Epi, NB>& b, bool ascending, in
         case F32Tile::k32x32Split: return launch_gemm_f32_tile<32, 32, 4, AKM, BKM, Epi, NB>(b, st);
         default: return launch_gemm_f32_tile<16, 32, 4, AKM, BKM, Epi, NB>(b, st);
     }
+}
+
+// One product with A k-contiguous and B k-major in shares (f32_shares): share z of the sums to epi.share(z).
+template <class EpiS> inline hipError_t launch_gemm_f32_shares(const GemmProblem<float>& p, const EpiS& epi, F32Shares plan, hipStream_t st) {
+    const F32Batch<EpiS, 1> b{{p}, {epi}};
+    return plan.tile == F32Tile::k32x32 ? launch_gemm_f32_tile<32, 32, 1, false, true, EpiS, 1, true>(b, st, plan.shares)
+                                        : launch_gemm_f32_tile<16, 32, 4, false, true, EpiS, 1, true>(b, st, plan.shares);
 }
 
 }  // namespace moc

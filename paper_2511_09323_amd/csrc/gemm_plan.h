@@ -307,5 +307,42 @@ inline F32Tile f32_tile(int M, int N, int batch, int64_t contraction, bool ascen
     if (ascending || (t32 >= cus && contraction <= 1024)) return F32Tile::k32x32;
     return t32 < cus ? F32Tile::k16x32Split : F32Tile::k32x32Split;
 }
+// Cost in microseconds of a launch of `tiles` 32 x 32 tiles (k-slices of 64, three workgroups to a compute unit) or 16 x 32 tiles whose slices
+// of 128 are split over the wavefronts (two), `slices` to a tile: workgroups of one compute unit share its matrix cores and hide each other's
+// latency.  Measured at 64 to 1024 rows, d 512 and 768, contractions of 1376 to 4096; within 10 %.
+inline double f32_cost(bool k32, int64_t tiles, int slices, int cus) {
+    const int64_t w = (tiles + cus - 1) / cus, most = k32 ? 3 : 2, rest = w % most;
+    const auto round = [&](int64_t n) { return k32 ? 3.0 + slices * (0.25 + 0.3 * n) : 2.7 + slices * (0.32 + 0.34 * n); };
+    return (w / most) * round(most) + (rest ? round(rest) : 0.0);
+}
+// Contraction in shares that run as workgroups of their own and are summed by a second launch (3.2 us and the shares' way through memory); shares
+// = 1 where that is not cheaper than whole tiles.  A result is the sum of no fewer partial sums than before: the split tiles add four, a share of
+// a 32 x 32 tile has two, of which three shares are asked for.  us, the tiles of f32_tile / the shares chosen here: 64 x 768 over 4096 21.9 / 13.3,
+// 256 x 512 over 2752 16.5 / 15.4, 256 x 768 over 2048 and 4096 19.5 / 16.8 and 33.2 / 24.4, 512 x 768 35.5 / 26.8 and 64.8 / 42.9.
+struct F32Shares {
+    F32Tile tile;
+    int shares;
+};
+inline F32Shares f32_shares(int M, int N, int Kc, int Kc2, size_t scratch_bytes, int cus) {
+    const F32Tile whole = f32_tile(M, N, 1, (int64_t)Kc + Kc2, false, cus);
+    F32Shares best{whole, 1};
+    if (whole != F32Tile::k16x32Split && whole != F32Tile::k32x32Split) return best;
+    const int64_t n32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32), n16 = (int64_t)((M + 15) / 16) * ((N + 31) / 32), out = (int64_t)M * N;
+    const int s32 = (Kc + 63) / 64 + (Kc2 + 63) / 64, s16 = (Kc + 127) / 128 + (Kc2 + 127) / 128;
+    // (32 x 32 split tiles: one workgroup per compute unit)
+    double cost = 0.97 * (whole == F32Tile::k16x32Split ? f32_cost(false, n16, s16, cus) : 2.7 + s16 * 1.05 * ((n32 + cus - 1) / cus));
+    for (int z = 2; z <= 8 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
+        const double sum = 3.2 + (z + 1) * out / 1.0e6;
+        if (s16 / z >= 2) {
+            const double c = f32_cost(false, z * n16, (s16 + z - 1) / z, cus) + sum;
+            if (c < cost) { best = F32Shares{F32Tile::k16x32Split, z}; cost = c; }
+        }
+        if (z >= 3 && s32 / z >= 2) {
+            const double c = f32_cost(true, z * n32, (s32 + z - 1) / z, cus) + sum;
+            if (c < cost) { best = F32Shares{F32Tile::k32x32, z}; cost = c; }
+        }
+    }
+    return best;
+}
 
 }  // namespace moc

@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from tests.test_gpu_f32_gemm import CASES as F32_CASES
+from tests.test_gpu_f32_gemm import CASES as F32_CASES, SHARE_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -38,7 +38,18 @@ static void f32(int T, int d, int F) {
     std::printf("gate_up=%s down=%s dz=%s dw=%s dx=%s\n", tile(T, F, 2, d, true), tile(T, d, 1, F, false), tile(T, F, 1, d, false),
                 tile(F, d, 3, T, false), tile(T, d, 1, 2 * (int64_t)F, false));
 }
+// what the products over the channels take, with the scratch that the layer has for their shares
+static void f32_over_channels(int T, int d, int F) {
+    static const char* const names[4] = {"64x64", "32x32", "32x32s", "16x32s"};
+    const size_t scratch = (size_t)T * ((F + kColPad - 1) / kColPad * kColPad) * 2 * sizeof(float);
+    for (int two : {0, 1}) {
+        const F32Shares r = f32_shares(T, d, F, two * F, scratch, kCus);
+        std::printf(r.shares > 1 ? "%s=%s/%d " : "%s=%s ", two ? "dx" : "down", names[(int)r.tile], r.shares);
+    }
+    std::puts("");
+}
 int main(int argc, char** argv) {
+    if (argc == 5) f32_over_channels(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
     if (argc == 1) offsets();
     else if (argc == 4) f32(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
@@ -63,6 +74,12 @@ def test_cases_take_the_kernels_they_name(plan):
     for T, d, F, _, want in F32_CASES:
         got = plan(T, d, F).stdout.split()
         assert set(want.split()) <= set(got), (T, d, F, want, got)
+
+
+def test_share_cases_take_the_shares_they_name(plan):
+    for T, d, F, _, want in SHARE_CASES:
+        r = plan(T, d, F, "shares")
+        assert r.stdout.split() == want.split(), (T, d, F, want, r.stdout, r.stderr)
 
 
 def test_cases_reach_every_tile():

@@ -27,3 +27,20 @@ CASES = [
 @pytest.mark.parametrize("T,d,F,K,kernels", CASES)
 def test_f32_products_at_tile_edges(T, d, F, K, kernels):
     run_fwd_bwd_case("f32-tiles " + kernels, 97, T, d, F, K, "f32")
+
+
+# Products over the channels whose contraction runs in shares (f32_shares; the tile of f32_tile is the one of the whole product): what down and dX take.
+SHARE_CASES = [
+    (64, 768, 2048, 256, "down=16x32s/4 dx=16x32s/5"),
+    (100, 512, 1373, 172, "down=16x32s/4 dx=16x32s/4"),                # both ends of a share inside the contraction's tail, a slice cut in a chunk
+    (65, 132, 1025, 128, "down=32x32/6 dx=16x32s/6"),                # 17 and 18 slices; a row and four columns past a tile
+    (256, 512, 1376, 172, "down=16x32s dx=32x32/4"),
+    (257, 772, 2050, 409, "down=16x32s dx=32x32/3"),
+    (1100, 260, 1031, 100, "down=32x32/3 dx=32x32/4"),
+    (1024, 512, 1376, 172, "down=32x32s dx=32x32/3"),                  # and whole
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,kernels", SHARE_CASES)
+def test_f32_products_in_shares(T, d, F, K, kernels):
+    run_fwd_bwd_case("f32-shares " + kernels, 96, T, d, F, K, "f32")
