@@ -153,17 +153,28 @@ struct StreamKArea {
 };
 unsigned long long next_streamk_tag();
 
+// What is missing from `have` bytes of memory that is free when down or dX runs (share_scratch_wanted).
+template <class E> size_t extra_share_bytes(const Dims& D, size_t have) {
+    const size_t want = std::is_same<E, uint16_t>::value ? share_scratch_wanted(D.T, D.d) : 0;
+    return want > have ? want - have : 0;
+}
+
 template <class E> struct FwdWs {      // dense scratch of the forward: fp32 gate, U, masked Z'
     float *G, *keys;                   // keys: transformed selection keys (Top-K position variants only)
     E *U, *Zd;
     uint16_t* zc;                      // compressed Z' of the structured-sparse down projection (MOC_GROUPED_SPARSE=1, bf16)
     uint32_t* zi;
     StreamKArea sk;
+    size_t share_bytes = 0;            // from G on: free while down runs
     size_t bytes;
     FwdWs(void* ws, const Dims& D, bool dense, bool keyed = false) {
         Carver c(ws);
         G = dense ? nullptr : c.take<float>((size_t)D.T * D.ldF);
         U = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
+        if (!dense) {
+            (void)c.take<unsigned char>(extra_share_bytes<E>(D, c.off));
+            share_bytes = c.off;
+        }
         Zd = c.take<E>((size_t)D.T * D.ldF);
         keys = keyed ? c.take<float>((size_t)D.T * D.ldF) : nullptr;
         const bool sparse = !dense && std::is_same<E, uint16_t>::value && options().grouped_sparse;
@@ -184,14 +195,20 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
     uint16_t* pref;
     E *dZd, *Zd, *dGd, *dUd;
     StreamKArea sk;
+    float* share = nullptr;            // free while dX runs: up to the end of Zd
+    size_t share_bytes = 0;
     size_t bytes;
     BwdWs(void* ws, const Dims& D, bool dense) {
         Carver c(ws);
         maskw = dense ? nullptr : c.take<uint32_t>((size_t)D.T * D.nw);
         pref = dense ? nullptr : c.take<uint16_t>((size_t)D.T * D.nw);
+        const size_t dense_bytes = (size_t)D.T * D.ldF * sizeof(E), before = c.off;
+        if (!dense) share = reinterpret_cast<float*>(c.take<unsigned char>(extra_share_bytes<E>(D, 2 * dense_bytes)));
         dZd = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
         const size_t rows = (size_t)D.T + kMaxExperts * (kRowPad - 1);
         Zd = c.take<E>(rows * D.ldF);
+        if (dense) share = reinterpret_cast<float*>(Zd);
+        share_bytes = dense ? dense_bytes : c.off - before;
         dGd = c.take<E>(rows * D.ldF);
         dUd = c.take<E>(rows * D.ldF);
         sk.carve<E>(c, D);

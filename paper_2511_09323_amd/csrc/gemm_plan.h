@@ -35,6 +35,18 @@ constexpr GemmTile kGemmTile[kGemmTiles] = {
     {256, 256, 3, 1, 12.0, 0.592, 0.851, 0.0}, {256, 192, 3, 1, 11.5, 0.457, 0.680, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
     {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.283, 0.378, 0.0},  {192, 128, 3, 1, 7.0, 0.290, 0.385, 0.0},
     {128, 128, 3, 3, 5.7, 0.222, 0.275, 0.275}, {64, 128, 5, 4, 4.7, 0.216, 0.225, 0.200}};
+// The same for products over the channels (down, dX) with 1.4 M results or rows of 2048 and 8 MB of weights or more, which do not stay in a
+// cache until they are read: measured with operands from memory, 32 to 6000 rows, d 512 to 4096.  The table above, measured with warm
+// operands, made such products up to 1.8 times as long as the best choice (2047 x 2048 over 2 * 5464 121 us against 80, 1024 x 4096 over 10928 121
+// against 80), this one 1.03 times on average.  Below 8 MB the warm table holds: 4096 x 768 over 2 * 2048, cold 46 us whole and 40 in shares, runs
+// in 40 and 42 inside a training step.
+constexpr GemmTile kGemmTileLong[kGemmTiles] = {
+    {256, 256, 3, 1, 12.0, 0.595, 0.850, 0.0}, {256, 192, 3, 1, 11.5, 0.510, 0.673, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
+    {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.299, 0.475, 0.0},  {192, 128, 3, 1, 6.4, 0.301, 0.381, 0.0},
+    {128, 128, 3, 3, 5.5, 0.241, 0.328, 0.297}, {64, 128, 5, 4, 4.9, 0.214, 0.257, 0.211}};
+inline bool long_product(int M, int N, int Kc, int Kc2) {
+    return 2 * ((int64_t)Kc + Kc2) * N >= 8000000 && (N >= 2048 || (int64_t)M * N >= 21 << 16);
+}
 // every shape; 256x256, 256x192, 128x128; and 256x128, 64x128; 192x128, 128x128, 64x128
 constexpr unsigned kTilesAll = 0xFF, kTilesBasic = 0x43, kTilesGroup = 0xCB, kTilesShares = 0xE0;
 // With a k-major B, the large tiles of gemm_pingpong.h take every product that 192x256 or 256x128 would be chosen for but those of operands
@@ -58,12 +70,13 @@ inline double gemm_cost(const GemmTile& t, int64_t tiles, int nk, int cus) {
 
 // The cheapest of the tile shapes in `mask` (the one named by `forced` if that is not negative); tiles_of(tile) counts the tiles of
 // the launch.
-template <class TilesOf> int cheapest_tile(unsigned mask, const TilesOf& tiles_of, int nk, int cus, int forced = -1, double* cost_out = nullptr) {
+template <class TilesOf>
+int cheapest_tile(unsigned mask, const TilesOf& tiles_of, int nk, int cus, int forced = -1, double* cost_out = nullptr, const GemmTile* table = kGemmTile) {
     int best = -1;
     double best_cost = 0.0;
     for (int c = 0; c < kGemmTiles; ++c) {
         if (!((mask >> c) & 1u) || (forced >= 0 && c != forced)) continue;
-        const double cost = gemm_cost(kGemmTile[c], tiles_of(kGemmTile[c]), nk, cus);
+        const double cost = gemm_cost(table[c], tiles_of(table[c]), nk, cus);
         if (best < 0 || cost < best_cost) { best = c; best_cost = cost; }
     }
     if (cost_out) *cost_out = best_cost;
@@ -75,16 +88,19 @@ template <class TilesOf> int cheapest_tile(unsigned mask, const TilesOf& tiles_o
 struct SharePlan {
     int tile, shares;
 };
-inline double shares_traffic_cost(int64_t out, int shares, int elem) { return 3.5 + (8.0 * shares + elem) * out / 4.0e6; }
-inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out = nullptr) {
+// (long products, see kGemmTileLong: as measured together with the products, the last-level cache holds the shares)
+inline double shares_traffic_cost(int64_t out, int shares, int elem, bool lng) {
+    return lng ? 3.3 + (8.0 * shares + elem) * out / 11.5e6 : 3.5 + (8.0 * shares + elem) * out / 4.0e6;
+}
+inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out, bool lng) {
+    const GemmTile* table = lng ? kGemmTileLong : kGemmTile;
     const int64_t out = (int64_t)M * N;
     SharePlan best{-1, 0};
-    double best_cost = 0.95 * whole_cost;
+    double best_cost = (lng ? 1.0 : 0.95) * whole_cost;
     for (int c = 0; c < kGemmTiles; ++c) {
         if (!((kTilesShares >> c) & 1u)) continue;
         for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
-            const double cost = gemm_cost(kGemmTile[c], z * tile_count(M, N, kGemmTile[c]), (nk + z - 1) / z, cus) +
-                                shares_traffic_cost(out, z, elem);
+            const double cost = gemm_cost(table[c], z * tile_count(M, N, table[c]), (nk + z - 1) / z, cus) + shares_traffic_cost(out, z, elem, lng);
             if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
         }
     }
@@ -108,6 +124,9 @@ constexpr int kPpTiles = 5;
 constexpr double kPpLaunch = 6.8;
 constexpr PpTile kPpTile[kPpTiles] = {
     {256, 256, 3.2, 1.04, 1.37}, {192, 256, 1.8, 0.84, 1.05}, {256, 192, 2.0, 0.86, 1.07}, {128, 256, 1.4, 0.69, 0.79}, {256, 128, 1.4, 0.68, 0.78}};
+
+constexpr PpTile kPpTileLong[kPpTiles] = {      // see kGemmTileLong
+    {256, 256, 3.2, 1.01, 1.26}, {192, 256, 2.0, 0.87, 1.02}, {256, 192, 2.0, 0.97, 1.13}, {128, 256, 1.4, 0.71, 0.82}, {256, 128, 1.3, 0.72, 0.84}};
 
 // A product as the kernel of gemm_pingpong.h sees it: leading dimensions, layouts (km: k-major) and zero padding of the operands as in
 // GemmProblem, and its result: columns stored, row pitch, distance of the shares of a split contraction, bytes of an element.
@@ -141,27 +160,32 @@ inline double pp_cost(const PpTile& t, int64_t tiles, int nk, int cus) {
     const double f = std::max(0.0, ((double)n / cus - 0.25) / 0.75);
     return kPpLaunch + (double)(tiles / cus) * (t.o + nk * t.hi) + (n ? t.o + nk * (t.lo + (t.hi - t.lo) * f * f) : 0.0);
 }
-template <class TilesOf> int cheapest_pp_tile(const TilesOf& tiles_of, int nk, int cus, double* cost_out) {
+template <class TilesOf> int cheapest_pp_tile(const TilesOf& tiles_of, int nk, int cus, double* cost_out, const PpTile* table = kPpTile) {
     int best = 0;
     for (int c = 0; c < kPpTiles; ++c) {
-        const double cost = pp_cost(kPpTile[c], tiles_of(kPpTile[c]), nk, cus);
+        const double cost = pp_cost(table[c], tiles_of(table[c]), nk, cus);
         if (c == 0 || cost < *cost_out) { best = c; *cost_out = cost; }
     }
     return best;
 }
 // As plan_shares, for the large tiles; at least four slices to a share.
-inline SharePlan plan_pp_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out) {
+inline SharePlan plan_pp_shares(int M, int N, int nk, int elem, size_t scratch_bytes, int cus, double whole_cost, double* cost_out, bool lng) {
+    const PpTile* table = lng ? kPpTileLong : kPpTile;
     const int64_t out = (int64_t)M * N;
     SharePlan best{-1, 0};
-    double best_cost = 0.95 * whole_cost;
+    double best_cost = (lng ? 1.0 : 0.95) * whole_cost;
     for (int c = 0; c < kPpTiles; ++c)
         for (int z = 2; z <= 16 && nk / z >= 4 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
-            const double cost = pp_cost(kPpTile[c], z * tile_count(M, N, kPpTile[c]), (nk + z - 1) / z, cus) + shares_traffic_cost(out, z, elem);
+            const double cost = pp_cost(table[c], z * tile_count(M, N, table[c]), (nk + z - 1) / z, cus) + shares_traffic_cost(out, z, elem, lng);
             if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
         }
     if (best.tile >= 0) *cost_out = best_cost;
     return best;
 }
+
+// Memory that a workspace holds for the shares of down and dX (bf16): up to eight, as far as 72 MB go (four of 2047 x 2048).  What else
+// is free at that time counts towards it.
+inline size_t share_scratch_wanted(int T, int d) { return std::min((size_t)8 * T * d * sizeof(float), (size_t)72 << 20); }
 
 // How a product runs: whole on a tile of gemm_mfma.h (`mask`; `forced` see cheapest_tile) or, with pp, of gemm_pingpong.h, or, with scratch
 // for it, with every tile's k-slices cut into shares that run as workgroups of their own and are summed afterwards.  The cheapest
@@ -172,22 +196,23 @@ struct GemmRoute {
 };
 inline GemmRoute gemm_route(unsigned mask, int M, int N, int Kc, int Kc2, int elem, bool pp, size_t scratch_bytes, int cus, int forced = -1) {
     const int nk = slice_count(Kc, Kc2), nk64 = pp_slice_count(Kc, Kc2);
+    const bool lng = scratch_bytes && long_product(M, N, Kc, Kc2);
     GemmRoute r;
     double cost = 0.0;
-    r.tile = cheapest_tile(mask, [&](const GemmTile& t) { return tile_count(M, N, t); }, nk, cus, forced, &cost);
+    r.tile = cheapest_tile(mask, [&](const GemmTile& t) { return tile_count(M, N, t); }, nk, cus, forced, &cost, lng ? kGemmTileLong : kGemmTile);
     if (scratch_bytes) {
-        const SharePlan p = plan_shares(M, N, nk, elem, scratch_bytes, cus, cost, &cost);
+        const SharePlan p = plan_shares(M, N, nk, elem, scratch_bytes, cus, cost, &cost, lng);
         if (p.tile >= 0) r = GemmRoute{false, p.tile, p.shares};
     }
     if (!pp) return r;
     double pp_whole = 0.0;
-    const int t = cheapest_pp_tile([&](const PpTile& p) { return tile_count(M, N, p); }, nk64, cus, &pp_whole);
+    const int t = cheapest_pp_tile([&](const PpTile& p) { return tile_count(M, N, p); }, nk64, cus, &pp_whole, lng ? kPpTileLong : kPpTile);
     if (pp_whole < cost) {
         r = GemmRoute{true, t, 1};
         cost = pp_whole;
     }
     if (scratch_bytes) {
-        const SharePlan p = plan_pp_shares(M, N, nk64, elem, scratch_bytes, cus, cost, &cost);
+        const SharePlan p = plan_pp_shares(M, N, nk64, elem, scratch_bytes, cus, cost, &cost, lng);
         if (p.tile >= 0) r = GemmRoute{true, p.tile, p.shares};
     }
     return r;

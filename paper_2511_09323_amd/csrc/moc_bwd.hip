@@ -71,7 +71,7 @@ moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
     // dX = dG W_gate^T + dU W_up^T (bp-5): one GEMM over the concatenated contraction
     GemmProblem<E> px{kc_operand<E>(W.dGd, D.ldF, W.dUd), km_operand<E>(wg, D.d, D.d, wu), D.T, D.d, D.F, D.F, true};
     // (the dense dZ' and Z' are not needed any more)
-    const ShareScratch scratch{reinterpret_cast<float*>(DENSE ? W.Zd : W.dZd), (size_t)D.T * D.ldF * (DENSE ? 1 : 2) * sizeof(E)};
+    const ShareScratch scratch{W.share, W.share_bytes};
     return run_gemm<E, false, true>("gemm_dx", px, EpiStore<E>{dx, D.d, D.d, 0}, st, nullptr, false, scratch);
 }
 

@@ -59,7 +59,7 @@ moc_status fwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
         }
     }
     // (G and U, one after the other, are not needed any more)
-    return down_projection<E>(D, W.Zd, wd, y, st, ShareScratch{W.G, (size_t)D.T * D.ldF * (sizeof(float) + sizeof(E))});
+    return down_projection<E>(D, W.Zd, wd, y, st, ShareScratch{W.G, W.share_bytes});
 }
 
 // ------------------------------------------------------------ MoC inside MoE experts

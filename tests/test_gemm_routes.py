@@ -8,7 +8,7 @@ import pytest
 
 from tests.test_gpu_experts import MIXTRAL_180M
 from tests.test_gpu_gemm_tiles import CASES as TILE_CASES
-from tests.test_gpu_large_tiles import CASES, EXPERT_CASES
+from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -44,6 +44,15 @@ static void products(int T, int d, int F) {
     say("dw", batch3_route(F, d, T, pp_sizes_ok(to_weights(T, d, F)), kCus));
     say("down", gemm_route(kTilesKm, T, d, F, 0, 2, pp_sizes_ok(to_model(T, d, F, 0)), (size_t)T * ldf(F) * 6, kCus));
     say("dx", gemm_route(kTilesKm, T, d, F, F, 2, pp_sizes_ok(to_model(T, d, F, F)), (size_t)T * ldf(F) * 4, kCus));
+    std::puts("");
+}
+// the products over the channels with all of a workspace's scratch
+static void over_channels(int T, int d, int F) {
+    for (int two : {0, 1}) {
+        EXPECT(two == 0 || long_product(T, d, F, F));
+        const size_t scratch = std::max((size_t)T * ldf(F) * (two ? 4 : 6), share_scratch_wanted(T, d));
+        say(two ? "dx" : "down", gemm_route(kTilesKm, T, d, F, two * F, 2, pp_sizes_ok(to_model(T, d, F, two * F)), scratch, kCus));
+    }
     std::puts("");
 }
 // of experts with `counts` rows
@@ -199,7 +208,8 @@ int main(int argc, char** argv) {
         std::vector<int> counts;
         for (int i = 4; i < argc; ++i) counts.push_back(std::atoi(argv[i]));
         experts(std::atoi(argv[2]), std::atoi(argv[3]), (int)counts.size(), counts.data());
-    } else products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
+    } else if (!std::strcmp(argv[1], "long")) over_channels(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
+    else products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
 
@@ -233,6 +243,12 @@ def test_decodes_that_take_the_streamed_gate(plan):
 def test_cases_take_the_kernels_they_name(plan):
     for T, d, F, _, want in CASES + TILE_CASES:
         got = plan(T, d, F).stdout.split()
+        assert set(want.split()) <= set(got), (T, d, F, want, got)
+
+
+def test_long_cases_take_the_kernels_they_name(plan):
+    for T, d, F, _, want in LONG_CASES:
+        got = plan("long", T, d, F).stdout.split()
         assert set(want.split()) <= set(got), (T, d, F, want, got)
 
 

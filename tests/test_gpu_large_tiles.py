@@ -42,6 +42,23 @@ def test_large_tiles(T, d, F, K, kernels):
     run_fwd_bwd_case("large tiles " + kernels, 97, T, d, F, K, "bf16")
 
 
+# Products over the channels whose weights come from memory (long_product), with the scratch that a workspace holds for their shares
+LONG_CASES = [
+    (40, 2048, 2050, 256, "down=64x128/8 dx=64x128/8"),        # as many shares as there is scratch for; a contraction of 32 slices and two channels
+    (300, 2048, 2050, 256, "down=64x128/3 dx=128x128/5"),
+    (130, 2112, 2000, 250, "down=64x128/5 dx=128x128/7"),
+    (700, 2048, 2100, 262, "down=64x128 dx=192x128/4"),
+    (1100, 1280, 3300, 412, "down=192x128/4 dx=192x128/4"),
+    (1500, 2048, 2056, 257, "down=128x128 dx=pp192x256/4"),
+    (2047, 2048, 2056, 257, "dx=pp128x256/2"),
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,kernels", LONG_CASES)
+def test_long_products(T, d, F, K, kernels):
+    run_fwd_bwd_case("long products " + kernels, 94, T, d, F, K, "bf16")
+
+
 # rows of the experts, d, F, K, kernels (a large tile of dw and down with its rounds of the workgroups: xN)
 EXPERT_CASES = [
     ([700, 0, 1, 513, 300, 64, 257, 900], 128, 2736, 342, "gate_up=pp192x256 dz=128x128 dw=pp256x128"),      # one short of and past a tile, no and one row
