@@ -138,7 +138,8 @@ struct PpOut {
 //   NB <= 3: the tiles of all problems in a row, XCD x takes the x-th eighth (neighbouring tiles share operand panels in its L2).
 //   NB > 3 (experts, whose row counts differ): XCD x takes the x-th eighth of EVERY problem, in the order of the problems, which the host
 //     sorts by the length of the contraction, and every second round of its workgroups goes backwards, so that long and short
-//     contractions add up alike.  Eight experts of 768 x 2048 with 2000 to 6000 rows each (24 weight gradients): 370 us with
+//     contractions add up alike.  Weight gradients go to one XCD whole (owner) where the XCDs' loads are as even that way (pp_owners): its
+//     L2 then serves every operand panel to all tiles.  Eight experts of 768 x 2048 with 2000 to 6000 rows each (24 weight gradients): 370 us with
 //     the whole list cut into eighths, where one XCD got one expert.
 template <int NB> struct PpWork {
     static constexpr bool kSpread = NB > 3;
@@ -147,6 +148,8 @@ template <int NB> struct PpWork {
     int tiles[NB];
     int cum[kSpread ? 8 : 1][NB + 1];      // items before problem z: of XCD x, or of all
     int nprob, tiles_n, nsplit;
+    int height = 4;                        // kSpread: rows of tiles in a band
+    int8_t owner[kSpread ? NB : 1];        // kSpread: the XCD that has all tiles of problem z, or -1
 };
 
 // F32: 0 = every result bf16, 1 = every result fp32, 2 = as PpOut says.
@@ -205,9 +208,9 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
 #pragma unroll
         for (int z = 1; z < NB; ++z) t.z += mapped >= cum[z];
         int logical = mapped - cum[t.z];
-        if (kSpread) logical += w.tiles[t.z] * xcd / 8;
+        if (kSpread && w.owner[t.z] < 0) logical += w.tiles[t.z] * xcd / 8;
         const int tiles_m = w.tiles[t.z] / w.tiles_n;
-        const int height = w.tiles_n >= 32 ? 8 : 4;      // band height, see gemm_bf16_mfma_tiles
+        const int height = kSpread ? w.height : w.tiles_n >= 32 ? 8 : 4;      // band height, see gemm_bf16_mfma_tiles
         const int band = logical / (height * w.tiles_n);
         const int first_m = band * height;
         const int rows = min(tiles_m - first_m, height);
@@ -454,9 +457,22 @@ template <int BM, int BN, bool AKM, bool BKM, int F32, int NB> inline hipError_t
     for (int z = 0; z < NB; ++z) w.tiles[z] = z < w.nprob ? (w.pr[z].M + BM - 1) / BM * w.tiles_n : 0;
     constexpr int kLists = PpWork<NB>::kSpread ? 8 : 1;
     int longest = 0;
+    if constexpr (kLists > 1) {
+        w.height = pp_band_height(BM, BN, *std::max_element(w.tiles, w.tiles + NB) / 8);
+        std::fill(w.owner, w.owner + NB, (int8_t)-1);
+        if constexpr (AKM && BKM) {
+            int slices[NB];
+            for (int z = 0; z < w.nprob; ++z) slices[z] = pp_slice_count(w.pr[z].Kc, w.pr[z].Kc2);
+            if (pp_owners(w.nprob, slices, w.tiles, std::max(1, wgs / 8), w.owner)) w.height = pp_band_height(BM, BN, std::min(w.tiles[0], wgs / 8));
+        }
+    }
     for (int x = 0; x < kLists; ++x) {
         w.cum[x][0] = 0;
-        for (int z = 0; z < NB; ++z) w.cum[x][z + 1] = w.cum[x][z] + (w.tiles[z] * (x + 1) / kLists - w.tiles[z] * x / kLists);
+        for (int z = 0; z < NB; ++z) {
+            int n = w.tiles[z] * (x + 1) / kLists - w.tiles[z] * x / kLists;
+            if (kLists > 1 && w.owner[z] >= 0) n = w.owner[z] == x ? w.tiles[z] : 0;
+            w.cum[x][z + 1] = w.cum[x][z] + n;
+        }
         longest = std::max(longest, w.cum[x][NB]);
     }
     const int total = kLists * longest * w.nsplit;

@@ -153,6 +153,47 @@ inline bool pp_sizes_ok(const PpSizes& s) {
     return s.out_n * s.elem % 16 == 0 && s.ldc * s.elem % 16 == 0 && s.stride * s.elem % 16 == 0 && 256 * s.ldc * s.elem < (1ll << 31);
 }
 
+// Rows of tiles in a band where an XCD takes `tiles` neighbouring tiles of a problem: the height at which these touch the fewest operand
+// panels, which come from beyond its L2 (four tiles: a 2 x 2 block instead of a column, see pp_owners).
+inline int pp_band_height(int bm, int bn, int tiles) {
+    int best = 1;
+    for (int h = 2; h <= 8; h *= 2)
+        if (h * bm + tiles * bn / h < best * bm + tiles * bn / best) best = h;
+    return best;
+}
+// Problems (in the order of their contraction lengths, `slices` to a tile, all of as many tiles) to whole XCDs of `width` workgroups, the longest
+// first to the XCD with the least work; false, and owner[] untouched, unless the busiest workgroup has no more to do than with an eighth of
+// every problem on every XCD.  Eight experts of 768 x 2048 with 2000 to 6000 rows (24 weight gradients of 32 tiles): an eighth of each means
+// panels of eight problems a round from beyond every L2, 5 TB/s of them: 310 us in bands of four tile rows, 296 in bands of two, 277 whole.
+inline bool pp_owners(int n, const int* slices, const int* tiles, int width, int8_t* owner) {
+    constexpr int kMost = 24, kWidth = 64;
+    if (n < 8 || n > kMost || width > kWidth || tiles[0] > 4 * width) return false;
+    for (int z = 1; z < n; ++z)
+        if (tiles[z] != tiles[0]) return false;
+    int8_t to[kMost];
+    int64_t load[8] = {};
+    for (int z = 0; z < n; ++z) {
+        to[z] = (int8_t)(std::min_element(load, load + 8) - load);
+        load[to[z]] += slices[z] + 2;      // (two slices' time to write a tile)
+    }
+    // the busiest workgroup, dealt as the kernel does: every second round backwards
+    const auto busiest = [&](bool whole) {
+        int64_t most = 0;
+        for (int x = 0; x < 8; ++x) {
+            int64_t wg[kWidth] = {};
+            int at = 0;
+            for (int z = 0; z < n; ++z) {
+                const int count = !whole ? tiles[z] * (x + 1) / 8 - tiles[z] * x / 8 : to[z] == x ? tiles[z] : 0;
+                for (int i = 0; i < count; ++i, ++at) wg[(at / width) & 1 ? width - 1 - at % width : at % width] += slices[z] + 2;
+            }
+            for (int i = 0; i < width; ++i) most = std::max(most, wg[i]);
+        }
+        return most;
+    };
+    if (100 * busiest(true) > 103 * busiest(false)) return false;
+    std::copy(to, to + n, owner);
+    return true;
+}
 inline int64_t tile_count(int M, int N, const PpTile& t) { return (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
 inline int pp_slice_count(int Kc, int Kc2) { return (Kc + kPpBK - 1) / kPpBK + (Kc2 + kPpBK - 1) / kPpBK; }
 inline double pp_cost(const PpTile& t, int64_t tiles, int nk, int cus) {

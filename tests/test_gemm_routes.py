@@ -184,6 +184,29 @@ static void sizes() {
     EXPECT(refused([](PpSizes& s) { s.stride = 4; }));
     std::puts("ok");
 }
+// Weight gradients of experts on whole XCDs: who owns what, and when.
+static void owners() {
+    int8_t own[24];
+    const auto take = [&](std::vector<int> rows, int F, int d, int bm, int bn) {
+        std::sort(rows.rbegin(), rows.rend());
+        std::vector<int> slices, tiles;
+        for (int r : rows)
+            for (int k = 0; k < 3; ++k) {
+                slices.push_back(pp_slice_count(r, 0));
+                tiles.push_back((F + bm - 1) / bm * ((d + bn - 1) / bn));
+            }
+        std::fill(own, own + 24, (int8_t)-1);
+        const bool whole = pp_owners((int)slices.size(), slices.data(), tiles.data(), 32, own);
+        for (size_t z = 0; z < slices.size(); ++z) EXPECT(whole ? own[z] >= 0 && own[z] < 8 : own[z] == -1);
+        return whole;
+    };
+    EXPECT(take({6000, 2500, 3000, 4100, 5200, 3300, 3900, 4768}, 2048, 768, 256, 192));      // 32 tiles a problem: whole
+    EXPECT(take({700, 1, 513, 300, 64, 257, 900}, 2736, 128, 256, 128));                      // (a case of test_gpu_large_tiles.py)
+    EXPECT(!take({4000, 4000}, 2048, 768, 256, 192));                                         // fewer problems than XCDs
+    EXPECT(!take({25000, 1000, 1000, 1000, 1000, 1000, 1000, 768}, 2048, 768, 256, 192));     // one expert has most rows
+    EXPECT(!take({4096, 4096, 4096, 4096, 4096, 4096, 4096, 4096}, 11008, 1024, 128, 256));   // many rounds: nothing shared beyond them
+    std::puts("ok");
+}
 static void gate() {
     struct Row { int B, d, F; bool grouped, pays; };
     for (const Row& r : {Row{1, 4096, 11008, false, false}, Row{2, 4096, 11008, false, true}, Row{4, 4096, 11008, true, true},
@@ -203,7 +226,7 @@ static void gate() {
 }
 int main(int argc, char** argv) {
     if (argc == 1) routes();
-    else if (argc == 2) (std::strcmp(argv[1], "gate") ? sizes : gate)();
+    else if (argc == 2) (!std::strcmp(argv[1], "gate") ? gate : !std::strcmp(argv[1], "owners") ? owners : sizes)();
     else if (!std::strcmp(argv[1], "experts")) {
         std::vector<int> counts;
         for (int i = 4; i < argc; ++i) counts.push_back(std::atoi(argv[i]));
@@ -231,6 +254,11 @@ def test_routes_stay_within_what_the_launchers_take(plan):
 def test_sizes_that_large_tiles_take(plan):
     """Every 32-bit offset of gemm_bf16_pp_kernel, up to the largest operands that pp_sizes_ok admits (near 4 GiB)."""
     r = plan("sizes")
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_weight_gradients_of_experts_on_whole_xcds(plan):
+    r = plan("owners")
     assert r.returncode == 0, r.stdout + r.stderr
 
 
