@@ -203,7 +203,7 @@ static void owners() {
     EXPECT(take({6000, 2500, 3000, 4100, 5200, 3300, 3900, 4768}, 2048, 768, 256, 192));      // 32 tiles a problem: whole
     EXPECT(take({700, 1, 513, 300, 64, 257, 900}, 2736, 128, 256, 128));                      // (a case of test_gpu_large_tiles.py)
     EXPECT(!take({4000, 4000}, 2048, 768, 256, 192));                                         // fewer problems than XCDs
-    EXPECT(!take({25000, 1000, 1000, 1000, 1000, 1000, 1000, 768}, 2048, 768, 256, 192));     // one expert has most rows
+    EXPECT(!take({25000, 1000, 1000, 1000, 1000, 1000, 1000, 768}, 4096, 768, 256, 192));     // one expert has most rows: two of its 64 tiles to a workgroup
     EXPECT(!take({4096, 4096, 4096, 4096, 4096, 4096, 4096, 4096}, 11008, 1024, 128, 256));   // many rounds: nothing shared beyond them
     std::puts("ok");
 }
