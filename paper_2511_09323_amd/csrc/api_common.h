@@ -196,7 +196,7 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
     E *dZd, *Zd, *dGd, *dUd;
     StreamKArea sk;
     float* share = nullptr;            // free while dX runs: up to the end of Zd
-    size_t share_bytes = 0;
+    size_t share_bytes = 0, dw_share_bytes = 0;      // (while the weight gradients run: up to the end of dZd)
     size_t bytes;
     BwdWs(void* ws, const Dims& D, bool dense) {
         Carver c(ws);
@@ -205,6 +205,7 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
         const size_t dense_bytes = (size_t)D.T * D.ldF * sizeof(E), before = c.off;
         if (!dense) share = reinterpret_cast<float*>(c.take<unsigned char>(extra_share_bytes<E>(D, 2 * dense_bytes)));
         dZd = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
+        dw_share_bytes = c.off - before;
         const size_t rows = (size_t)D.T + kMaxExperts * (kRowPad - 1);
         Zd = c.take<E>(rows * D.ldF);
         if (dense) share = reinterpret_cast<float*>(Zd);

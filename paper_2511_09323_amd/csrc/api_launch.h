@@ -226,7 +226,7 @@ template <bool AKM, bool BKM, int F32, int NB> hipError_t launch_pp_group(int ti
 // tiles of all three.
 template <class E>
 moc_status run_gemm_batch3(const char* name, const char* const names[3], const GemmProblem<E> pr[3], const EpiStore<E> epi[3],
-                           hipStream_t st, const StreamKArea* sk = nullptr) {
+                           hipStream_t st, const StreamKArea* sk = nullptr, const ShareScratch& scratch = ShareScratch{}) {
     if constexpr (std::is_same<E, bf16_t>::value) {
         const bool same = pr[0].M == pr[1].M && pr[0].M == pr[2].M && pr[0].N == pr[1].N && pr[0].N == pr[2].N &&
                           pr[0].Kc == pr[1].Kc && pr[0].Kc == pr[2].Kc && pr[0].Kc2 == 0 && pr[1].Kc2 == 0 && pr[2].Kc2 == 0;
@@ -238,10 +238,37 @@ moc_status run_gemm_batch3(const char* name, const char* const names[3], const G
             const GemmRoute route = batch3_route(pr[0].M, pr[0].N, pr[0].Kc, pp, std::max(1, device_cu_count()), forced_tile());
             if (route.pp) {
                 Span span(name, st);
+                const int M = pr[0].M, N = pr[0].N;
+                const bool tight = epi[0].ldc == N && epi[1].ldc == N && epi[2].ldc == N && epi[0].N == N && epi[1].N == N && epi[2].N == N;
+                const Batch3Split split = tight && scratch.p && persistent_workgroups() ? batch3_split(M, N, pr[0].Kc, route, scratch.bytes, std::max(1, device_cu_count()))
+                                                                                        : Batch3Split{};
                 PpWork<3> w;
                 for (int i = 0; i < 3; ++i) { w.pr[i] = pr[i]; w.out[i] = pp_out(epi[i]); }
                 w.nprob = 3;
-                const hipError_t e = launch_pp_group<true, true, 0, 3>(route.tile, w, st);
+                if (split.rows)
+                    for (int i = 0; i < 3; ++i) w.pr[i].M = split.rows;
+                hipError_t e = launch_pp_group<true, true, 0, 3>(split.rows ? split.main : route.tile, w, st);
+                if (e == hipSuccess && split.rows) {
+                    // the rows behind the whole rounds, their contraction in shares
+                    const int left = M - split.rows;
+                    const int64_t out = (int64_t)left * N, n4 = out / 4;
+                    ReduceOuts<bf16_t> outs;
+                    for (int i = 0; i < 3; ++i) {
+                        w.pr[i].M = left;
+                        w.pr[i].A.p += split.rows;
+                        w.pr[i].A.ext -= split.rows;
+                        w.out[i] = PpOut{scratch.p + (int64_t)i * split.shares * out, N, out, N, 1};
+                        outs.p[i] = epi[i].C + (int64_t)split.rows * N;
+                    }
+                    w.nsplit = split.shares;
+                    e = split.rest == 0 ? launch_gemm_bf16_pp<256, 256, true, true, 1, 3>(w, persistent_workgroups(), st)
+                                        : launch_gemm_bf16_pp<128, 256, true, true, 1, 3>(w, persistent_workgroups(), st);
+                    if (e == hipSuccess) {
+                        hipLaunchKernelGGL((reduce_shares_batch_kernel<bf16_t>), dim3((unsigned)((n4 + 255) / 256), 3), dim3(256), 0, st, scratch.p, split.shares,
+                                           out, n4, outs);
+                        e = hipGetLastError();
+                    }
+                }
                 if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
                 return MOC_OK;
             }

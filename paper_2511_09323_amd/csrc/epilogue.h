@@ -63,6 +63,21 @@ __global__ __launch_bounds__(256) void reduce_shares_kernel(const float* __restr
     store_vec4<E>(out + i * 4, v);
 }
 
+// The same for up to three products of one size (blockIdx.y), the shares of product b from part + b * nsplit * stride on.
+template <class E> struct ReduceOuts {
+    E* p[3];
+};
+template <class E>
+__global__ __launch_bounds__(256) void reduce_shares_batch_kernel(const float* __restrict__ part, int nsplit, int64_t stride, int64_t n4, ReduceOuts<E> out) {
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= n4) return;
+    const float* p = part + blockIdx.y * nsplit * stride + i * 4;
+    f32x4_t s = *reinterpret_cast<const f32x4_t*>(p);
+    for (int z = 1; z < nsplit; ++z) s += *reinterpret_cast<const f32x4_t*>(p + z * stride);
+    const float v[4] = {s[0], s[1], s[2], s[3]};
+    store_vec4<E>(out.p[blockIdx.y] + i * 4, v);
+}
+
 // Dense SwiGLU forward, second GEMM (m = token, n = channel): acc = U.  Reads the stored gate,
 // writes u_save and the dense activation Z = SiLU(G) . U (Eq. FFN-2) padded with zeros to ldz.
 template <class E> struct EpiSwigluAct {

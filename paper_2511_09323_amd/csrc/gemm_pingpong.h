@@ -132,7 +132,7 @@ struct PpOut {
 };
 
 // Up to NB problems in one launch that agree in N, both leading dimensions and the layouts; problem z has tiles[z] tiles, tiles_n to a
-// row of tiles.  With nsplit > 1 (one problem) item i is share i / tiles of tile i % tiles: the shares are ranges of whole slices.
+// row of tiles.  With nsplit > 1 (up to three problems) item i is share i / tiles of tile i % tiles: the shares are ranges of whole slices.
 //
 // The items are the tiles, dealt to the XCDs as follows; an XCD's workgroups take its items in turn.
 //   NB <= 3: the tiles of all problems in a row, XCD x takes the x-th eighth (neighbouring tiles share operand panels in its L2).
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     constexpr bool kSpread = PpWork<NB>::kSpread;
     const int xcd = blockIdx.x & 7;
     const int* const cum = w.cum[kSpread ? xcd : 0];
-    const int tiles = cum[NB], total = tiles * (NB == 1 ? w.nsplit : 1);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
+    const int tiles = cum[NB], total = tiles * (kSpread ? 1 : w.nsplit);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
     const uint32_t lda = (uint32_t)w.pr[0].A.ld, ldb = (uint32_t)w.pr[0].B.ld;
 
     const uint32_t lds_a = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem);
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     auto item_at = [&](int mapped) {
         Item t;
         t.share = 0;
-        if (NB == 1 && w.nsplit > 1) {
+        if (!kSpread && w.nsplit > 1) {
             t.share = mapped / tiles;
             mapped -= t.share * tiles;
         }
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     auto begin = [&](const Item& t, int& slices) {
         const MfmaProblem& pr = w.pr[t.z];
         const int nk0 = (pr.Kc + kPpBK - 1) / kPpBK, nk = nk0 + (pr.Kc2 + kPpBK - 1) / kPpBK;
-        const int from = NB == 1 ? nk * t.share / w.nsplit : 0, to = NB == 1 ? nk * (t.share + 1) / w.nsplit : nk;
+        const int from = kSpread ? 0 : nk * t.share / w.nsplit, to = kSpread ? nk : nk * (t.share + 1) / w.nsplit;
         slices = to - from;
         Stream s;
         s.a_bytes = (uint32_t)(AKM ? pr.Kc : pr.M) * lda * 2u;

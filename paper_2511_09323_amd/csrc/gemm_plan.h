@@ -294,6 +294,42 @@ inline GemmRoute batch3_route(int M, int N, int Kc, bool pp, int cus, int forced
     return group_route(kTilesKm, [&](const GemmTile& t) { return 3 * tile_count(M, N, t); }, [&](const PpTile& t) { return 3 * tile_count(M, N, t); },
                        slice_count(Kc, 0), pp_slice_count(Kc, 0), pp, cus, forced, &cost);
 }
+// Weight gradients of many tokens whose tiles fill whole rounds and a little of another: the first `rows` rows, whole rounds, in one launch on
+// tile `main`, the others in a second one on tile `rest` with their contraction in shares, summed by a third.  rows = 0 where that is not cheaper
+// than the one launch of batch3_route.  The costs are those of k-major operands from memory (the same shapes and formula as kPpTile).
+// The layer step of 8192 tokens, 2048 x 5461 (504 tiles in two rounds, then 85 rows in ten shares): 1393 -> 1325 us.
+constexpr PpTile kPpTileWeights[kPpTiles] = {
+    {256, 256, 3.2, 1.09, 1.40}, {192, 256, 1.8, 1.04, 1.27}, {256, 192, 2.0, 1.02, 1.19}, {128, 256, 1.4, 0.80, 0.85}, {256, 128, 1.4, 0.80, 0.85}};
+struct Batch3Split {
+    int rows = 0, main = 0, rest = 0, shares = 0;
+};
+constexpr int kBatch3MinSlices = 32;      // fewer tokens: the second and third launch are not won back
+inline Batch3Split batch3_split(int M, int N, int Kc, const GemmRoute& whole, size_t scratch_bytes, int cus) {
+    const int nk = pp_slice_count(Kc, 0);
+    Batch3Split best;
+    if (!whole.pp || nk < kBatch3MinSlices || N % 4 != 0) return best;
+    double cost = 0.97 * pp_cost(kPpTileWeights[whole.tile], 3 * tile_count(M, N, kPpTileWeights[whole.tile]), nk, cus);
+    for (int c = 0; c < kPpTiles; ++c) {
+        const PpTile& t = kPpTileWeights[c];
+        const int tiles_n = (N + t.bn - 1) / t.bn, strips = (M + t.bm - 1) / t.bm;
+        for (int r = 1; r <= 8; ++r) {
+            const int full = r * cus / (3 * tiles_n);      // strips of tile rows that r rounds hold
+            if (full < 1 || full >= strips) continue;
+            const int rows = full * t.bm, left = M - rows;
+            const double main = pp_cost(t, (int64_t)3 * full * tiles_n, nk, cus);
+            for (int q : {0, 3})
+                for (int z = 2; z <= 16 && nk / z >= 4 && (size_t)3 * z * left * N * sizeof(float) <= scratch_bytes; ++z) {
+                    const double c2 = main + pp_cost(kPpTileWeights[q], (int64_t)3 * z * tile_count(left, N, kPpTileWeights[q]), (nk + z - 1) / z, cus) +
+                                      shares_traffic_cost((int64_t)3 * left * N, z, 2, true);
+                    if (c2 < cost) {
+                        best = Batch3Split{rows, c, q, z};
+                        cost = c2;
+                    }
+                }
+        }
+    }
+    return best;
+}
 // Products of M[z] x N with contractions Kc[z], Kc2[z] (experts) in one launch; those without rows count for nothing.
 inline GemmRoute grouped_route(unsigned mask, int n, const int* M, int N, const int* Kc, const int* Kc2, bool pp, int cus, int forced, double* cost) {
     int64_t rows = 0, slices = 0, slices64 = 0;

@@ -67,7 +67,9 @@ moc_status bwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
         {km_operand<E>(W.dUd, D.ldF, D.ldF), km_operand<E>(x, D.d, D.d), D.F, D.d, D.T, 0, true}};
     const EpiStore<E> ew[3] = {{dwd, D.d, D.d, 0}, {dwg, D.d, D.d, 0}, {dwu, D.d, D.d, 0}};
     static const char* const wnames[3] = {"gemm_dwd", "gemm_dwg", "gemm_dwu"};
-    if ((s = run_gemm_batch3<E>("gemm_dw3", wnames, pw, ew, st, &W.sk)) != MOC_OK) return s;
+    // (dZ' is not needed any more)
+    const ShareScratch dw_scratch{DENSE ? nullptr : W.share, W.dw_share_bytes};
+    if ((s = run_gemm_batch3<E>("gemm_dw3", wnames, pw, ew, st, &W.sk, dw_scratch)) != MOC_OK) return s;
     // dX = dG W_gate^T + dU W_up^T (bp-5): one GEMM over the concatenated contraction
     GemmProblem<E> px{kc_operand<E>(W.dGd, D.ldF, W.dUd), km_operand<E>(wg, D.d, D.d, wu), D.T, D.d, D.F, D.F, true};
     // (the dense dZ' and Z' are not needed any more)

@@ -8,7 +8,7 @@ import pytest
 
 from tests.test_gpu_experts import MIXTRAL_180M
 from tests.test_gpu_gemm_tiles import CASES as TILE_CASES
-from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES
+from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES, SPLIT_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -54,6 +54,15 @@ static void over_channels(int T, int d, int F) {
         say(two ? "dx" : "down", gemm_route(kTilesKm, T, d, F, two * F, 2, pp_sizes_ok(to_model(T, d, F, two * F)), scratch, kCus));
     }
     std::puts("");
+}
+// the weight gradients with what a workspace has for them
+static void weights(int T, int d, int F) {
+    const size_t dense = (size_t)T * ldf(F) * 2, want = share_scratch_wanted(T, d), scratch = dense + (want > 2 * dense ? want - 2 * dense : 0);
+    const Batch3Split s = batch3_split(F, d, T, batch3_route(F, d, T, pp_sizes_ok(to_weights(T, d, F)), kCus), scratch, kCus);
+    EXPECT(s.rows == 0 || (s.rows < F && s.rows % kPpTile[s.main].bm == 0 && (size_t)3 * s.shares * (F - s.rows) * d * 4 <= scratch));
+    EXPECT(s.rows == 0 || s.rest == 0 || s.rest == 3);
+    if (s.rows) std::printf("%d pp%dx%d pp%dx%d/%d\n", s.rows, kPpTile[s.main].bm, kPpTile[s.main].bn, kPpTile[s.rest].bm, kPpTile[s.rest].bn, s.shares);
+    else std::puts("whole");
 }
 // of experts with `counts` rows
 static void experts(int d, int F, int n, const int* counts) {
@@ -232,6 +241,7 @@ int main(int argc, char** argv) {
         for (int i = 4; i < argc; ++i) counts.push_back(std::atoi(argv[i]));
         experts(std::atoi(argv[2]), std::atoi(argv[3]), (int)counts.size(), counts.data());
     } else if (!std::strcmp(argv[1], "long")) over_channels(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
+    else if (!std::strcmp(argv[1], "weights")) weights(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]));
     else products(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
 }
 """
@@ -278,6 +288,14 @@ def test_long_cases_take_the_kernels_they_name(plan):
     for T, d, F, _, want in LONG_CASES:
         got = plan("long", T, d, F).stdout.split()
         assert set(want.split()) <= set(got), (T, d, F, want, got)
+
+
+def test_weight_gradients_are_split_as_named(plan):
+    for T, d, F, _, want in SPLIT_CASES:
+        r = plan("weights", T, d, F)
+        assert r.stdout.strip() == want, (T, d, F, want, r.stdout)
+    for T, d, F in ((1984, 2048, 5461), (4096, 768, 2048), (8192, 2048, 200)):      # few tokens; one round; a few tiles
+        assert plan("weights", T, d, F).stdout.strip() == "whole", (T, d, F)
 
 
 def test_expert_cases_take_the_kernels_they_name(plan):

@@ -59,6 +59,22 @@ def test_long_products(T, d, F, K, kernels):
     run_fwd_bwd_case("long products " + kernels, 94, T, d, F, K, "bf16")
 
 
+# Weight gradients in whole rounds of tiles and a second launch for the rows behind them, whose contraction runs in shares (batch3_split): rows of
+# the first launch, its tile, tile and shares of the second.
+SPLIT_CASES = [
+    (2049, 1536, 3700, 462, "3584 pp256x256 pp128x256/7"),     # one token past a slice; 116 rows left
+    (2300, 2048, 2731, 341, "2560 pp256x256 pp128x256/4"),     # 171: a second tile of 43
+    # (d 1280: a gate value of 2048 products differs from float64 by up to 2^-24 sqrt(2048) = 2.7e-6 of its size, more than the 1e-6 window of the cut,
+    # which one row in thousands meets at 2048 x 6200)
+    (2049, 1280, 9939, 1242, "8704 pp256x256 pp256x256/2"),
+]
+
+
+@pytest.mark.parametrize("T,d,F,K,plan", SPLIT_CASES)
+def test_weight_gradients_in_two_launches(T, d, F, K, plan):
+    run_fwd_bwd_case("split " + plan, 93, T, d, F, K, "bf16")
+
+
 # rows of the experts, d, F, K, kernels (a large tile of dw and down with its rounds of the workgroups: xN)
 EXPERT_CASES = [
     ([700, 0, 1, 513, 300, 64, 257, 900], 128, 2736, 342, "gate_up=pp192x256 dz=128x128 dw=pp256x128"),      # one short of and past a tile, no and one row
