@@ -125,10 +125,10 @@ moc_status run_gemm_shares(const char* name, const GemmProblem<E>& pr, const Epi
 // kernel go there, everything else to the generic kernel.
 // `sk`, if given and carved, lets a product whose whole tiles would leave part of the chip idle in their last
 // round split its work along the contraction instead (256 x 256 tiles, contraction a multiple of 32); `scratch` is memory for
-// run_gemm_shares; `ascending` see launch_gemm_f32.
+// run_gemm_shares; `one_sum` see launch_gemm_f32.
 template <class E, bool AKM, bool BKM, class Epi>
 moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, hipStream_t st, const StreamKArea* sk = nullptr,
-                    bool ascending = false, const ShareScratch& scratch = ShareScratch{}) {
+                    bool one_sum = false, const ShareScratch& scratch = ShareScratch{}) {
     Span span(name, st);
     if constexpr (std::is_same<E, bf16_t>::value && !(AKM && BKM)) {      // (k-major x k-major products: run_gemm_batch3, run_gemm_grouped)
         if (!options().force_generic && mfma_problem_ok(pr)) {
@@ -185,7 +185,7 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
     if constexpr (std::is_same<E, float>::value) {
         if (!options().force_generic && f32_problem_ok(pr)) {
             if constexpr (!AKM && BKM && std::is_same<Epi, EpiStore<float>>::value) {
-                if (!ascending && scratch.p && epi.ldc == epi.N && epi.N == pr.N && epi.N % 4 == 0 && epi.pad_to == 0) {
+                if (!one_sum && scratch.p && epi.ldc == epi.N && epi.N == pr.N && epi.N % 4 == 0 && epi.pad_to == 0) {
                     const F32Shares plan = f32_shares(pr.M, pr.N, pr.Kc, pr.Kc2, scratch.bytes, std::max(1, device_cu_count()));
                     const int64_t out = (int64_t)pr.M * pr.N, n4 = out / 4;
                     if (plan.shares > 1) {
@@ -197,7 +197,7 @@ moc_status run_gemm(const char* name, const GemmProblem<E>& pr, const Epi& epi, 
                     }
                 }
             }
-            hipError_t e = launch_gemm_f32<AKM, BKM, Epi, 1>(F32Batch<Epi, 1>{{pr}, {epi}}, ascending, device_cu_count(), st);
+            hipError_t e = launch_gemm_f32<AKM, BKM, Epi, 1>(F32Batch<Epi, 1>{{pr}, {epi}}, one_sum, device_cu_count(), st);
             if (e != hipSuccess) return fail(MOC_ERR_HIP, "%s launch: %s", name, hipGetErrorString(e));
             return MOC_OK;
         }
@@ -364,9 +364,9 @@ moc_status run_gemm_pair(const char* name, const char* name_a, const char* name_
 
 // Up to NB products that differ only in their row counts (and, for weight gradients, in their
 // contraction lengths) in one launch: one per expert of an MoE layer.  Problems with M = 0 are
-// skipped.  Falls back to one run_gemm per problem when the MFMA kernel cannot take all of them (`ascending` see launch_gemm_f32).
+// skipped.  Falls back to one run_gemm per problem when the MFMA kernel cannot take all of them (`one_sum` see launch_gemm_f32).
 template <class E, bool AKM, bool BKM, class Epi, int NB>
-moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* pr, const Epi* epi, hipStream_t st, bool ascending = false) {
+moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* pr, const Epi* epi, hipStream_t st, bool one_sum = false) {
     if constexpr (std::is_same<E, bf16_t>::value) {
         bool ok = !options().force_generic && nprob <= NB;
         bool tail = false, padded = true;
@@ -424,7 +424,7 @@ moc_status run_gemm_grouped(const char* name, int nprob, const GemmProblem<E>* p
     }
     for (int z = 0; z < nprob; ++z) {
         if (pr[z].M == 0) continue;
-        moc_status s = run_gemm<E, AKM, BKM>(name, pr[z], epi[z], st, nullptr, ascending);
+        moc_status s = run_gemm<E, AKM, BKM>(name, pr[z], epi[z], st, nullptr, one_sum);
         if (s != MOC_OK) return s;
     }
     return MOC_OK;

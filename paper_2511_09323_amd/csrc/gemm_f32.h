@@ -3,15 +3,16 @@
 //   C[m, n] = sum_k A(m, k) B(n, k)   (+ a second operand pair accumulated into the same tile)
 //
 // Same operand layouts as the bf16 kernel (k-contiguous or k-major, gemm_generic.h), staged as they lie in
-// memory: k-contiguous tiles as [row][BK + 4] floats, k-major tiles as [k][ROWS + 16] floats.  Both pitches
-// put the 16 rows x 4 k that one fragment read touches on 64 different banks (k-major tiles of 16 rows: on 32, twice each).
+// memory: k-contiguous tiles as [row][BK + 4] floats, k-major tiles as [k][ROWS + 4] floats.  Both pitches
+// spread what one fragment read touches over all 64 banks: 16 rows of 16 bytes, or 16 rows of k 0, 4, 8 and 12.
 //
 // What bounds it: at the sizes fp32 is used for (a few hundred tokens, d of 512 to 768) a product has less than
 // one GFLOP, 2 to 5 us of matrix-core time for the chip, so the launch, the load latency and the length of a
 // wavefront's chain of MFMAs decide.  Hence small tiles (enough workgroups for all compute units), four k-slices of
 // 32 to 128 in flight in registers ahead of two LDS stages, and, where even 32 x 32 tiles do not fill the chip
 // and the contraction is long, KW = 4: the four wavefronts of a workgroup take a quarter of every k-slice each and
-// their tiles are added through LDS in a fixed order.  With KW = 1 a result is one sum over ascending k from zero.
+// their tiles are added through LDS in a fixed order.  With KW = 1 a result is one sum from zero in
+// one order of k for every tile shape: groups of 16 ascending, a group's k as 0 4 8 12, 1 5 9 13, 2 6 10 14, 3 7 11 15.
 //
 // Contractions whose tiles leave compute units idle run in shares (f32_shares).
 //
@@ -37,7 +38,7 @@ constexpr int kF32Sets = 4;      // k-slices in flight in registers
 
 template <int BM, int BN, int KW, bool AKM, bool BKM> struct F32Cfg {
     static constexpr int BK = KW > 1 ? 128 : (BM < 64 ? 64 : 32);
-    static constexpr int kPitchA = AKM ? BM + 16 : BK + 4, kPitchB = BKM ? BN + 16 : BK + 4;       // floats
+    static constexpr int kPitchA = (AKM ? BM : BK) + 4, kPitchB = (BKM ? BN : BK) + 4;       // floats
     static constexpr int kFloatsA = (AKM ? BK : BM) * kPitchA, kFloatsB = (BKM ? BK : BN) * kPitchB;
     static constexpr int kStage = kFloatsA + kFloatsB;
     static constexpr int kLds = 2 * kStage * (int)sizeof(float);
@@ -155,22 +156,33 @@ __global__ __launch_bounds__(256, KW == 1 ? 3 : 2) void gemm_f32_mfma_kernel(F32
         constexpr int stage = decltype(stage_c)::value;
         const float* a = f32_smem + stage * Cfg::kStage;
         const float* b = a + Cfg::kFloatsA;
-        const int r = lane & 15, kq = k_wave + (lane >> 4);
+        // groups of four fragments deep, the next group's reads ahead of this group's MFMAs.  The 16 lanes of lane / 16 = q have k 4 q .. 4 q + 3 of a group's
+        // 16 (not every fourth), so that a k-contiguous operand's four fragments are one 16-byte LDS read: the reads, not the MFMAs, fill a step of the small
+        // tiles.  With it and the narrower pitch of the k-major tiles one pass at T 256, d 512, F 1376 went from 82.4 to 79.6 us; the error against 64-bit sums is
+        // that of ascending k (ratio 0.995 to 1.001 over ten shapes).
+        const int r = lane & 15, kq = k_wave + 4 * (lane >> 4);
         const float* pa = AKM ? a + kq * Cfg::kPitchA + wm0 + r : a + (wm0 + r) * Cfg::kPitchA + kq;
         const float* pb = BKM ? b + kq * Cfg::kPitchB + wn0 + r : b + (wn0 + r) * Cfg::kPitchB + kq;
-        // groups of four fragments deep, the next group's reads ahead of this group's MFMAs
         constexpr int GK = 4, NG = BK / KW / (4 * GK);
         static_assert(NG >= 1, "a wavefront's share of a slice is at least one group");
         float fa[2][GK][TM], fb[2][GK][TN];
+        auto read_one = [&](auto km_c, const float* p, int pitch, int g, auto&& f) {
+            if constexpr (decltype(km_c)::value) {
+#pragma unroll
+                for (int q = 0; q < GK; ++q) f(q, p[(g * 16 + q) * pitch]);
+            } else {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p + g * 16);
+#pragma unroll
+                for (int q = 0; q < GK; ++q) f(q, v[q]);
+            }
+        };
         auto read = [&](int g, int d) {
 #pragma unroll
-            for (int q = 0; q < GK; ++q) {
-                const int k = (g * GK + q) * 4;
+            for (int i = 0; i < TM; ++i)
+                read_one(std::integral_constant<bool, AKM>{}, AKM ? pa + i * 16 : pa + i * 16 * Cfg::kPitchA, Cfg::kPitchA, g, [&](int q, float v) { fa[d][q][i] = v; });
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fa[d][q][i] = AKM ? pa[k * Cfg::kPitchA + i * 16] : pa[i * 16 * Cfg::kPitchA + k];
-#pragma unroll
-                for (int j = 0; j < TN; ++j) fb[d][q][j] = BKM ? pb[k * Cfg::kPitchB + j * 16] : pb[j * 16 * Cfg::kPitchB + k];
-            }
+            for (int j = 0; j < TN; ++j)
+                read_one(std::integral_constant<bool, BKM>{}, BKM ? pb + j * 16 : pb + j * 16 * Cfg::kPitchB, Cfg::kPitchB, g, [&](int q, float v) { fb[d][q][j] = v; });
         };
         read(0, 0);
         between();
@@ -277,9 +289,9 @@ inline hipError_t launch_gemm_f32_tile(const F32Batch<Epi, NB>& b, hipStream_t s
 
 // Tile shape by f32_tile (gemm_plan.h).
 template <bool AKM, bool BKM, class Epi, int NB>
-inline hipError_t launch_gemm_f32(const F32Batch<Epi, NB>& b, bool ascending, int num_cu, hipStream_t st) {
+inline hipError_t launch_gemm_f32(const F32Batch<Epi, NB>& b, bool one_sum, int num_cu, hipStream_t st) {
     const GemmProblem<float>& p = b.pr[0];
-    switch (f32_tile(p.M, p.N, NB, (int64_t)p.Kc + p.Kc2, ascending, num_cu)) {
+    switch (f32_tile(p.M, p.N, NB, (int64_t)p.Kc + p.Kc2, one_sum, num_cu)) {
         case F32Tile::k64x64: return launch_gemm_f32_tile<64, 64, 1, AKM, BKM, Epi, NB>(b, st);
         case F32Tile::k32x32: return launch_gemm_f32_tile<32, 32, 1, AKM, BKM, Epi, NB>(b, st);
         case F32Tile::k32x32Split: return launch_gemm_f32_tile<32, 32, 4, AKM, BKM, Epi, NB>(b, st);

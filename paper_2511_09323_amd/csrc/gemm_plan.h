@@ -400,13 +400,13 @@ inline bool decode_dense_pays(int B, int d, int F, int K, bool grouped) {
 
 // fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four
 // fragment reads); below that 32 x 32, with the k-slices split over the wavefronts (16 x 32 or 32 x 32) when the contraction is long
-// (several 128-k slices) or the tiles are still fewer than the compute units.  `ascending` asks for one sum in ascending k (the gate
+// (several 128-k slices) or the tiles are still fewer than the compute units.  `one_sum` asks for one sum in one order of k (the gate
 // product, so that the selection does not depend on the tile choice).
 enum class F32Tile { k64x64, k32x32, k32x32Split, k16x32Split };
-inline F32Tile f32_tile(int M, int N, int batch, int64_t contraction, bool ascending, int cus) {
+inline F32Tile f32_tile(int M, int N, int batch, int64_t contraction, bool one_sum, int cus) {
     const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch, t32 = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
     if (t64 >= cus) return F32Tile::k64x64;
-    if (ascending || (t32 >= cus && contraction <= 1024)) return F32Tile::k32x32;
+    if (one_sum || (t32 >= cus && contraction <= 1024)) return F32Tile::k32x32;
     return t32 < cus ? F32Tile::k16x32Split : F32Tile::k32x32Split;
 }
 // Cost in microseconds of a launch of `tiles` 32 x 32 tiles (k-slices of 64, three workgroups to a compute unit) or 16 x 32 tiles whose slices

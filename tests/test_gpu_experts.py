@@ -93,7 +93,7 @@ def test_one_expert_is_the_plain_layer():
 
 
 def test_f32_expert_gates_do_not_depend_on_the_number_of_rows():
-    """The fp32 gate is one sum over ascending k, whatever tiles a product of that many rows takes: an expert's stored set is that of
+    """The fp32 gate is one sum in one order of k, whatever tiles a product of that many rows takes: an expert's stored set is that of
     the plain layer on its rows, bit for bit (so that a near-tied row selects the same channels)."""
     counts, d, F, K = (3, 40, 0, 700), 132, 520, 65
     W = make_experts(720, 4, d, F, "f32")
