@@ -132,7 +132,7 @@ struct PpOut {
 };
 
 // Up to NB problems in one launch that agree in N, both leading dimensions and the layouts; problem z has tiles[z] tiles, tiles_n to a
-// row of tiles.  With nsplit > 1 (up to three problems) item i is share i / tiles of tile i % tiles: the shares are ranges of whole slices.
+// row of tiles.  With nsplit > 1 (pp_shares) item i is share i / tiles of tile i % tiles: the shares are ranges of whole slices.
 //
 // The items are the tiles, dealt to the XCDs as follows; an XCD's workgroups take its items in turn.
 //   NB <= 3: the tiles of all problems in a row, XCD x takes the x-th eighth (neighbouring tiles share operand panels in its L2).
@@ -153,6 +153,9 @@ template <int NB> struct PpWork {
 };
 
 // F32: 0 = every result bf16, 1 = every result fp32, 2 = as PpOut says.
+// Shares are for one problem, or for three with fp32 results: the other kernels are built without the divisions that find an item's share (gate
+// + up of 4096 x 768 x 2048, 12 slices a tile: 31.8 us with them, 31.5 without).
+template <int F32, int NB> constexpr bool pp_shares = NB == 1 || (NB == 3 && F32 == 1);
 template <int BM, int BN, bool AKM, bool BKM, int F32, int NB>
 __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> w) {
     using C = PpCfg<BM, BN>;
@@ -162,10 +165,10 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / C::WGN, wn = wave % C::WGN;
     const int group = wave >> 2;
-    constexpr bool kSpread = PpWork<NB>::kSpread;
+    constexpr bool kSpread = PpWork<NB>::kSpread, kShares = pp_shares<F32, NB>;
     const int xcd = blockIdx.x & 7;
     const int* const cum = w.cum[kSpread ? xcd : 0];
-    const int tiles = cum[NB], total = tiles * (kSpread ? 1 : w.nsplit);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
+    const int tiles = cum[NB], total = tiles * (kShares ? w.nsplit : 1);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
     const uint32_t lda = (uint32_t)w.pr[0].A.ld, ldb = (uint32_t)w.pr[0].B.ld;
 
     const uint32_t lds_a = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)smem);
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     auto item_at = [&](int mapped) {
         Item t;
         t.share = 0;
-        if (!kSpread && w.nsplit > 1) {
+        if (kShares && w.nsplit > 1) {
             t.share = mapped / tiles;
             mapped -= t.share * tiles;
         }
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     auto begin = [&](const Item& t, int& slices) {
         const MfmaProblem& pr = w.pr[t.z];
         const int nk0 = (pr.Kc + kPpBK - 1) / kPpBK, nk = nk0 + (pr.Kc2 + kPpBK - 1) / kPpBK;
-        const int from = kSpread ? 0 : nk * t.share / w.nsplit, to = kSpread ? nk : nk * (t.share + 1) / w.nsplit;
+        const int from = kShares ? nk * t.share / w.nsplit : 0, to = kShares ? nk * (t.share + 1) / w.nsplit : nk;
         slices = to - from;
         Stream s;
         s.a_bytes = (uint32_t)(AKM ? pr.Kc : pr.M) * lda * 2u;
@@ -475,6 +478,7 @@ template <int BM, int BN, bool AKM, bool BKM, int F32, int NB> inline hipError_t
         }
         longest = std::max(longest, w.cum[x][NB]);
     }
+    if (!pp_shares<F32, NB> && w.nsplit != 1) return hipErrorInvalidValue;
     const int total = kLists * longest * w.nsplit;
     if (total == 0) return hipSuccess;
     hipLaunchKernelGGL(kern, dim3(mfma_grid(total, wgs)), dim3(kPpThreads), C::kLds, st, w);
