@@ -50,7 +50,7 @@ def parse():
 
 
 # kernels of the headline step whose HBM traffic the committed counter summary holds, by the library's name of the launch
-TRAFFIC_KEYS = {"gemm_gate_up": "gemm_bf16_pp<256,256,KC,KC>, gate and up", "gemm_dw3": "gemm_bf16_pp<192,256,KM,KM>, three products"}
+TRAFFIC_KEYS = {"gemm_gate_up": "gemm_bf16_pp<256,256,KC,KC>, gate and up", "gemm_dw3": "gemm_bf16_pp<256,256,KM,KM>, three products, with the rows in shares and their sum"}
 
 
 def source_hash():
