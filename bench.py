@@ -89,7 +89,7 @@ def gemm_flops(T, d, F, K):
         "gemm_dwd": (ex, al),
         "gemm_dwg": (ex, al),
         "gemm_dwu": (ex, al),
-        "gemm_dw3": (3 * ex, 3 * al),                # dW_down, dW_gate, dW_up in one launch
+        "gemm_dw3": (3 * ex, 3 * al),                # dW_down, dW_gate, dW_up: one launch, or whole rounds, the rest and its sum
         "gemm_gate_up": (2 * ex, ex + al),           # gate and up projection in one launch (when that saves a round)
         "gemm_dx": (2 * ex, 2 * al),
     }
