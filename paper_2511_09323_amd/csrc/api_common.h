@@ -227,8 +227,12 @@ inline int decode_splits(int B, int K) {
 
 constexpr int kDecodeFusedMaxP = 512;
 
-constexpr size_t kDecodeSyncBytes = 32 * 1024;          // >= sizeof(moc::DecodeSync), checked where that type is known
+constexpr size_t kDecodeSyncBytes = 32 * 1024;
+constexpr size_t kDecodeArrivedAt = 24 * 1024;          // in them: >= sizeof(moc::DecodeSync), checked where that type is known
 constexpr size_t kDecodePartBudget = (size_t)4 << 20;   // partial outputs of the persistent kernel's down projection
+constexpr size_t kDecodeArrivedBytes = 256;
+static_assert(kDecodeArrivedAt + kDecodeArrivedBytes <= 28 * 1024, "the persistent kernel's trace is at 28 KB");
+static_assert((size_t)2 * 16 * 32768 * sizeof(float) <= kDecodePartBudget, "SiLU(g) and u of 16 tokens and the most channels that check_shape admits");
 
 struct DecodeWs {
     float *g, *gkeys, *gsel, *z, *part;
@@ -237,9 +241,12 @@ struct DecodeWs {
     // channel [F, 1 + token slots], partial outputs of its down projection, its flag words
     uint64_t *g2, *zt;
     float* part2;
-    float *sd, *ud;      // both projections as streams: SiLU(g) or kNotSelected and u of every channel, [T, ldF] each (in the place of g2)
+    // Both projections as streams: SiLU(g) or kNotSelected and u of every channel, [T, ldF] each, and counters of the down projection's slices, cleared
+    // in the launch before it.  They lie where the persistent kernel looks for no tag (in part2, whose values it reads after a tagged flag, and behind its
+    // DecodeSync): its tags mix in the generation that its last call on the workspace left there, and a replayed call repeats the rest.
+    float *sd, *ud;
+    uint32_t* arrived;
     void* sync;
-    uint32_t* arrived;   // counters of the down projection's slices, cleared in the launch before it (in the place of sync)
     size_t bytes;
     DecodeWs(void* ws, const Dims& D) {
         Carver c(ws);
@@ -253,12 +260,12 @@ struct DecodeWs {
         part = c.take<float>((size_t)shares * D.T * D.d);
         const int slots = D.T == 1 ? 1 : (D.T <= 4 ? 4 : 16);
         g2 = c.take<uint64_t>((size_t)D.T * D.ldF);
-        sd = reinterpret_cast<float*>(g2);
-        ud = sd + (g2 ? (size_t)D.T * D.ldF : 0);
         zt = c.take<uint64_t>((size_t)D.F * (1 + slots));
         part2 = c.take<float>(kDecodePartBudget / sizeof(float));
         sync = c.take<unsigned char>(kDecodeSyncBytes);
-        arrived = static_cast<uint32_t*>(sync);
+        sd = part2;
+        ud = sd ? sd + (size_t)D.T * D.ldF : nullptr;
+        arrived = sync ? reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(sync) + kDecodeArrivedAt) : nullptr;
         bytes = c.off;
     }
 };

@@ -111,6 +111,11 @@ moc_status launch_select_up_stream_ns(const Dims& D, const TopkArgs<float>& a, c
     if (steps <= 4) return launch_select_up_stream_nt<NCH, 4>(D, a, x, wu, u, arrived, st);
     return launch_select_up_stream_nt<NCH, 8>(D, a, x, wu, u, arrived, st);
 }
+// Slices of 64 columns where those of 128 would need many ranges, whose shares are added: d 512 6.8 us against 9.2, 2048 12.3 against 15.1;
+// at 4096 the twice as many slices read SiLU(g) and u twice as often, 30.0 against 24.8.
+constexpr int kDownNarrowMaxD = 2048;
+static_assert(kDownNarrowMaxD <= kDownArrived * DownStreamCfg<4>::kCols && kGateStreamMaxD <= kDownArrived * DownStreamCfg<8>::kCols, "a counter to a slice");
+static_assert(kDownArrived * sizeof(uint32_t) <= kDecodeArrivedBytes, "workspace reserve for the counters");
 // Ranges of channels: as many workgroups as the device has compute units, at least a step of 32 channels for every wavefront.
 template <int CT, bool NT>
 moc_status launch_down_stream(const Dims& D, const DecodeWs& W, const bf16_t* wd, bf16_t* y, hipStream_t st) {
@@ -145,9 +150,7 @@ moc_status decode_dense(const Dims& D, const DecodeWs& W, const bf16_t* x, const
         else s = launch_select_up_stream_ns<16>(D, a, x, wu, W.ud, W.arrived, st);
     }
     if (s != MOC_OK) return s;
-    // (slices of 64 columns where those of 128 would need many ranges, whose shares are added: d 512 6.8 us against 9.2, 2048 12.3 against 15.1;
-    // at 4096 the twice as many slices read SiLU(g) and u twice as often, 30.0 against 24.8)
-    if (D.d <= 2048) return gate_stream_nontemporal(D.d, D.F) ? launch_down_stream<4, true>(D, W, wd, y, st) : launch_down_stream<4, false>(D, W, wd, y, st);
+    if (D.d <= kDownNarrowMaxD) return gate_stream_nontemporal(D.d, D.F) ? launch_down_stream<4, true>(D, W, wd, y, st) : launch_down_stream<4, false>(D, W, wd, y, st);
     return gate_stream_nontemporal(D.d, D.F) ? launch_down_stream<8, true>(D, W, wd, y, st) : launch_down_stream<8, false>(D, W, wd, y, st);
 }
 
@@ -171,7 +174,7 @@ moc_status launch_decode_fused(const Dims& D, const E* x, const E* wg, const E* 
 }
 
 // ------------------------------------------------------- row-wide decode in one persistent launch
-static_assert(sizeof(DecodeSync) <= kDecodeSyncBytes, "workspace reserve for the decode flags");
+static_assert(sizeof(DecodeSync) <= kDecodeArrivedAt, "workspace reserve for the decode flags");
 
 // Host call counter that makes the flag epochs of different calls differ (decode_persist.h); seeded
 // randomly so that flags left in reused memory by another process cannot match either.

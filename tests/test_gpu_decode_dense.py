@@ -2,6 +2,10 @@
 slice of columns that hangs over d, ranges of channels that end inside a step of 32 or a group of four, one range (nothing to add) and many,
 wavefronts with more steps than pieces under way or none, every number of chunks of the selection, every group size, all channels
 selected.  Against the float64 oracle at the bf16 tolerance of the other parity tests."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -84,3 +88,31 @@ def test_calls_that_follow_each_other_share_a_workspace():
 @pytest.mark.parametrize("key", ["silu", "abs_silu"])
 def test_dense_keyed(key):
     test_gpu_keyed.test_keyed_decode(16, 1536, 4096, 700, key)
+
+
+def replays_of_a_persistent_call():
+    """(in a process with MOC_DECODE_PERSISTENT=1)  Replays repeat the host's share of the tag, the workspace's generation tells them apart: streamed
+    calls between them must leave it alone."""
+    B, d, F, K = 16, 1024, 8192, 1024
+    x, w = _layer(B, d, F, 21)
+    dt = torch.bfloat16
+    ws = torch.full((moc.workspace_bytes(B, d, F, K, dt, 2),), 0xAB, dtype=torch.uint8, device="cuda")
+    out = (torch.empty_like(x), torch.empty((B, K), dtype=torch.int32, device="cuda"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        moc.moc_ffn_decode(x, *w, K, ws=ws, out=out)
+    for i in range(6):
+        x.copy_(_layer(B, d, F, 30 + i)[0])
+        want = moc.moc_ffn_decode(x, *w, K)      # (a workspace of its own)
+        if i % 3 != 2:
+            moc.moc_ffn_decode_keyed(x, *w, K, "silu", ws=ws)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[1], want[1]) and torch.equal(out[0], want[0]), "replay %d" % i
+
+
+def test_streamed_calls_between_replays_of_a_persistent_call():
+    code = "import tests.test_gpu_decode_dense as t\nt.replays_of_a_persistent_call()\nprint('ok')\n"
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, MOC_DECODE_PERSISTENT="1"), capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-3000:] + r.stderr[-3000:]
