@@ -154,11 +154,12 @@ struct StreamKArea {
 unsigned long long next_streamk_tag();
 
 // What is missing from `have` bytes of memory that is free when down or dX runs (share_scratch_wanted).
-template <class E> size_t extra_share_bytes(const Dims& D, size_t have) {
-    const size_t want = std::is_same<E, uint16_t>::value ? share_scratch_wanted(D.T, D.d) : 0;
+template <class E> size_t extra_share_bytes(const Dims& D, bool dx, size_t have) {
+    const size_t want = std::is_same<E, uint16_t>::value ? share_scratch_wanted(D.T, D.d, D.F, dx ? D.F : 0) : 0;
     return want > have ? want - have : 0;
 }
 
+// (`shares` = false: of experts, whose products never run in shares; their workspaces may be larger than what they carve)
 template <class E> struct FwdWs {      // dense scratch of the forward: fp32 gate, U, masked Z'
     float *G, *keys;                   // keys: transformed selection keys (Top-K position variants only)
     E *U, *Zd;
@@ -167,12 +168,12 @@ template <class E> struct FwdWs {      // dense scratch of the forward: fp32 gat
     StreamKArea sk;
     size_t share_bytes = 0;            // from G on: free while down runs
     size_t bytes;
-    FwdWs(void* ws, const Dims& D, bool dense, bool keyed = false) {
+    FwdWs(void* ws, const Dims& D, bool dense, bool keyed = false, bool shares = true) {
         Carver c(ws);
         G = dense ? nullptr : c.take<float>((size_t)D.T * D.ldF);
         U = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
-        if (!dense) {
-            (void)c.take<unsigned char>(extra_share_bytes<E>(D, c.off));
+        if (!dense && shares) {
+            (void)c.take<unsigned char>(extra_share_bytes<E>(D, false, c.off));
             share_bytes = c.off;
         }
         Zd = c.take<E>((size_t)D.T * D.ldF);
@@ -198,12 +199,12 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
     float* share = nullptr;            // free while dX runs: up to the end of Zd
     size_t share_bytes = 0, dw_share_bytes = 0;      // (while the weight gradients run: up to the end of dZd)
     size_t bytes;
-    BwdWs(void* ws, const Dims& D, bool dense) {
+    BwdWs(void* ws, const Dims& D, bool dense, bool shares = true) {
         Carver c(ws);
         maskw = dense ? nullptr : c.take<uint32_t>((size_t)D.T * D.nw);
         pref = dense ? nullptr : c.take<uint16_t>((size_t)D.T * D.nw);
         const size_t dense_bytes = (size_t)D.T * D.ldF * sizeof(E), before = c.off;
-        if (!dense) share = reinterpret_cast<float*>(c.take<unsigned char>(extra_share_bytes<E>(D, 2 * dense_bytes)));
+        if (!dense) share = reinterpret_cast<float*>(c.take<unsigned char>(shares ? extra_share_bytes<E>(D, true, 2 * dense_bytes) : 0));
         dZd = dense ? nullptr : c.take<E>((size_t)D.T * D.ldF);
         dw_share_bytes = c.off - before;
         const size_t rows = (size_t)D.T + kMaxExperts * (kRowPad - 1);

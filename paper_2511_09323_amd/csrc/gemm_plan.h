@@ -224,9 +224,15 @@ inline SharePlan plan_pp_shares(int M, int N, int nk, int elem, size_t scratch_b
     return best;
 }
 
-// Memory that a workspace holds for the shares of down and dX (bf16): up to eight, as far as 72 MB go (four of 2047 x 2048).  What else
-// is free at that time counts towards it.
-inline size_t share_scratch_wanted(int T, int d) { return std::min((size_t)8 * T * d * sizeof(float), (size_t)72 << 20); }
+// Memory that a workspace holds for the shares of down (Kc2 = 0) or dX, bf16; what else is free at that time counts towards it.  Eight shares, or as
+// many as the contraction has groups of eight slices for (plan_shares), up to what the routes use over d 64 .. 8192, F d/2 .. 8 d and 16 to 12000
+// tokens with as much as they like: 12 MB (down) and 21 MB (dX) below the line of long_product, 64 MB (a round of 256 x 256 tiles) above it, where
+// the weight gradients' last rows take up to 72 MB.  Grows with the tokens for a layer, so that a workspace for many serves fewer.
+inline size_t share_scratch_wanted(int T, int d, int Kc, int Kc2) {
+    const int most = std::min(8, slice_count(Kc, Kc2) / 8);
+    const size_t cap = long_product(T, d, Kc, Kc2) ? (Kc2 ? 72 : 64) : (Kc2 ? 21 : 12);
+    return most < 2 ? 0 : std::min((size_t)most * T * d * sizeof(float), cap << 20);
+}
 
 // How a product runs: whole on a tile of gemm_mfma.h (`mask`; `forced` see cheapest_tile) or, with pp, of gemm_pingpong.h, or, with scratch
 // for it, with every tile's k-slices cut into shares that run as workgroups of their own and are summed afterwards.  The cheapest

@@ -88,7 +88,7 @@ template <class E>
 moc_status bwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const E* x, const E* wg, const E* wu, const E* wd,
                             const int32_t* idx, const E* gvals, const E* uvals, const E* dy, E* dx, E* dwg, E* dwu, E* dwd,
                             void* ws, hipStream_t st) {
-    BwdWs<E> W(ws, D, false);
+    BwdWs<E> W(ws, D, false, false);
     const int64_t wsz = (int64_t)D.F * D.d;
     const int Fs = round_up(D.F, 8);      // whole 16-byte pieces into the padded [T, ldF] array (its padding is never read)
     const size_t expand_lds = (size_t)3 * D.ldF * sizeof(E);

@@ -71,7 +71,7 @@ moc_status fwd_impl(const Dims& D, const E* x, const E* wg, const E* wu, const E
 template <class E>
 moc_status fwd_experts_impl(const Dims& D, int n_exp, const int32_t* off, const E* x, const E* wg, const E* wu, const E* wd,
                             E* y, int32_t* idx, E* gvals, E* uvals, void* ws, hipStream_t st) {
-    FwdWs<E> W(ws, D, false);
+    FwdWs<E> W(ws, D, false, false, false);
     const int64_t wsz = (int64_t)D.F * D.d;
     const int Fs = round_up(D.F, 8);      // see fwd_impl
     GemmProblem<E> pr[kMaxExperts], pu[kMaxExperts];

@@ -50,14 +50,14 @@ static void products(int T, int d, int F) {
 static void over_channels(int T, int d, int F) {
     for (int two : {0, 1}) {
         EXPECT(two == 0 || long_product(T, d, F, F));
-        const size_t scratch = std::max((size_t)T * ldf(F) * (two ? 4 : 6), share_scratch_wanted(T, d));
+        const size_t scratch = std::max((size_t)T * ldf(F) * (two ? 4 : 6), share_scratch_wanted(T, d, F, two * F));
         say(two ? "dx" : "down", gemm_route(kTilesKm, T, d, F, two * F, 2, pp_sizes_ok(to_model(T, d, F, two * F)), scratch, kCus));
     }
     std::puts("");
 }
 // the weight gradients with what a workspace has for them
 static void weights(int T, int d, int F) {
-    const size_t dense = (size_t)T * ldf(F) * 2, want = share_scratch_wanted(T, d), scratch = dense + (want > 2 * dense ? want - 2 * dense : 0);
+    const size_t dense = (size_t)T * ldf(F) * 2, want = share_scratch_wanted(T, d, F, F), scratch = dense + (want > 2 * dense ? want - 2 * dense : 0);
     const Batch3Split s = batch3_split(F, d, T, batch3_route(F, d, T, pp_sizes_ok(to_weights(T, d, F)), kCus), scratch, kCus);
     EXPECT(s.rows == 0 || (s.rows < F && s.rows % kPpTile[s.main].bm == 0 && (size_t)3 * s.shares * (F - s.rows) * d * 4 <= scratch));
     EXPECT(s.rows == 0 || s.rest == 0 || s.rest == 3);
