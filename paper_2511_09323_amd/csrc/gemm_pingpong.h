@@ -148,8 +148,9 @@ template <int NB> struct PpWork {
     int tiles[NB];
     int cum[kSpread ? 8 : 1][NB + 1];      // items before problem z: of XCD x, or of all
     int nprob, tiles_n, nsplit;
-    int height = 4;                        // kSpread: rows of tiles in a band
-    int8_t owner[kSpread ? NB : 1];        // kSpread: the XCD that has all tiles of problem z, or -1
+    // weight gradients with kSpread: rows of tiles in a band, and the XCD that has all tiles of problem z, or -1 (words, which the scalar cache can load)
+    int height = 4;
+    int owner[kSpread ? NB : 1];
 };
 
 // F32: 0 = every result bf16, 1 = every result fp32, 2 = as PpOut says.
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / C::WGN, wn = wave % C::WGN;
     const int group = wave >> 2;
-    constexpr bool kSpread = PpWork<NB>::kSpread, kShares = pp_shares<F32, NB>;
+    constexpr bool kSpread = PpWork<NB>::kSpread, kOwners = kSpread && AKM && BKM, kShares = pp_shares<F32, NB>;
     const int xcd = blockIdx.x & 7;
     const int* const cum = w.cum[kSpread ? xcd : 0];
     const int tiles = cum[NB], total = tiles * (kShares ? w.nsplit : 1);      // (cum[NB] is the total also with fewer problems; of this XCD if kSpread)
@@ -211,9 +212,9 @@ __global__ __launch_bounds__(kPpThreads, 2) void gemm_bf16_pp_kernel(PpWork<NB> 
 #pragma unroll
         for (int z = 1; z < NB; ++z) t.z += mapped >= cum[z];
         int logical = mapped - cum[t.z];
-        if (kSpread && w.owner[t.z] < 0) logical += w.tiles[t.z] * xcd / 8;
+        if (kSpread && (!kOwners || w.owner[t.z] < 0)) logical += w.tiles[t.z] * xcd / 8;
         const int tiles_m = w.tiles[t.z] / w.tiles_n;
-        const int height = kSpread ? w.height : w.tiles_n >= 32 ? 8 : 4;      // band height, see gemm_bf16_mfma_tiles
+        const int height = kOwners ? w.height : w.tiles_n >= 32 ? 8 : 4;      // band height, see gemm_bf16_mfma_tiles
         const int band = logical / (height * w.tiles_n);
         const int first_m = band * height;
         const int rows = min(tiles_m - first_m, height);
@@ -460,20 +461,19 @@ template <int BM, int BN, bool AKM, bool BKM, int F32, int NB> inline hipError_t
     for (int z = 0; z < NB; ++z) w.tiles[z] = z < w.nprob ? (w.pr[z].M + BM - 1) / BM * w.tiles_n : 0;
     constexpr int kLists = PpWork<NB>::kSpread ? 8 : 1;
     int longest = 0;
-    if constexpr (kLists > 1) {
+    constexpr bool kOwners = kLists > 1 && AKM && BKM;
+    if constexpr (kOwners) {
         w.height = pp_band_height(BM, BN, *std::max_element(w.tiles, w.tiles + NB) / 8);
-        std::fill(w.owner, w.owner + NB, (int8_t)-1);
-        if constexpr (AKM && BKM) {
-            int slices[NB];
-            for (int z = 0; z < w.nprob; ++z) slices[z] = pp_slice_count(w.pr[z].Kc, w.pr[z].Kc2);
-            if (pp_owners(w.nprob, slices, w.tiles, std::max(1, wgs / 8), w.owner)) w.height = pp_band_height(BM, BN, std::min(w.tiles[0], wgs / 8));
-        }
+        std::fill(w.owner, w.owner + NB, -1);
+        int slices[NB];
+        for (int z = 0; z < w.nprob; ++z) slices[z] = pp_slice_count(w.pr[z].Kc, w.pr[z].Kc2);
+        if (pp_owners(w.nprob, slices, w.tiles, std::max(1, wgs / 8), w.owner)) w.height = pp_band_height(BM, BN, std::min(w.tiles[0], wgs / 8));
     }
     for (int x = 0; x < kLists; ++x) {
         w.cum[x][0] = 0;
         for (int z = 0; z < NB; ++z) {
             int n = w.tiles[z] * (x + 1) / kLists - w.tiles[z] * x / kLists;
-            if (kLists > 1 && w.owner[z] >= 0) n = w.owner[z] == x ? w.tiles[z] : 0;
+            if (kOwners && w.owner[z] >= 0) n = w.owner[z] == x ? w.tiles[z] : 0;
             w.cum[x][z + 1] = w.cum[x][z] + n;
         }
         longest = std::max(longest, w.cum[x][NB]);

@@ -153,27 +153,30 @@ inline bool pp_sizes_ok(const PpSizes& s) {
     return s.out_n * s.elem % 16 == 0 && s.ldc * s.elem % 16 == 0 && s.stride * s.elem % 16 == 0 && 256 * s.ldc * s.elem < (1ll << 31);
 }
 
-// Rows of tiles in a band where an XCD takes `tiles` neighbouring tiles of a problem: the height at which these touch the fewest operand
-// panels, which come from beyond its L2 (four tiles: a 2 x 2 block instead of a column, see pp_owners).
+// Weight gradients of experts: rows of tiles in a band where an XCD takes `tiles` neighbouring tiles of a problem, the height at which these touch the
+// fewest operand panels, which come from beyond its L2 (four tiles: a 2 x 2 block instead of a column, see pp_owners).  Four at most: with
+// eight, which the count prefers by 6 % for 29 tiles of 192 x 256, three experts of 2048 x 5461 take 155 us instead of 147.
 inline int pp_band_height(int bm, int bn, int tiles) {
     int best = 1;
-    for (int h = 2; h <= 8; h *= 2)
+    for (int h = 2; h <= 4; h *= 2)
         if (h * bm + tiles * bn / h < best * bm + tiles * bn / best) best = h;
     return best;
 }
 // Problems (in the order of their contraction lengths, `slices` to a tile, all of as many tiles) to whole XCDs of `width` workgroups, the longest
-// first to the XCD with the least work; false, and owner[] untouched, unless the busiest workgroup has no more to do than with an eighth of
+// first to the XCD with the least work; false, and owner[] untouched, where the busiest workgroup has over 3 % more to do than with an eighth of
 // every problem on every XCD.  Eight experts of 768 x 2048 with 2000 to 6000 rows (24 weight gradients of 32 tiles): an eighth of each means
 // panels of eight problems a round from beyond every L2, 5 TB/s of them: 310 us in bands of four tile rows, 296 in bands of two, 277 whole.
-inline bool pp_owners(int n, const int* slices, const int* tiles, int width, int8_t* owner) {
+// The backward of six experts of 512 x 1376 (18 problems on eight XCDs), 2048 to 32768 rows: 0.93 to 0.98 of the time with eighths; of four (12 problems)
+// 0.97 to 0.99 from 16384 rows on, 0.97 to 1.03 below.
+inline bool pp_owners(int n, const int* slices, const int* tiles, int width, int* owner) {
     constexpr int kMost = 24, kWidth = 64;
     if (n < 8 || n > kMost || width > kWidth || tiles[0] > 4 * width) return false;
     for (int z = 1; z < n; ++z)
         if (tiles[z] != tiles[0]) return false;
-    int8_t to[kMost];
+    int to[kMost];
     int64_t load[8] = {};
     for (int z = 0; z < n; ++z) {
-        to[z] = (int8_t)(std::min_element(load, load + 8) - load);
+        to[z] = (int)(std::min_element(load, load + 8) - load);
         load[to[z]] += slices[z] + 2;      // (two slices' time to write a tile)
     }
     // the busiest workgroup, dealt as the kernel does: every second round backwards

@@ -195,7 +195,7 @@ static void sizes() {
 }
 // Weight gradients of experts on whole XCDs: who owns what, and when.
 static void owners() {
-    int8_t own[24];
+    int own[24];
     const auto take = [&](std::vector<int> rows, int F, int d, int bm, int bn) {
         std::sort(rows.rbegin(), rows.rend());
         std::vector<int> slices, tiles;
@@ -204,7 +204,7 @@ static void owners() {
                 slices.push_back(pp_slice_count(r, 0));
                 tiles.push_back((F + bm - 1) / bm * ((d + bn - 1) / bn));
             }
-        std::fill(own, own + 24, (int8_t)-1);
+        std::fill(own, own + 24, -1);
         const bool whole = pp_owners((int)slices.size(), slices.data(), tiles.data(), 32, own);
         for (size_t z = 0; z < slices.size(); ++z) EXPECT(whole ? own[z] >= 0 && own[z] < 8 : own[z] == -1);
         return whole;
