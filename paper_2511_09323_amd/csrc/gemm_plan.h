@@ -99,6 +99,10 @@ inline SharePlan plan_shares(int M, int N, int nk, int elem, size_t scratch_byte
     double best_cost = (lng ? 1.0 : 0.95) * whole_cost;
     for (int c = 0; c < kGemmTiles; ++c) {
         if (!((kTilesShares >> c) & 1u)) continue;
+        // A single row of tiles reads every weight once, from memory, and one workgroup to a compute unit has too little of them under way: 192 x 128 in
+        // eight shares against what is chosen now, whole call of 129 to 192 rows: dX 2048 x 8192 93.5 .. 104.8 -> 85.4 .. 92.0 us, 2560 x 6826 106.8 .. 114.5
+        // -> 103.0 .. 109.0, 3072 x 8192 131.5 .. 145.8 -> 127.8 .. 138.9, down 2560 x 6826 64.6 .. 71.5 -> 60.6 .. 66.7, the others 0.97 to 1.00.
+        if (lng && table[c].resident == 1 && M <= table[c].bm) continue;
         for (int z = 2; z <= 8 && nk / z >= 8 && (size_t)z * out * sizeof(float) <= scratch_bytes; ++z) {
             const double cost = gemm_cost(table[c], z * tile_count(M, N, table[c]), (nk + z - 1) / z, cus) + shares_traffic_cost(out, z, elem, lng);
             if (cost < best_cost) { best = SharePlan{c, z}; best_cost = cost; }
