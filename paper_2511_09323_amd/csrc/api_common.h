@@ -218,14 +218,6 @@ template <class E> struct BwdWs {      // dense [T, ldF] operands (+ the bit mas
     }
 };
 
-// Channel shares per token in the gather stage: shares x tokens fills the 256 CUs once (one
-// 512-thread workgroup per CU), and a multiple of 8 shares lets the kernel keep each share on one XCD.
-inline int decode_splits(int B, int K) {
-    const int by_batch = std::max(8, 256 / B / 8 * 8);
-    const int by_k = (K + 7) / 8;
-    return std::max(1, std::min(by_batch, by_k));
-}
-
 constexpr int kDecodeFusedMaxP = 512;
 
 constexpr size_t kDecodeSyncBytes = 32 * 1024;

@@ -396,19 +396,41 @@ inline bool gate_stream_pays(int B, int d, int F, bool grouped, int workgroups) 
 }
 
 // bf16 decode with both projections as streams (decode_dense.h) instead of gathers, by what the gathers would request of a matrix, B K / F
-// times its rows.  Whole call, this / gather, weights from memory, B 2 .. 16, K/F 1/8, 1/5 and 1:
-//   row-wide, from five tokens: 1536 x 4096 to 4096 x 11008 1.2 times 0.92 to 0.97 (3072 x 8192 1.06), 1.6 times 0.83 to 1.00, 3.2 times 0.75 to
-//     0.85; 0.8 times 1.02 to 1.11.  Long columns (F > 4 d), whose values every slice reads: 1.2 times 0.97 to 1.13, 2 times 0.86 to 0.96.
+// times its rows.  Whole call, this / gather, weights from memory:
+//   row-wide, 5 to 16 tokens, at 1.2 times: d 1024 to 2048 and 4096 0.88 to 1.00, where 1.0 times is 0.94 to 1.06.  Between 2048 and 4096 the down projection
+//     has eight ranges of channels and so leaves an eighth to a half of the compute units idle, which costs the more the more tokens a gathered row serves:
+//     at 1.2 times 2560 x 6816 1.02 (5 tokens) to 1.08 (16), 3072 x 8192 0.96 to 1.07, 3584 x 9552 0.90 to 1.02; on the line drawn for them (2560: 1.38 to
+//     1.88 times, 3072: 1.34 to 1.64) 0.92 to 1.01.
+//     Long columns (F > 4 d), whose values every slice reads: 1.2 times 0.93 to 1.08, 1.6 times 0.85 to 0.99, 2 times 0.78 to 0.93.
 //     Fewer tokens, whose gathers repeat less: 2 times 0.93 to 1.08, 4 times 0.73 to 0.86.
 //   grouped, where no selection runs beside it: 2.5 times 0.94 to 1.05, 3.25 times 0.60 to 0.98.
 //   layers below 12 MB a matrix, where the launches weigh: 512 x 1376 to 1024 x 2752 3.2 times 1.01 to 1.02, 6 times 0.88 to 0.99; wide rows (2560
 //     x 640) gain nothing.
+constexpr int kDownNarrowMaxD = 2048;      // up to here the down projection takes slices of 64 columns, above of 128
 inline bool decode_dense_pays(int B, int d, int F, int K, bool grouped) {
     const int64_t requested = (int64_t)B * K, bytes = 2ll * d * F;
     if (bytes < 12000000) return B > 4 && d <= 2048 && requested >= 6ll * F;
     if (B <= 4) return !grouped && bytes >= 24000000 && requested >= 3ll * F;
     if (grouped) return requested >= 3ll * F;
-    return F > 4 * d ? requested >= 2ll * F : 5 * requested >= 6ll * F;
+    if (F > 4 * d) return requested >= 2ll * F;
+    const int idle = d > kDownNarrowMaxD ? 32 - (d + 127) / 128 : 0;      // of 32 slices, eight compute units each
+    return 1440 * requested >= (int64_t)(1728 + 5 * idle * B) * F;        // 1.2 times, and 1/288 more for every token and idle slice
+}
+
+// Channel shares per token in the gather stage of decode: shares x tokens fills the 256 CUs once (one
+// 512-thread workgroup per CU), and a multiple of 8 shares lets the kernel keep each share on one XCD.
+inline int decode_splits(int B, int K) {
+    const int by_batch = std::max(8, 256 / B / 8 * 8);
+    const int by_k = (K + 7) / 8;
+    return std::max(1, std::min(by_batch, by_k));
+}
+// Ranges of channels of the streamed down projection: as many workgroups as the device has compute units, at least a step of 32 channels for every
+// wavefront, no more than the workspace has partial outputs for; whole eights, so that a range stays on one XCD (1536 x 4096 23.0 us with 8
+// ranges, 24.0 with the 10 that fill the chip).
+inline int down_stream_ranges(int B, int d, int F, int K, int workgroups) {
+    const int cols = d <= kDownNarrowMaxD ? 64 : 128, slices = (d + cols - 1) / cols;
+    const int P = std::min({std::max(1, workgroups / slices), (F + 127) / 128, decode_splits(B, K)});
+    return P > 8 ? P / 8 * 8 : P;
 }
 
 // fp32 tile shapes of gemm_f32.h: 64 x 64 once that gives every compute unit a workgroup (a wavefront then feeds four MFMAs from four

@@ -111,27 +111,24 @@ moc_status launch_select_up_stream_ns(const Dims& D, const TopkArgs<float>& a, c
     if (steps <= 4) return launch_select_up_stream_nt<NCH, 4>(D, a, x, wu, u, arrived, st);
     return launch_select_up_stream_nt<NCH, 8>(D, a, x, wu, u, arrived, st);
 }
-// Slices of 64 columns where those of 128 would need many ranges, whose shares are added: d 512 6.8 us against 9.2, 2048 12.3 against 15.1;
+// Slices of 64 columns (kDownNarrowMaxD) where those of 128 would need many ranges, whose shares are added: d 512 6.8 us against 9.2, 2048 12.3 against 15.1;
 // at 4096 the twice as many slices read SiLU(g) and u twice as often, 30.0 against 24.8.
-constexpr int kDownNarrowMaxD = 2048;
 static_assert(kDownNarrowMaxD <= kDownArrived * DownStreamCfg<4>::kCols && kGateStreamMaxD <= kDownArrived * DownStreamCfg<8>::kCols, "a counter to a slice");
 static_assert(kDownArrived * sizeof(uint32_t) <= kDecodeArrivedBytes, "workspace reserve for the counters");
-// Ranges of channels: as many workgroups as the device has compute units, at least a step of 32 channels for every wavefront.
 template <int CT, bool NT>
 moc_status launch_down_stream(const Dims& D, const DecodeWs& W, const bf16_t* wd, bf16_t* y, hipStream_t st) {
     auto kern = decode_down_stream_kernel<CT, NT>;
     LdsAttr<decode_down_stream_kernel<CT, NT>, DownStreamCfg<CT>::kLds>::use();
     Span span("decode_down_stream", st);
     const int slices = (D.d + 16 * CT - 1) / (16 * CT);
-    int P = std::min({std::max(1, gate_stream_workgroups() / slices), (D.F + 127) / 128, decode_splits(D.T, D.K)});
-    if (P > 8) P = P / 8 * 8;                 // (a range on one XCD: 1536 x 4096 23.0 us with 8 ranges, 24.0 with the 10 that fill the chip)
+    const int P = down_stream_ranges(D.T, D.d, D.F, D.K, gate_stream_workgroups());
     const int per = round_up((D.F + 4 * P - 1) / (4 * P), 4);
     hipLaunchKernelGGL(kern, dim3(P, slices), dim3(256), DownStreamCfg<CT>::kLds, st, W.sd, W.ud, (int64_t)D.ldF, wd, D.T, D.d, D.F, per, W.part,
                        W.arrived, y);
     HIP_TRY(hipGetLastError());
     return MOC_OK;
 }
-// After the gate: selection (row-wide; grouped selection happened in the gate) and up projection, down projection, sum of the shares.
+// After the gate: selection (row-wide; grouped selection happened in the gate) and up projection, then the down projection, which adds its own shares.
 moc_status decode_dense(const Dims& D, const DecodeWs& W, const bf16_t* x, const bf16_t* wu, const bf16_t* wd, bf16_t* y, int32_t* idx, int gb,
                         int key_mode, hipStream_t st) {
     moc_status s;

@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+from tests.test_gpu_decode_dense import CASES as DENSE_CASES, GROUPED_CASES as DENSE_GROUPED_CASES
 from tests.test_gpu_experts import MIXTRAL_180M
 from tests.test_gpu_gemm_tiles import CASES as TILE_CASES
 from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES, SPLIT_CASES
@@ -233,8 +234,14 @@ static void gate() {
     EXPECT(!gate_stream_nontemporal(4096, 1024) && gate_stream_nontemporal(4096, 1536) && gate_stream_nontemporal(4096, 11008) && gate_stream_nontemporal(4096, 32768));
     std::puts("ok");
 }
+// Decode with both projections as streams: the width of the down projection's slices and its ranges of channels, or "gather".
+static void dense(int B, int d, int F, int K, bool grouped) {
+    if (d % 64 != 0 || d > 4096 || !gate_stream_pays(B, d, F, grouped, kCus) || !decode_dense_pays(B, d, F, K, grouped)) std::puts("gather");
+    else std::printf("%d/%d\n", d <= kDownNarrowMaxD ? 64 : 128, down_stream_ranges(B, d, F, K, kCus));
+}
 int main(int argc, char** argv) {
     if (argc == 1) routes();
+    else if (!std::strcmp(argv[1], "dense")) dense(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]), std::atoi(argv[5]), std::atoi(argv[6]) != 0);
     else if (argc == 2) (!std::strcmp(argv[1], "gate") ? gate : !std::strcmp(argv[1], "owners") ? owners : sizes)();
     else if (!std::strcmp(argv[1], "experts")) {
         std::vector<int> counts;
@@ -276,6 +283,33 @@ def test_decodes_that_take_the_streamed_gate(plan):
     """By rows per workgroup and bytes of W_gate (gate_stream_pays, gate_stream_nontemporal)."""
     r = plan("gate")
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+# ranges of channels of test_gpu_decode_dense.py's cases, in their order
+DENSE_RANGES = ["64/8", "64/1", "64/1", "64/2", "64/16", "64/16", "64/8", "64/8", "64/8", "128/8", "128/8", "128/8", "64/32", "64/16", "64/16", "128/8", "64/8"]
+DENSE_GROUPED_RANGES = ["128/8", "64/8", "64/8", "64/8"]
+
+
+def test_decode_cases_take_the_streams(plan):
+    got = [plan("dense", *c, 0).stdout.strip() for c in DENSE_CASES]
+    assert got == DENSE_RANGES
+    got = [plan("dense", B, d, F, F // b * a, 1).stdout.strip() for B, d, F, a, b in DENSE_GROUPED_CASES]
+    assert got == DENSE_GROUPED_RANGES
+
+
+@pytest.mark.parametrize("B,d,F,requested,grouped,want", [
+    (16, 4096, 11008, 1.19, 0, "gather"), (16, 4096, 11008, 1.2, 0, "128/8"), (5, 1536, 4096, 1.19, 0, "gather"), (16, 1536, 4096, 1.2, 0, "64/8"),
+    # d between 2048 and 4096: with the tokens and the idle compute units
+    (16, 2560, 6816, 1.86, 0, "gather"), (16, 2560, 6816, 1.88, 0, "128/8"), (5, 2560, 6816, 1.4, 0, "gather"), (5, 2560, 6816, 1.41, 0, "128/8"),
+    (16, 3072, 8192, 1.64, 0, "gather"), (16, 3072, 8192, 1.65, 0, "128/8"), (5, 3072, 8192, 1.34, 0, "128/8"), (16, 3584, 9552, 1.43, 0, "128/8"),
+    (16, 1024, 6144, 1.99, 0, "gather"), (16, 1024, 6144, 2.0, 0, "64/16"),                                         # long columns
+    (4, 4096, 11008, 2.99, 0, "gather"), (4, 4096, 11008, 3.0, 0, "128/8"), (4, 2048, 5461, 4, 0, "gather"),        # few tokens
+    (16, 4096, 11008, 2.99, 1, "gather"), (12, 4096, 11008, 3, 1, "128/8"), (4, 4096, 11008, 4, 1, "gather"),       # grouped
+    (16, 512, 1376, 5.99, 0, "gather"), (16, 512, 1376, 6, 0, "64/8"), (16, 2560, 1376, 8, 0, "gather"),            # small layers
+])
+def test_lines_of_the_streamed_decode(plan, B, d, F, requested, grouped, want):
+    K = -(-int(requested * F * 1000) // (1000 * B)) if want != "gather" else int(requested * F / B)
+    assert plan("dense", B, d, F, K, grouped).stdout.strip() == want
 
 
 def test_cases_take_the_kernels_they_name(plan):

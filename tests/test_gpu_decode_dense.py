@@ -17,19 +17,24 @@ from tests.test_gpu_parity import run_decode_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,d,F,K", [
+# (tests/test_gemm_routes.py has the ranges of channels that the down projection of each takes)
+CASES = [
     (16, 64, 1024, 512), (7, 512, 5, 5), (6, 576, 37, 37),              # one range; five channels; a slice of which half lies past d
     (16, 512, 129, 60), (16, 768, 2051, 1000), (7, 1024, 4099, 3700),   # part-filled steps and fours
     (16, 1536, 4096, 512), (10, 2048, 5461, 683), (6, 2048, 5461, 1100),
     (16, 2112, 2900, 400), (12, 4096, 2052, 300),                       # slices of 128 columns, the last one half past d
     (16, 4096, 11008, 1376), (5, 512, 23440, 10000), (16, 1024, 12345, 2500), (13, 512, 32768, 12000),      # three, six and sixteen chunks of the selection
     (3, 4096, 4100, 4100), (4, 2048, 8200, 6200),                       # few tokens that select most channels
-])
+]
+GROUPED_CASES = [(16, 4096, 2052, 1, 4), (13, 2048, 5464, 2, 8), (16, 512, 1376, 3, 4), (16, 1536, 8208, 3, 16)]
+
+
+@pytest.mark.parametrize("B,d,F,K", CASES)
 def test_dense(B, d, F, K):
     run_decode_case("dense", 71, B, d, F, K, "bf16")
 
 
-@pytest.mark.parametrize("B,d,F,a,b", [(16, 4096, 2052, 1, 4), (13, 2048, 5464, 2, 8), (16, 512, 1376, 3, 4), (16, 1536, 8208, 3, 16)])
+@pytest.mark.parametrize("B,d,F,a,b", GROUPED_CASES)
 def test_dense_grouped(B, d, F, a, b):
     run_grouped_decode("dense", 72, B, d, F, a, b, "bf16")
 
