@@ -44,6 +44,9 @@ constexpr GemmTile kGemmTileLong[kGemmTiles] = {
     {256, 256, 3, 1, 12.0, 0.595, 0.850, 0.0}, {256, 192, 3, 1, 11.5, 0.510, 0.673, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
     {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.299, 0.475, 0.0},  {192, 128, 3, 1, 6.4, 0.301, 0.381, 0.0},
     {128, 128, 3, 3, 5.5, 0.241, 0.328, 0.297}, {64, 128, 5, 4, 4.9, 0.214, 0.257, 0.211}};
+// The lines: with this table / with the warm one, whole forward or backward, weights from memory, d 640 to 1536.  By results: 14 to 20 << 16 0.90 to 1.06, mean
+// 1.00 over 48 layers; 21 to 31 << 16 0.85 to 1.05, mean 0.94.  By bytes: 5 to 8 MB forward 0.99 to 1.01; backward 0.86 to 0.99 from 1700 to 3600 rows of 768 x
+// 2048, 1.02 and 1.03 at 4096 and 5000.
 inline bool long_product(int M, int N, int Kc, int Kc2) {
     return 2 * ((int64_t)Kc + Kc2) * N >= 8000000 && (N >= 2048 || (int64_t)M * N >= 21 << 16);
 }
@@ -316,12 +319,15 @@ constexpr PpTile kPpTileWeights[kPpTiles] = {
 struct Batch3Split {
     int rows = 0, main = 0, rest = 0, shares = 0;
 };
-constexpr int kBatch3MinSlices = 32;      // fewer tokens: the second and third launch are not won back
+// What the second and third launch cost beside what the tables say, from the step with and without them at d 768 to 4096 and 500 to 8192 tokens: where the
+// tables promise 4 to 9 us, it was 4 us longer to 1 shorter (1536 x 4096, 1900 to 2400 tokens, 2048 x 5461, 1500 to 2047), where 12 to 16, 0 to 4 shorter,
+// 35, 13 to 20, 51, 35 shorter.  So 10 us are taken off.
+constexpr double kBatch3Extra = 10.0;
 inline Batch3Split batch3_split(int M, int N, int Kc, const GemmRoute& whole, size_t scratch_bytes, int cus) {
     const int nk = pp_slice_count(Kc, 0);
     Batch3Split best;
-    if (!whole.pp || nk < kBatch3MinSlices || N % 4 != 0) return best;
-    double cost = 0.97 * pp_cost(kPpTileWeights[whole.tile], 3 * tile_count(M, N, kPpTileWeights[whole.tile]), nk, cus);
+    if (!whole.pp || N % 4 != 0) return best;
+    double cost = pp_cost(kPpTileWeights[whole.tile], 3 * tile_count(M, N, kPpTileWeights[whole.tile]), nk, cus) - kBatch3Extra;
     for (int c = 0; c < kPpTiles; ++c) {
         const PpTile& t = kPpTileWeights[c];
         const int tiles_n = (N + t.bn - 1) / t.bn, strips = (M + t.bm - 1) / t.bm;
@@ -330,6 +336,7 @@ inline Batch3Split batch3_split(int M, int N, int Kc, const GemmRoute& whole, si
             if (full < 1 || full >= strips) continue;
             const int rows = full * t.bm, left = M - rows;
             const double main = pp_cost(t, (int64_t)3 * full * tiles_n, nk, cus);
+            if (main + kPpLaunch >= cost) break;
             for (int q : {0, 3})
                 for (int z = 2; z <= 16 && nk / z >= 4 && (size_t)3 * z * left * N * sizeof(float) <= scratch_bytes; ++z) {
                     const double c2 = main + pp_cost(kPpTileWeights[q], (int64_t)3 * z * tile_count(left, N, kPpTileWeights[q]), (nk + z - 1) / z, cus) +

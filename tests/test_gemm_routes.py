@@ -9,7 +9,7 @@ import pytest
 from tests.test_gpu_decode_dense import CASES as DENSE_CASES, GROUPED_CASES as DENSE_GROUPED_CASES
 from tests.test_gpu_experts import MIXTRAL_180M
 from tests.test_gpu_gemm_tiles import CASES as TILE_CASES
-from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES, SPLIT_CASES
+from tests.test_gpu_large_tiles import CASES, EXPERT_CASES, LONG_CASES, SPLIT_CASES, STORED_SPLIT_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -325,10 +325,11 @@ def test_long_cases_take_the_kernels_they_name(plan):
 
 
 def test_weight_gradients_are_split_as_named(plan):
-    for T, d, F, _, want in SPLIT_CASES:
+    for T, d, F, _, want in SPLIT_CASES + STORED_SPLIT_CASES:
         r = plan("weights", T, d, F)
         assert r.stdout.strip() == want, (T, d, F, want, r.stdout)
-    for T, d, F in ((1984, 2048, 5461), (4096, 768, 2048), (8192, 2048, 200)):      # few tokens; one round; a few tiles
+    # few tokens, also where a split would save a little; one round; a few tiles
+    for T, d, F in ((1984, 2048, 5461), (2047, 2048, 5464), (2400, 1536, 4096), (4096, 768, 2048), (8192, 2048, 200)):
         assert plan("weights", T, d, F).stdout.strip() == "whole", (T, d, F)
 
 

@@ -9,7 +9,7 @@ import paper_2511_09323_amd as moc
 from paper_2511_09323_amd import inputs
 from tests import parity as P
 from tests.test_gpu_experts import run_experts_case
-from tests.test_gpu_parity import run_fwd_bwd_case
+from tests.test_gpu_parity import gpu_layer, run_fwd_bwd_case
 
 pytestmark = pytest.mark.gpu
 
@@ -65,15 +65,29 @@ def test_long_products(T, d, F, K, kernels):
 SPLIT_CASES = [
     (2049, 1536, 3700, 462, "3584 pp256x256 pp128x256/7"),     # one token past a slice; 116 rows left
     (2300, 2048, 2731, 341, "2560 pp256x256 pp128x256/4"),     # 171: a second tile of 43
-    # (d 1280: a gate value of 2048 products differs from float64 by up to 2^-24 sqrt(2048) = 2.7e-6 of its size, more than the 1e-6 window of the cut,
-    # which one row in thousands meets at 2048 x 6200)
-    (2049, 1280, 9939, 1242, "8704 pp256x256 pp256x256/2"),
 ]
+# 256 x 256 tiles in the second launch.  At this size a row of 2600 may have its K-th and K + 1-th gate values closer than the rounding of sums of 2048
+# products (up to 2^-24 sqrt(2048) = 2.7e-6 of their size), so the gradients are taken from the stored set, whatever it is.
+STORED_SPLIT_CASES = [(2600, 2048, 6200, 775, "5376 pp256x256 pp256x256/2")]
 
 
 @pytest.mark.parametrize("T,d,F,K,plan", SPLIT_CASES)
 def test_weight_gradients_in_two_launches(T, d, F, K, plan):
     run_fwd_bwd_case("split " + plan, 93, T, d, F, K, "bf16")
+
+
+@pytest.mark.parametrize("T,d,F,K,plan", STORED_SPLIT_CASES)
+def test_weight_gradients_in_two_launches_from_a_stored_set(T, d, F, K, plan):
+    print("[case] split %s T=%d d=%d F=%d K=%d" % (plan, T, d, F, K), flush=True)
+    L = inputs.make_layer(93, T, d, F, "bf16", with_dy=True)
+    g = gpu_layer(L, "bf16")
+    w = (g["wg"], g["wu"], g["wd"])
+    _, idx, gvals, uvals = moc.moc_ffn_fwd(g["x"], *w, K)
+    got = moc.moc_ffn_bwd(g["x"], *w, idx, gvals, uvals, g["dy"])
+    torch.cuda.synchronize()
+    want = P.oracle_backward_for(L, idx.cpu().numpy(), P.to_np(gvals), P.to_np(uvals))
+    for name, a, b in zip(("dx", "dwg", "dwu", "dwd"), got, want):
+        P.assert_close(name, P.to_np(a), b, P.TOL["bf16"])
 
 
 # rows of the experts, d, F, K, kernels (a large tile of dw and down with its rounds of the workgroups: xN)
