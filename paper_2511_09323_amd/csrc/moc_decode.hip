@@ -132,7 +132,8 @@ moc_status launch_down_stream(const Dims& D, const DecodeWs& W, const bf16_t* wd
 moc_status decode_dense(const Dims& D, const DecodeWs& W, const bf16_t* x, const bf16_t* wu, const bf16_t* wd, bf16_t* y, int32_t* idx, int gb,
                         int key_mode, hipStream_t st) {
     moc_status s;
-    TopkArgs<float> a{W.g, D.ldF, D.F, D.K, idx, W.gsel, nullptr, nullptr, 0, nullptr, nullptr, 0, nullptr, cut_far(D.F, D.K), W.sd};
+    // (gsel is what grouped selection has left; a row's selection leaves SiLU(g) only)
+    TopkArgs<float> a{W.g, D.ldF, D.F, D.K, idx, gb != 0 ? W.gsel : nullptr, nullptr, nullptr, 0, nullptr, nullptr, 0, nullptr, cut_far(D.F, D.K), W.sd};
     if (gb != 0) {
         s = launch_select_up_stream_ns<0>(D, a, x, wu, W.ud, W.arrived, st);
     } else {
