@@ -48,8 +48,9 @@ LONG_CASES = [
     (300, 2048, 2050, 256, "down=64x128/3 dx=128x128/5"),
     (130, 2112, 2000, 250, "down=64x128/5 dx=128x128/7"),
     (192, 2560, 2600, 325, "down=64x128/4 dx=128x128/6"),     # as many rows as a tile of 192 has
-    (700, 2048, 2100, 262, "down=64x128 dx=192x128/4"),
-    (1100, 1280, 3300, 412, "down=192x128/4 dx=192x128/4"),
+    (700, 2048, 2100, 262, "down=64x128 dx=pp128x256/5"),
+    (900, 1536, 2100, 262, "dx=192x128/4"),
+    (1100, 1280, 3300, 412, "down=192x128/4 dx=pp192x256/8"),
     (1500, 2048, 2056, 257, "down=128x128 dx=pp192x256/4"),
     (2047, 2048, 2056, 257, "dx=pp128x256/2"),
 ]
