@@ -16,10 +16,10 @@
 //
 // Contractions whose tiles leave compute units idle run in shares (f32_shares).
 //
-// Measured at T 256, d 512, F 1376 (forward + backward, ten products in five launches): gate + up 15.6 us, down 10.0, dZ' 10.0,
-// three weight gradients 18.0, dX 15.4, against 125, 222, 63, 143 and 424 us on the fp32-FMA kernel of gemm_generic.h, which has 32
-// to 88 workgroups and waits for every 16-k slice; about 72 TFLOP/s at the margin (142 on a large library product), the rest launch
-// and first loads.
+// Measured at T 256, d 512, F 1376 (forward + backward, ten products in five launches and a sum of shares; medians of a profile, which adds about 10 % to
+// launches of this length): gate + up 15.7 us, down 10.6, dZ' 11.7, three weight gradients 22.1, dX 13.4 + 4.4, against 125, 222, 63, 143 and 424 us on
+// the fp32-FMA kernel of gemm_generic.h, which has 32 to 88 workgroups and waits for every 16-k slice; about 72 TFLOP/s at the margin (142 on a large
+// library product), the rest launch and first loads.
 #pragma once
 #include "common.h"
 #include "gemm_generic.h"

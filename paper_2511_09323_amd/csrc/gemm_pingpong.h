@@ -5,10 +5,10 @@
 // Operands as in gemm_mfma.h: k-contiguous (KC) or k-major (KM), in the layout they have in memory.
 //
 // Bound: the matrix cores, as far as the hand-over and the rounds of tiles let them work, at the clock the power limit leaves (2.0 to
-// 2.15 GHz).  Counted (SQ_VALU_MFMA_BUSY_CYCLES of all SIMD cycles): 0.70 for one full round of 256 tiles, 8192 x 2048 x 5461 and 2 * 5461;
-// 0.61 and 0.59 for 2.75 and 5.5 rounds, 8192 x 5461 x 2048 to bf16 and as gate + up; 0.54 for three products 5461 x 2048 x 8192 on 192 x 256
-// tiles.  What the kernel of gemm_mfma.h (0.47 to 0.61) loses against that is the way of the operands: one wavefront per SIMD has to fit the
-// global loads, the writes to LDS and the fragment reads between its own MFMAs.  Here
+// 2.2 GHz).  Counted (SQ_VALU_MFMA_BUSY_CYCLES of all SIMD cycles): 0.70 for one full round of 256 tiles, 8192 x 2048 x 5461 and 2 * 5461;
+// 0.61 and 0.58 for 2.75 and 5.5 rounds, 8192 x 5461 x 2048 to bf16 and as gate + up; 0.68 for two rounds of three products, 5376 x 2048 x 8192 (0.55 when
+// 5461 rows ran on 192 x 256 tiles in 2.72 rounds).  What the kernel of gemm_mfma.h (0.47 to 0.61) loses against that is the way of the operands: one
+// wavefront per SIMD has to fit the global loads, the writes to LDS and the fragment reads between its own MFMAs.  Here
 //  - operands go from memory to LDS without passing through registers (buffer_load ... lds, 1 KB per instruction), so there are no
 //    staging registers and no LDS writes to issue; what lies past the end of an operand is delivered as zeros by the buffer's range
 //    check, so ragged rows, columns and contraction ends need no code;
