@@ -38,12 +38,12 @@ constexpr GemmTile kGemmTile[kGemmTiles] = {
 // The same for products over the channels (down, dX) with 1.4 M results or rows of 2048 and 8 MB of weights or more, which do not stay in a
 // cache until they are read: measured with operands from memory, 32 to 6000 rows, d 512 to 4096.  The table above, measured with warm
 // operands, made such products up to 1.8 times as long as the best choice (2047 x 2048 over 2 * 5464 121 us against 80, 1024 x 4096 over 10928 121
-// against 80), this one 1.01 times on average (502 products of 40 to 2600 rows; five of them 1.02 to 1.03 times what the table above takes).  Below 8 MB the warm table holds: 4096 x 768 over 2 * 2048, cold 46 us whole and 40 in shares, runs
+// against 80), this one 1.01 times on average (502 products of 40 to 2600 rows; three of them 1.02 to 1.03 times what the table above takes).  Below 8 MB the warm table holds: 4096 x 768 over 2 * 2048, cold 46 us whole and 40 in shares, runs
 // in 40 and 42 inside a training step.
 constexpr GemmTile kGemmTileLong[kGemmTiles] = {
     {256, 256, 3, 1, 12.0, 0.595, 0.850, 0.0}, {256, 192, 3, 1, 11.5, 0.510, 0.673, 0.0}, {192, 256, 3, 1, 11.0, 0.457, 0.668, 0.0},
     {256, 128, 3, 1, 9.0, 0.373, 0.484, 0.0},  {128, 192, 3, 1, 7.0, 0.299, 0.475, 0.0},  {192, 128, 3, 1, 8.0, 0.330, 0.381, 0.0},
-    {128, 128, 3, 3, 5.5, 0.241, 0.328, 0.297}, {64, 128, 5, 4, 4.9, 0.214, 0.257, 0.211}};
+    {128, 128, 3, 3, 5.5, 0.241, 0.308, 0.297}, {64, 128, 5, 4, 4.9, 0.214, 0.257, 0.211}};
 // The lines: with this table / with the warm one, whole forward or backward, weights from memory, d 640 to 1536.  By results: 14 to 20 << 16 0.90 to 1.06, mean
 // 1.00 over 48 layers; 21 to 31 << 16 0.85 to 1.05, mean 0.94.  By bytes: 5 to 8 MB forward 0.99 to 1.01; backward 0.86 to 0.99 from 1700 to 3600 rows of 768 x
 // 2048, 1.02 and 1.03 at 4096 and 5000.
@@ -320,9 +320,9 @@ struct Batch3Split {
     int rows = 0, main = 0, rest = 0, shares = 0;
 };
 // What the second and third launch cost beside what the tables say, from the step with and without them at d 768 to 4096 and 500 to 8192 tokens: where the
-// tables promise 4 to 9 us, it was 4 us longer to 1 shorter (1536 x 4096, 1900 to 2400 tokens, 2048 x 5461, 1500 to 2047), where 12 to 16, 0 to 4 shorter,
-// 35, 13 to 20, 51, 35 shorter.  So 10 us are taken off.
-constexpr double kBatch3Extra = 10.0;
+// tables promise 4 to 9.2 us, it was 4 us longer to 1 shorter (1536 x 4096, 1900 to 2400 tokens, 2048 x 5461, 1500 to 1984), where 9.8 to 16, 0 to 4 shorter
+// (2048 x 5461, 2047 to 2400), 35, 13 to 20, 51, 35 shorter.  So 9.5 us are taken off.
+constexpr double kBatch3Extra = 9.5;
 inline Batch3Split batch3_split(int M, int N, int Kc, const GemmRoute& whole, size_t scratch_bytes, int cus) {
     const int nk = pp_slice_count(Kc, 0);
     Batch3Split best;

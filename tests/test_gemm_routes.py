@@ -329,7 +329,7 @@ def test_weight_gradients_are_split_as_named(plan):
         r = plan("weights", T, d, F)
         assert r.stdout.strip() == want, (T, d, F, want, r.stdout)
     # few tokens, also where a split would save a little; one round; a few tiles
-    for T, d, F in ((1984, 2048, 5461), (2047, 2048, 5464), (2400, 1536, 4096), (4096, 768, 2048), (8192, 2048, 200)):
+    for T, d, F in ((1984, 2048, 5461), (2400, 1536, 4096), (4096, 768, 2048), (8192, 2048, 200)):
         assert plan("weights", T, d, F).stdout.strip() == "whole", (T, d, F)
 
 

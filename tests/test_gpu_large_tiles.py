@@ -45,12 +45,13 @@ def test_large_tiles(T, d, F, K, kernels):
 # Products over the channels whose weights come from memory (long_product), with the scratch that a workspace holds for their shares
 LONG_CASES = [
     (40, 2048, 2050, 256, "down=64x128/8 dx=64x128/8"),        # as many shares as there is scratch for; a contraction of 32 slices and two channels
-    (300, 2048, 2050, 256, "down=64x128/3 dx=128x128/5"),
+    (300, 2048, 2050, 256, "down=128x128/5 dx=128x128/5"),
     (130, 2112, 2000, 250, "down=64x128/5 dx=128x128/7"),
     (192, 2560, 2600, 325, "down=64x128/4 dx=128x128/6"),     # as many rows as a tile of 192 has
-    (700, 2048, 2100, 262, "down=64x128 dx=pp128x256/5"),
+    (700, 2048, 2100, 262, "down=128x128/2 dx=pp128x256/5"),
     (900, 1536, 2100, 262, "dx=192x128/4"),
-    (1100, 1280, 3300, 412, "down=192x128/4 dx=pp192x256/8"),
+    (560, 2304, 3300, 412, "down=192x128/4"),
+    (1100, 1280, 3300, 412, "down=128x128/2 dx=pp192x256/8"),
     (1500, 2048, 2056, 257, "down=128x128 dx=pp192x256/4"),
     (2047, 2048, 2056, 257, "dx=pp128x256/2"),
 ]
